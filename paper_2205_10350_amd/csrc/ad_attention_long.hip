@@ -26,7 +26,7 @@ __global__ __launch_bounds__(256) void k_attention_long(const bf16_t* __restrict
     attn_split_tiles(q, Kb, Vb, out, sd, row_begin, row_end, blockIdx.y, d, scale, nk_all, (bf16_t*)att_long_lds);
     return;
   }
-  attn_block<bf16_t, 64, true>(q, Kb, Vb, out, sd, row_begin, row_end, blockIdx.y, d, scale, att_long_lds, nk_cap);
+  attn_block<64, true>(q, Kb, Vb, out, sd, row_begin, row_end, blockIdx.y, d, scale, att_long_lds, nk_cap);
 }
 
 void launch_attention_long(const void* q, const void* K, const void* V, void* out, const SeqDesc* desc, dim3 grid, int d,

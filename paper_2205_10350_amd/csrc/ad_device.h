@@ -338,33 +338,6 @@ __device__ __forceinline__ void strip_epilogue(const Epi& e, const f32x4 (&acc)[
   epi_apply<T, MT>(e, acc, g, mt_used, m0, n0, M, N, lane);
 }
 
-// Epilogue of a single element (fp32 GEMM path).
-template <typename T>
-__device__ __forceinline__ void epi_store(const Epi& e, int m, int n, int N, float acc) {
-  if (e.bias) acc += e.bias[n];
-  switch (e.mode) {
-    case EPI_QKV: {
-      const int d = e.d;
-      if (n < d) Store<T>::store((T*)e.out0 + (size_t)m * d + n, acc);
-      else if (n < 2 * d) Store<T>::store((T*)e.out1 + (size_t)e.row_dst[m] * d + (n - d), acc);
-      else Store<T>::store((T*)e.out2 + (size_t)e.row_dst[m] * d + (n - 2 * d), acc);
-      break;
-    }
-    case EPI_KV: {
-      const int d = e.d, layer = n / (2 * d), c = n - layer * 2 * d;
-      T* kb = (T*)((char*)e.out1 + layer * e.layer_stride);
-      T* vb = (T*)((char*)e.out2 + layer * e.layer_stride);
-      if (c < d) Store<T>::store(kb + (size_t)e.row_dst[m] * d + c, acc);
-      else Store<T>::store(vb + (size_t)e.row_dst[m] * d + (c - d), acc);
-      break;
-    }
-    case EPI_STORE: Store<T>::store((T*)e.out0 + (size_t)m * N + n, acc); break;
-    case EPI_RELU: Store<T>::store((T*)e.out0 + (size_t)m * N + n, fmaxf(acc, 0.f)); break;
-    case EPI_RESID: ((float*)e.out0)[(size_t)m * N + n] = acc + e.resid[(size_t)m * N + n]; break;
-    default: break;
-  }
-}
-
 // Second stage of the arg max for one row by one wave; partials are loaded eight at a time.
 __device__ __forceinline__ void argmax_row(const float* __restrict__ pv, const int* __restrict__ pi, int n_strips,
                                            int lane, float& v, int& idx) {
@@ -394,19 +367,8 @@ __device__ __forceinline__ void argmax_row(const float* __restrict__ pv, const i
 //   pass 2  p = exp(s - max); the denominator sums the unrounded p; numerators are rounded to
 //           the storage type
 //   pass 3  lane c accumulates output channel c over the keys in ascending order
-// LDS bytes needed: attn_lds_bytes().
-template <typename T> struct LdsRow;
-template <> struct LdsRow<bf16_t> {
-  static constexpr int kPerDword = 2;
-  static __device__ __forceinline__ void unpack(unsigned w, float& lo, float& hi) {
-    lo = __uint_as_float(w << 16);
-    hi = __uint_as_float(w & 0xFFFF0000u);
-  }
-};
-template <> struct LdsRow<float> {
-  static constexpr int kPerDword = 1;
-};
-
+// LDS bytes needed: attn_lds_bytes().  (bf16 heads whose width is no multiple of 32; the others take attn_block_mfma,
+// the fp32 mode has ad_attention_f32.hip.)
 // (the key-split paths, attn_split_keys / attn_split_tiles: per wave a [64][kSplitLd] value tile and a [16][kSplitLd]
 // probability tile)
 constexpr int kSplitLd = 128 + 16;                                   // row stride (elements): 32 bytes past a multiple of 64
@@ -1134,16 +1096,16 @@ __device__ __forceinline__ void attn_block_mfma(const bf16_t* __restrict__ q, co
   __syncthreads();   // LDS is free for the next call
 }
 
-template <typename T, int DH, bool LONGK = false>
-__device__ __forceinline__ void attn_block(const T* __restrict__ q, const T* __restrict__ Kb, const T* __restrict__ Vb,
-                           T* __restrict__ out, const SeqDesc sd, int row_begin, int row_end, int h, int d,
+template <int DH, bool LONGK = false>
+__device__ __forceinline__ void attn_block(const bf16_t* __restrict__ q, const bf16_t* __restrict__ Kb, const bf16_t* __restrict__ Vb,
+                           bf16_t* __restrict__ out, const SeqDesc sd, int row_begin, int row_end, int h, int d,
                            float scale, unsigned* lds, int nk_cap) {
-  if constexpr (sizeof(T) == 2 && DH % 32 == 0) {
+  if constexpr (DH % 32 == 0) {
     const int nk_need = sd.causal ? sd.nk_base + row_end : sd.nk_base;
     attn_block_mfma<DH, LONGK>(q, Kb, Vb, out, sd, row_begin, row_end, h, d, scale, lds, nk_need);
     return;
   }
-  constexpr int RD = DH * (int)sizeof(T) / 4;   // dwords per key row
+  constexpr int RD = DH / 2;                    // dwords per key row
   constexpr int RS = RD + 1;                    // padded row stride
   const int waves = blockDim.x >> 6, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   unsigned* Ks = lds;
@@ -1155,7 +1117,7 @@ __device__ __forceinline__ void attn_block(const T* __restrict__ q, const T* __r
     // stage keys, values and the query rows; loads are issued four deep so that their latencies overlap
     const unsigned* kg = (const unsigned*)(Kb + (size_t)sd.kv_row0 * d + h * DH);
     const unsigned* vg = (const unsigned*)(Vb + (size_t)sd.kv_row0 * d + h * DH);
-    const size_t gs = (size_t)d * sizeof(T) / 4;   // global row stride in dwords
+    const size_t gs = (size_t)d / 2;   // global row stride in dwords
     const int n = nk_all * RD, nt = blockDim.x;
     for (int base = threadIdx.x; base < n; base += 4 * nt) {
       unsigned kv[4], vv[4];
@@ -1186,7 +1148,7 @@ __device__ __forceinline__ void attn_block(const T* __restrict__ q, const T* __r
         const int i = base + u * nt;
         if (i < nq) {
           const int rr = i / DH, c = i - rr * DH;
-          qv[u] = Store<T>::load(q + (size_t)(sd.q_row0 + row_begin + rr) * d + h * DH + c);
+          qv[u] = Store<bf16_t>::load(q + (size_t)(sd.q_row0 + row_begin + rr) * d + h * DH + c);
         }
       }
 #pragma unroll
@@ -1216,17 +1178,10 @@ __device__ __forceinline__ void attn_block(const T* __restrict__ q, const T* __r
 #pragma unroll
       for (int w = 0; w < RD; ++w) kw[w] = kr[w];
       float a = 0.f;
-      if constexpr (sizeof(T) == 2) {
 #pragma unroll
-        for (int w = 0; w < RD; ++w) {
-          float lo, hi;
-          LdsRow<bf16_t>::unpack(kw[w], lo, hi);
-          a = fmaf(qv[2 * w], lo, a);
-          a = fmaf(qv[2 * w + 1], hi, a);
-        }
-      } else {
-#pragma unroll
-        for (int w = 0; w < RD; ++w) a = fmaf(qv[w], __uint_as_float(kw[w]), a);
+      for (int w = 0; w < RD; ++w) {
+        a = fmaf(qv[2 * w], __uint_as_float(kw[w] << 16), a);
+        a = fmaf(qv[2 * w + 1], __uint_as_float(kw[w] & 0xFFFF0000u), a);
       }
       a *= scale;
       sc[t] = a;
@@ -1237,7 +1192,7 @@ __device__ __forceinline__ void attn_block(const T* __restrict__ q, const T* __r
     for (int t = lane; t < nk; t += 64) {
       const float p = expf(sc[t] - mx);
       l += p;
-      sc[t] = Store<T>::round(p);
+      sc[t] = Store<bf16_t>::round(p);
     }
     l = wave_sum(l);
     __builtin_amdgcn_wave_barrier();
@@ -1249,14 +1204,13 @@ __device__ __forceinline__ void attn_block(const T* __restrict__ q, const T* __r
         for (int j = 0; j < 8; ++j) {
           const int t = t0 + j < nk ? t0 + j : nk - 1;    // (past the end: re-read the last key, not used)
           pt[j] = sc[t];
-          if constexpr (sizeof(T) == 2) vt[j] = bf2f(((const bf16_t*)Vs)[(size_t)t * RS * 2 + c]);
-          else vt[j] = ((const float*)Vs)[(size_t)t * RS + c];
+          vt[j] = bf2f(((const bf16_t*)Vs)[(size_t)t * RS * 2 + c]);
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j)
           if (t0 + j < nk) a = fmaf(pt[j], vt[j], a);
       }
-      Store<T>::store(out + (size_t)m * d + h * DH + c, a / l);
+      Store<bf16_t>::store(out + (size_t)m * d + h * DH + c, a / l);
     }
     __builtin_amdgcn_wave_barrier();
   }

@@ -85,9 +85,18 @@ void launch_embed(int dtype, const void* emb, const float* pe, const int* tok, c
 // first.  Same values either way.
 int launch_gemm(int dtype, const void* A, const void* W, int M, int N, int K, const Epi& e, hipStream_t s,
                 const LnA& ln = LnA{}, bool* a_written = nullptr);
+// fp32 (ad_gemm_f32.hip): the same product, and the drafted tokens' scores with the same summation order
+// (`ln` only where gemm_f32_takes_ln says so)
+int launch_gemm_f32(const float* A, const float* W, int M, int N, int K, const Epi& e, hipStream_t s, const LnA& ln);
+bool gemm_f32_takes_ln(int M, int N, int K, const Epi& e);
+void launch_draft_logit_f32(const float* A, const float* W, int M, int N, int K, const int* row_seq, const int* row_start,
+                            const int* draft, int k_max, float* lp, int* col, hipStream_t s);
 // one attention problem per descriptor (n_seq of them, at most max_rows query rows each)
 void launch_attention(int dtype, const void* q, const void* K, const void* V, void* out, const SeqDesc* desc,
                       int n_seq, int max_rows, int H, int dh, int max_keys, hipStream_t s);
+// the same in fp32 (ad_attention_f32.hip)
+void launch_attention_f32(const float* q, const float* K, const float* V, float* out, const SeqDesc* desc, int n_seq,
+                          int max_rows, int H, int dh, int max_keys, hipStream_t s);
 // the same launch for long key ranges (ad_attention_long.hip; bf16, head width 64, grid and LDS bytes as launch_attention computes them)
 void launch_attention_long(const void* q, const void* K, const void* V, void* out, const SeqDesc* desc, dim3 grid, int d,
                            float scale, int max_keys, size_t lds_bytes, hipStream_t s);

@@ -589,56 +589,13 @@ static void launch_kchain(const bf16_t* A, const bf16_t* W, int M, int N, int K,
   else k_gemm_bf16_kchain<8><<<grid, 256, 0, s>>>(A, W, M, N, K, n_strips, e);
 }
 
-// ------------------------------------------------------------------------------------- fp32 GEMM
-// Plain fp32 path: one thread per output element, k ascending, fused multiply-add.
-__global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, const float* __restrict__ W, int M,
-                                                  int N, int K, Epi e) {
-  __shared__ float As[16][33];
-  __shared__ float Ws[16][33];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int n0 = blockIdx.x * 16, m0 = blockIdx.y * 16;
-  const int m = m0 + ty, n = n0 + tx;
-  float acc = 0.f;
-  for (int k0 = 0; k0 < K; k0 += 32) {
-    for (int i = threadIdx.x; i < 16 * 32; i += 256) {
-      const int rr = i >> 5, cc = i & 31;
-      const int am = m0 + rr < M ? m0 + rr : M - 1;
-      const int wn = n0 + rr < N ? n0 + rr : N - 1;
-      As[rr][cc] = A[(size_t)am * K + k0 + cc];
-      Ws[rr][cc] = W[(size_t)wn * K + k0 + cc];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 32; ++kk) acc = fmaf(As[ty][kk], Ws[tx][kk], acc);
-    __syncthreads();
-  }
-  if (e.mode == EPI_ARGMAX) {
-    // 16 columns per strip, reduced by the 16 threads of a row (they sit in one wave)
-    float v = acc;
-    int idx = n;
-    if (e.logits && m < M && n < N) e.logits[(size_t)m * N + n] = v;
-    argmax_row16(v, idx);
-    if (tx == 0 && m < M) {
-      e.part_val[(size_t)m * e.n_strips + blockIdx.x] = v;
-      e.part_idx[(size_t)m * e.n_strips + blockIdx.x] = idx;
-    }
-    return;
-  }
-  if (e.mode == EPI_COUNT) {
-    const int cnt = row16_sum_i(n < N && acc > e.thr[m < M ? m : M - 1] ? 1 : 0);
-    if (tx == 0 && m < M) e.part_idx[(size_t)m * e.n_strips + blockIdx.x] = cnt;
-    return;
-  }
-  if (m < M && n < N) epi_store<float>(e, m, n, N, acc);
-}
-
 int launch_gemm(int dtype, const void* A, const void* W, int M, int N, int K, const Epi& e, hipStream_t s,
                 const LnA& ln_in, bool* a_written) {
   if (M <= 0) return 0;
   if (a_written) *a_written = true;
   LnA ln = ln_in;
   const bool streams = dtype == AD_BF16 && K <= 4096 && K % 512 == 0;   // the A-in-LDS kernel takes it
-  if (ln.x && !(streams && (K == 512 || K == 1024))) {
+  if (ln.x && !(dtype == AD_F32 ? gemm_f32_takes_ln(M, N, K, e) : streams && (K == 512 || K == 1024))) {
     launch_layernorm(dtype, ln.x, ln.g, ln.b, M, K, ln.y, const_cast<void*>(A), s);
     ln = LnA{};
   }
@@ -739,23 +696,23 @@ int launch_gemm(int dtype, const void* A, const void* W, int M, int N, int K, co
     else
       k_gemm_bf16<4><<<dim3(nb, (M + 63) / 64), 256, 0, s>>>((const bf16_t*)A, (const bf16_t*)W, M, N, K, e);
   } else {
-    k_gemm_f32<<<dim3(N / 16, (M + 15) / 16), 256, 0, s>>>((const float*)A, (const float*)W, M, N, K, e);
+    return launch_gemm_f32((const float*)A, (const float*)W, M, N, K, e, s, ln);
   }
   return N / 16;
 }
 
 // ------------------------------------------------------------------------------------- attention
 // One block per (sequence, head, chunk of 64 query rows); see attn_block.
-template <typename T, int DH>
-__global__ __launch_bounds__(256) void k_attention(const T* __restrict__ q, const T* __restrict__ Kb,
-                                                   const T* __restrict__ Vb, T* __restrict__ out,
+template <int DH>
+__global__ __launch_bounds__(256) void k_attention(const bf16_t* __restrict__ q, const bf16_t* __restrict__ Kb,
+                                                   const bf16_t* __restrict__ Vb, bf16_t* __restrict__ out,
                                                    const SeqDesc* __restrict__ desc, int d, float scale, int nk_cap) {
   extern __shared__ unsigned att_lds[];
   const SeqDesc sd = desc[blockIdx.x];
   const int row_begin = blockIdx.z * 64;
   if (row_begin >= sd.nq) return;
   const int row_end = min(sd.nq, row_begin + 64);
-  attn_block<T, DH>(q, Kb, Vb, out, sd, row_begin, row_end, blockIdx.y, d, scale, att_lds, nk_cap);
+  attn_block<DH>(q, Kb, Vb, out, sd, row_begin, row_end, blockIdx.y, d, scale, att_lds, nk_cap);
 }
 
 // The same for launches whose bounds promise at most 64 keys and one chunk of rows (bf16, head width 64): the one path
@@ -795,35 +752,37 @@ __global__ __launch_bounds__(256) void k_attention_small(const bf16_t* __restric
   attn_tiles_mfma<DH, 4>(q, Kb, out, sd, row_begin, row_end, h, d, scale, Vt, Pw, ldv, nk_all, qf_pre, kf_pre, nullptr, nkp);
 }
 
-template <typename T>
-static void attention_dispatch(const void* q, const void* K, const void* V, void* out, const SeqDesc* desc,
-                               int n_seq, int max_rows, int H, int dh, int max_keys, hipStream_t s) {
+void launch_attention(int dtype, const void* q, const void* K, const void* V, void* out, const SeqDesc* desc,
+                      int n_seq, int max_rows, int H, int dh, int max_keys, hipStream_t s) {
+  if (n_seq <= 0 || max_rows <= 0) return;
+  if (dtype != AD_BF16) {
+    launch_attention_f32((const float*)q, (const float*)K, (const float*)V, (float*)out, desc, n_seq, max_rows, H, dh, max_keys, s);
+    return;
+  }
   const float scale = 1.0f / sqrtf((float)dh);
-  const size_t sh = attn_lds_bytes(max_keys, dh, sizeof(T), 4);
+  const size_t sh = attn_lds_bytes(max_keys, dh, 2, 4);
   dim3 g(n_seq, H, (max_rows + 63) / 64);
 #define AD_ATT(DH)                                                                                             \
   do {                                                                                                         \
     static size_t set_for = 0;                                                                                 \
     if (sh > set_for) {                                                                                        \
-      (void)hipFuncSetAttribute((const void*)k_attention<T, DH>, hipFuncAttributeMaxDynamicSharedMemorySize,   \
+      (void)hipFuncSetAttribute((const void*)k_attention<DH>, hipFuncAttributeMaxDynamicSharedMemorySize,      \
                                 (int)sh);                                                                      \
       set_for = sh;                                                                                            \
     }                                                                                                          \
-    k_attention<T, DH><<<g, 256, sh, s>>>((const T*)q, (const T*)K, (const T*)V, (T*)out, desc, H * dh, scale, \
-                                          max_keys);                                                           \
+    k_attention<DH><<<g, 256, sh, s>>>((const bf16_t*)q, (const bf16_t*)K, (const bf16_t*)V, (bf16_t*)out,      \
+                                       desc, H * dh, scale, max_keys);                                         \
   } while (0)
-  if constexpr (sizeof(T) == 2) {
-    // at most 64 keys and 64 rows per problem (the caller's bounds promise both): the compact kernel (measured against the
-    // generic one, base model: forward at 8 / 25 rows 183.2 / 186.8 -> 180.2 / 185.0 us, at 32 x 6 / 32 x 36 rows
-    // 228.5 / 446.4 -> 224.6 / 434.5 us)
-    if (dh == 64 && max_keys <= 64 && max_rows <= 64) {
-      k_attention_small<<<dim3(n_seq, H, 1), 256, sh, s>>>((const bf16_t*)q, (const bf16_t*)K, (const bf16_t*)V, (bf16_t*)out, desc, H * dh, scale);
-      return;
-    }
-    if (dh == 64 && max_keys >= kLongKeys) {   // long key ranges: a kernel in a code object of its own
-      launch_attention_long(q, K, V, out, desc, g, H * dh, scale, max_keys, sh, s);
-      return;
-    }
+  // at most 64 keys and 64 rows per problem (the caller's bounds promise both): the compact kernel (measured against the
+  // generic one, base model: forward at 8 / 25 rows 183.2 / 186.8 -> 180.2 / 185.0 us, at 32 x 6 / 32 x 36 rows
+  // 228.5 / 446.4 -> 224.6 / 434.5 us)
+  if (dh == 64 && max_keys <= 64 && max_rows <= 64) {
+    k_attention_small<<<dim3(n_seq, H, 1), 256, sh, s>>>((const bf16_t*)q, (const bf16_t*)K, (const bf16_t*)V, (bf16_t*)out, desc, H * dh, scale);
+    return;
+  }
+  if (dh == 64 && max_keys >= kLongKeys) {   // long key ranges: a kernel in a code object of its own
+    launch_attention_long(q, K, V, out, desc, g, H * dh, scale, max_keys, sh, s);
+    return;
   }
   switch (dh) {
     case 16: AD_ATT(16); break;
@@ -832,12 +791,6 @@ static void attention_dispatch(const void* q, const void* K, const void* V, void
     default: AD_ATT(128); break;
   }
 #undef AD_ATT
-}
-void launch_attention(int dtype, const void* q, const void* K, const void* V, void* out, const SeqDesc* desc,
-                      int n_seq, int max_rows, int H, int dh, int max_keys, hipStream_t s) {
-  if (n_seq <= 0 || max_rows <= 0) return;
-  if (dtype == AD_BF16) attention_dispatch<bf16_t>(q, K, V, out, desc, n_seq, max_rows, H, dh, max_keys, s);
-  else attention_dispatch<float>(q, K, V, out, desc, n_seq, max_rows, H, dh, max_keys, s);
 }
 
 // ------------------------------------------------- cross-attention with its query projection
@@ -1502,20 +1455,6 @@ __global__ __launch_bounds__(64) void k_draft_logit_bf16(const bf16_t* __restric
     col[m] = tok;
   }
 }
-// fp32 path: the fused multiply-add chain of k_gemm_f32, k ascending.
-__global__ void k_draft_logit_f32(const float* __restrict__ A, const float* __restrict__ W, int M, int N, int K,
-                                  const int* __restrict__ row_seq, const int* __restrict__ row_start,
-                                  const int* __restrict__ draft, int k_max, float* __restrict__ lp,
-                                  int* __restrict__ col) {
-  const int m = blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= M) return;
-  const int tok = drafted_token(row_seq, row_start, draft, k_max, m);
-  const int c = min(max(tok, 0), N - 1);
-  float acc = 0.f;
-  for (int k = 0; k < K; ++k) acc = fmaf(A[(size_t)m * K + k], W[(size_t)c * K + k], acc);
-  lp[m] = acc;
-  col[m] = tok;
-}
 void launch_draft_logit(int dtype, const void* A, const void* W, int M, int N, int K, const int* row_seq,
                         const int* row_start, const int* draft, int k_max, float* lp, int* col, hipStream_t s) {
   if (M <= 0) return;
@@ -1523,8 +1462,7 @@ void launch_draft_logit(int dtype, const void* A, const void* W, int M, int N, i
     k_draft_logit_bf16<<<(M + 15) / 16, 64, 0, s>>>((const bf16_t*)A, (const bf16_t*)W, M, N, K, row_seq, row_start, draft,
                                                     k_max, lp, col);
   else
-    k_draft_logit_f32<<<(M + 63) / 64, 64, 0, s>>>((const float*)A, (const float*)W, M, N, K, row_seq, row_start, draft,
-                                                   k_max, lp, col);
+    launch_draft_logit_f32((const float*)A, (const float*)W, M, N, K, row_seq, row_start, draft, k_max, lp, col, s);
 }
 
 }  // namespace ad
