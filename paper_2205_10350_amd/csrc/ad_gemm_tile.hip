@@ -1,0 +1,353 @@
+// bf16 GEMM for many rows (v_mfma_f32_16x16x32_bf16), a code object of its own.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <type_traits>
+
+#include "ad_device.h"
+
+namespace ad {
+
+// C[M,N] = A[M,K] . W[N,K]^T, A row-major, W in operand tiles.  A workgroup of four waves owns BM = 16*MT rows x BN = 64*SP
+// columns: every wave all the rows, SP of the 16-column strips.  K is walked 64 at a time; a stage's rows go through registers
+// into LDS (two buffers), its weights straight into operand registers, D stages requested ahead.
+// The products are taken with the weights as the left operand, so that a lane holds four consecutive columns of one row:
+// acc[t][i] = row m0 + 16 t + lane % 16, column n0 + 4 (lane / 16) + i.  Same value per element as strip_epilogue.
+// tile_request: what the epilogue reads and the product does not decide (bias, residual values, destination rows).
+template <int MT> struct TileRegs {
+  f32x4 bias;
+  uint4 res[MT];   // RESID: the residual values' bits; QKV / KV: .x = the destination row
+};
+template <int MT, int EM>
+__device__ __forceinline__ void tile_request(const Epi& e, int m0, int n0, int M, int N, int lane, TileRegs<MT>& g) {
+  const int r = lane & 15, c0 = 4 * (lane >> 4);
+  g.bias = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (e.bias) g.bias = __builtin_bit_cast(f32x4, ldg16(e.bias + n0 + c0));
+  const bool by_dst = EM == EPI_KV || (EM == EPI_QKV && n0 >= e.d);
+#pragma unroll
+  for (int t = 0; t < MT; ++t) {
+    const int m = min(m0 + 16 * t + r, M - 1);
+    if constexpr (EM == EPI_RESID) g.res[t] = ldg16(e.resid + (size_t)m * N + n0 + c0);
+    else g.res[t].x = by_dst ? (unsigned)gload(e.row_dst + m) : (unsigned)m;
+  }
+}
+template <int MT, int EM>
+__device__ __forceinline__ void tile_apply(const Epi& e, const f32x4 (&acc)[MT], const TileRegs<MT>& g, int m0, int n0, int M, int N,
+                                           int lane) {
+  const int r = lane & 15, c0 = 4 * (lane >> 4), d = e.d;
+  bf16_t* base = (bf16_t*)e.out0;
+  int ld = N, col = n0;
+  if constexpr (EM == EPI_QKV) {
+    const int part = n0 / d;   // (a strip lies inside one of the q / k / v ranges)
+    ld = d; col = n0 - part * d;
+    base = (bf16_t*)(part == 0 ? e.out0 : part == 1 ? e.out1 : e.out2);
+  } else if constexpr (EM == EPI_KV) {
+    const int layer = n0 / (2 * d), c = n0 - layer * 2 * d;
+    ld = d; col = c < d ? c : c - d;
+    base = (bf16_t*)((char*)(c < d ? e.out1 : e.out2) + layer * e.layer_stride);
+  }
+  base += col + c0;
+#pragma unroll
+  for (int t = 0; t < MT; ++t) {
+    const int m = m0 + 16 * t + r;
+    if (m >= M) continue;
+    f32x4 v = acc[t];
+    if (e.bias) v += g.bias;
+    if constexpr (EM == EPI_RESID) {
+      v += __builtin_bit_cast(f32x4, g.res[t]);
+      gstore((uint4*)((float*)e.out0 + (size_t)m * N + n0 + c0), __builtin_bit_cast(uint4, v));
+    } else {
+      if constexpr (EM == EPI_RELU) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = fmaxf(v[i], 0.f);
+      }
+      const uint2 w = uint2{(unsigned)f2bf(v[0]) | ((unsigned)f2bf(v[1]) << 16), (unsigned)f2bf(v[2]) | ((unsigned)f2bf(v[3]) << 16)};
+      gstore((uint2*)(base + (size_t)g.res[t].x * ld), w);
+    }
+  }
+}
+template <int MT, int SP, int D, int EM>
+__global__ __launch_bounds__(256) void k_gemm_bf16_tile(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M,
+                                                        int N, int K, int m_tiles, int n_tiles, Epi e) {
+  constexpr int BM = 16 * MT, NA = BM / 32, LD = 64 + 16;   // NA 16-byte pieces of a stage's rows per thread
+  static_assert(D == 2 || D == 4 || D == 8, "D divides the stages of every K that is a multiple of 512");
+  __shared__ bf16_t At[2][BM * LD];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = lane & 15, kq = lane >> 4;
+  // consecutive workgroups go to consecutive XCDs: XCD x works through the x-th eighth of the tiles, column tile by column
+  // tile, so that a column tile's weights stay in its L2 while the row tiles pass
+  const int per = (m_tiles * n_tiles + 7) >> 3, lin = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per || lin >= m_tiles * n_tiles) return;
+  const int tn = lin / m_tiles, tm = lin - tn * m_tiles;
+  const int m0 = tm * BM, n_strips = N >> 4, s0 = tn * 4 * SP + wave * SP;
+  const bf16_t* ap[NA];
+  int a_lds[NA];
+#pragma unroll
+  for (int i = 0; i < NA; ++i) {
+    const int row = (threadIdx.x >> 3) + 32 * i, c = threadIdx.x & 7;
+    ap[i] = A + (size_t)min(m0 + row, M - 1) * K + 8 * c;
+    a_lds[i] = row * LD + 8 * c;
+  }
+  const bf16_t* wp[SP];
+#pragma unroll
+  for (int j = 0; j < SP; ++j) wp[j] = W + (size_t)min(s0 + j, n_strips - 1) * 16 * K + lane * 8;
+  const int rounds = (K >> 6) / D;
+  uint4 ra[D][NA], rb[D][SP][2], af[2][2][MT];
+  auto req_a = [&](int q, int st) {
+#pragma unroll
+    for (int i = 0; i < NA; ++i) ra[q][i] = ldg16(ap[i] + 64 * st);
+  };
+  auto req_b = [&](int q, int st) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int j = 0; j < SP; ++j) rb[q][j][u] = ldg16(wp[j] + (size_t)st * 1024 + u * 512);
+  };
+  auto put_a = [&](int q, int buf) {
+#pragma unroll
+    for (int i = 0; i < NA; ++i) *(uint4*)(At[buf] + a_lds[i]) = ra[q][i];
+  };
+  auto get_a = [&](int buf) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int t = 0; t < MT; ++t) af[buf][u][t] = *(const uint4*)(At[buf] + (16 * t + r) * LD + 32 * u + 8 * kq);
+  };
+  // in the order of the loop's requests, so that its waits are exact from the first round on: rows of stages 0 and 1, then for
+  // every stage q its weights and the rows of stage q + 2
+  uint4 rp[2][NA];
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int i = 0; i < NA; ++i) rp[q][i] = ldg16(ap[i] + 64 * q);
+#pragma unroll
+  for (int q = 0; q < D; ++q) {
+    req_a((q + 2) % D, min(q + 2, (K >> 6) - 1));
+    req_b(q, q);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  // (the small tiles have the registers to request the epilogue's operands here)
+  constexpr bool PRE = MT * SP <= 4;
+  TileRegs<MT> g[SP];
+  if constexpr (PRE) {
+#pragma unroll
+    for (int j = 0; j < SP; ++j) tile_request<MT, EM>(e, m0, min(s0 + j, n_strips - 1) << 4, M, N, lane, g[j]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  f32x4 acc[SP][MT];
+#pragma unroll
+  for (int j = 0; j < SP; ++j)
+#pragma unroll
+    for (int t = 0; t < MT; ++t) acc[j][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int i = 0; i < NA; ++i) *(uint4*)(At[q] + a_lds[i]) = rp[q][i];
+  __builtin_amdgcn_sched_barrier(0);
+  __syncthreads();
+  get_a(0);
+  __syncthreads();
+  // stage st: its row fragments are in registers; the next stage's are read, the one after that is written into the
+  // buffer the present one came from, and the registers are refilled D stages ahead
+  auto round = [&](auto more_c, int st0) {
+    constexpr bool MORE = decltype(more_c)::value;
+#pragma unroll
+    for (int q = 0; q < D; ++q) {
+      const int st = st0 + q;
+      __builtin_amdgcn_sched_barrier(0);
+      if (MORE || q + 2 < D) put_a((q + 2) % D, q & 1);
+      if (MORE || q + 1 < D) get_a((q + 1) & 1);
+      if (MORE) req_a((q + 2) % D, q + 2 < D ? st + 2 + D : min(st + 2 + D, (K >> 6) - 1));
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int j = 0; j < SP; ++j) {
+#pragma unroll
+          for (int t = 0; t < MT; ++t)
+            acc[j][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, rb[q][j][u]), __builtin_bit_cast(bf16x8, af[q & 1][u][t]), acc[j][t], 0, 0, 0);
+          if (MORE) rb[q][j][u] = ldg16(wp[j] + (size_t)(st + D) * 1024 + u * 512);
+        }
+      if (MORE || q + 2 < D) __builtin_amdgcn_sched_group_barrier(0x200, NA, 0);
+#pragma unroll
+      for (int g = 0; g < 2 * SP; ++g) {
+#pragma unroll
+        for (int i = 0; i < MT / 2; ++i) {
+          const int at = g * (MT / 2) + i;   // of SP * MT steps
+          __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+          if ((MORE || q + 1 < D) && 2 * at < 2 * MT) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+          if (MORE && at < NA) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        }
+        if (MORE) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (MORE || q + 1 < D) __syncthreads();
+    }
+  };
+  for (int rd = 0; rd + 1 < rounds; ++rd) round(std::true_type{}, rd * D);
+  round(std::false_type{}, (rounds - 1) * D);
+#pragma unroll
+  for (int j = 0; j < SP; ++j)
+    if (s0 + j < n_strips) {
+      if constexpr (!PRE) tile_request<MT, EM>(e, m0, (s0 + j) << 4, M, N, lane, g[j]);
+      tile_apply<MT, EM>(e, acc[j], g[j], m0, (s0 + j) << 4, M, N, lane);
+    }
+}
+
+// The same product for many rows, where the matrix cores and not latencies are the bound: one register set per operand,
+// refilled as soon as its last MFMA is issued (a row fragment from LDS for the next 32 k, the weights and the rows' pieces for the
+// next stage), so that a 128 x 256 tile fits 256 registers and two workgroups a CU, which cover each other's waits.
+// Three LDS buffers: one being read, the next one ready, one being written.
+template <int MT, int SP, int EM>
+__global__ __launch_bounds__(256, 2) void k_gemm_bf16_roll(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M,
+                                                           int N, int K, int m_tiles, int n_tiles, Epi e) {
+  constexpr int BM = 16 * MT, NA = BM / 32, LD = 64 + 16, BUF = BM * LD;
+  __shared__ bf16_t At[3 * BUF];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = lane & 15, kq = lane >> 4;
+  const int per = (m_tiles * n_tiles + 7) >> 3, lin = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per || lin >= m_tiles * n_tiles) return;
+  const int tn = lin / m_tiles, tm = lin - tn * m_tiles;
+  const int m0 = tm * BM, n_strips = N >> 4, s0 = tn * 4 * SP + wave * SP;
+  const bf16_t* ap[NA];
+#pragma unroll
+  for (int i = 0; i < NA; ++i) ap[i] = A + (size_t)min(m0 + (int)(threadIdx.x >> 3) + 32 * i, M - 1) * K + 8 * (threadIdx.x & 7);
+  bf16_t* a_put = At + (threadIdx.x >> 3) * LD + 8 * (threadIdx.x & 7);
+  const bf16_t* a_get = At + r * LD + 8 * kq;
+  const bf16_t* wp[SP];
+#pragma unroll
+  for (int j = 0; j < SP; ++j) wp[j] = W + (size_t)min(s0 + j, n_strips - 1) * 16 * K + lane * 8;
+  const int n_st = K >> 6;
+  uint4 ra[NA], rb[2][SP], af[MT];
+  {
+    uint4 r1[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) ra[i] = ldg16(ap[i]);
+#pragma unroll
+    for (int i = 0; i < NA; ++i) r1[i] = ldg16(ap[i] + 64);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int j = 0; j < SP; ++j) rb[u][j] = ldg16(wp[j] + u * 512);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < NA; ++i) *(uint4*)(a_put + 32 * i * LD) = ra[i];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) *(uint4*)(a_put + BUF + 32 * i * LD) = r1[i];
+  }
+#pragma unroll
+  for (int i = 0; i < NA; ++i) ra[i] = ldg16(ap[i] + 64 * min(2, n_st - 1));
+  f32x4 acc[SP][MT];
+#pragma unroll
+  for (int j = 0; j < SP; ++j)
+#pragma unroll
+    for (int t = 0; t < MT; ++t) acc[j][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < MT; ++t) af[t] = *(const uint4*)(a_get + 16 * t * LD);
+  int cur = 0, nxt = BUF, wrt = 2 * BUF;
+  for (int st = 0; st < n_st; ++st) {
+    const int st1 = min(st + 1, n_st - 1), st3 = min(st + 3, n_st - 1);   // (past the end: requested again, not used)
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < NA; ++i) *(uint4*)(a_put + wrt + 32 * i * LD) = ra[i];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) ra[i] = ldg16(ap[i] + 64 * st3);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const bf16_t* an = u == 0 ? a_get + cur + 32 : a_get + nxt;
+#pragma unroll
+      for (int t = 0; t < MT; ++t) {
+#pragma unroll
+        for (int j = 0; j < SP; ++j)
+          acc[j][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, rb[u][j]), __builtin_bit_cast(bf16x8, af[t]), acc[j][t], 0, 0, 0);
+        af[t] = *(const uint4*)(an + 16 * t * LD);
+      }
+#pragma unroll
+      for (int j = 0; j < SP; ++j) rb[u][j] = ldg16(wp[j] + (size_t)st1 * 1024 + u * 512);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x200, NA, 0);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+#pragma unroll
+      for (int t = 0; t < MT; ++t) {
+        __builtin_amdgcn_sched_group_barrier(0x008, SP, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        if (u == 0 && t < NA) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x020, SP, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();
+    const int x = cur;
+    cur = nxt; nxt = wrt; wrt = x;
+  }
+#pragma unroll
+  for (int j = 0; j < SP; ++j)
+    if (s0 + j < n_strips) {
+      TileRegs<MT> g;
+      tile_request<MT, EM>(e, m0, (s0 + j) << 4, M, N, lane, g);
+      tile_apply<MT, EM>(e, acc[j], g, m0, (s0 + j) << 4, M, N, lane);
+    }
+}
+
+template <int MT, int SP, typename Go>
+static void with_tile_shape(int M, int N, const Epi& e, const Go& go) {
+  const int m_tiles = (M + 16 * MT - 1) / (16 * MT), n_tiles = (N / 16 + 4 * SP - 1) / (4 * SP);
+  const int grid = (m_tiles * n_tiles + 7) / 8 * 8;
+  switch (e.mode) {
+    case EPI_QKV: go(std::integral_constant<int, EPI_QKV>{}, grid, m_tiles, n_tiles); break;
+    case EPI_KV: go(std::integral_constant<int, EPI_KV>{}, grid, m_tiles, n_tiles); break;
+    case EPI_STORE: go(std::integral_constant<int, EPI_STORE>{}, grid, m_tiles, n_tiles); break;
+    case EPI_RELU: go(std::integral_constant<int, EPI_RELU>{}, grid, m_tiles, n_tiles); break;
+    default: go(std::integral_constant<int, EPI_RESID>{}, grid, m_tiles, n_tiles); break;
+  }
+}
+template <int MT, int SP, int D>
+static void launch_tile(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epi& e, hipStream_t s) {
+  with_tile_shape<MT, SP>(M, N, e, [&](auto em_c, int grid, int m_tiles, int n_tiles) {
+    k_gemm_bf16_tile<MT, SP, D, decltype(em_c)::value><<<grid, 256, 0, s>>>(A, W, M, N, K, m_tiles, n_tiles, e);
+  });
+}
+template <int MT, int SP>
+static void launch_roll(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epi& e, hipStream_t s) {
+  with_tile_shape<MT, SP>(M, N, e, [&](auto em_c, int grid, int m_tiles, int n_tiles) {
+    k_gemm_bf16_roll<MT, SP, decltype(em_c)::value><<<grid, 256, 0, s>>>(A, W, M, N, K, m_tiles, n_tiles, e);
+  });
+}
+
+// Which layer GEMMs come here rather than to the kernels that keep all of K of their rows in LDS (measured, us there / here; a
+// pending LayerNorm, 2.5-3 us as a launch of its own, is inside both figures):
+//  K = 1024, LayerNorm pending: 64 / 80 / 130 / 250 / 626 rows x N 3072 6.1 / 6.4 / 8.5 / 11.5 / 15.9 there, 6.7 / 6.8 / 6.9 / 8.1 /
+//    10.8 here, x N 4096 6.2 / 8.1 / 10.6 / 11.5 / 20.5 there, 6.4 / 6.5 / 7.9 / 8.1 / 14.7 here; N 12288 (memory keys and values) 25
+//    rows 8.4 / 6.5, 626 rows 38.8 / 25, 3252 rows 221 / 100
+//  K = 1024, none: 80 / 130 / 626 / 3252 rows 3.4 / 4.7 / 6.4 / 26.1 there, 3.8 / 4.0 / 5.4 / 16.5 here
+//  K = 4096: 100 / 130 / 626 / 3252 rows 8.2 / 12.7 / 22.2 / 80 there, 8.1 / 8.2 / 14.6 / 43 here
+//  K = 512, LayerNorm pending: N 1536 1120 / 1500 rows 7.8 / 14.0 there, 9.1 / 10.7 here; N 2048 800 / 1120 rows 8.5 / 11.8 there and
+//    8.6 / 10.2 here; N 6144 128 / 200 / 1120 rows 7.0 / 10.2 / 30.3 there, 7.1 / 8.4 / 17.8 here
+//  K = 512, none: 400 / 576 / 1120 rows 2.8 / 3.9 / 4.2 there, 3.2 / 3.0 / 4.1 here
+//  K = 2048: 400 / 576 / 1120 rows 5.6 / 8.1 / 8.7 there, 5.4 / 5.4 / 8.8 here
+bool gemm_tile_takes(int M, int N, int K, bool has_ln, const Epi& e) {
+  if (K % 512 || K < 512 || e.mode == EPI_ARGMAX || e.mode == EPI_COUNT) return false;
+  if (K == 512) return has_ln ? (N >= 4096 ? M > 160 : N >= 2048 ? M > 1024 : M > 1344) : M >= 520;
+  if (K == 2048) return M >= 520 && (M <= 1024 || M > 2048);
+  return has_ln ? M > (N > 4096 ? 16 : N == 4096 ? 64 : 96) : M > 128;
+}
+// Tile by the number of workgroups w(rows x columns of a tile): the smallest while they fit the CUs at once (a stage's latency is
+// the bound), larger ones as soon as there are enough of them (operand traffic from L2 and then the matrix cores are).
+// Measured at K = 1024 (64 x 128 / 64 x 128 rolling / 128 x 128 / 128 x 256): N 3072 x 626 rows (w 240) 8.3 / 9.0 / 12.0 / 18.4 us,
+// x 2000 (768) 23.1 / 21.3 / 23.0 / 26.7; N 4096 x 2000 (1024) 28.0 / 26.5 / 23.0 / 25.4, x 3252 (1632) 44 / 43 / 42 / 35.5 (770
+// TFLOP/s); N 12288 x 3252 120 / 122 / 108 / 94.6 (865 TFLOP/s).
+void launch_gemm_tile(const void* A_, const void* W_, int M, int N, int K, const Epi& e, hipStream_t s) {
+  const bf16_t *A = (const bf16_t*)A_, *W = (const bf16_t*)W_;
+  auto w = [&](int rows, int cols) { return ((M + rows - 1) / rows) * ((N + cols - 1) / cols); };
+  if (w(32, 64) <= 256) launch_tile<2, 1, 4>(A, W, M, N, K, e, s);
+  else if (w(64, 64) <= 256) launch_tile<4, 1, 4>(A, W, M, N, K, e, s);
+  else if (w(64, 128) <= 450) {
+    if (K >= 2048) launch_tile<4, 2, 4>(A, W, M, N, K, e, s);
+    else launch_tile<4, 2, 2>(A, W, M, N, K, e, s);
+  } else if (w(64, 128) <= 900) launch_roll<4, 2>(A, W, M, N, K, e, s);
+  else if (w(128, 256) < 350) launch_roll<8, 2>(A, W, M, N, K, e, s);
+  else launch_roll<8, 4>(A, W, M, N, K, e, s);
+}
+
+}  // namespace ad

@@ -85,6 +85,9 @@ void launch_embed(int dtype, const void* emb, const float* pe, const int* tok, c
 // first.  Same values either way.
 int launch_gemm(int dtype, const void* A, const void* W, int M, int N, int K, const Epi& e, hipStream_t s,
                 const LnA& ln = LnA{}, bool* a_written = nullptr);
+// bf16, many rows (ad_gemm_tile.hip): which products go there, and their launch (A as rows, no LayerNorm)
+bool gemm_tile_takes(int M, int N, int K, bool has_ln, const Epi& e);
+void launch_gemm_tile(const void* A, const void* W, int M, int N, int K, const Epi& e, hipStream_t s);
 // fp32 (ad_gemm_f32.hip): the same product, and the drafted tokens' scores with the same summation order
 // (`ln` only where gemm_f32_takes_ln says so)
 int launch_gemm_f32(const float* A, const float* W, int M, int N, int K, const Epi& e, hipStream_t s, const LnA& ln);

@@ -461,55 +461,27 @@ static int launch_astat(const bf16_t* A, const bf16_t* W, int M, int N, int K, c
     k_gemm_bf16_astat<MT, AMAX, SP, ONE, LNM, EMV, NW><<<grid, 64 * NW, lds, s>>>(A, W, M, N, K, per_wg, gx, chunks, ln.x, ln.g, ln.b, ln.y, e);
   };
   if constexpr (NW != 4) {   // the wide workgroups serve the layer GEMMs only
-    // (the combinations that occur with the pending LayerNorm and the epilogue as compile-time constants, as for the
+    // (with the pending LayerNorm and the epilogue as compile-time constants where the combination occurs, as for the
     // few-row kernels below: forward at 1152 rows 432.6 -> 425.6 us, at 720 rows 370.5 -> 366.5 us)
-    auto wide = [&](auto one_c, auto ln_c, auto em_c) {
-      constexpr bool ONE = decltype(one_c)::value;
-      constexpr int LNM = decltype(ln_c)::value, EMV = decltype(em_c)::value;
-      static size_t set_wide = 0;
-      if (lds > set_wide) {
-        (void)hipFuncSetAttribute((const void*)k_gemm_bf16_astat<MT, 0, SP, ONE, LNM, EMV, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        set_wide = lds;
-      }
-      k_gemm_bf16_astat<MT, 0, SP, ONE, LNM, EMV, NW><<<grid, 64 * NW, lds, s>>>(A, W, M, N, K, per_wg, gx, chunks, ln.x, ln.g, ln.b, ln.y, e);
-    };
     using L0 = std::integral_constant<int, 0>;
     using L1 = std::integral_constant<int, 1>;
-    using EQKV = std::integral_constant<int, EPI_QKV>;
-    using ERES = std::integral_constant<int, EPI_RESID>;
     if constexpr (NW == 16) {
-      if (K == 512 && ln.x && e.mode == EPI_QKV) { wide(std::true_type{}, L1{}, EQKV{}); return gx; }
-      if (K == 512 && !ln.x && e.mode == EPI_QKV) { wide(std::true_type{}, L0{}, EQKV{}); return gx; }
+      if (K == 512 && e.mode == EPI_QKV) fixed_variant(I0{}, L1{}, std::integral_constant<int, EPI_QKV>{}, std::true_type{});
+      else go(I0{}, std::true_type{});
     } else {
-      if (K == 512 && !ln.x && e.mode == EPI_RESID) { wide(std::true_type{}, L0{}, ERES{}); return gx; }
-      if (K == 2048 && !ln.x && e.mode == EPI_RESID) { wide(std::false_type{}, L0{}, ERES{}); return gx; }
+      if (e.mode == EPI_RESID) fixed_variant(I0{}, L0{}, std::integral_constant<int, EPI_RESID>{}, std::false_type{});
+      else go(I0{}, std::false_type{});
     }
-    if (K == 512) go(I0{}, std::true_type{});
-    else go(I0{}, std::false_type{});
     return gx;
   } else
   if (K == 512) {
     if (amax) go(I1{}, std::true_type{});
     else if (count) go(I3{}, std::true_type{});
-    else if constexpr (MT == 1 && SP == 2 && NW == 4) {
-      // FFN1 at many rows (forward at 1152 rows 424.6 -> 412.6 us; the same for the 32-row variant at 720 rows, for FFN2
-      // at 192..384 rows and for the many-row output projection measured no gain and was not kept)
-      if (ln.x && e.mode == EPI_RELU) fixed_variant(I0{}, std::integral_constant<int, 1>{}, std::integral_constant<int, EPI_RELU>{}, std::true_type{});
-      else go(I0{}, std::true_type{});
-    }
     else if constexpr (MT == 1 && SP == 1 && NW == 4) {
       // the layer GEMMs of the few-row regime: the pending LayerNorm (or none) and the epilogue mode as
       // compile-time constants, a kernel per combination that occurs (run-time branches around loads in
       // flight make the compiler wait for all of them: 0.1-0.2 us per launch)
-      auto hot = [&](auto ln_c, auto em_c) {
-        constexpr int LNM = decltype(ln_c)::value, EMV = decltype(em_c)::value;
-        static size_t set_hot = 0;
-        if (lds > set_hot) {
-          (void)hipFuncSetAttribute((const void*)k_gemm_bf16_astat<1, 0, 1, true, LNM, EMV>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-          set_hot = lds;
-        }
-        k_gemm_bf16_astat<1, 0, 1, true, LNM, EMV><<<grid, 256, lds, s>>>(A, W, M, N, K, per_wg, gx, chunks, ln.x, ln.g, ln.b, ln.y, e);
-      };
+      auto hot = [&](auto ln_c, auto em_c) { fixed_variant(I0{}, ln_c, em_c, std::true_type{}); };
       using L0 = std::integral_constant<int, 0>;
       using L1 = std::integral_constant<int, 1>;
       if (ln.x && e.mode == EPI_QKV) hot(L1{}, std::integral_constant<int, EPI_QKV>{});
@@ -595,44 +567,42 @@ int launch_gemm(int dtype, const void* A, const void* W, int M, int N, int K, co
   if (a_written) *a_written = true;
   LnA ln = ln_in;
   const bool streams = dtype == AD_BF16 && K <= 4096 && K % 512 == 0;   // the A-in-LDS kernel takes it
-  if (ln.x && !(dtype == AD_F32 ? gemm_f32_takes_ln(M, N, K, e) : streams && (K == 512 || K == 1024))) {
+  const bool tile = dtype == AD_BF16 && gemm_tile_takes(M, N, K, ln.x != nullptr, e);
+  if (ln.x && (tile || !(dtype == AD_F32 ? gemm_f32_takes_ln(M, N, K, e) : streams && (K == 512 || K == 1024)))) {
     launch_layernorm(dtype, ln.x, ln.g, ln.b, M, K, ln.y, const_cast<void*>(A), s);
     ln = LnA{};
+  }
+  if (tile) {
+    launch_gemm_tile(A, W, M, N, K, e, s);
+    return N / 16;
   }
   if (ln.x && a_written) *a_written = false;
   if (dtype == AD_BF16) {
     const int nb = (N / 16 + 3) / 4;
     if (K <= 4096 && K % 512 == 0) {
       const bf16_t *a = (const bf16_t*)A, *w = (const bf16_t*)W;
-      // up to 160 rows of a K of several slices, as they are: the slices side by side in the waves
-      // (measured, forward with this kernel up to 64 / 128 / 256 rows: base model 144 rows 253 / 253 / 249 us,
-      // 288 rows 285 / 286 / 285 us (293 us with a limit of 512); wide model 100 rows 365 / 352 / 352 us, 200 rows
-      // 430 / 430 / 477 us)
+      // up to 160 rows (K = 1024 and 4096: 128, gemm_tile_takes) of a K of several slices, as they are: the slices side by
+      // side in the waves (measured, forward with this kernel up to 64 / 128 / 256 rows: base model 144 rows
+      // 253 / 253 / 249 us, 288 rows 285 / 286 / 285 us; wide model 100 rows 365 / 352 / 352 us)
       if (M <= 160 && !ln.x && (K == 1024 || K == 2048 || K == 4096) && e.mode != EPI_ARGMAX && e.mode != EPI_COUNT) {
         launch_kchain(a, w, M, N, K, e, s);
         return N / 16;
       }
-      // Few rows (measured: up to 64 for the wide output projection, up to 1024 for the layer
-      // GEMMs: forward at 792..1008 rows 420-438 us this way, 431-449 us by the cost model below; from
-      // 1080 rows the other way round, 520 against 489 us): latency decides, so 16 rows per workgroup
-      // (32 from 520 rows, see below), one strip per wave, workgroups of four strips until the chip is
-      // covered (at most about 512 workgroups for the layer GEMMs); more rows are more row chunks of
-      // the same shape.
+      // Few rows (up to 64 for the wide output projection, up to 1024 for the layer GEMMs that do not take the tiled
+      // kernels): latency decides, so 16 rows per workgroup, one strip per wave, workgroups of four strips until the
+      // chip is covered (at most about 512 workgroups for the layer GEMMs); more rows are more row chunks of the same
+      // shape.
       const int mt = 1;
       const bool want_logits = e.mode == EPI_ARGMAX && e.logits != nullptr;
-      // 520 rows and more of the d = 512 layer GEMMs: 32 rows per workgroup in workgroups of 16 or 8 waves, one
-      // strip and one unit per 512-slice for each wave, while the launch stays within one round of the chip
-      // (a wave stages 2 or 4 rows instead of 8, and every wave's weights are requested at once; measured at
-      // 1152 rows: QKV with the LayerNorm 12.4 -> 9.6 us, attention output projections 7.0 -> 5.5 us, FFN2
-      // 12.9 -> 11.0 us; forward at 576 / 720 / 864 / 1008 / 1152 rows 372 / 411 / 425 / 453 / 517 ->
-      // 362 / 393 / 401 / 417 / 458 us, at 432 rows 321 -> 350 us the other way; FFN1's 128 strips would need
-      // two rounds and gained nothing in any shape tried, in one round of two 8-wave workgroups per CU either; K = 1024: drafter forward of the wide model at 626
-      // rows 983 -> 1073 us, so those shapes keep the rules below)
+      // 520 rows and more: 32 rows per workgroup in workgroups of 16 waves (K = 512 with the LayerNorm pending) or 8
+      // waves (K = 2048), one strip and one unit per 512-slice for each wave, while the launch stays within one round of
+      // the chip (a wave stages 2 or 4 rows instead of 8, and every wave's weights are requested at once; measured at
+      // 1152 rows: QKV with the LayerNorm 12.4 -> 9.6 us, FFN2 12.9 -> 11.0 us)
       if (M >= 520 && e.mode != EPI_ARGMAX && e.mode != EPI_COUNT) {
         const int n_strips = N / 16, chunks2 = (M + 31) / 32;
-        if (K == 512 && n_strips >= 64 && n_strips % 16 == 0 && (n_strips / 16) * chunks2 <= 256)
+        if (K == 512 && ln.x && n_strips >= 64 && n_strips % 16 == 0 && (n_strips / 16) * chunks2 <= 256)
           return launch_astat<2, 1, 16>(a, w, M, N, K, e, 16, s, ln);
-        if ((K == 512 || K == 2048) && !ln.x && n_strips % 8 == 0 && (n_strips / 8) * chunks2 <= 256)
+        if (K == 2048 && !ln.x && n_strips % 8 == 0 && (n_strips / 8) * chunks2 <= 256)
           return launch_astat<2, 1, 8>(a, w, M, N, K, e, 8, s, ln);
       }
       if ((M <= 64 || (M <= 1024 && N <= 4096) || want_logits) && astat_lds_bytes(mt, K) <= 150 * 1024) {
@@ -642,9 +612,8 @@ int launch_gemm(int dtype, const void* A, const void* W, int M, int N, int K, co
           // (measured at 33..64 rows of the wide output projection: 12-16 strips per workgroup, about 500
           // workgroups = one round on the chip, 9.0-9.6 us against 11-13 us with 8 strips)
           if (N <= 4096 || chunks > 2) per_wg = 4 * std::max(1, (n_strips * chunks + 4 * 512 - 1) / (4 * 512));
-          // wider K (measured at 400..700 rows of the d = 1024 shapes): at most 16 strips per workgroup while
-          // two workgroups fit a CU (more rounds beat longer workgroups); one round of 256 workgroups while
-          // the A tile leaves room for one only (K = 4096)
+          // wider K: at most 16 strips per workgroup while two workgroups fit a CU (more rounds beat longer
+          // workgroups); one round of 256 workgroups while the A tile leaves room for one only
           if (K > 512 && N <= 4096) {
             if (astat_lds_bytes(1, K) * 2 <= 160 * 1024) {
               per_wg = std::min(per_wg, 16);
@@ -664,17 +633,6 @@ int launch_gemm(int dtype, const void* A, const void* W, int M, int N, int K, co
             while (groups_of(pw) > 8 && groups_of(pw) % 8 != 0) pw += 4;
             return pw;
           };
-          // 520 rows and more (layer GEMMs only): 32 rows per workgroup, so that the weights cross from L2 to
-          // the CUs half as often (every 16-row chunk reads the whole matrix: at 576 rows x N 1536 that is
-          // 55 MB per launch, more than the launch takes to do anything else); below that the shorter staging
-          // of a 16-row tile wins (measured: 504 rows 347 / 362 us forward with 16 / 32 rows, 576 rows 387 / 374,
-          // 648 rows 408 / 399, 756 rows 416 / 416)
-          if (M >= 520 && e.mode != EPI_ARGMAX && e.mode != EPI_COUNT && astat_lds_bytes(2, K) <= 150 * 1024) {
-            const int chunks2 = (M + 31) / 32;
-            int pw2 = 4 * std::max(1, (n_strips * chunks2 + 4 * 512 - 1) / (4 * 512));
-            if (K > 512 && astat_lds_bytes(2, K) * 2 <= 160 * 1024) pw2 = std::min(pw2, 16);
-            return launch_astat<2, 1>(a, w, M, N, K, e, balanced(pw2), s, ln);
-          }
           return launch_astat<1, 1>(a, w, M, N, K, e, balanced(per_wg), s, ln);
         }
       } else {
