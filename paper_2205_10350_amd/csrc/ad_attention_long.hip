@@ -1,6 +1,6 @@
 // Attention for configurations with long key ranges (bf16, head width 64; the host selects it from the key capacity,
-// kLongKeys and more): a chunk of up to 64 query rows that sees 129..512 keys goes to the body in which the four waves
-// split the keys for all its row tiles (attn_split_tiles), everything else to the generic body (attn_block).
+// kLongKeys and more): up to 512 keys with keys and values staged once per 128 query rows (k_attention_rows), beyond that the
+// generic body (attn_block).
 // A source file, hence a code object, of its own: the attention kernels are larger than the instruction cache, and the
 // speed of the short-range ones, which are the batch-1 path, moved with every addition to their code object although
 // their own instructions stayed the same (0.5 us per launch at 1152 rows).
@@ -13,6 +13,188 @@
 
 namespace ad {
 
+// Up to 128 query rows of a (sequence, head), head width 64, at most 512 keys: keys and transposed values are staged in LDS
+// once per workgroup of eight waves (read from L2 by every wave, they were the bound: 41 us for eight sources of 301..512
+// tokens), and a wave takes 16 rows from the scores to the output.
+//  * The products are taken transposed, S^T = K Q^T and O^T = V^T P^T: a lane then holds one query row (lane % 16) and four
+//    consecutive keys of every key tile, so the whole score row stays in registers (NSB super-blocks of 128 keys, 32 registers
+//    each), the mask limit is one value per lane, and the probabilities become the right operand of the output product by
+//    two lane swaps per 32 keys (permlane32 / permlane16) instead of a trip through LDS.
+//  * Same order as attn_tiles_mfma<64, 16, true>: super-block sb adds into accumulator sb, the four are combined as
+//    (a0 + a1) + (a2 + a3); a row's denominator adds keys of equal key % 16 in ascending order, then pairs, quads, halves
+//    and rows of 16 as row16_sum does (four of the sixteen partial sums sit in each of four lanes).
+// Eight sources of 301..512 tokens, 16 heads: 25.7 us (54 us with the four waves of a 64-row chunk splitting the keys).
+constexpr int kRowsKeys = 512, kRowsKld = 64 + 16;   // most keys; row stride of the staged keys (32 bytes past a multiple of 64)
+template <int NSB>
+__device__ __forceinline__ void attn_rows_tile(const uint4 (&qf)[2], bf16_t* __restrict__ out, const SeqDesc sd, int row0, int row_end,
+                                               int h, int d, float scale, const bf16_t* Ks, const bf16_t* Vt, int ldv) {
+  constexpr int DH = 64;
+  const int lane = threadIdx.x & 63, r = lane & 15, kq = lane >> 4;
+  const int nkr = sd.causal ? sd.nk_base + row0 + r + 1 : sd.nk_base;   // keys this lane's row sees
+  const int nk_full = sd.causal ? sd.nk_base + row0 + 1 : sd.nk_base;   // keys every row of the tile sees
+  // the raw products: the scale, 1/8, is a power of two, so scaling them in the subtraction of the maximum rounds as
+  // scaling them first does
+  f32x4 S[NSB][8];
+  float m = -INFINITY;
+#pragma unroll
+  for (int sb = 0; sb < NSB; ++sb) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      f32x4 c = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const uint4 kf = *(const uint4*)(Ks + (128 * sb + 16 * j + r) * kRowsKld + 32 * s + 8 * kq);
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kf), __builtin_bit_cast(bf16x8, qf[s]), c, 0, 0, 0);
+      }
+      S[sb][j] = c;
+    }
+    if (128 * (sb + 1) > nk_full) {   // (the same for the whole wave: super-blocks every row sees whole need no mask)
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) S[sb][j][i] = 128 * sb + 16 * j + 4 * kq + i < nkr ? S[sb][j][i] : -INFINITY;
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) m = fmaxf(m, S[sb][j][i]);
+  }
+  {
+    auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+    m = fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+    p = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+    m = fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1])) * scale;
+  }
+  const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 O[2][4], psum[2];   // accumulators 2 h and 2 h + 1 of half h, combined when it ends
+  f32x4 Oh[2][4], ph[2];
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      psum[a] = zero;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) O[a][c] = zero;
+    }
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      const int sb = 2 * half + a;
+      if (sb < NSB) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          unsigned x[2][2];
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+            float p[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              p[i] = __builtin_amdgcn_exp2f(fmaf(S[sb < NSB ? sb : 0][2 * b + t][i], scale, -m) * 1.44269504088896340736f);
+              psum[a][i] += p[i];
+            }
+            x[t][0] = f2bf_pair(p[0], p[1]);
+            x[t][1] = f2bf_pair(p[2], p[3]);
+          }
+          uint4 pf;
+          {
+            auto u = __builtin_amdgcn_permlane32_swap(x[0][0], x[1][0], false, false);
+            auto w = __builtin_amdgcn_permlane16_swap(u[0], u[1], false, false);
+            pf.x = w[0]; pf.z = w[1];
+            u = __builtin_amdgcn_permlane32_swap(x[0][1], x[1][1], false, false);
+            w = __builtin_amdgcn_permlane16_swap(u[0], u[1], false, false);
+            pf.y = w[0]; pf.w = w[1];
+          }
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            const uint4 vf = *(const uint4*)(Vt + (16 * c + r) * ldv + 128 * sb + 32 * b + 8 * kq);
+            O[a][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf), __builtin_bit_cast(bf16x8, pf), O[a][c], 0, 0, 0);
+          }
+        }
+      }
+    }
+    ph[half] = psum[0] + psum[1];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) Oh[half][c] = O[0][c] + O[1][c];
+  }
+  const f32x4 ps = ph[0] + ph[1];
+  float l = (ps[0] + ps[1]) + (ps[2] + ps[3]);
+  {
+    auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(l), __float_as_uint(l), false, false);
+    l = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    p = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l), false, false);
+    l = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+  }
+  if (row0 + r < row_end) {
+    bf16_t* op = out + (size_t)(sd.q_row0 + row0 + r) * d + h * DH + 4 * kq;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const f32x4 o = Oh[0][c] + Oh[1][c];
+      gstore((uint2*)(op + 16 * c), uint2{f2bf_pair(o[0] / l, o[1] / l), f2bf_pair(o[2] / l, o[3] / l)});
+    }
+  }
+}
+__host__ __device__ inline size_t attn_rows_lds_bytes(int nk) {
+  const size_t nkp = (size_t)(nk + 127) / 128 * 128;
+  return (nkp * kRowsKld + 64 * (nkp + 16)) * 2;
+}
+__global__ __launch_bounds__(512) void k_attention_rows(const bf16_t* __restrict__ q, const bf16_t* __restrict__ Kb,
+                                                        const bf16_t* __restrict__ Vb, bf16_t* __restrict__ out,
+                                                        const SeqDesc* __restrict__ desc, int d, float scale) {
+  extern __shared__ uint4 att_rows_lds[];
+  const SeqDesc sd = desc[blockIdx.x];
+  const int row_begin = blockIdx.z * 128, h = blockIdx.y;
+  if (row_begin >= sd.nq) return;
+  const int row_end = min(sd.nq, row_begin + 128);
+  const int nk_all = min(sd.causal ? sd.nk_base + row_end : sd.nk_base, kRowsKeys);   // (the host promises the bound)
+  const int n_sb = (nk_all + 127) >> 7, nkp = 128 * n_sb, ldv = nkp + 16;
+  bf16_t* Ks = (bf16_t*)att_rows_lds;   // [nkp][kRowsKld]
+  bf16_t* Vt = Ks + nkp * kRowsKld;     // [64][ldv]
+  const int lane = threadIdx.x & 63, r = lane & 15, kq = lane >> 4;
+  const int row0 = row_begin + 16 * (threadIdx.x >> 6);
+  uint4 qf[2], kr[8], vr[8];
+  const bf16_t* qp = q + (size_t)(sd.q_row0 + min(row0 + r, row_end - 1)) * d + h * 64 + kq * 8;
+#pragma unroll
+  for (int s = 0; s < 2; ++s) qf[s] = ldg16(qp + 32 * s);
+  // keys: 16-byte pieces, eight per key; values: items of 8 keys x 8 channels, transposed in registers (keys past the last
+  // one: the last key again, masked below; values: zeros)
+  const int g = threadIdx.x & 7, t0 = (threadIdx.x >> 3) << 3;
+  const bf16_t* kg = Kb + (size_t)sd.kv_row0 * d + h * 64 + g * 8;
+  const bf16_t* vg = Vb + (size_t)sd.kv_row0 * d + h * 64 + g * 8;
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    if (64 * i < nkp) kr[i] = ldg16(kg + (size_t)min(64 * i + (int)(threadIdx.x >> 3), nk_all - 1) * d);
+  if (t0 < nkp) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) vr[i] = ldg16(vg + (size_t)min(t0 + i, nk_all - 1) * d);
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    if (64 * i < nkp) *(uint4*)(Ks + (64 * i + (threadIdx.x >> 3)) * kRowsKld + 8 * g) = kr[i];
+  if (t0 < nkp) {
+    unsigned in[8][4];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const bool there = t0 + i < nk_all;
+      in[i][0] = there ? vr[i].x : 0u; in[i][1] = there ? vr[i].y : 0u; in[i][2] = there ? vr[i].z : 0u; in[i][3] = there ? vr[i].w : 0u;
+    }
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      unsigned o[4];
+#pragma unroll
+      for (int pr = 0; pr < 4; ++pr) {
+        const unsigned lo = in[2 * pr][c >> 1], hi = in[2 * pr + 1][c >> 1];
+        o[pr] = (c & 1) ? __builtin_amdgcn_perm(hi, lo, 0x07060302u) : __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+      }
+      *(uint4*)(Vt + (size_t)(g * 8 + c) * ldv + t0) = uint4{o[0], o[1], o[2], o[3]};
+    }
+  }
+  __syncthreads();
+  if (row0 >= row_end) return;
+  if (n_sb == 1) attn_rows_tile<1>(qf, out, sd, row0, row_end, h, d, scale, Ks, Vt, ldv);
+  else if (n_sb == 2) attn_rows_tile<2>(qf, out, sd, row0, row_end, h, d, scale, Ks, Vt, ldv);
+  else if (n_sb == 3) attn_rows_tile<3>(qf, out, sd, row0, row_end, h, d, scale, Ks, Vt, ldv);
+  else attn_rows_tile<4>(qf, out, sd, row0, row_end, h, d, scale, Ks, Vt, ldv);
+}
+// key capacities beyond that
 __global__ __launch_bounds__(256) void k_attention_long(const bf16_t* __restrict__ q, const bf16_t* __restrict__ Kb,
                                                         const bf16_t* __restrict__ Vb, bf16_t* __restrict__ out,
                                                         const SeqDesc* __restrict__ desc, int d, float scale, int nk_cap) {
@@ -20,17 +202,22 @@ __global__ __launch_bounds__(256) void k_attention_long(const bf16_t* __restrict
   const SeqDesc sd = desc[blockIdx.x];
   const int row_begin = blockIdx.z * 64;
   if (row_begin >= sd.nq) return;
-  const int row_end = min(sd.nq, row_begin + 64);
-  const int nk_all = sd.causal ? sd.nk_base + row_end : sd.nk_base;
-  if (nk_all > 128 && nk_all <= 512) {
-    attn_split_tiles(q, Kb, Vb, out, sd, row_begin, row_end, blockIdx.y, d, scale, nk_all, (bf16_t*)att_long_lds);
-    return;
-  }
-  attn_block<64, true>(q, Kb, Vb, out, sd, row_begin, row_end, blockIdx.y, d, scale, att_long_lds, nk_cap);
+  attn_block<64, true>(q, Kb, Vb, out, sd, row_begin, min(sd.nq, row_begin + 64), blockIdx.y, d, scale, att_long_lds, nk_cap);
 }
 
 void launch_attention_long(const void* q, const void* K, const void* V, void* out, const SeqDesc* desc, dim3 grid, int d,
                            float scale, int max_keys, size_t lds_bytes, hipStream_t s) {
+  if (max_keys <= kRowsKeys) {
+    const size_t rows_bytes = attn_rows_lds_bytes(max_keys);
+    static size_t set_rows = 0;
+    if (rows_bytes > set_rows) {
+      (void)hipFuncSetAttribute((const void*)k_attention_rows, hipFuncAttributeMaxDynamicSharedMemorySize, (int)rows_bytes);
+      set_rows = rows_bytes;
+    }
+    grid.z = (grid.z + 1) / 2;   // (the caller's grid has chunks of 64 rows)
+    k_attention_rows<<<grid, 512, rows_bytes, s>>>((const bf16_t*)q, (const bf16_t*)K, (const bf16_t*)V, (bf16_t*)out, desc, d, scale);
+    return;
+  }
   static size_t set_for = 0;
   if (lds_bytes > set_for) {
     (void)hipFuncSetAttribute((const void*)k_attention_long, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);

@@ -19,6 +19,11 @@ __device__ __forceinline__ float bf2f(bf16_t v) { return __uint_as_float(((unsig
 __device__ __forceinline__ bf16_t f2bf(float f) {   // round to nearest, ties to even (the hardware conversion)
   return __builtin_bit_cast(bf16_t, (__bf16)f);
 }
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+__device__ __forceinline__ unsigned f2bf_pair(float lo, float hi) {   // two of them in one instruction
+  return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){lo, hi}, bf16x2));
+}
 // Memory accesses name the global address space explicitly: that keeps the compiler from falling
 // back to the slower flat instructions when it cannot see where a pointer came from.
 #define AD_GLOBAL __attribute__((address_space(1)))
@@ -369,21 +374,19 @@ __device__ __forceinline__ void argmax_row(const float* __restrict__ pv, const i
 //   pass 3  lane c accumulates output channel c over the keys in ascending order
 // LDS bytes needed: attn_lds_bytes().  (bf16 heads whose width is no multiple of 32; the others take attn_block_mfma,
 // the fp32 mode has ad_attention_f32.hip.)
-// (the key-split paths, attn_split_keys / attn_split_tiles: per wave a [64][kSplitLd] value tile and a [16][kSplitLd]
+// (the key-split path, attn_split_keys: per wave a [64][kSplitLd] value tile and a [16][kSplitLd]
 // probability tile)
 constexpr int kSplitLd = 128 + 16;                                   // row stride (elements): 32 bytes past a multiple of 64
 constexpr int kSplitWaveElems = (64 + 16) * kSplitLd;                // bf16 elements of a wave's two tiles
 constexpr int kSplitXchBytes = 4 * 16 * 4 + 4 * 64 * 16 + 4 * 4 * 64 * 16;   // attn_split_keys: maxima, denominators, partial outputs
-constexpr int kLongKeys = 256;   // key capacity from which the generic attention launch is the kernel that can split the keys
-constexpr int kSplitTilesBytes = 4 * kSplitWaveElems * 2 + 4 * 64 * 4;      // attn_split_tiles: the waves' tiles and the row maxima
+constexpr int kLongKeys = 256;   // key capacity from which the attention launches are those of ad_attention_long.hip
 __host__ __device__ inline size_t attn_lds_bytes(int nk_cap, int dh, int esz, int waves) {
   const size_t row_dwords = (size_t)dh * esz / 4 + 1;
   const size_t scalar_path = 2 * (size_t)nk_cap * row_dwords * 4 + 64 * (size_t)dh * 4 + (size_t)waves * nk_cap * 4;
   // matrix-core path: transposed values [dh][keys + 16] and one 16-row probability tile per wave
   // (row stride = 32 bytes past a multiple of 64: the 16-byte fragment reads meet no bank twice)
   const size_t ldv = (size_t)((nk_cap + 31) & ~31) + 16;
-  size_t mfma_path = ((size_t)dh + 16 * (size_t)waves) * ldv * 2;
-  if (dh == 64 && esz == 2 && nk_cap >= kLongKeys && mfma_path < (size_t)kSplitTilesBytes) mfma_path = kSplitTilesBytes;
+  const size_t mfma_path = ((size_t)dh + 16 * (size_t)waves) * ldv * 2;
   return scalar_path > mfma_path ? scalar_path : mfma_path;
 }
 
@@ -527,7 +530,7 @@ __device__ __forceinline__ void attn_tiles_mfma(const bf16_t* __restrict__ q, co
     // 128 keys (NT = 16): the keys are taken in super-blocks of 128, super-block sb adds into accumulator sb % 4 (output
     // sums and denominators alike, ascending inside an accumulator), and the four are combined as (a0 + a1) + (a2 + a3)
     // at the end.  The order depends on the key index alone, so the kernels that give the four accumulators to four
-    // waves (attn_split_keys, attn_split_tiles) produce the same bits; with at most 128 keys there is one chain.
+    // waves (attn_split_keys) or keep a row in one (attn_rows_tile) produce the same bits; with at most 128 keys there is one chain.
     // Otherwise one chain for any key count: no kernel of such a configuration splits the keys, and the short-range
     // kernels, the batch-1 path, stay as small as they were (the four accumulator sets alone cost their launches
     // 0.3 us each, forward at 25 rows 186.6 -> 188.4 us, although that code never ran).
@@ -931,143 +934,6 @@ __device__ __forceinline__ void attn_split_keys(const uint4 (&qf)[2], const uint
   for (int i = 0; i < 4; ++i) {
     const int row = row_begin + 4 * kq + i;
     if (row < row_end) Store<bf16_t>::store(out + (size_t)(sd.q_row0 + row) * d + h * DH + 16 * wave + r, o[i] / l[i]);
-  }
-}
-// Up to four 16-row tiles (one per wave in the other kernels) against 129..512 keys, head width 64, four waves: the split
-// of attn_split_keys for every row tile of the chunk.  Wave w owns super-block w: its key fragments are fetched once
-// and multiply the queries of all tiles; the row maxima of all tiles cross LDS behind one barrier; then, tile by tile,
-// exponentials, probabilities (the wave's own LDS tile), output product against the wave's own transposed values.
-// Behind a second barrier the partial outputs and denominators go through LDS (over the tiles, which nobody reads any
-// more) and wave c combines and stores channel block c of every tile.  Keys and values cross from memory once per
-// workgroup instead of once (values) and twice (keys) per wave.  Same bits as attn_tiles_mfma<64, 16>.
-__device__ __forceinline__ void attn_split_tiles(const bf16_t* __restrict__ q, const bf16_t* __restrict__ Kb,
-                                                 const bf16_t* __restrict__ Vb, bf16_t* __restrict__ out, const SeqDesc sd,
-                                                 int row_begin, int row_end, int h, int d, float scale, int nk_all,
-                                                 bf16_t* lds) {
-  constexpr int DH = 64, CT = 4, LD = kSplitLd;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int r = lane & 15, kq = lane >> 4;
-  const int nt = (row_end - row_begin + 15) >> 4;     // 1..4 row tiles
-  bf16_t* Vw = lds + wave * kSplitWaveElems;          // [64][LD]
-  bf16_t* Pw = Vw + 64 * LD;                          // [16][LD]
-  float* xmax = (float*)(lds + 4 * kSplitWaveElems);  // [4 waves][64 rows]
-  f32x4* xout = (f32x4*)lds;                          // [(wave * 4 + tile) * 4 + channel block][64 lanes], over the tiles
-  f32x4* xsum = xout + 4 * 4 * 4 * 64;                // [wave * 4 + tile][64 lanes]
-  const int n_sb = (nk_all + 127) >> 7;
-  const bool mine = wave < n_sb;
-  uint4 kf[8][2];
-  split_request_keys(Kb, sd, h, d, nk_all, wave, kf);
-  uint4 qf[4][2];
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const int row = min(row_begin + 16 * min(t, nt - 1) + r, row_end - 1);
-    const bf16_t* qp = q + (size_t)(sd.q_row0 + row) * d + h * DH + kq * 8;
-#pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2) qf[t][s2] = ldg16(qp + 32 * s2);
-  }
-  f32x4 S[4][8];
-  float m[4][4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) m[t][i] = -INFINITY;
-    if (mine && t < nt) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        S[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2)
-          S[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, qf[t][s2]), __builtin_bit_cast(bf16x8, kf[j][s2]), S[t][j], 0, 0, 0);
-        const int key = 128 * wave + 16 * j + r;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int nkr = sd.causal ? sd.nk_base + row_begin + 16 * t + 4 * kq + i + 1 : sd.nk_base;
-          S[t][j][i] = key < nkr ? S[t][j][i] * scale : -INFINITY;
-          m[t][i] = fmaxf(m[t][i], S[t][j][i]);
-        }
-      }
-    }
-  }
-  uint4 vraw[2][8];
-  split_request_values(Vb, sd, h, d, nk_all, wave, vraw);
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) m[t][i] = row16_max(m[t][i]);
-  if (r == 0) {
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) xmax[wave * 64 + 16 * t + 4 * kq + i] = m[t][i];
-  }
-  __syncthreads();
-  f32x4 O[4][CT];
-  f32x4 psum[4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    psum[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int c = 0; c < CT; ++c) O[t][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
-  if (mine) {
-    split_stage_values(vraw, Vw, wave, nk_all);
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      if (t < nt) {
-        float mx[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int row = 16 * t + 4 * kq + i;
-          mx[i] = fmaxf(fmaxf(xmax[row], xmax[64 + row]), fmaxf(xmax[128 + row], xmax[192 + row]));
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float pv = __builtin_amdgcn_exp2f((S[t][j][i] - mx[i]) * 1.44269504088896340736f);
-            psum[t][i] += pv;
-            Pw[(4 * kq + i) * LD + r + 16 * j] = f2bf(pv);
-          }
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb) {
-          const uint4 pa = *(const uint4*)(Pw + r * LD + 32 * kb + 8 * kq);
-          uint4 vb[CT];
-#pragma unroll
-          for (int c = 0; c < CT; ++c) vb[c] = *(const uint4*)(Vw + (16 * c + r) * LD + 32 * kb + 8 * kq);
-#pragma unroll
-          for (int c = 0; c < CT; ++c)
-            O[t][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pa), __builtin_bit_cast(bf16x8, vb[c]), O[t][c], 0, 0, 0);
-        }
-        __builtin_amdgcn_wave_barrier();   // the probability tile is reused by the next row tile
-      }
-    }
-  }
-  __syncthreads();   // every wave is done with its tiles: the exchange area lies over them
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    if (t < nt) {
-#pragma unroll
-      for (int c = 0; c < CT; ++c) xout[((wave * 4 + t) * 4 + c) * 64 + lane] = O[t][c];
-      xsum[(wave * 4 + t) * 64 + lane] = psum[t];
-    }
-  }
-  __syncthreads();
-  // wave c: channel block c of every tile
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    if (t < nt) {
-      const f32x4 o = (xout[((0 * 4 + t) * 4 + wave) * 64 + lane] + xout[((1 * 4 + t) * 4 + wave) * 64 + lane]) +
-                      (xout[((2 * 4 + t) * 4 + wave) * 64 + lane] + xout[((3 * 4 + t) * 4 + wave) * 64 + lane]);
-      const f32x4 sm = (xsum[(0 * 4 + t) * 64 + lane] + xsum[(1 * 4 + t) * 64 + lane]) +
-                       (xsum[(2 * 4 + t) * 64 + lane] + xsum[(3 * 4 + t) * 64 + lane]);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float l = row16_sum(sm[i]);
-        const int row = row_begin + 16 * t + 4 * kq + i;
-        if (row < row_end) Store<bf16_t>::store(out + (size_t)(sd.q_row0 + row) * d + h * DH + 16 * wave + r, o[i] / l);
-      }
-    }
   }
 }
 template <int DH, bool LONGK = false>

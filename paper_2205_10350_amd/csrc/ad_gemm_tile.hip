@@ -61,8 +61,7 @@ __device__ __forceinline__ void tile_apply(const Epi& e, const f32x4 (&acc)[MT],
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = fmaxf(v[i], 0.f);
       }
-      const uint2 w = uint2{(unsigned)f2bf(v[0]) | ((unsigned)f2bf(v[1]) << 16), (unsigned)f2bf(v[2]) | ((unsigned)f2bf(v[3]) << 16)};
-      gstore((uint2*)(base + (size_t)g.res[t].x * ld), w);
+      gstore((uint2*)(base + (size_t)g.res[t].x * ld), uint2{f2bf_pair(v[0], v[1]), f2bf_pair(v[2], v[3])});
     }
   }
 }
