@@ -25,7 +25,7 @@ namespace ad {
 //    and rows of 16 as row16_sum does (four of the sixteen partial sums sit in each of four lanes).
 // Eight sources of 301..512 tokens, 16 heads: 25.7 us (54 us with the four waves of a 64-row chunk splitting the keys).
 constexpr int kRowsKeys = 512, kRowsKld = 64 + 16;   // most keys; row stride of the staged keys (32 bytes past a multiple of 64)
-template <int NSB>
+template <int NSB, bool LONGK>
 __device__ __forceinline__ void attn_rows_tile(const uint4 (&qf)[2], bf16_t* __restrict__ out, const SeqDesc sd, int row0, int row_end,
                                                int h, int d, float scale, const bf16_t* Ks, const bf16_t* Vt, int ldv) {
   constexpr int DH = 64;
@@ -66,57 +66,52 @@ __device__ __forceinline__ void attn_rows_tile(const uint4 (&qf)[2], bf16_t* __r
     m = fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1])) * scale;
   }
   const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
-  f32x4 O[2][4], psum[2];   // accumulators 2 h and 2 h + 1 of half h, combined when it ends
-  f32x4 Oh[2][4], ph[2];
+  f32x4 O[LONGK ? 4 : 1][4], psum[LONGK ? 4 : 1];
 #pragma unroll
-  for (int half = 0; half < 2; ++half) {
+  for (int a = 0; a < (LONGK ? 4 : 1); ++a) {
+    psum[a] = zero;
 #pragma unroll
-    for (int a = 0; a < 2; ++a) {
-      psum[a] = zero;
+    for (int c = 0; c < 4; ++c) O[a][c] = zero;
+  }
 #pragma unroll
-      for (int c = 0; c < 4; ++c) O[a][c] = zero;
-    }
+  for (int sb = 0; sb < NSB; ++sb) {
+    const int a = LONGK ? sb : 0;
 #pragma unroll
-    for (int a = 0; a < 2; ++a) {
-      const int sb = 2 * half + a;
-      if (sb < NSB) {
+    for (int b = 0; b < 4; ++b) {
+      unsigned x[2][2];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          unsigned x[2][2];
+      for (int t = 0; t < 2; ++t) {
+        float p[4];
 #pragma unroll
-          for (int t = 0; t < 2; ++t) {
-            float p[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              p[i] = __builtin_amdgcn_exp2f(fmaf(S[sb < NSB ? sb : 0][2 * b + t][i], scale, -m) * 1.44269504088896340736f);
-              psum[a][i] += p[i];
-            }
-            x[t][0] = f2bf_pair(p[0], p[1]);
-            x[t][1] = f2bf_pair(p[2], p[3]);
-          }
-          uint4 pf;
-          {
-            auto u = __builtin_amdgcn_permlane32_swap(x[0][0], x[1][0], false, false);
-            auto w = __builtin_amdgcn_permlane16_swap(u[0], u[1], false, false);
-            pf.x = w[0]; pf.z = w[1];
-            u = __builtin_amdgcn_permlane32_swap(x[0][1], x[1][1], false, false);
-            w = __builtin_amdgcn_permlane16_swap(u[0], u[1], false, false);
-            pf.y = w[0]; pf.w = w[1];
-          }
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            const uint4 vf = *(const uint4*)(Vt + (16 * c + r) * ldv + 128 * sb + 32 * b + 8 * kq);
-            O[a][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf), __builtin_bit_cast(bf16x8, pf), O[a][c], 0, 0, 0);
-          }
+        for (int i = 0; i < 4; ++i) {
+          p[i] = __builtin_amdgcn_exp2f(fmaf(S[sb][2 * b + t][i], scale, -m) * 1.44269504088896340736f);
+          psum[a][i] += p[i];
         }
+        x[t][0] = f2bf_pair(p[0], p[1]);
+        x[t][1] = f2bf_pair(p[2], p[3]);
+      }
+      uint4 pf;
+      {
+        auto u = __builtin_amdgcn_permlane32_swap(x[0][0], x[1][0], false, false);
+        auto w = __builtin_amdgcn_permlane16_swap(u[0], u[1], false, false);
+        pf.x = w[0]; pf.z = w[1];
+        u = __builtin_amdgcn_permlane32_swap(x[0][1], x[1][1], false, false);
+        w = __builtin_amdgcn_permlane16_swap(u[0], u[1], false, false);
+        pf.y = w[0]; pf.w = w[1];
+      }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const uint4 vf = *(const uint4*)(Vt + (16 * c + r) * ldv + 128 * sb + 32 * b + 8 * kq);
+        O[a][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf), __builtin_bit_cast(bf16x8, pf), O[a][c], 0, 0, 0);
       }
     }
-    ph[half] = psum[0] + psum[1];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) Oh[half][c] = O[0][c] + O[1][c];
   }
-  const f32x4 ps = ph[0] + ph[1];
-  float l = (ps[0] + ps[1]) + (ps[2] + ps[3]);
+  if constexpr (LONGK) {
+    psum[0] = (psum[0] + psum[1]) + (psum[2] + psum[3]);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) O[0][c] = (O[0][c] + O[1][c]) + (O[2][c] + O[3][c]);
+  }
+  float l = (psum[0][0] + psum[0][1]) + (psum[0][2] + psum[0][3]);
   {
     auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(l), __float_as_uint(l), false, false);
     l = __uint_as_float(p[0]) + __uint_as_float(p[1]);
@@ -127,7 +122,7 @@ __device__ __forceinline__ void attn_rows_tile(const uint4 (&qf)[2], bf16_t* __r
     bf16_t* op = out + (size_t)(sd.q_row0 + row0 + r) * d + h * DH + 4 * kq;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      const f32x4 o = Oh[0][c] + Oh[1][c];
+      const f32x4 o = O[0][c];
       gstore((uint2*)(op + 16 * c), uint2{f2bf_pair(o[0] / l, o[1] / l), f2bf_pair(o[2] / l, o[3] / l)});
     }
   }
@@ -136,6 +131,9 @@ __host__ __device__ inline size_t attn_rows_lds_bytes(int nk) {
   const size_t nkp = (size_t)(nk + 127) / 128 * 128;
   return (nkp * kRowsKld + 64 * (nkp + 16)) * 2;
 }
+// LONGK: the order of configurations whose key capacity is kLongKeys or more; otherwise one chain for all keys, as in the
+// other kernels of such configurations (at most kLongKeys keys then).
+template <bool LONGK>
 __global__ __launch_bounds__(512) void k_attention_rows(const bf16_t* __restrict__ q, const bf16_t* __restrict__ Kb,
                                                         const bf16_t* __restrict__ Vb, bf16_t* __restrict__ out,
                                                         const SeqDesc* __restrict__ desc, int d, float scale) {
@@ -144,7 +142,7 @@ __global__ __launch_bounds__(512) void k_attention_rows(const bf16_t* __restrict
   const int row_begin = blockIdx.z * 128, h = blockIdx.y;
   if (row_begin >= sd.nq) return;
   const int row_end = min(sd.nq, row_begin + 128);
-  const int nk_all = min(sd.causal ? sd.nk_base + row_end : sd.nk_base, kRowsKeys);   // (the host promises the bound)
+  const int nk_all = min(sd.causal ? sd.nk_base + row_end : sd.nk_base, LONGK ? kRowsKeys : kLongKeys);   // (the host promises the bound)
   const int n_sb = (nk_all + 127) >> 7, nkp = 128 * n_sb, ldv = nkp + 16;
   bf16_t* Ks = (bf16_t*)att_rows_lds;   // [nkp][kRowsKld]
   bf16_t* Vt = Ks + nkp * kRowsKld;     // [64][ldv]
@@ -189,10 +187,11 @@ __global__ __launch_bounds__(512) void k_attention_rows(const bf16_t* __restrict
   }
   __syncthreads();
   if (row0 >= row_end) return;
-  if (n_sb == 1) attn_rows_tile<1>(qf, out, sd, row0, row_end, h, d, scale, Ks, Vt, ldv);
-  else if (n_sb == 2) attn_rows_tile<2>(qf, out, sd, row0, row_end, h, d, scale, Ks, Vt, ldv);
-  else if (n_sb == 3) attn_rows_tile<3>(qf, out, sd, row0, row_end, h, d, scale, Ks, Vt, ldv);
-  else attn_rows_tile<4>(qf, out, sd, row0, row_end, h, d, scale, Ks, Vt, ldv);
+  auto tile = [&](auto n_c) { attn_rows_tile<decltype(n_c)::value, LONGK>(qf, out, sd, row0, row_end, h, d, scale, Ks, Vt, ldv); };
+  if (n_sb == 1) tile(std::integral_constant<int, 1>{});
+  else if (!LONGK || n_sb == 2) tile(std::integral_constant<int, 2>{});
+  else if (n_sb == 3) tile(std::integral_constant<int, 3>{});
+  else tile(std::integral_constant<int, 4>{});
 }
 // key capacities beyond that
 __global__ __launch_bounds__(256) void k_attention_long(const bf16_t* __restrict__ q, const bf16_t* __restrict__ Kb,
@@ -209,13 +208,18 @@ void launch_attention_long(const void* q, const void* K, const void* V, void* ou
                            float scale, int max_keys, size_t lds_bytes, hipStream_t s) {
   if (max_keys <= kRowsKeys) {
     const size_t rows_bytes = attn_rows_lds_bytes(max_keys);
-    static size_t set_rows = 0;
-    if (rows_bytes > set_rows) {
-      (void)hipFuncSetAttribute((const void*)k_attention_rows, hipFuncAttributeMaxDynamicSharedMemorySize, (int)rows_bytes);
-      set_rows = rows_bytes;
-    }
     grid.z = (grid.z + 1) / 2;   // (the caller's grid has chunks of 64 rows)
-    k_attention_rows<<<grid, 512, rows_bytes, s>>>((const bf16_t*)q, (const bf16_t*)K, (const bf16_t*)V, (bf16_t*)out, desc, d, scale);
+    auto go = [&](auto long_c) {
+      constexpr bool LONGK = decltype(long_c)::value;
+      static size_t set_rows = 0;
+      if (rows_bytes > set_rows) {
+        (void)hipFuncSetAttribute((const void*)k_attention_rows<LONGK>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)rows_bytes);
+        set_rows = rows_bytes;
+      }
+      k_attention_rows<LONGK><<<grid, 512, rows_bytes, s>>>((const bf16_t*)q, (const bf16_t*)K, (const bf16_t*)V, (bf16_t*)out, desc, d, scale);
+    };
+    if (max_keys >= kLongKeys) go(std::true_type{});
+    else go(std::false_type{});
     return;
   }
   static size_t set_for = 0;

@@ -738,14 +738,13 @@ void launch_attention(int dtype, const void* q, const void* K, const void* V, vo
     k_attention_small<<<dim3(n_seq, H, 1), 256, sh, s>>>((const bf16_t*)q, (const bf16_t*)K, (const bf16_t*)V, (bf16_t*)out, desc, H * dh, scale);
     return;
   }
-  if (dh == 64 && max_keys >= kLongKeys) {   // long key ranges: a kernel in a code object of its own
+  if (dh == 64) {   // everything beyond that: kernels in a code object of their own
     launch_attention_long(q, K, V, out, desc, g, H * dh, scale, max_keys, sh, s);
     return;
   }
   switch (dh) {
     case 16: AD_ATT(16); break;
     case 32: AD_ATT(32); break;
-    case 64: AD_ATT(64); break;
     default: AD_ATT(128); break;
   }
 #undef AD_ATT
