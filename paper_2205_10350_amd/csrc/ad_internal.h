@@ -88,6 +88,10 @@ int launch_gemm(int dtype, const void* A, const void* W, int M, int N, int K, co
 // bf16, many rows (ad_gemm_tile.hip): which products go there, and their launch (A as rows, no LayerNorm)
 bool gemm_tile_takes(int M, int N, int K, bool has_ln, const Epi& e);
 void launch_gemm_tile(const void* A, const void* W, int M, int N, int K, const Epi& e, hipStream_t s);
+// bf16, few rows (ad_gemm_few.hip): K of 1024, 2048 or 4096 shared by the waves, rows as they are; K = 1024 with the
+// LayerNorm pending (false = not covered)
+void launch_kchain(const void* A, const void* W, int M, int N, int K, const Epi& e, hipStream_t s);
+bool launch_lnchain(const void* W, int M, int N, int K, const Epi& e, hipStream_t s, const LnA& ln);
 // fp32 (ad_gemm_f32.hip): the same product, and the drafted tokens' scores with the same summation order
 // (`ln` only where gemm_f32_takes_ln says so)
 int launch_gemm_f32(const float* A, const float* W, int M, int N, int K, const Epi& e, hipStream_t s, const LnA& ln);

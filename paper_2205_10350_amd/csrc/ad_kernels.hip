@@ -498,69 +498,6 @@ static int launch_astat(const bf16_t* A, const bf16_t* W, int M, int N, int K, c
   return gx;
 }
 
-// ---------------------------------------------------------------- few rows, K of several 512-slices
-// C = A . W^T for up to 160 rows when K is 1024, 2048 or 4096 and no LayerNorm is pending (FFN2, the
-// attention output projections of the wide model).  The A-in-LDS kernel above walks a strip's
-// 512-slices one after the other in one wave, a round trip to memory per slice.  Here a workgroup
-// owns one 16-column strip of one 16-row chunk and its wave w owns the slices w, w + 4, ...: every
-// wave requests its slice of the rows (into an LDS tile of its own: no barrier before the first
-// MFMA; fragments requested straight from the row-major rows, 16 rows x 64 bytes per wave
-// instruction, measured 1 us slower per launch) and of the weights at once, so the workgroup waits
-// for memory once.  The sum itself stays one chain: the accumulators go from
-// wave to wave through LDS in slice order (k ascending, 32 at a time, one accumulator per element:
-// the same bits as every other GEMM kernel here), and the wave of the last slice runs the epilogue.
-// a 512-slice of 16 rows into a wave's LDS tile (one row per wave instruction, 16 bytes per lane)
-// and of a strip's weights into registers; all requests before the first LDS store
-__device__ __forceinline__ void kchain_request(const bf16_t* __restrict__ A, const bf16_t* __restrict__ wp, bf16_t* At,
-                                               int m0, int M, int K, int slice, int lane, uint4 (&b)[16]) {
-  constexpr int LD = 512 + 16;
-  uint4 av[16];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) av[i] = *(const uint4*)(A + (size_t)min(m0 + i, M - 1) * K + slice * 512 + lane * 8);
-#pragma unroll
-  for (int u = 0; u < 16; ++u) b[u] = *(const uint4*)(wp + (size_t)slice * 8192 + u * 512);
-#pragma unroll
-  for (int i = 0; i < 16; ++i) *(uint4*)(At + i * LD + lane * 8) = av[i];
-}
-template <int NS>
-__global__ __launch_bounds__(256) void k_gemm_bf16_kchain(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
-                                                         int M, int N, int K, int n_strips, Epi e) {
-  constexpr int LD = 512 + 16;               // row stride of a wave's tile (elements): see the kernel above
-  __shared__ uint4 tiles[4 * 16 * LD / 8];   // [wave][16 rows][LD]: each wave stages its own slice, no barrier
-  __shared__ f32x4 hand[64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int r = lane & 15, kq = lane >> 4;
-  const int strip = blockIdx.x % n_strips, m0 = (blockIdx.x / n_strips) * 16, n0 = strip << 4;
-  bf16_t* At = (bf16_t*)tiles + wave * 16 * LD;
-  const bf16_t* a_lane = At + r * LD + kq * 8;
-  const bf16_t* wp = W + (size_t)n0 * K + lane * 8;
-  uint4 b[16];
-  if (wave < NS) kchain_request(A, wp, At, m0, M, K, wave, lane, b);
-  constexpr int LAST = (NS - 1) & 3;
-  EpiRegs<1> g;
-  if (wave == LAST) epi_preload<1>(e, 1, m0, n0, M, N, lane, g);
-  f32x4 acc[1] = {f32x4{0.f, 0.f, 0.f, 0.f}};
-#pragma unroll
-  for (int p = 0; p < NS; ++p) {
-    if (wave == (p & 3)) {
-      if (p > 0) acc[0] = hand[lane];
-#pragma unroll
-      for (int u = 0; u < 16; ++u)
-        acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, *(const uint4*)(a_lane + 32 * u)), __builtin_bit_cast(bf16x8, b[u]), acc[0], 0, 0, 0);
-      if (p + 1 < NS) hand[lane] = acc[0];
-      if (p + 4 < NS) kchain_request(A, wp, At, m0, M, K, p + 4, lane, b);
-    }
-    if (p + 1 < NS) __syncthreads();
-  }
-  if (wave == LAST) epi_apply<bf16_t, 1>(e, acc, g, 1, m0, n0, M, N, lane);
-}
-static void launch_kchain(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epi& e, hipStream_t s) {
-  const int n_strips = N / 16, grid = n_strips * ((M + 15) / 16);
-  if (K == 1024) k_gemm_bf16_kchain<2><<<grid, 256, 0, s>>>(A, W, M, N, K, n_strips, e);
-  else if (K == 2048) k_gemm_bf16_kchain<4><<<grid, 256, 0, s>>>(A, W, M, N, K, n_strips, e);
-  else k_gemm_bf16_kchain<8><<<grid, 256, 0, s>>>(A, W, M, N, K, n_strips, e);
-}
-
 int launch_gemm(int dtype, const void* A, const void* W, int M, int N, int K, const Epi& e, hipStream_t s,
                 const LnA& ln_in, bool* a_written) {
   if (M <= 0) return 0;
@@ -588,6 +525,7 @@ int launch_gemm(int dtype, const void* A, const void* W, int M, int N, int K, co
         launch_kchain(a, w, M, N, K, e, s);
         return N / 16;
       }
+      if (launch_lnchain(w, M, N, K, e, s, ln)) return N / 16;
       // Few rows (up to 64 for the wide output projection, up to 1024 for the layer GEMMs that do not take the tiled
       // kernels): latency decides, so 16 rows per workgroup, one strip per wave, workgroups of four strips until the
       // chip is covered (at most about 512 workgroups for the layer GEMMs); more rows are more row chunks of the same
