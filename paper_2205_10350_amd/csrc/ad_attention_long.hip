@@ -234,8 +234,8 @@ void launch_attention_long(const void* q, const void* K, const void* V, void* ou
 // Cross-attention with its query projection for a source capacity of kLongKeys or more (head width 64, d 512 or 1024,
 // bf16: launch_crossq_attention has checked that and chosen the rows per workgroup).  One row tile per workgroup: the
 // waves split the keys (k_crossq_attention_split); several: every wave walks all keys with the four accumulators
-// (k_crossq_attention<.., LONGK = true>).  false: the tiles do not fit in LDS, the caller launches projection and
-// attention separately.
+// (k_crossq_attention<.., LONGK = true>).  false: the tiles do not fit in LDS or two launches are faster, the caller launches
+// projection and attention separately.
 bool launch_crossq_attention_long(const LnA& ln, const void* A, const void* W, const float* bias, const void* K, const void* V,
                                   void* out, const SeqDesc* desc, int n_seq, int max_rows, int H, int chunk, int max_keys,
                                   hipStream_t s) {
@@ -260,6 +260,12 @@ bool launch_crossq_attention_long(const LnA& ln, const void* A, const void* W, c
     else go(std::integral_constant<int, 4>{});
     return true;
   }
+  // Model width 1024: projection and k_attention_rows as two launches are faster (a workgroup here reads 128 KB of the query
+  // matrix and stages one head's values for 32 or 64 rows, k_attention_rows for 128 with twice the waves).  Verify forward, one
+  // launch / two, us: 8 x 40 rows 555 / 498, 16 x 25 rows 588 / 525, 4 x 72 rows 539 / 488 (512 source tokens), 479 / 469 for
+  // 16 x 25 rows of 100; drafter forward, 8 sources of 512, 502 / 451.  Width 512 goes on with one: half the matrix, and 16 x 40 rows
+  // take 409 / 368 with 512 source tokens but 324 / 334 with 100.
+  if (d == 1024 && max_keys <= kRowsKeys) return false;
   const size_t sh = crossq_lds_bytes(max_keys, mt, d);
   if (sh > 160 * 1024) return false;
   if (n_seq <= 0 || max_rows <= 0) return true;
