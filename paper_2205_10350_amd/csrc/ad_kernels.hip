@@ -580,6 +580,23 @@ int launch_gemm(int dtype, const void* A, const void* W, int M, int N, int K, co
         const float c1 = astat_plan(1, M, N, K, ln.x != nullptr, &pw[0]);
         const float c2 = K <= 2048 ? astat_plan(2, M, N, K, ln.x != nullptr, &pw[1]) : 1e30f;
         const float c4 = K <= 1024 ? astat_plan(4, M, N, K, ln.x != nullptr, &pw[2]) : 1e30f;
+        // The output projection: 32 rows up to 192, 64 beyond (every row chunk reads the matrix from L2), and with at most four
+        // chunks as many strips as make it one workgroup per CU.  Measured against the model's choice, matrix from memory /
+        // from the last-level cache, us: K = 512, 96 rows 17.6 / 12.8 (16 rows a workgroup) -> 15.2 / 10.8, 128 rows 20.4 /
+        // 14.6 -> 15.2 / 11.5, 256 rows 22.3 / 17.5 (32 rows) -> 19.7 / 17.1, 400 rows 32.8 / 26.0 -> 26.9 / 24.3; K = 1024,
+        // 136 rows 38.1 / 29.3 (16) -> 30.1 / 23.3, 200 rows 36.3 / 28.8 (32) -> 31.5 / 26.4, 300 rows 44.7 / 36.0 ->
+        // 38.4 / 33.3.  The line: 160 rows of K = 1024 in 64-row workgroups 31.6 / 25.7, in 32-row ones 30.5 / 23.4; 192 rows
+        // 31.5 / 26.0 and 33.0 / 26.1.
+        if (K <= 1024 && (e.mode == EPI_ARGMAX || e.mode == EPI_COUNT)) {
+          const int mt_v = M <= 192 ? 2 : 4, chunks = (M + 16 * mt_v - 1) / (16 * mt_v), n_strips = N / 16;
+          int per_wg = mt_v == 2 ? pw[1] : pw[2];
+          if (chunks <= 4) {
+            auto per_xcd = [&](int x) { return ((n_strips + x - 1) / x + 7) / 8 * chunks; };
+            per_wg = 8;
+            while (per_wg < n_strips && per_xcd(per_wg) > 32) per_wg += 8;
+          }
+          return mt_v == 2 ? launch_astat<2, 2>(a, w, M, N, K, e, per_wg, s, ln) : launch_astat<4, 2>(a, w, M, N, K, e, per_wg, s, ln);
+        }
         if (c4 <= c2 && c4 <= c1) return launch_astat<4, 2>(a, w, M, N, K, e, pw[2], s, ln);
         if (c2 <= c1) return launch_astat<2, 2>(a, w, M, N, K, e, pw[1], s, ln);
         return launch_astat<1, 2>(a, w, M, N, K, e, pw[0], s, ln);
@@ -710,8 +727,8 @@ bool launch_crossq_attention(int dtype, const LnA& ln, const void* A, const void
   // (measured forward times, base model, 16 / 32 / 64 rows per workgroup; batch x rows:
   //  1 x 25: 237 / 248 / 247 us, 1 x 64: 243 / 254 / 271, 8 x 36: 288 / 298 / 306, 12 x 36: 354 / 332 / 342,
   //  16 x 36: 434 / 409 / 418, 24 x 36: 477 / 455 / 431, 32 x 36: 535 / 514 / 487)
-  // (Where the tiles of a 64-row chunk do not fit in LDS, 512-token sources of the wide model, the projection and the
-  // attention stay two launches: 32-row chunks would fit and measured slower, drafter forward at 626 rows 957 -> 1051 us.)
+  // (The wide model with a long source capacity and more than one row tile per workgroup: two launches,
+  // launch_crossq_attention_long.)
   const int chunk = n_seq * H * ((max_rows + 15) / 16) <= 256 ? 16 : (n_seq * H * ((max_rows + 31) / 32) <= 256 ? 32 : 64);
   const int mt = (std::min(max_rows, chunk) + 15) / 16;
   // a long source capacity: the kernels of the other code object (the summation order beyond 128 keys; with one row
