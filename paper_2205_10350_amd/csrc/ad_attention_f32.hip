@@ -11,8 +11,9 @@ namespace ad {
 // their keys (key % 16 = lane) in ascending order; the output product walks all keys in ascending order, wave w for
 // channels 16 w .. + 15 (and 64 further on), its first values requested at the kernel's start.
 // A fragment is one 16-byte load (4 consecutive channels or probabilities) or four 4-byte loads (values) per lane, and
-// MFMA i multiplies element i of both, as in the fp32 GEMM.  Keys a row does not see have probability 0, so a row's
-// result depends on the keys it sees alone, not on the block it is verified in.
+// MFMA i multiplies element i of both, as in the fp32 GEMM.  Keys a row does not see have probability 0, and where they
+// stand in one unit with keys that it sees, values that are not finite are left out of the product (0 x Inf is NaN) and
+// added for the rows that see them only: a row's result depends on the keys it sees alone, not on the block it is verified in.
 // (base model, 4 sequences of 10..60 keys, kernel trace average: 4.4 us; one wave per query row on the vector units with
 // keys and values staged in LDS, which this replaces: 14.5 us)
 template <int DH>
@@ -30,6 +31,7 @@ __global__ __launch_bounds__(256) void k_attention_f32(const float* __restrict__
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int r = lane & 15, kq = lane >> 4;
   const int nk_all = sd.causal ? sd.nk_base + row_end : sd.nk_base, nt = (nk_all + 15) >> 4;
+  const int nk_full = sd.causal ? sd.nk_base + row_begin + 1 : sd.nk_base;   // keys every row of the tile sees
   auto f4 = [](const float* p) { return __builtin_bit_cast(float4, ldg16(p)); };
   float4 qf[KS], kf[KS];
   const float* qp = q + (size_t)(sd.q_row0 + min(row_begin + r, row_end - 1)) * d + h * DH + 4 * kq;
@@ -93,6 +95,32 @@ __global__ __launch_bounds__(256) void k_attention_f32(const float* __restrict__
 #pragma unroll
     for (int p = 0; p < PRE; ++p) {
       if (u0 + p < nt) {
+        if (16 * (u0 + p + 1) > nk_full) {   // (the same for the whole workgroup: at most two units)
+          bool left_out = false;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const bool there = 16 * (u0 + p) + 4 * kq + i < nk_all;
+#pragma unroll
+            for (int c = 0; c < CW; ++c) {
+              const bool fin = __builtin_isfinite(v[p][c][i]);
+              left_out |= there && !fin;
+              v[p][c][i] = there && fin ? v[p][c][i] : 0.f;
+            }
+          }
+          if (__any(left_out)) {
+            for (int key = 16 * (u0 + p); key < min(nk_all, 16 * (u0 + p + 1)); ++key) {
+#pragma unroll
+              for (int c = 0; c < CW; ++c) {
+                const float x = gload(vp + (size_t)key * d + 64 * c);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                  const int nkr = sd.causal ? sd.nk_base + row_begin + 4 * kq + i + 1 : sd.nk_base;
+                  if (!__builtin_isfinite(x) && key < nkr) acc[c][i] += S[(4 * kq + i) * ld + key] * x;
+                }
+              }
+            }
+          }
+        }
         const float4 pf = *(const float4*)(S + r * ld + 16 * (u0 + p) + 4 * kq);
 #pragma unroll
         for (int c = 0; c < CW; ++c) acc[c] = unit(pf, float4{v[p][c][0], v[p][c][1], v[p][c][2], v[p][c][3]}, acc[c]);

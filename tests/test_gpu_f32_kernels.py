@@ -53,3 +53,28 @@ def test_fp32_rows_against_the_oracle_and_across_launch_shapes(name):
                     bits = seen[b][1].setdefault(i, own[i].view(np.uint32))
                     assert np.array_equal(bits, own[i].view(np.uint32)), (ks, b, i)
                 r0 += k
+
+
+@pytest.mark.parametrize("dh", [16, 32, 64, 128])
+def test_fp32_rows_do_not_feel_values_that_are_not_finite_behind_them(dh):
+    """A token whose embedding overflows gives keys and values that are not finite; the rows of the block before it must
+    keep their bits (a row's keys end at its own: equality), wherever in a 16-row tile and a 16-key unit it stands."""
+    dims = dict(enc_layers=1, dec_layers=2, d_model=128, n_heads=128 // dh, d_ffn=128, vocab=512)
+    w = init_weights(dims, 21)
+    bad = 300
+    w["emb"][bad] = 3e38
+    cfg = ad.make_config(dims, max_batch=1, max_src=32, max_len=48, k_max=40, dtype="fp32", special=SPECIAL, debug_logits=True)
+    rng = np.random.default_rng(22)
+    src = rng.integers(5, 300, size=19).astype(np.int32)
+    good = [int(t) for t in rng.integers(5, 300, size=40)]
+    with ad.Context(cfg, w) as ctx:
+        def rows(block):
+            ctx.encode(ad.AD_VERIFIER, [src])
+            ctx.verify([block])
+            return ctx.debug_logits()
+        want = rows(good)
+        assert np.isfinite(want).all()
+        for at in (0, 1, 6, 14, 15, 16, 30, 38):   # the token of row at + 1
+            got = rows(good[:at] + [bad] + good[at + 1:])
+            assert not np.isfinite(got[at + 1:]).any(), at
+            assert np.array_equal(got[:at + 1].view(np.uint32), want[:at + 1].view(np.uint32)), at
