@@ -1,6 +1,5 @@
-// Attention for configurations with long key ranges (bf16, head width 64; the host selects it from the key capacity,
-// kLongKeys and more): up to 512 keys with keys and values staged once per 128 query rows (k_attention_rows), beyond that the
-// generic body (attn_block).
+// Attention beyond 64 keys or 64 rows (bf16, head width 64), keys and values staged once per 128 query rows
+// (k_attention_rows), and the cross-attention with its query projection for source capacities of kLongKeys and more.
 // A source file, hence a code object, of its own: the attention kernels are larger than the instruction cache, and the
 // speed of the short-range ones, which are the batch-1 path, moved with every addition to their code object although
 // their own instructions stayed the same (0.5 us per launch at 1152 rows).
@@ -13,18 +12,21 @@
 
 namespace ad {
 
-// Up to 128 query rows of a (sequence, head), head width 64, at most 512 keys: keys and transposed values are staged in LDS
-// once per workgroup of eight waves (read from L2 by every wave, they were the bound: 41 us for eight sources of 301..512
-// tokens), and a wave takes 16 rows from the scores to the output.
+// Up to 128 query rows of a (sequence, head), head width 64, at most 544 keys (526 is the most a configuration of that width
+// may have): keys and transposed values are staged in LDS once per workgroup of eight waves (read from L2 by every wave, they
+// were the bound: 41 us for eight sources of 301..512 tokens), and a wave takes 16 rows from the scores to the output.
 //  * The products are taken transposed, S^T = K Q^T and O^T = V^T P^T: a lane then holds one query row (lane % 16) and four
 //    consecutive keys of every key tile, so the whole score row stays in registers (NSB super-blocks of 128 keys, 32 registers
-//    each), the mask limit is one value per lane, and the probabilities become the right operand of the output product by
-//    two lane swaps per 32 keys (permlane32 / permlane16) instead of a trip through LDS.
-//  * Same order as attn_tiles_mfma<64, 16, true>: super-block sb adds into accumulator sb, the four are combined as
+//    each; a fifth one ends after 32 keys, as the LDS does), the mask limit is one value per lane, and the probabilities
+//    become the right operand of the output product by two lane swaps per 32 keys (permlane32 / permlane16) instead of a
+//    trip through LDS.
+//  * Same order as attn_tiles_mfma<64, 16, true>: super-block sb adds into accumulator sb % 4, the four are combined as
 //    (a0 + a1) + (a2 + a3); a row's denominator adds keys of equal key % 16 in ascending order, then pairs, quads, halves
 //    and rows of 16 as row16_sum does (four of the sixteen partial sums sit in each of four lanes).
 // Eight sources of 301..512 tokens, 16 heads: 25.7 us (54 us with the four waves of a 64-row chunk splitting the keys).
-constexpr int kRowsKeys = 512, kRowsKld = 64 + 16;   // most keys; row stride of the staged keys (32 bytes past a multiple of 64)
+constexpr int kRowsKeys = 512, kRowsKeysTail = 544;   // most keys without / with the fifth super-block
+constexpr int kRowsKld = 64 + 16;                     // row stride of the staged keys (32 bytes past a multiple of 64)
+constexpr int rows_key_tiles(int sb) { return sb < 4 ? 8 : 2; }   // 16-key tiles of super-block sb
 template <int NSB, bool LONGK>
 __device__ __forceinline__ void attn_rows_tile(const uint4 (&qf)[2], bf16_t* __restrict__ out, const SeqDesc sd, int row0, int row_end,
                                                int h, int d, float scale, const bf16_t* Ks, const bf16_t* Vt, int ldv) {
@@ -34,12 +36,12 @@ __device__ __forceinline__ void attn_rows_tile(const uint4 (&qf)[2], bf16_t* __r
   const int nk_full = sd.causal ? sd.nk_base + row0 + 1 : sd.nk_base;   // keys every row of the tile sees
   // the raw products: the scale, 1/8, is a power of two, so scaling them in the subtraction of the maximum rounds as
   // scaling them first does
-  f32x4 S[NSB][8];
+  f32x4 S[NSB][8];   // (of a fifth super-block: two)
   float m = -INFINITY;
 #pragma unroll
   for (int sb = 0; sb < NSB; ++sb) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < rows_key_tiles(sb); ++j) {
       f32x4 c = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
@@ -48,14 +50,14 @@ __device__ __forceinline__ void attn_rows_tile(const uint4 (&qf)[2], bf16_t* __r
       }
       S[sb][j] = c;
     }
-    if (128 * (sb + 1) > nk_full) {   // (the same for the whole wave: super-blocks every row sees whole need no mask)
+    if (128 * sb + 16 * rows_key_tiles(sb) > nk_full) {   // (the same for the whole wave: super-blocks every row sees whole need no mask)
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
+      for (int j = 0; j < rows_key_tiles(sb); ++j)
 #pragma unroll
         for (int i = 0; i < 4; ++i) S[sb][j][i] = 128 * sb + 16 * j + 4 * kq + i < nkr ? S[sb][j][i] : -INFINITY;
     }
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
+    for (int j = 0; j < rows_key_tiles(sb); ++j)
 #pragma unroll
       for (int i = 0; i < 4; ++i) m = fmaxf(m, S[sb][j][i]);
   }
@@ -75,9 +77,9 @@ __device__ __forceinline__ void attn_rows_tile(const uint4 (&qf)[2], bf16_t* __r
   }
 #pragma unroll
   for (int sb = 0; sb < NSB; ++sb) {
-    const int a = LONGK ? sb : 0;
+    const int a = LONGK ? sb & 3 : 0;
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
+    for (int b = 0; b < rows_key_tiles(sb) / 2; ++b) {
       unsigned x[2][2];
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
@@ -127,13 +129,18 @@ __device__ __forceinline__ void attn_rows_tile(const uint4 (&qf)[2], bf16_t* __r
     }
   }
 }
+__host__ __device__ inline int attn_rows_padded(int nk) { return nk <= kRowsKeys ? (nk + 127) / 128 * 128 : (nk + 31) / 32 * 32; }
 __host__ __device__ inline size_t attn_rows_lds_bytes(int nk) {
-  const size_t nkp = (size_t)(nk + 127) / 128 * 128;
+  const size_t nkp = attn_rows_padded(nk);
   return (nkp * kRowsKld + 64 * (nkp + 16)) * 2;
 }
 // LONGK: the order of configurations whose key capacity is kLongKeys or more; otherwise one chain for all keys, as in the
 // other kernels of such configurations (at most kLongKeys keys then).
-template <bool LONGK>
+// TAIL: key capacities beyond kRowsKeys, whose last keys are a fifth super-block; a kernel of its own, as it takes 236 registers
+// and the other 164.  Eight sequences of 40 rows against 512 keys, 16 heads: 9.3 us, 23.3 in the generic attn_block (a wave
+// walks all keys of its tile), 12.7 with the four waves of a workgroup splitting the keys; 526 rows against 526 keys 23.6 us,
+// 72.7 and 60.4 there.
+template <bool LONGK, bool TAIL>
 __global__ __launch_bounds__(512) void k_attention_rows(const bf16_t* __restrict__ q, const bf16_t* __restrict__ Kb,
                                                         const bf16_t* __restrict__ Vb, bf16_t* __restrict__ out,
                                                         const SeqDesc* __restrict__ desc, int d, float scale) {
@@ -142,8 +149,8 @@ __global__ __launch_bounds__(512) void k_attention_rows(const bf16_t* __restrict
   const int row_begin = blockIdx.z * 128, h = blockIdx.y;
   if (row_begin >= sd.nq) return;
   const int row_end = min(sd.nq, row_begin + 128);
-  const int nk_all = min(sd.causal ? sd.nk_base + row_end : sd.nk_base, LONGK ? kRowsKeys : kLongKeys);   // (the host promises the bound)
-  const int n_sb = (nk_all + 127) >> 7, nkp = 128 * n_sb, ldv = nkp + 16;
+  const int nk_all = min(sd.causal ? sd.nk_base + row_end : sd.nk_base, TAIL ? kRowsKeysTail : LONGK ? kRowsKeys : kLongKeys);   // (the host promises the bound)
+  const int n_sb = (nk_all + 127) >> 7, nkp = TAIL ? attn_rows_padded(nk_all) : 128 * n_sb, ldv = nkp + 16;
   bf16_t* Ks = (bf16_t*)att_rows_lds;   // [nkp][kRowsKld]
   bf16_t* Vt = Ks + nkp * kRowsKld;     // [64][ldv]
   const int lane = threadIdx.x & 63, r = lane & 15, kq = lane >> 4;
@@ -167,7 +174,7 @@ __global__ __launch_bounds__(512) void k_attention_rows(const bf16_t* __restrict
 #pragma unroll
   for (int i = 0; i < 8; ++i)
     if (64 * i < nkp) *(uint4*)(Ks + (64 * i + (threadIdx.x >> 3)) * kRowsKld + 8 * g) = kr[i];
-  if (t0 < nkp) {
+  auto put_values = [&](int t0) {
     unsigned in[8][4];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -184,6 +191,16 @@ __global__ __launch_bounds__(512) void k_attention_rows(const bf16_t* __restrict
       }
       *(uint4*)(Vt + (size_t)(g * 8 + c) * ldv + t0) = uint4{o[0], o[1], o[2], o[3]};
     }
+  };
+  if (t0 < nkp) put_values(t0);
+  if constexpr (TAIL) {   // the (at most 32) keys past the first 512: one piece per thread, values by the first four items of keys
+    const int key = kRowsKeys + (int)(threadIdx.x >> 3), t1 = kRowsKeys + t0;
+    if (key < nkp) *(uint4*)(Ks + key * kRowsKld + 8 * g) = ldg16(kg + (size_t)min(key, nk_all - 1) * d);
+    if (t1 < nkp) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) vr[i] = ldg16(vg + (size_t)min(t1 + i, nk_all - 1) * d);
+      put_values(t1);
+    }
   }
   __syncthreads();
   if (row0 >= row_end) return;
@@ -191,44 +208,26 @@ __global__ __launch_bounds__(512) void k_attention_rows(const bf16_t* __restrict
   if (n_sb == 1) tile(std::integral_constant<int, 1>{});
   else if (!LONGK || n_sb == 2) tile(std::integral_constant<int, 2>{});
   else if (n_sb == 3) tile(std::integral_constant<int, 3>{});
-  else tile(std::integral_constant<int, 4>{});
-}
-// key capacities beyond that
-__global__ __launch_bounds__(256) void k_attention_long(const bf16_t* __restrict__ q, const bf16_t* __restrict__ Kb,
-                                                        const bf16_t* __restrict__ Vb, bf16_t* __restrict__ out,
-                                                        const SeqDesc* __restrict__ desc, int d, float scale, int nk_cap) {
-  extern __shared__ unsigned att_long_lds[];
-  const SeqDesc sd = desc[blockIdx.x];
-  const int row_begin = blockIdx.z * 64;
-  if (row_begin >= sd.nq) return;
-  attn_block<64, true>(q, Kb, Vb, out, sd, row_begin, min(sd.nq, row_begin + 64), blockIdx.y, d, scale, att_long_lds, nk_cap);
+  else if (!TAIL || n_sb == 4) tile(std::integral_constant<int, 4>{});
+  else tile(std::integral_constant<int, 5>{});
 }
 
-void launch_attention_long(const void* q, const void* K, const void* V, void* out, const SeqDesc* desc, dim3 grid, int d,
-                           float scale, int max_keys, size_t lds_bytes, hipStream_t s) {
-  if (max_keys <= kRowsKeys) {
-    const size_t rows_bytes = attn_rows_lds_bytes(max_keys);
-    grid.z = (grid.z + 1) / 2;   // (the caller's grid has chunks of 64 rows)
-    auto go = [&](auto long_c) {
-      constexpr bool LONGK = decltype(long_c)::value;
-      static size_t set_rows = 0;
-      if (rows_bytes > set_rows) {
-        (void)hipFuncSetAttribute((const void*)k_attention_rows<LONGK>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)rows_bytes);
-        set_rows = rows_bytes;
-      }
-      k_attention_rows<LONGK><<<grid, 512, rows_bytes, s>>>((const bf16_t*)q, (const bf16_t*)K, (const bf16_t*)V, (bf16_t*)out, desc, d, scale);
-    };
-    if (max_keys >= kLongKeys) go(std::true_type{});
-    else go(std::false_type{});
-    return;
-  }
-  static size_t set_for = 0;
-  if (lds_bytes > set_for) {
-    (void)hipFuncSetAttribute((const void*)k_attention_long, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-    set_for = lds_bytes;
-  }
-  k_attention_long<<<grid, 256, lds_bytes, s>>>((const bf16_t*)q, (const bf16_t*)K, (const bf16_t*)V, (bf16_t*)out, desc, d, scale,
-                                               max_keys);
+void launch_attention_long(const void* q, const void* K, const void* V, void* out, const SeqDesc* desc, int n_seq, int max_rows,
+                           int H, float scale, int max_keys, hipStream_t s) {
+  const size_t lds = attn_rows_lds_bytes(max_keys);   // (at most 155 KB: ad_config_check admits 526 keys)
+  const dim3 grid(n_seq, H, (max_rows + 127) / 128);
+  auto go = [&](auto long_c, auto tail_c) {
+    constexpr bool LONGK = decltype(long_c)::value, TAIL = decltype(tail_c)::value;
+    static size_t set_rows = 0;
+    if (lds > set_rows) {
+      (void)hipFuncSetAttribute((const void*)k_attention_rows<LONGK, TAIL>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      set_rows = lds;
+    }
+    k_attention_rows<LONGK, TAIL><<<grid, 512, lds, s>>>((const bf16_t*)q, (const bf16_t*)K, (const bf16_t*)V, (bf16_t*)out, desc, H * 64, scale);
+  };
+  if (max_keys > kRowsKeys) go(std::true_type{}, std::true_type{});
+  else if (max_keys >= kLongKeys) go(std::true_type{}, std::false_type{});
+  else go(std::false_type{}, std::false_type{});
 }
 
 // Cross-attention with its query projection for a source capacity of kLongKeys or more (head width 64, d 512 or 1024,
@@ -265,23 +264,18 @@ bool launch_crossq_attention_long(const LnA& ln, const void* A, const void* W, c
   // launch / two, us: 8 x 40 rows 555 / 498, 16 x 25 rows 588 / 525, 4 x 72 rows 539 / 488 (512 source tokens), 479 / 469 for
   // 16 x 25 rows of 100; drafter forward, 8 sources of 512, 502 / 451.  Width 512 goes on with one: half the matrix, and 16 x 40 rows
   // take 409 / 368 with 512 source tokens but 324 / 334 with 100.
-  if (d == 1024 && max_keys <= kRowsKeys) return false;
+  if (d == 1024) return false;
   const size_t sh = crossq_lds_bytes(max_keys, mt, d);
   if (sh > 160 * 1024) return false;
   if (n_seq <= 0 || max_rows <= 0) return true;
   dim3 g(n_seq, H, (max_rows + chunk - 1) / chunk);
-  auto go = [&](auto nv_c) {
-    constexpr int NV = decltype(nv_c)::value;
-    static size_t set_for = 0;
-    if (sh > set_for) {
-      (void)hipFuncSetAttribute((const void*)k_crossq_attention<NV, 0, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
-      set_for = sh;
-    }
-    k_crossq_attention<NV, 0, true><<<g, 256, sh, s>>>(desc, chunk, scale, (const bf16_t*)W, (const bf16_t*)K, (const bf16_t*)V,
-                                                           ln.x, ln.g, ln.b, ln.y, (const bf16_t*)A, bias, (bf16_t*)out);
-  };
-  if (d == 512) go(std::integral_constant<int, 2>{});
-  else go(std::integral_constant<int, 4>{});
+  static size_t set_for = 0;
+  if (sh > set_for) {
+    (void)hipFuncSetAttribute((const void*)k_crossq_attention<2, 0, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
+    set_for = sh;
+  }
+  k_crossq_attention<2, 0, true><<<g, 256, sh, s>>>(desc, chunk, scale, (const bf16_t*)W, (const bf16_t*)K, (const bf16_t*)V, ln.x, ln.g,
+                                                    ln.b, ln.y, (const bf16_t*)A, bias, (bf16_t*)out);
   return true;
 }
 

@@ -936,7 +936,7 @@ __device__ __forceinline__ void attn_split_keys(const uint4 (&qf)[2], const uint
     if (row < row_end) Store<bf16_t>::store(out + (size_t)(sd.q_row0 + row) * d + h * DH + 16 * wave + r, o[i] / l[i]);
   }
 }
-template <int DH, bool LONGK = false>
+template <int DH>
 __device__ __forceinline__ void attn_block_mfma(const bf16_t* __restrict__ q, const bf16_t* __restrict__ Kb,
                                 const bf16_t* __restrict__ Vb, bf16_t* __restrict__ out, const SeqDesc sd,
                                 int row_begin, int row_end, int h, int d, float scale, unsigned* lds, int nk_all) {
@@ -958,17 +958,17 @@ __device__ __forceinline__ void attn_block_mfma(const bf16_t* __restrict__ q, co
   __syncthreads();
   if (nkp <= 64) attn_tiles_mfma<DH, 4>(q, Kb, out, sd, row_begin, row_end, h, d, scale, Vt, Pw, ldv, nk_all, qf_pre, kf_pre, Sbuf, nkp);
   else if (nkp <= 128) attn_tiles_mfma<DH, 8>(q, Kb, out, sd, row_begin, row_end, h, d, scale, Vt, Pw, ldv, nk_all, qf_pre, kf_pre, Sbuf, nkp);
-  else attn_tiles_mfma<DH, 16, LONGK>(q, Kb, out, sd, row_begin, row_end, h, d, scale, Vt, Pw, ldv, nk_all, qf_pre, kf_pre, Sbuf, nkp);
+  else attn_tiles_mfma<DH, 16>(q, Kb, out, sd, row_begin, row_end, h, d, scale, Vt, Pw, ldv, nk_all, qf_pre, kf_pre, Sbuf, nkp);
   __syncthreads();   // LDS is free for the next call
 }
 
-template <int DH, bool LONGK = false>
+template <int DH>
 __device__ __forceinline__ void attn_block(const bf16_t* __restrict__ q, const bf16_t* __restrict__ Kb, const bf16_t* __restrict__ Vb,
                            bf16_t* __restrict__ out, const SeqDesc sd, int row_begin, int row_end, int h, int d,
                            float scale, unsigned* lds, int nk_cap) {
   if constexpr (DH % 32 == 0) {
     const int nk_need = sd.causal ? sd.nk_base + row_end : sd.nk_base;
-    attn_block_mfma<DH, LONGK>(q, Kb, Vb, out, sd, row_begin, row_end, h, d, scale, lds, nk_need);
+    attn_block_mfma<DH>(q, Kb, Vb, out, sd, row_begin, row_end, h, d, scale, lds, nk_need);
     return;
   }
   constexpr int RD = DH / 2;                    // dwords per key row

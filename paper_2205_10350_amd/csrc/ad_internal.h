@@ -104,9 +104,9 @@ void launch_attention(int dtype, const void* q, const void* K, const void* V, vo
 // the same in fp32 (ad_attention_f32.hip)
 void launch_attention_f32(const float* q, const float* K, const float* V, float* out, const SeqDesc* desc, int n_seq,
                           int max_rows, int H, int dh, int max_keys, hipStream_t s);
-// the same launch for long key ranges (ad_attention_long.hip; bf16, head width 64, grid and LDS bytes as launch_attention computes them)
-void launch_attention_long(const void* q, const void* K, const void* V, void* out, const SeqDesc* desc, dim3 grid, int d,
-                           float scale, int max_keys, size_t lds_bytes, hipStream_t s);
+// the same beyond 64 keys or rows (ad_attention_long.hip; bf16, head width 64, at most 544 keys)
+void launch_attention_long(const void* q, const void* K, const void* V, void* out, const SeqDesc* desc, int n_seq, int max_rows,
+                           int H, float scale, int max_keys, hipStream_t s);
 bool launch_crossq_attention_long(const LnA& ln, const void* A, const void* W, const float* bias, const void* K, const void* V,
                                   void* out, const SeqDesc* desc, int n_seq, int max_rows, int H, int chunk, int max_keys,
                                   hipStream_t s);

@@ -694,7 +694,7 @@ void launch_attention(int dtype, const void* q, const void* K, const void* V, vo
     return;
   }
   if (dh == 64) {   // everything beyond that: kernels in a code object of their own
-    launch_attention_long(q, K, V, out, desc, g, H * dh, scale, max_keys, sh, s);
+    launch_attention_long(q, K, V, out, desc, n_seq, max_rows, H, scale, max_keys, s);
     return;
   }
   switch (dh) {
