@@ -86,7 +86,7 @@ void launch_embed(int dtype, const void* emb, const float* pe, const int* tok, c
 int launch_gemm(int dtype, const void* A, const void* W, int M, int N, int K, const Epi& e, hipStream_t s,
                 const LnA& ln = LnA{}, bool* a_written = nullptr);
 // bf16, many rows (ad_gemm_tile.hip): which products go there, and their launch (A as rows, no LayerNorm)
-bool gemm_tile_takes(int M, int N, int K, bool has_ln, const Epi& e);
+bool gemm_tile_takes(int M, int N, int K, bool has_ln, int mode);
 void launch_gemm_tile(const void* A, const void* W, int M, int N, int K, const Epi& e, hipStream_t s);
 // bf16, few rows (ad_gemm_few.hip): K of 1024, 2048 or 4096 shared by the waves, rows as they are; K = 1024 with the
 // LayerNorm pending (false = not covered)

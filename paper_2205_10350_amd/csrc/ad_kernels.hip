@@ -504,7 +504,7 @@ int launch_gemm(int dtype, const void* A, const void* W, int M, int N, int K, co
   if (a_written) *a_written = true;
   LnA ln = ln_in;
   const bool streams = dtype == AD_BF16 && K <= 4096 && K % 512 == 0;   // the A-in-LDS kernel takes it
-  const bool tile = dtype == AD_BF16 && gemm_tile_takes(M, N, K, ln.x != nullptr, e);
+  const bool tile = dtype == AD_BF16 && gemm_tile_takes(M, N, K, ln.x != nullptr, e.mode);
   if (ln.x && (tile || !(dtype == AD_F32 ? gemm_f32_takes_ln(M, N, K, e) : streams && (K == 512 || K == 1024)))) {
     launch_layernorm(dtype, ln.x, ln.g, ln.b, M, K, ln.y, const_cast<void*>(A), s);
     ln = LnA{};
@@ -518,8 +518,8 @@ int launch_gemm(int dtype, const void* A, const void* W, int M, int N, int K, co
     const int nb = (N / 16 + 3) / 4;
     if (K <= 4096 && K % 512 == 0) {
       const bf16_t *a = (const bf16_t*)A, *w = (const bf16_t*)W;
-      // up to 160 rows (K = 1024 and 4096: 128, gemm_tile_takes) of a K of several slices, as they are: the slices side by
-      // side in the waves (measured, forward with this kernel up to 64 / 128 / 256 rows: base model 144 rows
+      // up to 160 rows (K = 1024 and 4096: as far as gemm_tile_takes leaves them) of a K of several slices, as they are: the
+      // slices side by side in the waves (measured, forward with this kernel up to 64 / 128 / 256 rows: base model 144 rows
       // 253 / 253 / 249 us, 288 rows 285 / 286 / 285 us; wide model 100 rows 365 / 352 / 352 us)
       if (M <= 160 && !ln.x && (K == 1024 || K == 2048 || K == 4096) && e.mode != EPI_ARGMAX && e.mode != EPI_COUNT) {
         launch_kchain(a, w, M, N, K, e, s);
