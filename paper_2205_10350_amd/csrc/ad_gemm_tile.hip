@@ -319,20 +319,25 @@ static void launch_roll(const bf16_t* A, const bf16_t* W, int M, int N, int K, c
 //  K = 1024, LayerNorm pending: 64 / 80 / 130 / 250 / 626 rows x N 3072 6.1 / 6.4 / 8.5 / 11.5 / 15.9 there, 6.7 / 6.8 / 6.9 / 8.1 /
 //    10.8 here, x N 4096 6.2 / 8.1 / 10.6 / 11.5 / 20.5 there, 6.4 / 6.5 / 7.9 / 8.1 / 14.7 here; N 12288 (memory keys and values) 25
 //    rows 8.4 / 6.5, 626 rows 38.8 / 25, 3252 rows 221 / 100
-//  K = 1024, none: 80 / 130 / 626 / 3252 rows 3.4 / 4.7 / 6.4 / 26.1 there, 3.8 / 4.0 / 5.4 / 16.5 here
+//  K = 1024, none: N 1024 80 / 130 / 626 / 3252 rows 3.4 / 4.7 / 6.4 / 26.1 there, 3.8 / 4.0 / 5.4 / 16.5 here; N 512 and 768
+//    130 / 160 / 161 rows 3.7 / 3.7 / 4.6 and 3.9 / 4.0 / 6.3 there, 4.0 / 4.1 / 4.1 and 4.2 / 4.2 / 4.1 here
 //  K = 4096: k_gemm_bf16_kchain while its workgroups, 136 KB of LDS each, are one per CU: N 1024 64 / 65 / 96 / 128 rows 6.4 / 9.8 /
 //    10.7 / 11.1 there, 8.8 / 8.5 / 8.9 / 8.9 here; N 2048 32 / 33 / 64 / 96 rows 7.2 / 10.7 / 12.0 / 16.9 there, 9.0 / 8.6 / 9.1 /
 //    9.2 here; N 512 128 rows 6.3 / 8.7.  130 / 626 / 3252 rows 12.7 / 22.2 / 80 there, 8.2 / 14.6 / 43 here
 //  K = 512, LayerNorm pending: N 1536 1120 / 1500 rows 7.8 / 14.0 there, 9.1 / 10.7 here; N 2048 800 / 1120 rows 8.5 / 11.8 there and
 //    8.6 / 10.2 here; N 6144 128 / 200 / 1120 rows 7.0 / 10.2 / 30.3 there, 7.1 / 8.4 / 17.8 here
 //  K = 512, none: 400 / 576 / 1120 rows 2.8 / 3.9 / 4.2 there, 3.2 / 3.0 / 4.1 here
-//  K = 2048: 400 / 576 / 1120 rows 5.6 / 8.1 / 8.7 there, 5.4 / 5.4 / 8.8 here
+//  K = 2048: N 512 400 / 576 / 1120 rows 5.6 / 8.1 / 8.7 there, 5.4 / 5.4 / 8.8 here, 1365 / 1800 / 2048 rows 9.8 / 11.0 / 12.3 there,
+//    10.2 / 11.8 / 12.9 here: beyond 1024 rows the eight-wave workgroups while they make one round; past it N 1024 1025 / 2048 rows
+//    20.1 / 20.8 there, 12.9 / 16.0 here, N 2048 1365 rows 29.9 / 21.8
+//  K = 1536: the same from 1600 rows, N 512 1300 / 1800 / 2048 / 2049 rows 9.3 / 9.6 / 10.0 / 13.9 there, 7.9 / 10.3 / 11.1 / 12.8 here
 bool gemm_tile_takes(int M, int N, int K, bool has_ln, int mode) {
   if (K % 512 || K < 512 || mode == EPI_ARGMAX || mode == EPI_COUNT) return false;
   if (K == 512) return has_ln ? (N >= 4096 ? M > 160 : N >= 2048 ? M > 1024 : M > 1344) : M >= 520;
-  if (K == 2048) return M >= 520 && (M <= 1024 || M > 2048);
+  if (K == 2048) return M >= 520 && !(M > 1024 && gemm_one_round(M, N, 8));
   if (K == 4096) return M > 128 || (N / 16) * ((M + 15) / 16) > 256;
-  return has_ln ? M > (N > 4096 ? 16 : N == 4096 ? 64 : 96) : M > 128;
+  if (K == 1536 && M > 1600 && gemm_one_round(M, N, 8)) return false;
+  return has_ln ? M > (N > 4096 ? 16 : N == 4096 ? 64 : 96) : M > (K == 1024 && N < 1024 ? 160 : 128);
 }
 // Tile by the number of workgroups w(rows x columns of a tile): the smallest while they fit the CUs at once (a stage's latency is
 // the bound), larger ones as soon as there are enough of them (operand traffic from L2 and then the matrix cores are).

@@ -87,6 +87,8 @@ int launch_gemm(int dtype, const void* A, const void* W, int M, int N, int K, co
                 const LnA& ln = LnA{}, bool* a_written = nullptr);
 // bf16, many rows (ad_gemm_tile.hip): which products go there, and their launch (A as rows, no LayerNorm)
 bool gemm_tile_takes(int M, int N, int K, bool has_ln, int mode);
+// whether the A-in-LDS kernel with 32 rows and `strips` strips per workgroup makes one round of the 256 CUs
+inline bool gemm_one_round(int M, int N, int strips) { return N / 16 % strips == 0 && N / 16 / strips * ((M + 31) / 32) <= 256; }
 void launch_gemm_tile(const void* A, const void* W, int M, int N, int K, const Epi& e, hipStream_t s);
 // bf16, few rows (ad_gemm_few.hip): K of 1024, 2048 or 4096 shared by the waves, rows as they are; K = 1024 with the
 // LayerNorm pending (false = not covered)

@@ -537,11 +537,8 @@ int launch_gemm(int dtype, const void* A, const void* W, int M, int N, int K, co
       // the chip (a wave stages 2 or 4 rows instead of 8, and every wave's weights are requested at once; measured at
       // 1152 rows: QKV with the LayerNorm 12.4 -> 9.6 us, FFN2 12.9 -> 11.0 us)
       if (M >= 520 && e.mode != EPI_ARGMAX && e.mode != EPI_COUNT) {
-        const int n_strips = N / 16, chunks2 = (M + 31) / 32;
-        if (K == 512 && ln.x && n_strips >= 64 && n_strips % 16 == 0 && (n_strips / 16) * chunks2 <= 256)
-          return launch_astat<2, 1, 16>(a, w, M, N, K, e, 16, s, ln);
-        if (K == 2048 && !ln.x && n_strips % 8 == 0 && (n_strips / 8) * chunks2 <= 256)
-          return launch_astat<2, 1, 8>(a, w, M, N, K, e, 8, s, ln);
+        if (K == 512 && ln.x && N >= 1024 && gemm_one_round(M, N, 16)) return launch_astat<2, 1, 16>(a, w, M, N, K, e, 16, s, ln);
+        if (K == 2048 && !ln.x && gemm_one_round(M, N, 8)) return launch_astat<2, 1, 8>(a, w, M, N, K, e, 8, s, ln);
       }
       if ((M <= 64 || (M <= 1024 && N <= 4096) || want_logits) && astat_lds_bytes(mt, K) <= 150 * 1024) {
         {

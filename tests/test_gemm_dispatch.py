@@ -21,3 +21,20 @@ def takes():
 def test_k_4096_leaves_the_kernel_whose_waves_share_k_while_that_is_one_workgroup_per_cu(takes, N, last):
     assert not takes(last, N, 4096, False, RESID)
     assert takes(last + 1, N, 4096, False, RESID)
+
+
+@pytest.mark.parametrize("N", [512, 768, 1024, 1536, 2048])
+def test_k_2048_leaves_the_eight_wave_workgroups_when_they_need_a_second_round(takes, N):
+    last = 32 * (256 // (N // 128))   # rows of one round: N / 128 workgroups per 32 rows on 256 CUs
+    assert not takes(519, N, 2048, False, RESID)
+    assert takes(520, N, 2048, False, RESID) and takes(1024, N, 2048, False, RESID)
+    for M in (1025, 1365, max(1024, last), max(1024, last) + 1, 2048, 2049, 4000):
+        assert takes(M, N, 2048, False, RESID) == (M <= 1024 or M > last), M
+        if M > 1600:
+            assert takes(M, N, 1536, False, RESID) == (M > last), M
+
+
+def test_k_1024_with_few_columns_stays_with_the_few_row_kernel_up_to_its_160_rows(takes):
+    for N in (512, 768):
+        assert not takes(160, N, 1024, False, RESID) and takes(161, N, 1024, False, RESID)
+    assert not takes(128, 1024, 1024, False, RESID) and takes(129, 1024, 1024, False, RESID)
