@@ -344,9 +344,9 @@ bool gemm_tile_takes(int M, int N, int K, bool has_ln, int mode) {
 // 64 x 128: four stages ahead while there is one workgroup per CU, two (and two workgroups per CU) beyond: K = 1536, N 1536 x 700 /
 // 1024 / 1600 rows (w 132 / 192 / 300) 10.5 / 11.8 / 19.5 us with four, 12.6 / 13.8 / 18.0 with two; K = 512, N 3072 x 519 rows (216)
 // 8.9 / 9.4; K = 2048, N 1024 x 2049 rows (264) 21.9 / 19.3.
-// 128 x 128 rolling: two workgroups per CU, so at most 512 of them; one more is another round, and the 64 x 128 rolling shape
-// wins until 128 x 256 has enough workgroups: K = 512, N 3072 x 3000 rows (w(128, 128) 576) 28.5 / 26.2 us, K = 1536, N 6144 x 1300
-// (528) 54.0 / 44.0; K = 2048, N 2048 x 4096 (512) 45.1 / 49.7.
+// 128 x 128 rolling: two workgroups per CU; up to 640 of them a second round is nearly empty and the 64 x 128 rolling shape
+// wins: K = 512, N 3072 x 3000 rows (w(128, 128) 576) 28.5 / 26.2 us, K = 1536, N 6144 x 1300 (528) 54.0 / 44.0; but K = 2048,
+// N 2048 x 4096 (512) 45.1 / 49.7, K = 1024, N 3072 x 3531 (672) 40.8 / 43.1.
 // Measured at K = 1024 (64 x 128 / 64 x 128 rolling / 128 x 128 / 128 x 256): N 3072 x 626 rows (w 240) 8.3 / 9.0 / 12.0 / 18.4 us,
 // x 2000 (768) 23.1 / 21.3 / 23.0 / 26.7; N 4096 x 2000 (1024) 28.0 / 26.5 / 23.0 / 25.4, x 3252 (1632) 44 / 43 / 42 / 35.5 (770
 // TFLOP/s); N 12288 x 3252 120 / 122 / 108 / 94.6 (865 TFLOP/s).
@@ -358,7 +358,7 @@ void launch_gemm_tile(const void* A_, const void* W_, int M, int N, int K, const
   else if (w(64, 128) <= 256) launch_tile<4, 2, 4>(A, W, M, N, K, e, s);
   else if (w(64, 128) <= 450) launch_tile<4, 2, 2>(A, W, M, N, K, e, s);
   else if (w(64, 128) > 900 && w(128, 256) >= 350) launch_roll<8, 4>(A, W, M, N, K, e, s);
-  else if (w(64, 128) > 900 && w(128, 128) <= 512) launch_roll<8, 2>(A, W, M, N, K, e, s);
+  else if (w(64, 128) > 900 && (w(128, 128) <= 512 || w(128, 128) > 640)) launch_roll<8, 2>(A, W, M, N, K, e, s);
   else launch_roll<4, 2>(A, W, M, N, K, e, s);
 }
 
