@@ -477,6 +477,12 @@ static int launch_astat(const bf16_t* A, const bf16_t* W, int M, int N, int K, c
   if (K == 512) {
     if (amax) go(I1{}, std::true_type{});
     else if (count) go(I3{}, std::true_type{});
+    else if constexpr (MT == 1 && SP == 2) {
+      // FFN1 where the cost model takes 16 rows per workgroup (N 8192 x 100 / 160 rows 7.4 -> 6.7 and 9.8 -> 8.1 us, N 1568 x 1100
+      // rows 11.4 -> 9.9; the same for the 32-row variant, for FFN2 and for the output projection gained nothing)
+      if (ln.x && e.mode == EPI_RELU) fixed_variant(I0{}, std::integral_constant<int, 1>{}, std::integral_constant<int, EPI_RELU>{}, std::true_type{});
+      else go(I0{}, std::true_type{});
+    }
     else if constexpr (MT == 1 && SP == 1 && NW == 4) {
       // the layer GEMMs of the few-row regime: the pending LayerNorm (or none) and the epilogue mode as
       // compile-time constants, a kernel per combination that occurs (run-time branches around loads in

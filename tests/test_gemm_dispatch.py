@@ -38,3 +38,12 @@ def test_k_1024_with_few_columns_stays_with_the_few_row_kernel_up_to_its_160_row
     for N in (512, 768):
         assert not takes(160, N, 1024, False, RESID) and takes(161, N, 1024, False, RESID)
     assert not takes(128, 1024, 1024, False, RESID) and takes(129, 1024, 1024, False, RESID)
+
+
+@pytest.mark.parametrize("N,first", [(1536, 1400), (2048, 1025), (2560, 801), (3072, 513), (4096, 257), (6144, 161)])
+def test_k_512_behind_a_layernorm(takes, N, first):
+    """2048 and 2560 columns: the rows at which the 16-wave workgroups (256 columns x 32 rows) fill the 256 CUs."""
+    mode = QKV if N == 1536 else RELU
+    assert not takes(first - 1, N, 512, True, mode) and takes(first, N, 512, True, mode) and takes(4000, N, 512, True, mode)
+    for few in (512, 1024, 1280):
+        assert not any(takes(M, few, 512, True, RELU) for M in (520, 1025, 1345, 2048, 4000))
