@@ -324,10 +324,11 @@ static void launch_roll(const bf16_t* A, const bf16_t* W, int M, int N, int K, c
 //  K = 4096: k_gemm_bf16_kchain while its workgroups, 136 KB of LDS each, are one per CU: N 1024 64 / 65 / 96 / 128 rows 6.4 / 9.8 /
 //    10.7 / 11.1 there, 8.8 / 8.5 / 8.9 / 8.9 here; N 2048 32 / 33 / 64 / 96 rows 7.2 / 10.7 / 12.0 / 16.9 there, 9.0 / 8.6 / 9.1 /
 //    9.2 here; N 512 128 rows 6.3 / 8.7.  130 / 626 / 3252 rows 12.7 / 22.2 / 80 there, 8.2 / 14.6 / 43 here
-//  K = 512, LayerNorm pending: below 1536 columns never (N 512 2048 rows 8.7 / 9.9, N 1024 1345 / 2048 / 4000 rows 8.7 / 9.4 / 15.7
-//    there, 10.5 / 12.0 / 17.9 here); below 2048 from 1400 rows (N 1536 1345 / 1400 / 2048 rows 11.3 / 13.5 / 15.0 there, 11.9 / 12.0 /
-//    14.1 here; N 1568 1100 / 1344 / 1600 rows 9.9 / 11.4 / 12.4 there, 9.8 / 11.7 / 12.5 here); below 3072 from 520 rows where the
-//    16-wave workgroups need a second round (N 2048 800 / 1120 rows 8.5 / 11.8 there and 8.6 / 10.2 here); below 4096 from 513 rows
+//  K = 512, LayerNorm pending: below 1408 columns never (N 512 2048 rows 8.7 / 9.9, N 1024 1345 / 2048 / 4000 rows 8.7 / 9.4 / 15.7
+//    there, 10.5 / 12.0 / 17.9 here, N 1280 2048 / 3000 rows 12.0 / 17.3 there, 13.5 / 16.3 here); below 2048 from 1400 rows (N 1408
+//    1345 / 1400 rows 9.9 / 12.4 there, 10.7 / 10.8 here, N 1536 1345 / 1400 / 2048 rows 11.3 / 13.5 / 15.0 there, 11.9 / 12.0 / 14.1
+//    here); below 3072 from 600 rows where the 16-wave workgroups need a second round (N 2048 800 / 1120 rows 8.5 / 11.8 there and
+//    8.6 / 10.2 here, N 2080 567 / 620 / 900 rows 7.6 / 9.6 / 10.0 there, 8.6 / 8.7 / 9.5 here); below 4096 from 513 rows
 //    (N 3072 512 / 519 / 673 / 1024 rows 8.4 / 11.2 / 11.4 / 12.6 there, 8.8 / 8.9 / 10.4 / 12.0 here); N 4096 160 / 256 / 300 rows 6.1 /
 //    6.5 / 8.5 there with the ReLU, whose epilogue is a constant there, 6.7 / 7.0 / 8.5 here, 211 rows of keys and values 7.4 / 7.0; N 6144 128 / 160 / 200 / 1120 rows 7.0 / 7.7 / 10.2 / 30.3 there, 7.1 / 8.4 / 8.4 / 17.8 here
 //  K = 512, none: 400 / 576 / 1120 rows 2.8 / 3.9 / 4.2 there, 3.2 / 3.0 / 4.1 here
@@ -338,8 +339,8 @@ static void launch_roll(const bf16_t* A, const bf16_t* W, int M, int N, int K, c
 bool gemm_tile_takes(int M, int N, int K, bool has_ln, int mode) {
   if (K % 512 || K < 512 || mode == EPI_ARGMAX || mode == EPI_COUNT) return false;
   if (K == 512 && has_ln) {
-    if (N < 2048) return N >= 1536 && M >= 1400;
-    if (N < 3072) return M >= 520 && !gemm_one_round(M, N, 16);
+    if (N < 2048) return N >= 1408 && M >= 1400;
+    if (N < 3072) return M >= 600 && !gemm_one_round(M, N, 16);
     return M > (N < 4096 ? 512 : N < 6144 && mode == EPI_RELU ? 256 : 160);
   }
   if (K == 512) return M >= 520;

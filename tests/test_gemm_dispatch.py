@@ -40,7 +40,7 @@ def test_k_1024_with_few_columns_stays_with_the_few_row_kernel_up_to_its_160_row
     assert not takes(128, 1024, 1024, False, RESID) and takes(129, 1024, 1024, False, RESID)
 
 
-@pytest.mark.parametrize("N,first", [(1536, 1400), (2048, 1025), (2560, 801), (3072, 513), (4096, 257), (6144, 161)])
+@pytest.mark.parametrize("N,first", [(1408, 1400), (1536, 1400), (2048, 1025), (2080, 600), (2560, 801), (3072, 513), (4096, 257), (6144, 161)])
 def test_k_512_behind_a_layernorm(takes, N, first):
     """2048 and 2560 columns: the rows at which the 16-wave workgroups (256 columns x 32 rows) fill the 256 CUs."""
     mode = QKV if N == 1536 else RELU
