@@ -379,7 +379,7 @@ __device__ __forceinline__ void argmax_row(const float* __restrict__ pv, const i
 constexpr int kSplitLd = 128 + 16;                                   // row stride (elements): 32 bytes past a multiple of 64
 constexpr int kSplitWaveElems = (64 + 16) * kSplitLd;                // bf16 elements of a wave's two tiles
 constexpr int kSplitXchBytes = 4 * 16 * 4 + 4 * 64 * 16 + 4 * 4 * 64 * 16;   // attn_split_keys: maxima, denominators, partial outputs
-constexpr int kLongKeys = 256;   // key capacity from which the attention launches are those of ad_attention_long.hip
+constexpr int kLongKeys = 256;   // key capacity from which keys are summed in super-blocks of 128 (LONGK, attn_tiles_mfma)
 __host__ __device__ inline size_t attn_lds_bytes(int nk_cap, int dh, int esz, int waves) {
   const size_t row_dwords = (size_t)dh * esz / 4 + 1;
   const size_t scalar_path = 2 * (size_t)nk_cap * row_dwords * 4 + 64 * (size_t)dh * 4 + (size_t)waves * nk_cap * 4;

@@ -419,6 +419,35 @@ static float astat_plan(int mt, int M, int N, int K, bool with_ln, int* per_wg_o
   }
   return best;
 }
+// The same for the output projection of K = 512 and 1024, where the matrix is what a launch waits for: every row chunk reads all of
+// it from L2, 0.03 us per MB and chunk, and two workgroups of a CU share its MFMA pipes.  Constants fitted to 13000 launches,
+// vocabulary 4112..50000 x 65..2048 rows x every shape, with the matrix in the last-level cache and from memory.  The shapes it picks
+// take 0.95 of the time of the model above at K = 512 and 0.97 at K = 1024 (from memory 0.90 and 0.92), and 0.89 and 0.94 (0.92 and
+// 0.96) of a rule that took 32 rows per workgroup up to 192 and 64 beyond; a single shape loses up to 14 % in one of the two
+// regimes where it gains in the other (K = 1024, vocabulary 32000, 112 rows 19.9 -> 22.7 us, from memory 25.2 -> 23.2).
+// K = 512, vocabulary 32000, model above / that rule / this: 96 rows 12.5 / 12.7 / 12.4 us, 128 rows 14.2 / 12.8 / 12.4, 160 rows 16.7 /
+// 14.4 / 13.9, 288 rows 18.1 / 20.4 / 18.0, 512 rows 26.3 / 24.2 / 22.7; vocabulary 8000, 256 rows 9.3 / 12.1 / 8.8.
+struct VocabPlan { int mt, per_wg; };
+static VocabPlan vocab_plan(int M, int N, int K, bool with_ln) {
+  const int n_strips = N / 16, halves = K / 512;
+  VocabPlan best{1, 8};
+  float best_us = 1e30f;
+  for (int mt = 1; mt <= 4; mt *= 2) {
+    const size_t lds = astat_lds_bytes(mt, K);
+    if (mt > 1 && lds > 150 * 1024) break;
+    const int chunks = (M + mt * 16 - 1) / (mt * 16);
+    const float wg_us = 2.4f + 1.5f * mt * (with_ln ? 1.f : 0.2f), matrix_us = 0.03f * chunks * (2e-6f * N * K);
+    for (int per_wg = 8; per_wg <= 128; per_wg += 8) {
+      const int groups = (n_strips + per_wg - 1) / per_wg, units = per_wg / 8 * halves;
+      const int wgs_cu = ((groups >= 8 ? (groups + 7) / 8 * chunks : (groups * chunks + 7) / 8) + 31) / 32;   // of the busiest XCD's CUs
+      const float one_us = wg_us + units * (0.15f + 0.42f * mt), two_us = wg_us + units * (0.28f + 0.86f * mt);
+      const float us = matrix_us + (lds * 2 <= 160 * 1024 ? wgs_cu / 2 * two_us + wgs_cu % 2 * one_us : wgs_cu * one_us);
+      if (us < best_us) { best_us = us; best = VocabPlan{mt, per_wg}; }
+      if (groups == 1) break;
+    }
+  }
+  return best;
+}
 template <int MT, int SP, int NW = 4>
 static int launch_astat(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epi& e, int per_wg, hipStream_t s,
                         const LnA& ln) {
@@ -577,29 +606,18 @@ int launch_gemm(int dtype, const void* A, const void* W, int M, int N, int K, co
           return launch_astat<1, 1>(a, w, M, N, K, e, balanced(per_wg), s, ln);
         }
       } else {
+        if (K <= 1024 && (e.mode == EPI_ARGMAX || e.mode == EPI_COUNT)) {
+          const VocabPlan v = vocab_plan(M, N, K, ln.x != nullptr);
+          if (v.mt == 4) return launch_astat<4, 2>(a, w, M, N, K, e, v.per_wg, s, ln);
+          if (v.mt == 2) return launch_astat<2, 2>(a, w, M, N, K, e, v.per_wg, s, ln);
+          return launch_astat<1, 2>(a, w, M, N, K, e, v.per_wg, s, ln);
+        }
         // rows per workgroup (16, 32 or 64, as far as the A tile fits in LDS) and strips per
         // workgroup by the cost model
         int pw[3] = {8, 8, 8};
         const float c1 = astat_plan(1, M, N, K, ln.x != nullptr, &pw[0]);
         const float c2 = K <= 2048 ? astat_plan(2, M, N, K, ln.x != nullptr, &pw[1]) : 1e30f;
         const float c4 = K <= 1024 ? astat_plan(4, M, N, K, ln.x != nullptr, &pw[2]) : 1e30f;
-        // The output projection: 32 rows up to 192, 64 beyond (every row chunk reads the matrix from L2), and with at most four
-        // chunks as many strips as make it one workgroup per CU.  Measured against the model's choice, matrix from memory /
-        // from the last-level cache, us: K = 512, 96 rows 17.6 / 12.8 (16 rows a workgroup) -> 15.2 / 10.8, 128 rows 20.4 /
-        // 14.6 -> 15.2 / 11.5, 256 rows 22.3 / 17.5 (32 rows) -> 19.7 / 17.1, 400 rows 32.8 / 26.0 -> 26.9 / 24.3; K = 1024,
-        // 136 rows 38.1 / 29.3 (16) -> 30.1 / 23.3, 200 rows 36.3 / 28.8 (32) -> 31.5 / 26.4, 300 rows 44.7 / 36.0 ->
-        // 38.4 / 33.3.  The line: 160 rows of K = 1024 in 64-row workgroups 31.6 / 25.7, in 32-row ones 30.5 / 23.4; 192 rows
-        // 31.5 / 26.0 and 33.0 / 26.1.
-        if (K <= 1024 && (e.mode == EPI_ARGMAX || e.mode == EPI_COUNT)) {
-          const int mt_v = M <= 192 ? 2 : 4, chunks = (M + 16 * mt_v - 1) / (16 * mt_v), n_strips = N / 16;
-          int per_wg = mt_v == 2 ? pw[1] : pw[2];
-          if (chunks <= 4) {
-            auto per_xcd = [&](int x) { return ((n_strips + x - 1) / x + 7) / 8 * chunks; };
-            per_wg = 8;
-            while (per_wg < n_strips && per_xcd(per_wg) > 32) per_wg += 8;
-          }
-          return mt_v == 2 ? launch_astat<2, 2>(a, w, M, N, K, e, per_wg, s, ln) : launch_astat<4, 2>(a, w, M, N, K, e, per_wg, s, ln);
-        }
         if (c4 <= c2 && c4 <= c1) return launch_astat<4, 2>(a, w, M, N, K, e, pw[2], s, ln);
         if (c2 <= c1) return launch_astat<2, 2>(a, w, M, N, K, e, pw[1], s, ln);
         return launch_astat<1, 2>(a, w, M, N, K, e, pw[0], s, ln);
