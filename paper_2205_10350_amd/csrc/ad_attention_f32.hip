@@ -11,9 +11,10 @@ namespace ad {
 // their keys (key % 16 = lane) in ascending order; the output product walks all keys in ascending order, wave w for
 // channels 16 w .. + 15 (and 64 further on), its first values requested at the kernel's start.
 // A fragment is one 16-byte load (4 consecutive channels or probabilities) or four 4-byte loads (values) per lane, and
-// MFMA i multiplies element i of both, as in the fp32 GEMM.  Keys a row does not see have probability 0, and where they
-// stand in one unit with keys that it sees, values that are not finite are left out of the product (0 x Inf is NaN) and
-// added for the rows that see them only: a row's result depends on the keys it sees alone, not on the block it is verified in.
+// MFMA i multiplies element i of both, as in the fp32 GEMM.  Keys a row does not see have probability 0; should a result not be
+// finite, the product is taken once more with the values that are not finite held out of the units that rows see in part (0 x Inf
+// is NaN) and added for the rows that see them only: a row's result depends on the keys it sees alone, not on the block it
+// is verified in.
 // (base model, 4 sequences of 10..60 keys, kernel trace average: 4.4 us; one wave per query row on the vector units with
 // keys and values staged in LDS, which this replaces: 14.5 us)
 template <int DH>
@@ -95,32 +96,6 @@ __global__ __launch_bounds__(256) void k_attention_f32(const float* __restrict__
 #pragma unroll
     for (int p = 0; p < PRE; ++p) {
       if (u0 + p < nt) {
-        if (16 * (u0 + p + 1) > nk_full) {   // (the same for the whole workgroup: at most two units)
-          bool left_out = false;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const bool there = 16 * (u0 + p) + 4 * kq + i < nk_all;
-#pragma unroll
-            for (int c = 0; c < CW; ++c) {
-              const bool fin = __builtin_isfinite(v[p][c][i]);
-              left_out |= there && !fin;
-              v[p][c][i] = there && fin ? v[p][c][i] : 0.f;
-            }
-          }
-          if (__any(left_out)) {
-            for (int key = 16 * (u0 + p); key < min(nk_all, 16 * (u0 + p + 1)); ++key) {
-#pragma unroll
-              for (int c = 0; c < CW; ++c) {
-                const float x = gload(vp + (size_t)key * d + 64 * c);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                  const int nkr = sd.causal ? sd.nk_base + row_begin + 4 * kq + i + 1 : sd.nk_base;
-                  if (!__builtin_isfinite(x) && key < nkr) acc[c][i] += S[(4 * kq + i) * ld + key] * x;
-                }
-              }
-            }
-          }
-        }
         const float4 pf = *(const float4*)(S + r * ld + 16 * (u0 + p) + 4 * kq);
 #pragma unroll
         for (int c = 0; c < CW; ++c) acc[c] = unit(pf, float4{v[p][c][0], v[p][c][1], v[p][c][2], v[p][c][3]}, acc[c]);
@@ -129,6 +104,45 @@ __global__ __launch_bounds__(256) void k_attention_f32(const float* __restrict__
     if (u0 + PRE < nt) {
 #pragma unroll
       for (int p = 0; p < PRE; ++p) request_values(p, u0 + PRE + p);
+    }
+  }
+  bool odd = false;
+#pragma unroll
+  for (int c = 0; c < CW; ++c)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) odd |= !__builtin_isfinite(acc[c][i]);
+  if (__any(odd)) {   // the product once more, in the same order, with those values held apart
+#pragma unroll
+    for (int c = 0; c < CW; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int u = 0; u < nt; ++u) {
+      const bool in_part = 16 * (u + 1) > nk_full;   // (the same for the whole workgroup)
+      float x[CW][4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int key = 16 * u + 4 * kq + i;
+#pragma unroll
+        for (int c = 0; c < CW; ++c) {
+          x[c][i] = gload(vp + (size_t)min(key, nk_all - 1) * d + 64 * c);
+          if (in_part && (key >= nk_all || !__builtin_isfinite(x[c][i]))) x[c][i] = 0.f;
+        }
+      }
+      const float4 pf = *(const float4*)(S + r * ld + 16 * u + 4 * kq);
+#pragma unroll
+      for (int c = 0; c < CW; ++c) acc[c] = unit(pf, float4{x[c][0], x[c][1], x[c][2], x[c][3]}, acc[c]);
+      if (!in_part) continue;
+#pragma unroll 1
+      for (int key = 16 * u; key < min(nk_all, 16 * u + 16); ++key) {
+#pragma unroll
+        for (int c = 0; c < CW; ++c) {
+          const float y = gload(vp + (size_t)key * d + 64 * c);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int nkr = sd.causal ? sd.nk_base + row_begin + 4 * kq + i + 1 : sd.nk_base;
+            if (!__builtin_isfinite(y) && key < nkr) acc[c][i] += S[(4 * kq + i) * ld + key] * y;
+          }
+        }
+      }
     }
   }
 #pragma unroll
