@@ -30,7 +30,8 @@ def test_fp32_rows_against_the_oracle_and_across_launch_shapes(name):
     cfg = ad.make_config(dims, max_batch=B, max_src=70, max_len=48, k_max=km, dtype="fp32", special=SPECIAL, debug_logits=True)
     rng = np.random.default_rng(12)
     srcs = [rng.integers(5, dims["vocab"], size=n).astype(np.int32) for n in (1, 17, 33, 70)]
-    # blocks of rows: their sums (1, 16, 17, 33, 71, 141, 207) select every launch shape
+    # blocks of rows: their sums (1, 16, 17, 33, 71, 141, 207) select every launch shape (of the counting pass:
+    # test_gpu_vocab_rows.py)
     sizes = [[1], [16], [17], [1, 32], [16, 17, 38], [1, 2, 68, 70], [70, 1, 66, 70]]
     m = O.Model(dims, w, np.float64, max_pos=160)
     seen = {}
@@ -78,3 +79,25 @@ def test_fp32_rows_do_not_feel_values_that_are_not_finite_behind_them(dh):
             got = rows(good[:at] + [bad] + good[at + 1:])
             assert not np.isfinite(got[at + 1:]).any(), at
             assert np.array_equal(got[:at + 1].view(np.uint32), want[:at + 1].view(np.uint32)), at
+
+
+@pytest.mark.parametrize("dh", [32, 64])
+def test_fp32_attention_over_many_keys(dh):
+    """Key ranges of up to 500 (head width 64: 270, about what the configuration check admits), several 16-row tiles, self-attention
+    over a long prefix and cross-attention over long sources, against the oracle."""
+    dims = dict(enc_layers=1, dec_layers=1, d_model=128, n_heads=128 // dh, d_ffn=128, vocab=512)
+    cap = 500 if dh == 32 else 270
+    w = init_weights(dims, 31)
+    cfg = ad.make_config(dims, max_batch=2, max_src=cap, max_len=20, k_max=cap - 20, dtype="fp32", special=SPECIAL, debug_logits=True)
+    rng = np.random.default_rng(32)
+    srcs = [rng.integers(5, 512, size=n).astype(np.int32) for n in (cap, 129)]
+    blocks = [[int(t) for t in rng.integers(5, 512, size=n)] for n in (cap - 20, 150)]
+    m = O.Model(dims, w, np.float64, max_pos=cap + 1)
+    with ad.Context(cfg, w) as ctx:
+        ctx.encode(ad.AD_VERIFIER, srcs)
+        ctx.verify(blocks)
+        lg, r0 = ctx.debug_logits(), 0
+        for s, b in zip(srcs, blocks):
+            want = m.decode_full(m.encode(s), [SPECIAL["bos"]] + b[:-1])
+            assert np.abs(lg[r0:r0 + len(b)] - want).max() < 1e-4
+            r0 += len(b)

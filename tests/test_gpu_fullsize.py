@@ -167,8 +167,9 @@ def test_rows_of_the_wide_model_do_not_depend_on_the_gemm_kernel_the_row_count_s
 def test_long_source_rows_do_not_depend_on_how_the_cross_attention_splits_the_keys(name, src_lens):
     """Sources of more than 128 tokens, bit-exact.  One row tile per workgroup (a sequence alone, or few rows of
     each): the four waves of the cross-attention kernel split the keys in super-blocks of 128; several row tiles
-    per workgroup (40 rows of each of 8 sequences): every wave walks all keys with four accumulators; the
-    projection and attention as two launches: the generic attention kernel.  All three sum a row's keys in the
+    per workgroup (40 rows of each of 8 sequences): every wave walks all keys with four accumulators (base model; the
+    wide model takes two launches there in either mode); the projection and attention as two launches: the kernel that
+    stages keys and values once per 128 rows.  All three sum a row's keys in the
     order the key index fixes, so the logits of sequence 0 agree whatever the launch is; sources of 40, 129, 130
     tokens leave waves without keys, 512 fills all four."""
     dims = model_dims(name)
