@@ -84,7 +84,7 @@ void launch_embed(int dtype, const void* emb, const float* pe, const int* tok, c
 // (then the storage-type rows `A` are NOT written); otherwise a LayerNorm launch fills ln.y and A
 // first.  Same values either way.
 int launch_gemm(int dtype, const void* A, const void* W, int M, int N, int K, const Epi& e, hipStream_t s,
-                const LnA& ln = LnA{}, bool* a_written = nullptr);
+                const LnA& ln = LnA{});
 // bf16, many rows (ad_gemm_tile.hip): which products go there, and their launch (A as rows, no LayerNorm)
 bool gemm_tile_takes(int M, int N, int K, bool has_ln, int mode);
 // whether the A-in-LDS kernel with 32 rows and `strips` strips per workgroup makes one round of the 256 CUs

@@ -534,9 +534,8 @@ static int launch_astat(const bf16_t* A, const bf16_t* W, int M, int N, int K, c
 }
 
 int launch_gemm(int dtype, const void* A, const void* W, int M, int N, int K, const Epi& e, hipStream_t s,
-                const LnA& ln_in, bool* a_written) {
+                const LnA& ln_in) {
   if (M <= 0) return 0;
-  if (a_written) *a_written = true;
   LnA ln = ln_in;
   const bool streams = dtype == AD_BF16 && K <= 4096 && K % 512 == 0;   // the A-in-LDS kernel takes it
   const bool tile = dtype == AD_BF16 && gemm_tile_takes(M, N, K, ln.x != nullptr, e.mode);
@@ -548,7 +547,6 @@ int launch_gemm(int dtype, const void* A, const void* W, int M, int N, int K, co
     launch_gemm_tile(A, W, M, N, K, e, s);
     return N / 16;
   }
-  if (ln.x && a_written) *a_written = false;
   if (dtype == AD_BF16) {
     const int nb = (N / 16 + 3) / 4;
     if (K <= 4096 && K % 512 == 0) {

@@ -136,8 +136,8 @@ def test_heads_of_width_128(dtype):
 def test_rows_of_the_wide_model_do_not_depend_on_the_gemm_kernel_the_row_count_selects():
     """Big model (d 1024, FFN 4096), bit-exact: the logits of one sequence's 25-row block verified
     alone (the attention output projections and FFN2 run in the kernel that puts a strip's
-    512-slices side by side in the waves) and in the middle of 8 sequences (200 packed rows: the
-    kernel that walks the slices one after the other, several strips per workgroup)."""
+    512-slices side by side in the waves) and in the middle of 3 (75 packed rows: FFN2 tiled) and of 8
+    sequences (200 packed rows: all of them tiled)."""
     dims = model_dims("big")
     w = init_weights(dims, 411)
     ctx = ad.Context(ad.make_config(dims, max_batch=8, max_src=40, max_len=40, k_max=32, dtype="bf16", special=SPECIAL,
@@ -151,7 +151,7 @@ def test_rows_of_the_wide_model_do_not_depend_on_the_gemm_kernel_the_row_count_s
         ctx.verify(blocks[:1])
         alone = ctx.debug_logits().view(np.uint32).copy()
         assert alone.shape[0] == 25
-        for n in (3, 8):   # 75 rows: still the first kernel, several row chunks; 200 rows: the other
+        for n in (3, 8):
             order = list(range(1, n // 2 + 1)) + [0] + list(range(n // 2 + 1, n))
             ctx.encode(ad.AD_VERIFIER, [srcs[i] for i in order])
             ctx.verify([blocks[i] for i in order])

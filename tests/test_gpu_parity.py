@@ -243,8 +243,8 @@ def test_rows_do_not_depend_on_block_or_batch_shape():
 def test_rows_do_not_depend_on_the_row_regime_of_the_gemm_kernels():
     """Base model, bit-exact: the logits of one sequence's 36-row block verified alone (16 rows per
     workgroup), among 9 / 16 / 20 / 26 sequences (324 / 576 / 720 / 936 packed rows: 16-row chunks with more
-    strips per workgroup; from 520 rows 32 rows per workgroup in workgroups of 8 and 16 waves) and among 30
-    (1080 rows: the many-row variants)."""
+    strips per workgroup; from 520 rows 32 rows per workgroup in workgroups of 16 waves, and the tiled kernels) and
+    among 30 (1080 rows: FFN1 tiled, FFN2 in workgroups of eight waves)."""
     B = 30
     rig = Rig("base", "bf16", 83, B=B, max_src=40, max_len=48, k_max=40)
     try:
@@ -270,12 +270,12 @@ def test_rows_do_not_depend_on_the_row_regime_of_the_gemm_kernels():
 
 def test_rows_do_not_depend_on_the_attention_kernel_the_key_bound_selects():
     """Base model, bit-exact.  A verify call whose longest prefix + block stays within 64 keys runs the compact
-    self-attention kernel, any other the generic one, and the bound is part of the call shape a graph is kept for.
+    self-attention kernel, any other the one that stages keys and values once per 128 rows, and the bound is part of the call shape a graph is kept for.
     One sequence is verified 8 rows at a time along its own greedy output (every block is accepted whole, so the
     prefix grows by 8 per call and passes 64 keys at the ninth call; the call shape stays the same throughout: the early
     calls are replayed from a graph built with the compact kernel, the late ones must not be).  Every call's logits must
     equal those of the same rows (a) with graphs off and (b) verified beside a second sequence whose 70-row block forces
-    the generic kernel in every call."""
+    the other kernel in every call."""
     rig = Rig("base", "bf16", 91, B=2, max_src=40, max_len=96, k_max=72)
     try:
         V = rig.dims["vocab"]
@@ -300,7 +300,7 @@ def test_rows_do_not_depend_on_the_attention_kernel_the_key_bound_selects():
         c = run(1, True)
         for i in range(len(a)):
             assert np.array_equal(a[i], b[i]), ("graphs on / off", i)
-            assert np.array_equal(a[i], c[i]), ("compact / generic kernel", i)
+            assert np.array_equal(a[i], c[i]), ("compact / other kernel", i)
     finally:
         rig.ctx.set_option(ad.AD_OPT_GRAPHS, 1)
         rig.close()
