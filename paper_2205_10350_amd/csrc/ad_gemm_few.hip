@@ -18,15 +18,18 @@ namespace ad {
 // wave to wave through LDS in slice order (k ascending, 32 at a time, one accumulator per element:
 // the same bits as every other GEMM kernel here), and the wave of the last slice runs the epilogue.
 // Rows past M are not requested, four at a time (what the tile holds in their place reaches no row that is stored): with one
-// row a workgroup takes in a fifth of the bytes, 4.26 -> 3.54 us at K = 2048.  A wave per slice: K = 4096 with four waves of
-// two slices each asked for the second half of everything once the first was multiplied, 9.7 us at 25 rows and 8.2 at 11,
-// now 6.7 and 5.4.
+// row a workgroup takes in a fifth of the bytes, 4.26 -> 3.54 us at K = 2048.
+// K = 4096: eight waves, a wave per slice, while that is at most one workgroup per CU (136 KB of LDS each); four waves of two
+// slices, the second requested once the first is multiplied, two workgroups per CU, up to twice as many.  Wide model, N 1024,
+// matrix from memory / from the last-level cache, eight waves / four, us: 64 rows 6.8 / 6.4 and 9.1 / 8.0, 80 rows 10.9 / 10.6
+// and 9.9 / 8.7, 100 rows 11.1 / 10.8 and 10.1 / 8.9, 128 rows 11.5 / 11.1 and 10.5 / 9.3; in a verify forward of 4 x 25 rows (kernel
+// trace) 12.2 and 10.4.  The tiled kernel's few workgroups wait for memory stage after stage: 11.8 / 8.9 at 100 rows, 12.7 in the
+// forward, but with more workgroups than that it wins (N 2048, 96 rows 14.0 / 9.2 against 17.2 / 15.8).
 constexpr int kChainLd = 512 + 16;   // row stride of a wave's tile (elements): 32 bytes past a multiple of 64
-static size_t kchain_lds_bytes(int ns) { return (size_t)(ns < 4 ? 4 : ns) * 16 * kChainLd * 2 + 64 * 16; }
+static size_t kchain_lds_bytes(int nw) { return (size_t)nw * 16 * kChainLd * 2 + 64 * 16; }
 template <int NS, int NW>
 __global__ __launch_bounds__(64 * NW, 2) void k_gemm_bf16_kchain(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
                                                               int M, int N, int K, int n_strips, Epi e) {
-  static_assert(NS <= NW, "a wave owns at most one slice");
   extern __shared__ uint4 kchain_lds[];   // [wave][16 rows][LD], the accumulators handed on
   f32x4* hand = (f32x4*)((bf16_t*)kchain_lds + NW * 16 * kChainLd);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -35,9 +38,9 @@ __global__ __launch_bounds__(64 * NW, 2) void k_gemm_bf16_kchain(const bf16_t* _
   bf16_t* At = (bf16_t*)kchain_lds + wave * 16 * kChainLd;
   const bf16_t* a_lane = At + r * kChainLd + kq * 8;
   uint4 b[16];
-  if (NS == NW || wave < NS) {
+  auto request = [&](int slice) {
     uint4 av[16];
-    const bf16_t* ap = A + wave * 512 + lane * 8;
+    const bf16_t* ap = A + slice * 512 + lane * 8;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       if (q == 0 || m0 + 4 * q < M) {
@@ -48,27 +51,30 @@ __global__ __launch_bounds__(64 * NW, 2) void k_gemm_bf16_kchain(const bf16_t* _
         for (int i = 4 * q; i < 4 * q + 4; ++i) av[i] = uint4{0u, 0u, 0u, 0u};
       }
     }
-    const bf16_t* wp = W + (size_t)n0 * K + (size_t)wave * 8192 + lane * 8;
+    const bf16_t* wp = W + (size_t)n0 * K + (size_t)slice * 8192 + lane * 8;
 #pragma unroll
     for (int u = 0; u < 16; ++u) b[u] = ldg16(wp + u * 512);
 #pragma unroll
     for (int i = 0; i < 16; ++i) *(uint4*)(At + i * kChainLd + lane * 8) = av[i];
-  }
+  };
+  if (NS >= NW || wave < NS) request(wave);
+  constexpr int LAST = (NS - 1) % NW;
   EpiRegs<1> g;
-  if (wave == NS - 1) epi_preload<1>(e, 1, m0, n0, M, N, lane, g);
+  if (wave == LAST) epi_preload<1>(e, 1, m0, n0, M, N, lane, g);
   f32x4 acc[1] = {f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
   for (int p = 0; p < NS; ++p) {
-    if (wave == p) {
+    if (wave == p % NW) {
       if (p > 0) acc[0] = hand[lane];
 #pragma unroll
       for (int u = 0; u < 16; ++u)
         acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, *(const uint4*)(a_lane + 32 * u)), __builtin_bit_cast(bf16x8, b[u]), acc[0], 0, 0, 0);
       if (p + 1 < NS) hand[lane] = acc[0];
+      if (p + NW < NS) request(p + NW);   // (the wave's own tile and registers: no barrier)
     }
     if (p + 1 < NS) __syncthreads();
   }
-  if (wave == NS - 1) epi_apply<bf16_t, 1>(e, acc, g, 1, m0, n0, M, N, lane);
+  if (wave == LAST) epi_apply<bf16_t, 1>(e, acc, g, 1, m0, n0, M, N, lane);
 }
 void launch_kchain(const void* A, const void* W, int M, int N, int K, const Epi& e, hipStream_t s) {
   const int n_strips = N / 16, grid = n_strips * ((M + 15) / 16);
@@ -83,7 +89,8 @@ void launch_kchain(const void* A, const void* W, int M, int N, int K, const Epi&
   using I8 = std::integral_constant<int, 8>;
   if (K == 1024) go(I2{}, I4{});
   else if (K == 2048) go(I4{}, I4{});
-  else go(I8{}, I8{});
+  else if (grid <= 256) go(I8{}, I8{});
+  else go(I8{}, I4{});
 }
 
 // ---------------------------------------------------------------- rows through the pending LayerNorm: K = 1024

@@ -321,9 +321,8 @@ static void launch_roll(const bf16_t* A, const bf16_t* W, int M, int N, int K, c
 //    rows 8.4 / 6.5, 626 rows 38.8 / 25, 3252 rows 221 / 100
 //  K = 1024, none: N 1024 80 / 130 / 626 / 3252 rows 3.4 / 4.7 / 6.4 / 26.1 there, 3.8 / 4.0 / 5.4 / 16.5 here; N 512 and 768
 //    130 / 160 / 161 rows 3.7 / 3.7 / 4.6 and 3.9 / 4.0 / 6.3 there, 4.0 / 4.1 / 4.1 and 4.2 / 4.2 / 4.1 here
-//  K = 4096: k_gemm_bf16_kchain while its workgroups, 136 KB of LDS each, are one per CU: N 1024 64 / 65 / 96 / 128 rows 6.4 / 9.8 /
-//    10.7 / 11.1 there, 8.8 / 8.5 / 8.9 / 8.9 here; N 2048 32 / 33 / 64 / 96 rows 7.2 / 10.7 / 12.0 / 16.9 there, 9.0 / 8.6 / 9.1 /
-//    9.2 here; N 512 128 rows 6.3 / 8.7.  130 / 626 / 3252 rows 12.7 / 22.2 / 80 there, 8.2 / 14.6 / 43 here
+//  K = 4096: beyond the two rounds of one workgroup per CU that k_gemm_bf16_kchain makes (its comment); N 1024 130 / 626 / 3252 rows
+//    12.7 / 22.2 / 80 there, 8.2 / 14.6 / 43 here (matrix from the last-level cache; from memory 160 rows 15.3 / 13.6)
 //  K = 512, LayerNorm pending: below 1408 columns never (N 512 2048 rows 8.7 / 9.9, N 1024 1345 / 2048 / 4000 rows 8.7 / 9.4 / 15.7
 //    there, 10.5 / 12.0 / 17.9 here, N 1280 2048 / 3000 rows 12.0 / 17.3 there, 13.5 / 16.3 here); below 2048 from 1400 rows (N 1408
 //    1345 / 1400 rows 9.9 / 12.4 there, 10.7 / 10.8 here, N 1536 1345 / 1400 / 2048 rows 11.3 / 13.5 / 15.0 there, 11.9 / 12.0 / 14.1
@@ -345,7 +344,7 @@ bool gemm_tile_takes(int M, int N, int K, bool has_ln, int mode) {
   }
   if (K == 512) return M >= 520;
   if (K == 2048) return M >= 520 && !(M > 1024 && gemm_one_round(M, N, 8));
-  if (K == 4096) return M > 128 || (N / 16) * ((M + 15) / 16) > 256;
+  if (K == 4096) return M > 160 || (N / 16) * ((M + 15) / 16) > 512;
   if (K == 1536 && M > 1600 && gemm_one_round(M, N, 8)) return false;
   return has_ln ? M > (N > 4096 ? 16 : N == 4096 ? 64 : 96) : M > (K == 1024 && N < 1024 ? 160 : 128);
 }

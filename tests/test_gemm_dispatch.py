@@ -17,8 +17,8 @@ def takes():
     return lambda M, N, K, ln, mode: f(M, N, K, ln, mode)
 
 
-@pytest.mark.parametrize("N,last", [(512, 128), (1024, 64), (2048, 32)])
-def test_k_4096_leaves_the_kernel_whose_waves_share_k_while_that_is_one_workgroup_per_cu(takes, N, last):
+@pytest.mark.parametrize("N,last", [(512, 160), (768, 160), (1024, 128), (1536, 80), (2048, 64)])
+def test_k_4096_stays_with_the_kernel_whose_waves_share_k_up_to_two_workgroups_per_cu(takes, N, last):
     assert not takes(last, N, 4096, False, RESID)
     assert takes(last + 1, N, 4096, False, RESID)
 
