@@ -420,13 +420,14 @@ static float astat_plan(int mt, int M, int N, int K, bool with_ln, int* per_wg_o
   return best;
 }
 // The same for the output projection of K = 512 and 1024, where the matrix is what a launch waits for: every row chunk reads all of
-// it from L2, 0.03 us per MB and chunk, and two workgroups of a CU share its MFMA pipes.  Constants fitted to 13000 launches,
-// vocabulary 4112..50000 x 65..2048 rows x every shape, with the matrix in the last-level cache and from memory.  The shapes it picks
-// take 0.95 of the time of the model above at K = 512 and 0.97 at K = 1024 (from memory 0.90 and 0.92), and 0.89 and 0.94 (0.92 and
-// 0.96) of a rule that took 32 rows per workgroup up to 192 and 64 beyond; a single shape loses up to 14 % in one of the two
-// regimes where it gains in the other (K = 1024, vocabulary 32000, 112 rows 19.9 -> 22.7 us, from memory 25.2 -> 23.2).
-// K = 512, vocabulary 32000, model above / that rule / this: 96 rows 12.5 / 12.7 / 12.4 us, 128 rows 14.2 / 12.8 / 12.4, 160 rows 16.7 /
-// 14.4 / 13.9, 288 rows 18.1 / 20.4 / 18.0, 512 rows 26.3 / 24.2 / 22.7; vocabulary 8000, 256 rows 9.3 / 12.1 / 8.8.
+// it from L2, 0.02 us per MB and chunk, and two workgroups of a CU share its MFMA pipes.  Constants fitted to 13000 launches,
+// vocabulary 4112..50000 x 65..2048 rows x every shape, the matrix in the last-level cache (where a decode with one model finds
+// it) counting more than from memory.  The shapes it picks take 0.95 of the time of the model above at K = 512 and 0.96 at
+// K = 1024 (from memory 0.91 and 0.93), and 0.89 and 0.93 (0.94 and 0.97) of a rule that took 32 rows per workgroup up to 192 and 64
+// beyond; the worst single pick is 8 % behind the better of the two (from memory 16 %).
+// K = 512, vocabulary 32000, model above / that rule / this: 96 rows 12.6 / 12.7 / 12.5 us, 128 rows 14.6 / 12.9 / 12.6, 160 rows 16.9 /
+// 14.4 / 13.9, 288 rows 18.0 / 20.3 / 18.0, 512 rows 25.8 / 24.5 / 22.6; vocabulary 8000, 256 rows 9.8 / 12.2 / 8.9; K = 1024, 112 rows
+// 20.9 / 20.0 / 19.5.
 struct VocabPlan { int mt, per_wg; };
 static VocabPlan vocab_plan(int M, int N, int K, bool with_ln) {
   const int n_strips = N / 16, halves = K / 512;
@@ -436,11 +437,11 @@ static VocabPlan vocab_plan(int M, int N, int K, bool with_ln) {
     const size_t lds = astat_lds_bytes(mt, K);
     if (mt > 1 && lds > 150 * 1024) break;
     const int chunks = (M + mt * 16 - 1) / (mt * 16);
-    const float wg_us = 2.4f + 1.5f * mt * (with_ln ? 1.f : 0.2f), matrix_us = 0.03f * chunks * (2e-6f * N * K);
+    const float wg_us = 0.86f + (1.28f + 0.19f * halves) * mt * (with_ln ? 1.f : 0.2f), matrix_us = 0.02f * chunks * (2e-6f * N * K);
     for (int per_wg = 8; per_wg <= 128; per_wg += 8) {
       const int groups = (n_strips + per_wg - 1) / per_wg, units = per_wg / 8 * halves;
       const int wgs_cu = ((groups >= 8 ? (groups + 7) / 8 * chunks : (groups * chunks + 7) / 8) + 31) / 32;   // of the busiest XCD's CUs
-      const float one_us = wg_us + units * (0.15f + 0.42f * mt), two_us = wg_us + units * (0.28f + 0.86f * mt);
+      const float one_us = wg_us + units * (0.15f + 0.19f * mt), two_us = wg_us + units * (0.22f + 0.46f * mt);
       const float us = matrix_us + (lds * 2 <= 160 * 1024 ? wgs_cu / 2 * two_us + wgs_cu % 2 * one_us : wgs_cu * one_us);
       if (us < best_us) { best_us = us; best = VocabPlan{mt, per_wg}; }
       if (groups == 1) break;
