@@ -34,6 +34,9 @@ AD_OPT_GRAPHS_CAPTURED = 4
 AD_OPT_SPIN_WAIT = 5
 AD_OPT_FUSE_CROSSQ = 6
 AD_OPT_OVERLAP_ENCODERS = 7
+AD_OPT_TEAMS = 8
+AD_OPT_TEAM_FAILURES = 9
+AD_OPT_TEAM_WAIT = 10
 
 
 class AdConfig(C.Structure):

@@ -5,13 +5,16 @@
 #include <string.h>
 
 #include <algorithm>
+#include <array>
 #include <chrono>
 #include <string>
 #include <map>
+#include <tuple>
 #include <utility>
 #include <vector>
 
 #include "ad_internal.h"
+#include "ad_team.h"
 
 namespace ad {
 const char* global_error();
@@ -48,6 +51,7 @@ struct Plan {
   size_t cache_k, cache_v, cache_layer_stride;          // [NL][B*l_cap, d]
   size_t mem_k[2], mem_v[2], mem_layer_stride;          // per model: [NL][B*max_src, d]
   size_t row_tok, row_pos, row_seq, row_dst, row_dst2, row_start, self_desc, cross_desc;
+  size_t team_words[3];                                 // barrier state of the team launches: the encoders' (per model), the decoders'
   size_t len, pending, finished, max_out, src_len[2], out, result, k_dev, draft_dev, src_dev, draft_out;
 };
 
@@ -111,6 +115,7 @@ static Plan make_plan(const ad_config& c, bool with_drafter) {
   p.draft_dev = p.k_dev + B * 4;
   p.src_dev = take(B * 4 * 2 + B * c.max_src * 4);   // src_len[B], max_out[B], src[B, max_src]: one upload
   p.draft_out = take(B * c.k_max * 4);
+  for (int i = 0; i < 3; ++i) p.team_words[i] = take(kTeamWords * 4);
   p.total = off;
   return p;
 }
@@ -170,6 +175,9 @@ static void* static_scratch_for_current_device() {
 
 using namespace ad;
 
+// One team launch: its arguments, the most rows of a team and the most keys of a problem (they select the kernel).
+struct TeamRun { TeamArgs a; int max_rows, max_keys; };
+
 struct ad_ctx {
   ad_config cfg;
   Plan plan;
@@ -211,10 +219,21 @@ struct ad_ctx {
   // One launch per stage: the launches of a verify call (row assembly, forward, acceptance) are
   // captured into a graph per call shape on the shape's third appearance and replayed after.
   bool graphs_on = true;
-  typedef std::pair<unsigned long long, unsigned long long> GraphKey;   // (kind | shape, further shape values)
+  typedef std::array<int, 28> TeamPart;   // how a team launch deals out the rows (all zero: no team launch)
+  typedef std::tuple<unsigned long long, unsigned long long, TeamPart> GraphKey;   // (kind | shape, further shape values)
   std::map<GraphKey, hipGraphExec_t> graphs;
   std::map<GraphKey, int> graph_seen;
   std::vector<int> last_k;       // k[b] of the last verify call
+
+  // Stacks of layers as one launch (ad_team.hip).  can_team: the model and the device fit it.  A launch that could not
+  // bring its team together (other work held compute units of the XCD) leaves the call to the launches, and so the next
+  // team_rest calls.
+  bool can_team[2][2] = {{false, false}, {false, false}};   // [model][encoder, decoder]
+  bool team_on = true;
+  int team_ticks = kTeamFormTicks;
+  int team_rest = 0, team_failures = 0;
+  bool last_team = false;
+  TeamRun last_run{};
 
   // the drafter's encoder beside the verifier's: a stream of the library's own (default priority),
   // the second activation block, and the two events that order it against the context's stream
@@ -263,6 +282,112 @@ static VerifyTables tables(const ad_ctx* c) {
   t.row_dst = c->at<int>(p.row_dst); t.row_dst2 = c->at<int>(p.row_dst2); t.row_start = c->at<int>(p.row_start);
   t.self_desc = c->at<SeqDesc>(p.self_desc); t.cross_desc = c->at<SeqDesc>(p.cross_desc);
   return t;
+}
+
+// ---- stacks of layers as one launch
+static bool team_layout_ok(const ad_config& c, const ModelW& w, bool dec) {
+  if (c.dtype != AD_BF16 || c.d_model != kTeamD || c.n_heads != kTeamD / 64 || c.d_ffn != kTeamF) return false;
+  auto is = [](const void* p, const void* base, int off) { return (const char*)p == (const char*)base + off; };
+  if (dec) {
+    typedef TeamOff<true> O;
+    const char* b = (const char*)w.dec[0].self.wqkv;
+    for (const DecLayerW& L : w.dec) {
+      if (!is(L.self.wqkv, b, O::wqkv) || !is(L.self.wo, b, O::wo) || !is(L.self.bqkv, b, O::bqkv) || !is(L.self.bo, b, O::bo) ||
+          !is(L.ln1.g, b, O::ln1g) || !is(L.ln1.b, b, O::ln1b) || !is(L.cross.wqkv, b, O::cwq) || !is(L.cross.wo, b, O::cwo) ||
+          !is(L.cross.bqkv, b, O::cbq) || !is(L.cross.bo, b, O::cbo) || !is(L.ln2.g, b, O::ln2g) || !is(L.ln2.b, b, O::ln2b) ||
+          !is(L.ffn.w1, b, O::w1) || !is(L.ffn.b1, b, O::b1) || !is(L.ffn.w2, b, O::w2) || !is(L.ffn.b2, b, O::b2) ||
+          !is(L.ln3.g, b, O::ln_lg) || !is(L.ln3.b, b, O::ln_lb))
+        return false;
+      b += O::kLayerBytes;
+    }
+    return true;
+  }
+  typedef TeamOff<false> O;
+  const char* b = (const char*)w.enc[0].self.wqkv;
+  for (const EncLayerW& L : w.enc) {
+    if (!is(L.self.wqkv, b, O::wqkv) || !is(L.self.wo, b, O::wo) || !is(L.self.bqkv, b, O::bqkv) || !is(L.self.bo, b, O::bo) ||
+        !is(L.ln1.g, b, O::ln1g) || !is(L.ln1.b, b, O::ln1b) || !is(L.ffn.w1, b, O::w1) || !is(L.ffn.b1, b, O::b1) ||
+        !is(L.ffn.w2, b, O::w2) || !is(L.ffn.b2, b, O::b2) || !is(L.ln2.g, b, O::ln_lg) || !is(L.ln2.b, b, O::ln_lb))
+      return false;
+    b += O::kLayerBytes;
+  }
+  return true;
+}
+// Deals n problems of rows[i] (+ rows2[i]) packed rows out to teams, whole problems, in order; up to eight problems get a
+// team each, more are cut where the running row count passes an eighth of all.  false: a team would exceed the limits.
+static bool team_deal(const int* rows, const int* rows2, int n, TeamRun* t) {
+  int live = 0, M = 0;
+  for (int i = 0; i < n; ++i) {
+    const int w = rows[i] + (rows2 ? rows2[i] : 0);
+    M += w;
+    live += w > 0;
+  }
+  if (live < 1) return false;
+  TeamArgs& a = t->a;
+  int team = -1, last_part = -1, at = 0, r0 = 0, r1 = 0, team_rows = 0, in_team = 0;
+  if (rows2)
+    for (int i = 0; i < n; ++i) r1 += rows[i];
+  t->max_rows = 0;
+  for (int i = 0; i < n; ++i) {
+    const int w = rows[i] + (rows2 ? rows2[i] : 0);
+    if (w > 0) {
+      const int part = live <= 8 ? last_part + 1 : std::max(last_part, std::min(7, (int)((2LL * at + w) * 8 / (2LL * M))));
+      if (part != last_part) {
+        last_part = part;
+        ++team;
+        a.row_lo[0][team] = r0; a.row_lo[1][team] = r1; a.prob[team] = i;
+        team_rows = 0; in_team = 0;
+      }
+    }
+    if (team >= 0) {
+      ++in_team;
+      if (in_team * (rows2 ? 2 : 1) > 64) return false;   // a lane each when the team's chunks are listed
+    }
+    team_rows += w; at += w; r0 += rows[i]; r1 += rows2 ? rows2[i] : 0;
+    t->max_rows = std::max(t->max_rows, team_rows);
+  }
+  a.n_teams = team + 1;
+  a.row_lo[0][team + 1] = r0; a.row_lo[1][team + 1] = r1; a.prob[team + 1] = n;
+  return t->max_rows <= kTeamMaxRows;
+}
+static bool team_usable(ad_ctx* c, int model, bool dec) {
+  if (!c->team_on || !c->can_team[model][dec]) return false;
+  if (c->team_rest > 0) { --c->team_rest; return false; }
+  return true;
+}
+static void team_common(const ad_ctx* c, int model, bool dec, int words, TeamRun* t) {
+  const Plan& p = c->plan;
+  TeamArgs& a = t->a;
+  a.xcd0 = 0; a.head_only = 0; a.prob2_off = 0;
+  a.layers = dec ? c->cfg.dec_layers : c->cfg.enc_layers;
+  a.scale = 1.0f / sqrtf(64.0f);
+  a.form_ticks = (unsigned)c->team_ticks;
+  a.w = (const char*)(dec ? c->w[model].dec[0].self.wqkv : c->w[model].enc[0].self.wqkv);
+  a.x = c->at<float>(p.x); a.s = c->at<float>(p.s);
+  a.xa = c->at<bf16_storage>(p.xa); a.q = c->at<bf16_storage>(p.q); a.att = c->at<bf16_storage>(p.att); a.f = c->at<bf16_storage>(p.f);
+  a.K = c->at<bf16_storage>(p.tk); a.V = c->at<bf16_storage>(p.tv); a.kv_stride = 0;
+  a.Km = dec ? (const bf16_storage*)(c->ws + p.mem_k[model]) : nullptr;
+  a.Vm = dec ? (const bf16_storage*)(c->ws + p.mem_v[model]) : nullptr;
+  a.m_stride = p.mem_layer_stride;
+  const VerifyTables vt = tables(c);
+  a.self_desc = vt.self_desc; a.cross_desc = vt.cross_desc; a.row_dst = vt.row_dst;
+  a.words = (unsigned*)(c->ws + p.team_words[words]); a.fail = a.words + kTeamFail;
+}
+static ad_ctx::TeamPart team_part(const TeamRun* t) {
+  ad_ctx::TeamPart k{};
+  if (!t) return k;
+  int i = 0;
+  k[i++] = t->a.n_teams; k[i++] = t->max_rows > 32 ? 4 : t->max_rows > 16 ? 2 : 1; k[i++] = t->max_keys > 64 ? 2 : 1;
+  for (int j = 1; j <= 8; ++j) { k[i++] = j <= t->a.n_teams ? t->a.row_lo[0][j] : 0; k[i++] = j <= t->a.n_teams ? t->a.prob[j] : 0; k[i++] = j <= t->a.n_teams ? t->a.prob[j - 1] : 0; }
+  return k;
+}
+// A team launch's arguments say how the rows are dealt out; with many sequences that hardly ever comes back, and four launches
+// cost the host no more than a graph's: no graph is built for it.
+constexpr int kTeamGraphBatch = 4;
+// a team did not come together: the launches take over, for the next calls too (32, 64, .. 4096 of them)
+static void team_failed(ad_ctx* c) {
+  c->team_rest = 32 << std::min(c->team_failures, 7);
+  ++c->team_failures;
 }
 
 // s = x + A W^T + bias; the LayerNorm s -> (x, xa) is left to the next consumer of the rows:
@@ -356,7 +481,7 @@ static void embed_rows(ad_ctx* c, const ModelW& w, int M) {
   c->ln_pending = nullptr;
   VerifyTables t = tables(c);
   launch_embed(c->cfg.dtype, w.emb, c->at<float>(p.pe), t.row_tok, t.row_pos, M, c->cfg.d_model,
-               sqrtf((float)c->cfg.d_model), c->at<float>(p.x), c->at<void>(p.xa), c->stream);
+               sqrtf((float)c->cfg.d_model), c->at<float>(p.x), c->at<void>(p.xa), c->stream, (unsigned*)(c->ws + p.team_words[2]));
 }
 
 // Output projection fused with the per-row arg max; `A` holds Mv rows.
@@ -385,12 +510,16 @@ static void vocab_finish(ad_ctx* c, int Mv, int n_part, const PartialBuf* pb = n
 // projection multiplies are in memory (xa) for whoever multiplies them again
 // embedded = true: the rows are embedded already (x, xa)
 static int verify_forward(ad_ctx* c, int M, hipEvent_t ev_a = nullptr, hipEvent_t ev_b = nullptr, bool finish = true,
-                          bool plain_rows = false, bool embedded = false, const PartialBuf* pb = nullptr) {
+                          bool plain_rows = false, bool embedded = false, const PartialBuf* pb = nullptr,
+                          const TeamRun* team = nullptr /* the layers as one launch */) {
   const Plan& p = c->plan;
   const ModelW& w = c->w[AD_VERIFIER];
   if (embedded) c->ln_pending = nullptr;
   else embed_rows(c, w, M);
-  for (int l = 0; l < c->cfg.dec_layers; ++l) {
+  if (team) {
+    launch_team(team->a, true, team->max_rows, team->max_keys, c->stream);
+    c->ln_pending = &w.dec.back().ln3;
+  } else for (int l = 0; l < c->cfg.dec_layers; ++l) {
     const DecLayerW& L = w.dec[l];
     self_attn_block(c, L.self, L.ln1, M, c->ws + p.cache_k + l * p.cache_layer_stride,
                     c->ws + p.cache_v + l * p.cache_layer_stride, p.l_cap);
@@ -545,7 +674,20 @@ int ad_create(const ad_config* cfg, const void* verifier_w, const void* drafter_
         return bail("hipMemcpyAsync(memory projections)", e);
     }
   }
+  for (int i = 0; i < 3; ++i)
+    if ((e = hipMemsetAsync(c->ws + plan.team_words[i], 0, kTeamWords * 4, c->stream)) != hipSuccess) return bail("hipMemsetAsync", e);
   if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return bail("hipStreamSynchronize", e);
+  {
+    // (the kernel's grid is dealt out to eight XCDs of 32 compute units)
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus == 8 * kTeamMembers &&
+        (size_t)plan.m_cap * kTeamF * 2 < (1u << 31) && plan.cache_layer_stride < (1u << 31)) {   // (32-bit offsets in the kernel)
+      for (int i = 0; i < (c->has_drafter ? 2 : 1); ++i)
+        for (int dec = 0; dec < 2; ++dec) c->can_team[i][dec] = team_layout_ok(*cfg, c->w[i], dec != 0) && prepare_team(dec != 0);
+    } else {
+      (void)hipGetLastError();
+    }
+  }
   c->h_len.assign(B, 0); c->h_finished.assign(B, 1); c->h_max_out.assign(B, 0);
   c->h_src_len[0].assign(B, 0); c->h_src_len[1].assign(B, 0);
   *out = c;
@@ -580,9 +722,9 @@ static unsigned long long shape_key(int rows, int max_rows, int n_seq, int knob)
 // for the context (a stream that cannot be captured, e.g. the null stream, is such a failure).
 template <typename F>
 static bool run_as_graph(ad_ctx* c, hipStream_t stream, unsigned long long shape, const F& launches,
-                         unsigned long long more = 0) {
+                         unsigned long long more = 0, const ad_ctx::TeamPart& part = ad_ctx::TeamPart{}) {
   if (!c->graphs_on) return false;
-  const ad_ctx::GraphKey key(shape, more);
+  const ad_ctx::GraphKey key(shape, more, part);
   auto it = c->graphs.find(key);
   if (it != c->graphs.end()) {
     if (hipGraphLaunch(it->second, stream) == hipSuccess) return true;
@@ -614,6 +756,70 @@ static bool run_as_graph(ad_ctx* c, hipStream_t stream, unsigned long long shape
   return false;
 }
 
+// kernels and device-to-device copies of an encoder forward over the inputs at `dev` (src_len[B], max_out[B], src[B, max_src])
+static void encode_launches(ad_ctx* c, int model, const int* dev, int M, int B, const TeamRun* team) {
+  const ad_config& cf = c->cfg;
+  const Plan& p = c->plan;
+  const int d = cf.d_model, S = cf.max_src;
+  VerifyTables t = tables(c);
+  const ModelW& w = c->w[model];
+  const bool ver = model == AD_VERIFIER;
+  launch_assemble_embed_encoder(cf.dtype, dev + 2 * B, S, dev, dev + B, B, S, t, c->at<int>(p.src_len[model]),
+                                c->at<int>(p.max_out), ver ? c->at<int>(p.len) : nullptr, c->at<int>(p.pending),
+                                c->at<int>(p.finished), cf.bos, M, w.emb, c->at<float>(p.pe), d, sqrtf((float)d),
+                                c->at<float>(p.x), c->at<void>(p.xa), c->stream, team ? team->a.words : nullptr);
+  c->ln_pending = nullptr;
+  if (team) {
+    launch_team(team->a, false, team->max_rows, team->max_keys, c->stream);
+    c->ln_pending = &w.enc.back().ln2;
+  } else for (int l = 0; l < cf.enc_layers; ++l) {
+    const EncLayerW& L = w.enc[l];
+    // the sentence's own keys/values live in the packed temporaries: key row = packed row
+    Epi e{};
+    e.mode = EPI_QKV; e.d = d; e.bias = L.self.bqkv; e.out0 = c->at<void>(p.q);
+    e.out1 = c->at<void>(p.tk); e.out2 = c->at<void>(p.tv); e.row_dst = t.row_dst;
+    gemm_rows(c, L.self.wqkv, M, 3 * d, e);
+    launch_attention(cf.dtype, c->at<void>(p.q), c->at<void>(p.tk), c->at<void>(p.tv), c->at<void>(p.att),
+                     t.self_desc, B, c->fw_max_rows, cf.n_heads, d / cf.n_heads, c->fw_max_rows <= 64 ? 64 : S, c->stream);
+    gemm_resid_ln(c, c->at<void>(p.att), L.self.wo, L.self.bo, M, d, d, L.ln1);
+    ffn_block(c, L.ffn, L.ln2, M);
+  }
+  // cross-attention keys and values of every decoder layer: memory . [wk; wv]^T + [bk; bv], the
+  // layers' matrices side by side (copied so at ad_create), the encoder's last LayerNorm applied
+  // while the rows are staged
+  {
+    Epi e{};
+    e.mode = EPI_KV; e.d = d; e.bias = c->at<float>(p.kv_b[model]);
+    e.out1 = c->ws + p.mem_k[model]; e.out2 = c->ws + p.mem_v[model];
+    e.layer_stride = p.mem_layer_stride;
+    e.row_dst = t.row_dst2;
+    gemm_rows(c, c->ws + p.kv_w[model], M, cf.dec_layers * 2 * d, e);
+  }
+}
+// After a result that says so (TeamFail): the team launches' outputs do not exist.  Waits, runs the encoders concerned
+// launch by launch over the inputs that still lie in the staging buffer, and leaves the fail words clear.  The caller
+// repeats its own launches.
+static int team_recover(ad_ctx* c) {
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  if (c->stream2) HIP_TRY(c, hipStreamSynchronize(c->stream2));
+  unsigned fail[3];
+  for (int i = 0; i < 3; ++i) {
+    unsigned* w = (unsigned*)(c->ws + c->plan.team_words[i]) + kTeamFail;
+    HIP_TRY(c, hipMemcpy(&fail[i], w, 4, hipMemcpyDeviceToHost));
+    HIP_TRY(c, hipMemset(w, 0, 4));
+  }
+  team_failed(c);
+  for (int model = 0; model < 2; ++model) {
+    if (!fail[model] || !c->encoded[model]) continue;
+    int M = 0;
+    c->fw_nseq = c->B; c->fw_max_rows = 0;
+    for (int b = 0; b < c->B; ++b) { M += c->h_src_len[model][b]; c->fw_max_rows = std::max(c->fw_max_rows, c->h_src_len[model][b]); }
+    encode_launches(c, model, c->pin_dev + c->pl.enc[model], M, c->B, nullptr);
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+  }
+  return AD_OK;
+}
+
 extern "C" {
 
 int ad_encode(ad_ctx* c, int model, const int32_t* src, const int32_t* src_len, int B, const int32_t* max_out) {
@@ -626,7 +832,7 @@ int ad_encode(ad_ctx* c, int model, const int32_t* src, const int32_t* src_len, 
       if (max_out[b] < 1 || max_out[b] > c->cfg.max_len) return fail(c, AD_EINVAL, "max_out outside [1, max_len]");
   const ad_config& cf = c->cfg;
   const Plan& p = c->plan;
-  const int d = cf.d_model, S = cf.max_src;
+  const int S = cf.max_src;
   // The two encoders of a draft-then-verify decode side by side (their forwards are independent and
   // both are needed before the first draft): the verifier's encode marks the point of the
   // context's stream it starts at; the drafter's encode that follows runs on the library's second
@@ -670,44 +876,28 @@ int ad_encode(ad_ctx* c, int model, const int32_t* src, const int32_t* src_len, 
     HIP_TRY(c, hipEventRecord(c->ev_up[model], c->stream));
     c->up_pending[model] = true;
   }
-  VerifyTables t = tables(c);
   c->fw_nseq = B;
   c->fw_max_rows = *std::max_element(src_len, src_len + B);
-  // kernels and device-to-device copies of the encoder forward: replayed as a graph per call shape
-  auto launches = [&]() {
-    const ModelW& w = c->w[model];
-    const bool ver = model == AD_VERIFIER;
-    launch_assemble_embed_encoder(cf.dtype, dev + 2 * B, S, dev, dev + B, B, S, t, c->at<int>(p.src_len[model]),
-                                  c->at<int>(p.max_out), ver ? c->at<int>(p.len) : nullptr, c->at<int>(p.pending),
-                                  c->at<int>(p.finished), cf.bos, M, w.emb, c->at<float>(p.pe), d, sqrtf((float)d),
-                                  c->at<float>(p.x), c->at<void>(p.xa), c->stream);
-    c->ln_pending = nullptr;
-    for (int l = 0; l < cf.enc_layers; ++l) {
-      const EncLayerW& L = w.enc[l];
-      // the sentence's own keys/values live in the packed temporaries: key row = packed row
-      Epi e{};
-      e.mode = EPI_QKV; e.d = d; e.bias = L.self.bqkv; e.out0 = c->at<void>(p.q);
-      e.out1 = c->at<void>(p.tk); e.out2 = c->at<void>(p.tv); e.row_dst = t.row_dst;
-      gemm_rows(c, L.self.wqkv, M, 3 * d, e);
-      launch_attention(cf.dtype, c->at<void>(p.q), c->at<void>(p.tk), c->at<void>(p.tv), c->at<void>(p.att),
-                       t.self_desc, B, c->fw_max_rows, cf.n_heads, d / cf.n_heads, c->fw_max_rows <= 64 ? 64 : S, c->stream);
-      gemm_resid_ln(c, c->at<void>(p.att), L.self.wo, L.self.bo, M, d, d, L.ln1);
-      ffn_block(c, L.ffn, L.ln2, M);
-    }
-    // cross-attention keys and values of every decoder layer: memory . [wk; wv]^T + [bk; bv], the
-    // layers' matrices side by side (copied so at ad_create), the encoder's last LayerNorm applied
-    // while the rows are staged
-    {
-      Epi e{};
-      e.mode = EPI_KV; e.d = d; e.bias = c->at<float>(p.kv_b[model]);
-      e.out1 = c->ws + p.mem_k[model]; e.out2 = c->ws + p.mem_v[model];
-      e.layer_stride = p.mem_layer_stride;
-      e.row_dst = t.row_dst2;
-      gemm_rows(c, c->ws + p.kv_w[model], M, cf.dec_layers * 2 * d, e);
-    }
-  };
+  // the layers as one launch where the teams can hold the rows; the two models' encoders side by side need XCDs of their own
+  TeamRun run;
+  run.max_keys = c->fw_max_rows;
+  bool team = mapped && run.max_keys <= kTeamMaxKeys && team_deal(src_len, nullptr, B, &run) && (!side.on || run.a.n_teams <= 4) &&
+              team_usable(c, model, false);
+  if (team) {
+    team_common(c, model, false, model, &run);
+    if (side.on) run.a.xcd0 = 8 - run.a.n_teams;
+  }
+  auto launches = [&]() { encode_launches(c, model, dev, M, B, team ? &run : nullptr); };
   const unsigned long long key = (1ull << 63) | ((unsigned long long)model << 62) | shape_key(M, c->fw_max_rows, B, side.on ? 1 : 0);
-  if (!run_as_graph(c, c->stream, key, launches)) launches();
+  // Beyond 16 rows a team the launches, replayed as a graph, are as fast or faster (one sequence of 27 tokens, encode to first
+  // result: 286 against 308 us; launched one by one 340): the team serves the shapes that have no graph yet.
+  bool launched = false;
+  if (!team || run.max_rows > 16) {
+    launched = run_as_graph(c, c->stream, key, [&]() { encode_launches(c, model, dev, M, B, nullptr); });
+  } else if (B <= kTeamGraphBatch) {
+    launched = run_as_graph(c, c->stream, key, launches, 0, team_part(&run));
+  }
+  if (!launched) launches();
   if (side.on) {
     HIP_TRY(c, hipEventRecord(c->ev_enc2, c->stream));
     c->enc2_pending = true;
@@ -747,6 +937,8 @@ struct VerifyLaunch {
   int* part_idx;
   int part_stride;
   int M, B;
+  const TeamRun* team;               // the layers as one launch (null: launch by launch)
+  TeamFail fail;
 };
 // The launches of one verify call: row assembly + embedding, the forward, arg-max finish + acceptance.
 static void verify_launches(ad_ctx* c, const VerifyLaunch& v) {
@@ -759,15 +951,15 @@ static void verify_launches(ad_ctx* c, const VerifyLaunch& v) {
     launch_argmax_accept(pv, pi, stride, n_part, c->at<int>(p.o_hat), c->at<float>(p.o_val), v.k_src, v.draft_src, km,
                          t.row_start, v.B, cf.eos, cf.max_len, c->at<int>(p.max_out), c->at<int>(p.len),
                          c->at<int>(p.pending), c->at<int>(p.finished), c->at<int>(p.out), v.result_dst, v.ticket_in,
-                         v.ticket_out, c->fw_max_rows, v.M, c->stream, gp);
+                         v.ticket_out, c->fw_max_rows, v.M, c->stream, gp, v.fail);
   };
   launch_assemble_embed_verify(cf.dtype, v.k_src, v.draft_src, v.rows_src, v.rows_stride, km, c->at<int>(p.len), c->at<int>(p.pending),
                                c->at<int>(p.src_len[0]), v.B, p.l_cap, cf.max_src, t, v.M, c->w[AD_VERIFIER].emb,
                                c->at<float>(p.pe), cf.d_model, sqrtf((float)cf.d_model), c->at<float>(p.x),
-                               c->at<void>(p.xa), c->stream);
+                               c->at<void>(p.xa), c->stream, v.team ? v.team->a.words : nullptr);
   PartialBuf pb{v.part_val, v.part_idx, v.part_stride};
   if (!gadpp) {
-    const int n_part = verify_forward(c, v.M, nullptr, nullptr, false, false, true, &pb);
+    const int n_part = verify_forward(c, v.M, nullptr, nullptr, false, false, true, &pb, v.team);
     accept(v.part_val, v.part_idx, v.part_stride, n_part, GadppIn{});
     return;
   }
@@ -775,7 +967,7 @@ static void verify_launches(ad_ctx* c, const VerifyLaunch& v) {
   // a second pass of the output projection that counts the columns scoring above it (the
   // logits still never reach memory), the relaxed replacement of o_hat, and acceptance
   const ModelW& w = c->w[AD_VERIFIER];
-  (void)verify_forward(c, v.M, nullptr, nullptr, true, true, true, &pb);
+  (void)verify_forward(c, v.M, nullptr, nullptr, true, true, true, &pb, v.team);
   launch_draft_logit(cf.dtype, c->at<void>(p.xa), w.out_w, v.M, cf.vocab, cf.d_model, t.row_seq, t.row_start,
                      v.draft_src, km, c->at<float>(p.draft_lp), c->at<int>(p.draft_col), c->stream);
   Epi e{};
@@ -789,6 +981,14 @@ static void verify_launches(ad_ctx* c, const VerifyLaunch& v) {
   accept(c->at<float>(p.o_val), c->at<int>(p.o_hat), 1, 1, gp);
 }
 
+static TeamFail team_fail_words(const ad_ctx* c, int model) {
+  TeamFail f;
+  if (c->can_team[model][0] || c->can_team[model][1]) {
+    f.a = (const unsigned*)(c->ws + c->plan.team_words[2]) + kTeamFail;
+    f.b = (const unsigned*)(c->ws + c->plan.team_words[model]) + kTeamFail;
+  }
+  return f;
+}
 // ad_verify and its no-allocation variant.  static_scratch: the arg-max partials go to the
 // library's static device array, every launch is made eagerly (no graph is built or replayed) and
 // nothing on the way allocates.
@@ -883,38 +1083,60 @@ static int verify_call(ad_ctx* c, const int32_t* draft, const int32_t* k, int32_
     v.ticket_in = c->pin_dev + pl.v_ticket;
     v.ticket_out = (unsigned long long*)(c->pin_dev + pl.v_slots);
   }
-  // every launch argument is a function of (rows, sequences, longest block), of the GAD++
+  TeamRun run;
+  run.max_keys = std::max(self_keys, cross_keys);
+  bool team = mapped && !static_scratch && run.max_keys <= kTeamMaxKeys && team_deal(k, nullptr, B, &run) && team_usable(c, AD_VERIFIER, true);
+  if (team) {
+    team_common(c, AD_VERIFIER, true, 2, &run);
+    run.a.K = (bf16_storage*)(c->ws + p.cache_k); run.a.V = (bf16_storage*)(c->ws + p.cache_v); run.a.kv_stride = p.cache_layer_stride;
+  }
+  v.fail = team_fail_words(c, AD_VERIFIER);
+  // every launch argument is a function of (rows, sequences, longest block), of how the rows are dealt out to teams, of the GAD++
   // setting, of whether the acceptance kernel posts the ticket, and of pointers fixed for the
   // context's life
   const bool gadpp = c->gadpp_beta > 1;
-  bool launched = false;
-  if (mapped && !static_scratch) {
-    const unsigned long long key = shape_key(M, max_rows, B, (gadpp ? 1 : 0) | (watch ? 2 : 0) | (c->fuse_crossq ? 4 : 0) | (self_keys <= 64 ? 8 : 0) | (cross_keys <= 64 ? 16 : 0));
-    unsigned tau_bits;
-    memcpy(&tau_bits, &c->gadpp_tau, 4);
-    const unsigned long long more = gadpp ? ((unsigned long long)c->gadpp_beta << 32) | tau_bits : 0;
-    launched = run_as_graph(c, c->stream, key, [&]() { verify_launches(c, v); }, more);
-  }
-  if (!launched) verify_launches(c, v);
   int32_t* res = c->pin + pl.result;
   int32_t* oh = c->pin + pl.o_hat;
-  if (!mapped) HIP_TRY(c, hipMemcpyAsync(res, c->at<int>(p.result), (size_t)B * 8, hipMemcpyDeviceToHost, c->stream));
-  if (verified) HIP_TRY(c, hipMemcpyAsync(oh, c->at<int>(p.o_hat), (size_t)M * 4, hipMemcpyDeviceToHost, c->stream));
-  bool seen = false;
-  if (watch) {
-    const int want = c->ticket;
-    const auto t_end = std::chrono::steady_clock::now() + std::chrono::milliseconds(50);
-    for (unsigned spin = 1;; ++spin) {
-      int b = 0;
-      while (b < B && (int)(__atomic_load_n(ticket_out + b, __ATOMIC_ACQUIRE) >> 46) == want) ++b;
-      if (b == B) { seen = true; break; }
-      if ((spin & 1023u) == 0 && std::chrono::steady_clock::now() > t_end) break;   // fall back to the stream
-      __builtin_ia32_pause();
+  for (;;) {
+    v.team = team ? &run : nullptr;
+    c->last_team = team;
+    if (team) c->last_run = run;
+    bool launched = false;
+    if (mapped && !static_scratch && (!team || B <= kTeamGraphBatch)) {
+      const unsigned long long key = shape_key(M, max_rows, B, (gadpp ? 1 : 0) | (watch ? 2 : 0) | (c->fuse_crossq ? 4 : 0) | (self_keys <= 64 ? 8 : 0) | (cross_keys <= 64 ? 16 : 0));
+      unsigned tau_bits;
+      memcpy(&tau_bits, &c->gadpp_tau, 4);
+      const unsigned long long more = gadpp ? ((unsigned long long)c->gadpp_beta << 32) | tau_bits : 0;
+      launched = run_as_graph(c, c->stream, key, [&]() { verify_launches(c, v); }, more, team_part(v.team));
     }
-  }
-  if (!seen) {
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    HIP_TRY(c, hipGetLastError());
+    if (!launched) verify_launches(c, v);
+    if (!mapped) HIP_TRY(c, hipMemcpyAsync(res, c->at<int>(p.result), (size_t)B * 8, hipMemcpyDeviceToHost, c->stream));
+    if (verified) HIP_TRY(c, hipMemcpyAsync(oh, c->at<int>(p.o_hat), (size_t)M * 4, hipMemcpyDeviceToHost, c->stream));
+    bool seen = false;
+    if (watch) {
+      const int want = c->ticket;
+      const auto t_end = std::chrono::steady_clock::now() + std::chrono::milliseconds(50);
+      for (unsigned spin = 1;; ++spin) {
+        int b = 0;
+        while (b < B && (int)(__atomic_load_n(ticket_out + b, __ATOMIC_ACQUIRE) >> 46) == want) ++b;
+        if (b == B) { seen = true; break; }
+        if ((spin & 1023u) == 0 && std::chrono::steady_clock::now() > t_end) break;   // fall back to the stream
+        __builtin_ia32_pause();
+      }
+    }
+    if (!seen) {
+      HIP_TRY(c, hipStreamSynchronize(c->stream));
+      HIP_TRY(c, hipGetLastError());
+    }
+    // (a team that did not come together says so for every sequence: the first tells)
+    const int first = watch ? (int)((__atomic_load_n(ticket_out, __ATOMIC_ACQUIRE) >> 32) & 0x3fff) : res[0];
+    if (!v.fail.a || first != kTeamFailed) break;
+    const int rc = team_recover(c);
+    if (rc != AD_OK) return rc;
+    c->fw_nseq = B; c->fw_max_rows = max_rows; c->fw_self_keys = self_keys; c->fw_cross_keys = cross_keys;
+    if (watch)
+      for (int b = 0; b < B; ++b) ticket_out[b] = 0;
+    team = false;
   }
   int r0 = 0;
   for (int b = 0; b < B; ++b) {
@@ -988,6 +1210,18 @@ int ad_draft_nat(ad_ctx* c, int k, int32_t* draft_out) {
   unsigned long long* slots = (unsigned long long*)(c->pin + c->pl.d_slots);   // [B, k_max]
   int32_t* ticket_in = c->pin + c->pl.d_ticket;
   const bool watch = c->pin_dev != nullptr && c->spin_wait;
+  // the layers as one launch: a sequence's mask rows (segment 0) and prefix rows (segment 1) belong to one team
+  TeamRun run;
+  std::vector<int> seg[2];
+  for (int b = 0; b < B; ++b)
+    if (!c->h_finished[b]) { seg[0].push_back(k); seg[1].push_back(c->h_len[b] + 1); }
+  const TeamFail tf = team_fail_words(c, AD_DRAFTER);
+  run.max_keys = std::max(self_keys, *std::max_element(c->h_src_len[AD_DRAFTER].begin(), c->h_src_len[AD_DRAFTER].begin() + B));
+  bool team = watch && run.max_keys <= kTeamMaxKeys && team_deal(seg[0].data(), seg[1].data(), live, &run) && team_usable(c, AD_DRAFTER, true);
+  if (team) {
+    team_common(c, AD_DRAFTER, true, 2, &run);
+    run.a.head_only = 1; run.a.prob2_off = live;
+  }
   // the drafter forward's launches (made one by one: the prefix is recomputed every iteration,
   // so a call shape seldom comes back and a graph per shape costs more to build than it saves).
   // The mask rows are the first Mv packed rows; two attention problems per sequence (mask rows and
@@ -999,13 +1233,17 @@ int ad_draft_nat(ad_ctx* c, int k, int32_t* draft_out) {
     launch_assemble_embed_drafter(cf.dtype, c->at<int>(p.out), cf.max_len, c->at<int>(p.len), c->at<int>(p.finished),
                                   c->at<int>(p.src_len[1]), B, k, cf.bos, cf.mask, cf.max_src, t, M, w.emb,
                                   c->at<float>(p.pe), cf.d_model, sqrtf((float)cf.d_model), c->at<float>(p.x),
-                                  c->at<void>(p.xa), c->stream);
+                                  c->at<void>(p.xa), c->stream, team ? run.a.words : nullptr);
     int rows = M;
+    if (team) {
+      launch_team(run.a, true, run.max_rows, run.max_keys, c->stream);
+      c->ln_pending = &w.dec.back().ln3;
+    }
     c->fw_nseq = 2 * live;
     c->fw_max_rows = max_rows;
     c->fw_self_keys = self_keys;
     c->fw_cross_keys = *std::max_element(c->h_src_len[AD_DRAFTER].begin(), c->h_src_len[AD_DRAFTER].begin() + B);
-    for (int l = 0; l < cf.dec_layers; ++l) {
+    for (int l = 0; !team && l < cf.dec_layers; ++l) {
       const DecLayerW& L = w.dec[l];
       if (l + 1 == cf.dec_layers) {
         self_attn_block(c, L.self, L.ln1, M, c->at<void>(p.tk), c->at<void>(p.tv), cf.max_len + km, Mv, live, k);
@@ -1025,48 +1263,60 @@ int ad_draft_nat(ad_ctx* c, int k, int32_t* draft_out) {
       // the drafted tokens go straight to the host: (ticket, token) per 8-byte slot of the mapped buffer
       launch_argmax_draft(c->at<float>(p.part_val), c->at<int>(p.part_idx), Mv, p.n_strips, n_part, c->at<int>(p.o_hat),
                           c->at<int>(p.finished), B, k, km, c->pin_dev + c->pl.d_ticket,
-                          (unsigned long long*)(c->pin_dev + c->pl.d_slots), c->stream);
+                          (unsigned long long*)(c->pin_dev + c->pl.d_slots), c->stream, tf);
     } else {
       vocab_finish(c, Mv, n_part);
       launch_draft_scatter(c->at<int>(p.o_hat), c->at<int>(p.finished), B, k, km, c->at<int>(p.draft_out), c->stream);
     }
   };
-  if (watch) {
-    if (++c->ticket >= (1 << 18)) c->ticket = 1;
-    *ticket_in = c->ticket;
-    for (int b = 0; b < B; ++b)
-      if (!c->h_finished[b])
-        for (int i = 0; i < k; ++i) slots[(size_t)b * km + i] = 0;
-  }
-  launches();
-  bool seen = false;
-  if (watch) {
-    // wait for the last slot of every live sequence first (it is written about when the others are),
-    // then make sure of all of them
-    const auto t_end = std::chrono::steady_clock::now() + std::chrono::milliseconds(50);
-    seen = true;
-    for (int b = 0; b < B && seen; ++b) {
-      if (c->h_finished[b]) continue;
-      for (int i = k - 1; i >= 0 && seen; --i)
-        for (unsigned spin = 1; (int)(__atomic_load_n(slots + (size_t)b * km + i, __ATOMIC_ACQUIRE) >> 32) != c->ticket; ++spin) {
-          if ((spin & 1023u) == 0 && std::chrono::steady_clock::now() > t_end) { seen = false; break; }
-          __builtin_ia32_pause();
-        }
-    }
-    if (seen) {
+  for (;;) {
+    if (watch) {
+      if (++c->ticket >= (1 << 18)) c->ticket = 1;
+      *ticket_in = c->ticket;
       for (int b = 0; b < B; ++b)
-        for (int i = 0; i < km; ++i)
-          draft_out[(size_t)b * km + i] = !c->h_finished[b] && i < k ? (int32_t)(unsigned)slots[(size_t)b * km + i] : AD_NEVER;
-    } else {
-      // fall back to the stream: the tokens are in o_hat; scatter them as the other path does
-      launch_draft_scatter(c->at<int>(p.o_hat), c->at<int>(p.finished), B, k, km, c->at<int>(p.draft_out), c->stream);
+        if (!c->h_finished[b])
+          for (int i = 0; i < k; ++i) slots[(size_t)b * km + i] = 0;
     }
-  }
-  if (!seen) {
-    HIP_TRY(c, hipMemcpyAsync(h, c->at<int>(p.draft_out), (size_t)B * km * 4, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    HIP_TRY(c, hipGetLastError());
-    memcpy(draft_out, h, (size_t)B * km * 4);
+    launches();
+    bool seen = false, failed = false;
+    if (watch) {
+      // wait for the last slot of every live sequence first (it is written about when the others are),
+      // then make sure of all of them
+      const auto t_end = std::chrono::steady_clock::now() + std::chrono::milliseconds(50);
+      seen = true;
+      for (int b = 0; b < B && seen; ++b) {
+        if (c->h_finished[b]) continue;
+        for (int i = k - 1; i >= 0 && seen; --i)
+          for (unsigned spin = 1; (int)(__atomic_load_n(slots + (size_t)b * km + i, __ATOMIC_ACQUIRE) >> 32) != c->ticket; ++spin) {
+            if ((spin & 1023u) == 0 && std::chrono::steady_clock::now() > t_end) { seen = false; break; }
+            __builtin_ia32_pause();
+          }
+      }
+      if (!seen) HIP_TRY(c, hipStreamSynchronize(c->stream));   // (the slots are written then too)
+      for (int b = 0; b < B; ++b)
+        failed = failed || (!c->h_finished[b] && (int32_t)(unsigned)__atomic_load_n(slots + (size_t)b * km, __ATOMIC_ACQUIRE) == AD_NEVER - 1);
+      if (failed) {
+        const int rc = team_recover(c);
+        if (rc != AD_OK) return rc;
+        team = false;
+        continue;
+      }
+      if (seen) {
+        for (int b = 0; b < B; ++b)
+          for (int i = 0; i < km; ++i)
+            draft_out[(size_t)b * km + i] = !c->h_finished[b] && i < k ? (int32_t)(unsigned)slots[(size_t)b * km + i] : AD_NEVER;
+      } else {
+        // fall back to the stream: the tokens are in o_hat; scatter them as the other path does
+        launch_draft_scatter(c->at<int>(p.o_hat), c->at<int>(p.finished), B, k, km, c->at<int>(p.draft_out), c->stream);
+      }
+    }
+    if (!seen) {
+      HIP_TRY(c, hipMemcpyAsync(h, c->at<int>(p.draft_out), (size_t)B * km * 4, hipMemcpyDeviceToHost, c->stream));
+      HIP_TRY(c, hipStreamSynchronize(c->stream));
+      HIP_TRY(c, hipGetLastError());
+      memcpy(draft_out, h, (size_t)B * km * 4);
+    }
+    break;
   }
   c->last_logit_rows = Mv;
   c->last_M = 0;   // the row tables now describe the drafter's rows
@@ -1199,6 +1449,20 @@ int ad_set_option(ad_ctx* c, int option, int value) {
     c->fuse_crossq = value != 0;
     return AD_OK;
   }
+  if (option == AD_OPT_TEAMS) {
+    if (value != 0 && value != 1) return fail(c, AD_EINVAL, "AD_OPT_TEAMS must be 0 or 1");
+    c->team_on = value != 0;
+    c->team_rest = 0;
+    return AD_OK;
+  }
+  if (option == AD_OPT_TEAM_WAIT) {
+    if (value < 0 || value > 100000) return fail(c, AD_EINVAL, "AD_OPT_TEAM_WAIT must be 0 .. 100000 (10 ns steps)");
+    c->team_ticks = value;
+    c->team_rest = 0;
+    for (auto& kv : c->graphs) (void)hipGraphExecDestroy(kv.second);   // (the wait is an argument of captured launches)
+    c->graphs.clear();
+    return AD_OK;
+  }
   if (option == AD_OPT_OVERLAP_ENCODERS) {
     if (value != 0 && value != 1) return fail(c, AD_EINVAL, "AD_OPT_OVERLAP_ENCODERS must be 0 or 1");
     if (value && !c->stream2) return fail(c, AD_ESTATE, "no second stream (no drafter, or the context runs on the null stream)");
@@ -1215,6 +1479,9 @@ int ad_get_option(ad_ctx* c, int option, int* value) {
   else if (option == AD_OPT_GRAPHS_CAPTURED) *value = (int)c->graphs.size();
   else if (option == AD_OPT_SPIN_WAIT) *value = c->spin_wait ? 1 : 0;
   else if (option == AD_OPT_FUSE_CROSSQ) *value = c->fuse_crossq ? 1 : 0;
+  else if (option == AD_OPT_TEAMS) *value = c->team_on ? 1 : 0;
+  else if (option == AD_OPT_TEAM_FAILURES) *value = c->team_failures;
+  else if (option == AD_OPT_TEAM_WAIT) *value = c->team_ticks;
   else if (option == AD_OPT_OVERLAP_ENCODERS) *value = c->overlap_encoders ? 1 : 0;
   else return fail(c, AD_EINVAL, "unknown option");
   return AD_OK;
@@ -1265,10 +1532,14 @@ int ad_time_verify_forward(ad_ctx* c, int reps, double* forward_us, double* voca
   if (c->last_M < 1) return fail(c, AD_ESTATE, "the last forward was not an ad_verify");
   double tot = 0, voc = 0;
   c->fw_nseq = c->last_nseq; c->fw_max_rows = c->last_max_rows; c->fw_self_keys = c->last_self_keys; c->fw_cross_keys = c->last_cross_keys;
-  verify_forward(c, c->last_M);   // warm
+  const TeamRun* team = c->last_team ? &c->last_run : nullptr;
+  auto forward = [&](hipEvent_t ev_a = nullptr, hipEvent_t ev_b = nullptr) {
+    verify_forward(c, c->last_M, ev_a, ev_b, true, false, false, nullptr, team);
+  };
+  forward();   // warm
   // the whole forward, reps times back to back between two events
   HIP_TRY(c, hipEventRecord(c->ev0, c->stream));
-  for (int r = 0; r < reps; ++r) verify_forward(c, c->last_M);
+  for (int r = 0; r < reps; ++r) forward();
   HIP_TRY(c, hipEventRecord(c->ev3, c->stream));
   HIP_TRY(c, hipEventSynchronize(c->ev3));
   float a = 0, b = 0;
@@ -1277,7 +1548,7 @@ int ad_time_verify_forward(ad_ctx* c, int reps, double* forward_us, double* voca
   // the output projection + arg max kernel: one launch at a time, bracketed by two events inside
   // a forward (the figure a kernel trace reports for it)
   for (int r = 0; r < reps; ++r) {
-    verify_forward(c, c->last_M, c->ev1, c->ev2);
+    forward(c->ev1, c->ev2);
     HIP_TRY(c, hipEventSynchronize(c->ev2));
     HIP_TRY(c, hipEventElapsedTime(&b, c->ev1, c->ev2));
     voc += b * 1e3;

@@ -76,8 +76,10 @@ struct Epi {
 };
 
 // ---- launchers (ad_kernels.hip).  dtype: AD_F32 / AD_BF16 selects storage + arithmetic ---------
+// (`team_words`, here and below: barrier state of a launch_team that follows, cleared by this launch; null: none)
 void launch_embed(int dtype, const void* emb, const float* pe, const int* tok, const int* pos, int M,
-                  int d, float sqrt_d, float* x, void* xa, hipStream_t s);
+                  int d, float sqrt_d, float* x, void* xa, hipStream_t s, unsigned* team_words = nullptr);
+constexpr int kTeamFail = 8 * 64, kTeamWords = kTeamFail + 64;   // per team a line for the member count and one for the arrivals; the fail word
 // C[M,N] = A[M,K] . W[N,K]^T with epilogue.  A, W in the storage type.
 // returns the number of arg-max partials per row an EPI_ARGMAX launch wrote (row stride e.n_strips)
 // With `ln` set, A is LayerNorm(ln.x): kernels that can, normalise the rows while staging them
@@ -132,11 +134,15 @@ void launch_argmax_finish(const float* part_val, const int* part_idx, int M, int
 // drafted token col[m] (negative: the never-matching id).
 void launch_draft_logit(int dtype, const void* A, const void* W, int M, int N, int K, const int* row_seq,
                         const int* row_start, const int* draft, int k_max, float* lp, int* col, hipStream_t s);
+// Fail words of the launch_team launches a result rests on (null: there was none).  One of them set: the rows are
+// not there; the result says so (accepted length kTeamFailed, drafted token AD_NEVER - 1) and the decode state stays as it was.
+struct TeamFail { const unsigned *a = nullptr, *b = nullptr; };
+constexpr int kTeamFailed = 0x3fff;
 // second stage of the arg max over the drafter's M = live * k mask rows; token i of the l-th unfinished
 // sequence b goes to the 8-byte slot [b * k_max + i] of `slots` (host-visible) as (*ticket_in << 32 | token)
 void launch_argmax_draft(const float* part_val, const int* part_idx, int M, int stride, int n_part, int* o_hat,
                          const int* finished, int B, int k, int k_max, const int* ticket_in, unsigned long long* slots,
-                         hipStream_t s);
+                         hipStream_t s, const TeamFail& tf = TeamFail{});
 
 // Row assembly of a verify call: from k[B], draft[B,k_max], len[B], pending[B] builds the
 // packed row tables and both attention descriptors.
@@ -149,7 +155,7 @@ struct VerifyTables {
 void launch_assemble_embed_verify(int dtype, const int* k, const int* draft, const int* rows, int rows_stride, int k_max, const int* len,
                                   const int* pending, const int* src_len, int B, int l_cap, int s_max, VerifyTables t,
                                   int M, const void* emb, const float* pe, int d, float sqrt_d, float* x, void* xa,
-                                  hipStream_t s);
+                                  hipStream_t s, unsigned* team_words = nullptr);
 // GAD++ inputs of the acceptance kernel (Section 3.2.3; part_cnt == nullptr: plain verification):
 // a row's drafted token `col` (score `lp`) replaces its arg max where fewer than `beta` columns
 // score above it (the counting pass's partials, n_part per row at `stride`) and the top score is
@@ -170,14 +176,14 @@ void launch_argmax_accept(const float* part_val, const int* part_idx, int stride
                           const int* k, const int* draft, int k_max, const int* row_start, int B, int eos, int max_len,
                           const int* max_out, int* len, int* pending, int* finished, int* out, int* result,
                           const int* ticket_in, unsigned long long* ticket_out, int max_rows, int M /* sum of k */,
-                          hipStream_t s, const GadppIn& gp = GadppIn{});
+                          hipStream_t s, const GadppIn& gp = GadppIn{}, const TeamFail& tf = TeamFail{});
 // Row tables for the encoder (rows = source tokens) and for the drafter (prefix + masks).
 // the encoder's row tables, the embedding of the M rows, the copy of src_len (and, with len set, of
 // max_out and the start state of a decode) in one launch; the three inputs may be host memory
 void launch_assemble_embed_encoder(int dtype, const int* src, int max_src, const int* src_len, const int* max_out_in,
                                    int B, int s_max, VerifyTables t, int* src_len_out, int* max_out, int* len,
                                    int* pending, int* finished, int bos, int M, const void* emb, const float* pe, int d,
-                                   float sqrt_d, float* x, void* xa, hipStream_t s);
+                                   float sqrt_d, float* x, void* xa, hipStream_t s, unsigned* team_words = nullptr);
 // Drafter rows: the k mask rows of every unfinished sequence first (l-th unfinished sequence at
 // [l*k, l*k + k)), then the prefix rows; descriptors [0, live) = mask rows as queries,
 // [live, 2 live) = prefix rows (self_desc and cross_desc hold 2 B entries).
@@ -185,7 +191,7 @@ void launch_assemble_embed_encoder(int dtype, const int* src, int max_src, const
 void launch_assemble_embed_drafter(int dtype, const int* out, int max_len, const int* len, const int* finished,
                                    const int* src_len, int B, int k, int bos, int mask, int s_max, VerifyTables t,
                                    int M, const void* emb, const float* pe, int d, float sqrt_d, float* x, void* xa,
-                                   hipStream_t s);
+                                   hipStream_t s, unsigned* team_words = nullptr);
 void launch_draft_scatter(const int* o_hat, const int* finished, int B, int k, int k_max, int* draft_out,
                           hipStream_t s);
 

@@ -17,12 +17,18 @@
 
 namespace ad {
 
+// barrier state of a launch_team that follows
+__device__ __forceinline__ void clear_team_words(unsigned* words) {
+  for (int i = threadIdx.x; i < kTeamWords; i += blockDim.x) words[i] = 0u;
+}
 // ------------------------------------------------------------------------------------- embed
 // x[m] = E[tok[m]] * sqrt(d) + PE[pos[m]]
 template <typename T>
 __global__ void k_embed(const T* __restrict__ emb, const float* __restrict__ pe, const int* __restrict__ tok,
-                        const int* __restrict__ pos, int d, float sqrt_d, float* __restrict__ x, T* __restrict__ xa) {
+                        const int* __restrict__ pos, int d, float sqrt_d, float* __restrict__ x, T* __restrict__ xa,
+                        unsigned* __restrict__ team_words) {
   const int m = blockIdx.x;
+  if (m == 0 && team_words) clear_team_words(team_words);
   const T* e = emb + (size_t)tok[m] * d;
   const float* p = pe + (size_t)pos[m] * d;
   for (int c = threadIdx.x; c < d; c += blockDim.x) {
@@ -33,12 +39,12 @@ __global__ void k_embed(const T* __restrict__ emb, const float* __restrict__ pe,
 }
 
 void launch_embed(int dtype, const void* emb, const float* pe, const int* tok, const int* pos, int M, int d,
-                  float sqrt_d, float* x, void* xa, hipStream_t s) {
+                  float sqrt_d, float* x, void* xa, hipStream_t s, unsigned* team_words) {
   if (M <= 0) return;
   if (dtype == AD_BF16)
-    k_embed<bf16_t><<<M, 128, 0, s>>>((const bf16_t*)emb, pe, tok, pos, d, sqrt_d, x, (bf16_t*)xa);
+    k_embed<bf16_t><<<M, 128, 0, s>>>((const bf16_t*)emb, pe, tok, pos, d, sqrt_d, x, (bf16_t*)xa, team_words);
   else
-    k_embed<float><<<M, 128, 0, s>>>((const float*)emb, pe, tok, pos, d, sqrt_d, x, (float*)xa);
+    k_embed<float><<<M, 128, 0, s>>>((const float*)emb, pe, tok, pos, d, sqrt_d, x, (float*)xa, team_words);
 }
 
 // ------------------------------------------------------------------------------------- bf16 MFMA GEMM
@@ -918,10 +924,11 @@ __global__ __launch_bounds__(256) void k_argmax_draft(const float* __restrict__ 
                                                       int stride, int n_part, int* __restrict__ o_hat,
                                                       const int* __restrict__ finished, int B, int k, int k_max,
                                                       const int* __restrict__ ticket_in,
-                                                      unsigned long long* __restrict__ slots) {
+                                                      unsigned long long* __restrict__ slots, TeamFail tf) {
   const int m = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (m >= M) return;
   const int ticket = *ticket_in;
+  const unsigned failed = (tf.a ? *tf.a : 0u) | (tf.b ? *tf.b : 0u);
   const int l = m / k, i = m - l * k;
   int b = 0;
   for (int seen = 0; b < B; ++b) {
@@ -934,14 +941,15 @@ __global__ __launch_bounds__(256) void k_argmax_draft(const float* __restrict__ 
   argmax_row(pv + (size_t)m * stride, pi + (size_t)m * stride, n_part, lane, v, idx);
   if (lane == 0) {
     o_hat[m] = idx;
-    __hip_atomic_store(slots + (size_t)b * k_max + i, ((unsigned long long)(unsigned)ticket << 32) | (unsigned)idx,
+    __hip_atomic_store(slots + (size_t)b * k_max + i, ((unsigned long long)(unsigned)ticket << 32) | (unsigned)(failed ? AD_NEVER - 1 : idx),
                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 void launch_argmax_draft(const float* pv, const int* pi, int M, int stride, int n_part, int* o_hat, const int* finished,
-                         int B, int k, int k_max, const int* ticket_in, unsigned long long* slots, hipStream_t s) {
+                         int B, int k, int k_max, const int* ticket_in, unsigned long long* slots, hipStream_t s,
+                         const TeamFail& tf) {
   if (M <= 0) return;
-  k_argmax_draft<<<(M + 3) / 4, 256, 0, s>>>(pv, pi, M, stride, n_part, o_hat, finished, B, k, k_max, ticket_in, slots);
+  k_argmax_draft<<<(M + 3) / 4, 256, 0, s>>>(pv, pi, M, stride, n_part, o_hat, finished, B, k, k_max, ticket_in, slots, tf);
 }
 
 
@@ -999,7 +1007,8 @@ __global__ __launch_bounds__(128) void k_assemble_embed_verify(const int* __rest
                                                                const float* __restrict__ pe, float* __restrict__ x,
                                                                T* __restrict__ xa, int k_max, int B, int d, float sqrt_d,
                                                                int M, int l_cap, int s_max,
-                                                               const int* __restrict__ src_len, VerifyTables t) {
+                                                               const int* __restrict__ src_len, VerifyTables t,
+                                                               unsigned* __restrict__ team_words) {
   // k lives in host memory (a trip over the bus); with one sequence it is the row count M
   __shared__ int where[2];
   __shared__ int chunk[128];
@@ -1034,6 +1043,7 @@ __global__ __launch_bounds__(128) void k_assemble_embed_verify(const int* __rest
     return;
   }
   // workgroup 0: the per-sequence tables
+  if (team_words) clear_team_words(team_words);
   if (B > 1) packed_row_starts(k, B, chunk, t.row_start);
   else {
     if (threadIdx.x == 0) { t.row_start[0] = 0; t.row_start[1] = M; }
@@ -1051,14 +1061,14 @@ __global__ __launch_bounds__(128) void k_assemble_embed_verify(const int* __rest
 void launch_assemble_embed_verify(int dtype, const int* k, const int* draft, const int* rows, int rows_stride, int k_max, const int* len,
                                   const int* pending, const int* src_len, int B, int l_cap, int s_max, VerifyTables t,
                                   int M, const void* emb, const float* pe, int d, float sqrt_d, float* x, void* xa,
-                                  hipStream_t s) {
+                                  hipStream_t s, unsigned* team_words) {
   if (M <= 0) return;
   if (dtype == AD_BF16)
     k_assemble_embed_verify<bf16_t><<<M + 1, 128, 0, s>>>(k, draft, rows, rows_stride, len, pending, (const bf16_t*)emb, pe, x, (bf16_t*)xa, k_max,
-                                                      B, d, sqrt_d, M, l_cap, s_max, src_len, t);
+                                                      B, d, sqrt_d, M, l_cap, s_max, src_len, t, team_words);
   else
     k_assemble_embed_verify<float><<<M + 1, 128, 0, s>>>(k, draft, rows, rows_stride, len, pending, (const float*)emb, pe, x, (float*)xa, k_max, B,
-                                                     d, sqrt_d, M, l_cap, s_max, src_len, t);
+                                                     d, sqrt_d, M, l_cap, s_max, src_len, t, team_words);
 }
 
 // Encoder: rows = x_1..x_n of every sentence at positions 0..n-1, full self-attention over the
@@ -1077,7 +1087,8 @@ __global__ __launch_bounds__(128) void k_assemble_embed_encoder(const int* __res
                                                                 int* __restrict__ pending, int* __restrict__ finished,
                                                                 int bos, const T* __restrict__ emb,
                                                                 const float* __restrict__ pe, int d, float sqrt_d,
-                                                                float* __restrict__ x, T* __restrict__ xa) {
+                                                                float* __restrict__ x, T* __restrict__ xa,
+                                                                unsigned* __restrict__ team_words) {
   __shared__ int where[2];
   __shared__ int chunk[128];
   if (blockIdx.x != 0) {
@@ -1101,6 +1112,7 @@ __global__ __launch_bounds__(128) void k_assemble_embed_encoder(const int* __res
     }
     return;
   }
+  if (team_words) clear_team_words(team_words);
   packed_row_starts(src_len, B, chunk, t.row_start);
   for (int b = threadIdx.x; b < B; b += blockDim.x) {
     const int n = t.row_start[b + 1] - t.row_start[b];
@@ -1115,16 +1127,16 @@ __global__ __launch_bounds__(128) void k_assemble_embed_encoder(const int* __res
 void launch_assemble_embed_encoder(int dtype, const int* src, int max_src, const int* src_len, const int* max_out_in,
                                    int B, int s_max, VerifyTables t, int* src_len_out, int* max_out, int* len,
                                    int* pending, int* finished, int bos, int M, const void* emb, const float* pe, int d,
-                                   float sqrt_d, float* x, void* xa, hipStream_t s) {
+                                   float sqrt_d, float* x, void* xa, hipStream_t s, unsigned* team_words) {
   if (M <= 0) return;
   if (dtype == AD_BF16)
     k_assemble_embed_encoder<bf16_t><<<M + 1, 128, 0, s>>>(src, max_src, src_len, max_out_in, B, s_max, t, src_len_out, max_out,
                                                            len, pending, finished, bos, (const bf16_t*)emb, pe, d, sqrt_d, x,
-                                                           (bf16_t*)xa);
+                                                           (bf16_t*)xa, team_words);
   else
     k_assemble_embed_encoder<float><<<M + 1, 128, 0, s>>>(src, max_src, src_len, max_out_in, B, s_max, t, src_len_out, max_out,
                                                           len, pending, finished, bos, (const float*)emb, pe, d, sqrt_d, x,
-                                                          (float*)xa);
+                                                          (float*)xa, team_words);
 }
 
 // Drafter: rows = (o_0..o_j, [MASK] x k) at positions 0..j+k for every unfinished sequence
@@ -1145,8 +1157,9 @@ __global__ __launch_bounds__(256) void k_assemble_embed_drafter(const int* __res
                                                                 int mask, int s_max, VerifyTables t,
                                                                 const T* __restrict__ emb, const float* __restrict__ pe,
                                                                 int d, float sqrt_d, float* __restrict__ x,
-                                                                T* __restrict__ xa) {
+                                                                T* __restrict__ xa, unsigned* __restrict__ team_words) {
   if (blockIdx.x == 0) {
+    if (team_words) clear_team_words(team_words);
     __shared__ int s_live;
     if (threadIdx.x == 0) {
       int live = 0;
@@ -1228,13 +1241,13 @@ __global__ __launch_bounds__(256) void k_assemble_embed_drafter(const int* __res
 void launch_assemble_embed_drafter(int dtype, const int* out, int max_len, const int* len, const int* finished,
                                    const int* src_len, int B, int k, int bos, int mask, int s_max, VerifyTables t,
                                    int M, const void* emb, const float* pe, int d, float sqrt_d, float* x, void* xa,
-                                   hipStream_t s) {
+                                   hipStream_t s, unsigned* team_words) {
   if (dtype == AD_BF16)
     k_assemble_embed_drafter<bf16_t><<<M + 1, 256, 0, s>>>(out, max_len, len, finished, src_len, B, k, bos, mask, s_max, t,
-                                                           (const bf16_t*)emb, pe, d, sqrt_d, x, (bf16_t*)xa);
+                                                           (const bf16_t*)emb, pe, d, sqrt_d, x, (bf16_t*)xa, team_words);
   else
     k_assemble_embed_drafter<float><<<M + 1, 256, 0, s>>>(out, max_len, len, finished, src_len, B, k, bos, mask, s_max, t,
-                                                          (const float*)emb, pe, d, sqrt_d, x, (float*)xa);
+                                                          (const float*)emb, pe, d, sqrt_d, x, (float*)xa, team_words);
 }
 
 // Drafted tokens of the unfinished sequences, back in [B, k_max] order (AD_NEVER elsewhere).
@@ -1269,14 +1282,22 @@ __global__ __launch_bounds__(1024) void k_argmax_accept(const int* __restrict__ 
                                                        float* __restrict__ o_val, int eos, int max_len,
                                                        int* __restrict__ pending, int* __restrict__ finished,
                                                        int* __restrict__ out, int* __restrict__ result,
-                                                       unsigned long long* __restrict__ ticket_out, GadppIn gp) {
+                                                       unsigned long long* __restrict__ ticket_out, GadppIn gp, TeamFail tf) {
   const int b = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   // what the end of the kernel needs and nothing here depends on is requested first (k, the draft and the ticket
   // sit in host memory, one trip over the bus for all of them: the draft as all of the sequence's slots, so that
   // its request does not wait for k)
   const int my_draft = (int)threadIdx.x < k_max ? draft[b * k_max + threadIdx.x] : 0;
   const int ticket = threadIdx.x == 0 && ticket_out ? *ticket_in : 0;
+  const unsigned failed = (tf.a ? *tf.a : 0u) | (tf.b ? *tf.b : 0u);
   const int kb = gridDim.x == 1 ? M : k[b];   // a lone sequence owns all M rows
+  if (failed) {
+    if (threadIdx.x == 0) {
+      if (ticket_out) __hip_atomic_store(ticket_out + b, ((unsigned long long)ticket << 46) | ((unsigned long long)kTeamFailed << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      else result[2 * b] = kTeamFailed;
+    }
+    return;
+  }
   if (kb == 0) {
     if (threadIdx.x == 0) {
       if (ticket_out) __hip_atomic_store(ticket_out + b, (unsigned long long)ticket << 46, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -1345,11 +1366,11 @@ void launch_argmax_accept(const float* pv, const int* pi, int stride, int n_part
                           const int* draft, int k_max, const int* row_start, int B, int eos, int max_len,
                           const int* max_out, int* len, int* pending, int* finished, int* out, int* result,
                           const int* ticket_in, unsigned long long* ticket_out, int max_rows, int M, hipStream_t s,
-                          const GadppIn& gp) {
+                          const GadppIn& gp, const TeamFail& tf) {
   // as many waves as the longest block has rows (4 to 16): a wave finishes a row at a time
   const int waves = std::min(16, std::max(4, max_rows));
   k_argmax_accept<<<B, 64 * waves, 0, s>>>(k, draft, ticket_in, row_start, pv, pi, len, M, k_max, stride, n_part, max_out,
-                                    o_hat, o_val, eos, max_len, pending, finished, out, result, ticket_out, gp);
+                                    o_hat, o_val, eos, max_len, pending, finished, out, result, ticket_out, gp, tf);
 }
 // ------------------------------------------------------------------------------------- GAD++ (Section 3.2.3)
 // The drafted token of packed row m: draft[b][i] for row i of sequence b.

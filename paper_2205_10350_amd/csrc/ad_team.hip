@@ -1,0 +1,803 @@
+// A whole stack of layers in one launch: the rows of a few sequences stay on one XCD.
+//
+// A forward of a few rows as a launch per stage is a chain of 35-45 launches of 3-8 us whose products take 0.1 us each:
+// what they spend is the launch boundary (2.4 us), the trip of the rows from another XCD's writes and the fetch of
+// weights that could not be requested earlier.  Here the 32 compute units of an XCD form a team: one workgroup per CU,
+// resident for the whole stack, the stages separated by a barrier through that XCD's L2 (0.7 us; a stage's rows come
+// from the same L2, 0.3 us away), the next stage's weights requested before the barrier and brought into the L2 one to
+// two stages earlier by a wave that does nothing else.  Sequences never share a row of an attention or a LayerNorm, so
+// teams on different XCDs work on different sequences and never talk to each other; with one sequence seven XCDs idle,
+// which costs nothing: one XCD streams the base model's decoder layers (44 MB) from the last-level cache in 34 us.
+//
+// Stages of a layer: QKV | self-attention | output projection | cross-attention with its query projection | output
+// projection | FFN1 | FFN2 (the encoder without the middle two).  Members of a team split the columns of a product
+// (16-column strips), every member normalises or copies the rows it multiplies into LDS.
+//
+// Every value is computed as the launch-per-stage kernels compute it (k ascending, 32 at a time, one accumulator; the
+// LayerNorm of ad_device.h; attention sums in the same order over keys), so a row's bits do not depend on which path
+// serves it.
+//
+// Exchanged rows are read with loads that miss the vector cache (sc1): a CU's L1 may hold the row of an earlier layer.
+// Waiting is bounded everywhere: a team that is not complete within form_ticks, or a barrier that takes kWaitTicks,
+// sets the fail word, the remaining waits return at once, and the caller runs the launches instead.
+#include <hip/hip_runtime.h>
+
+#include "ad_device.h"
+#include "ad_team.h"
+
+namespace ad {
+
+constexpr int kGW = 4, kTW = 2 * kGW;          // two groups of four waves
+constexpr int kTeamThreads = 64 * kTW;
+constexpr int kTD = kTeamD, kTF = kTeamF, kTH = kTD / 64;
+constexpr int kTLd = kTD + 16;                 // row stride in LDS (elements): 32 bytes past a multiple of 64
+constexpr int kSlices = kTF / kTD;             // 512-k slices of FFN2
+constexpr unsigned long long kWaitTicks = 200000;   // 100 MHz ticks: 2 ms
+
+struct TeamChunk { int row, n, off, causal, nk_base, kv_self, kv_cross, nk_cross; };   // up to 16 query rows of one attention problem
+
+__device__ __forceinline__ unsigned xcc_id() {
+  unsigned v;
+  asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(v));
+  return v & 15;
+}
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+// loads of rows another CU of the XCD wrote during this launch: past the vector cache, from the L2
+__device__ __forceinline__ uint4 ld16_l2(const void* base, unsigned off) {
+  __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0x7fffffff, 0x00027000);
+  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 16));
+}
+__device__ __forceinline__ float ld4_l2(const void* base, unsigned off) {
+  __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0x7fffffff, 0x00027000);
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, 0, 16));
+}
+// workgroup barrier that leaves memory requests in flight
+__device__ __forceinline__ void wg_bar() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+struct TeamSync {
+  unsigned* count;
+  unsigned* fail;
+  unsigned target;
+  unsigned long long limit;
+};
+// A stage ends: the group that computed waits for its stores (they are in the L2 then); every wave passes; one wave of
+// that group says so to the team and watches for the other members; every wave passes again.
+// (The watching wave must have no requests of its own in flight: they would return before its polls do.)
+__device__ __forceinline__ void team_end(TeamSync& ts, bool computed, bool watch, int lane) {
+  if (computed) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  wg_bar();
+  ts.target += kTeamMembers;
+  if (watch && lane == 0) (void)__hip_atomic_fetch_add(ts.count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void team_begin(TeamSync& ts, bool watch, int lane) {
+  if (watch) {
+    if (lane == 0) {
+      const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
+      for (unsigned spin = 0; ts.limit && __hip_atomic_load(ts.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < ts.target; ++spin)
+        if ((spin & 15) == 15 && __builtin_amdgcn_s_memrealtime() - t0 >= ts.limit) ts.limit = 0;
+      if (ts.limit) ts.limit = kWaitTicks;
+      else __hip_atomic_store(ts.fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+  wg_bar();
+}
+// a value the compiler cannot see through: what is computed from it is computed where it is used, not kept in registers
+// over the whole stack of layers
+__device__ __forceinline__ int here(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+__device__ __forceinline__ int here_s(int v) {
+  asm volatile("" : "+s"(v));
+  return v;
+}
+
+// the 16 weight fragments (512 k) of the 16-column strip at column n0 of W [*, K], from step u0
+template <int U0 = 0, int U1 = 16>
+__device__ __forceinline__ void load_strip(const bf16_t* W, int n0, int K, int u0, int lane, uint4 (&b)[16]) {
+  const bf16_t* wp = W + (size_t)n0 * K + u0 * 512 + lane * 8;
+#pragma unroll
+  for (int u = U0; u < U1; ++u) b[u] = ldg16(wp + u * 512);
+}
+// T tiles of 16 x 16 over 512 k, added to acc.  The operand reads are issued well before the products: left to itself the compiler
+// puts each read next to its use and the chain waits for LDS sixteen times (0.7 us instead of 0.3).
+// ready(): called with the first reads on their way.
+template <int T, typename F = NoOp>
+__device__ __forceinline__ void mm16(const bf16_t* a_lane, const uint4 (&b)[16], f32x4 (&acc)[T], const F& ready = F{}) {
+  constexpr int U = 16 / T;
+#pragma unroll
+  for (int u0 = 0; u0 < 16; u0 += U) {
+    uint4 af[T][U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int t = 0; t < T; ++t) af[t][u] = *(const uint4*)(a_lane + t * 16 * kTLd + 32 * (u0 + u));
+    if (u0 == 0) ready();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int t = 0; t < T; ++t)
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[t][u]), __builtin_bit_cast(bf16x8, b[u0 + u]), acc[t], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+template <int T>
+__device__ __forceinline__ void zero(f32x4 (&acc)[T]) {
+#pragma unroll
+  for (int t = 0; t < T; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+}
+__device__ __forceinline__ void load_ln(const float* g, const float* b, int lane, float4 (&gv)[2], float4 (&bv)[2]) {
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    gv[j] = gload((const float4*)(g + 4 * lane + 256 * j));
+    bv[j] = gload((const float4*)(b + 4 * lane + 256 * j));
+  }
+}
+// Rows row0, row0 + step, .. (NR of them; local indices, clamped to `last`) through LayerNorm into the same rows of At;
+// xres (nullable): the fp32 values of this member's 16 columns, the residual of its later strip; y (nullable): the fp32 rows in memory.
+template <int NR>
+__device__ __forceinline__ void stage_ln_rows(const float* s, const int* grow, int row0, int step, int last, const float4 (&gv)[2],
+                                              const float4 (&bv)[2], bf16_t* At, float* xres, int idx, float* y, int lane) {
+  float4 xv[NR][2];
+  int g[NR];
+#pragma unroll
+  for (int i = 0; i < NR; ++i) g[i] = __builtin_amdgcn_readfirstlane(grow[min(row0 + step * i, last)]);
+#pragma unroll
+  for (int i = 0; i < NR; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const uint4 u = ld16_l2(s, (unsigned)g[i] * (kTD * 4) + 16 * lane + 1024 * j);
+      xv[i][j] = float4{__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w)};
+    }
+  float mean[NR], rstd[NR];
+#pragma unroll
+  for (int i = 0; i < NR; ++i) ln_stats4<2>(xv[i], kTD, mean[i], rstd[i]);
+#pragma unroll
+  for (int i = 0; i < NR; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      float4& o = xv[i][j];
+      o = float4{ln_value(o.x, mean[i], rstd[i], gv[j].x, bv[j].x), ln_value(o.y, mean[i], rstd[i], gv[j].y, bv[j].y),
+                 ln_value(o.z, mean[i], rstd[i], gv[j].z, bv[j].z), ln_value(o.w, mean[i], rstd[i], gv[j].w, bv[j].w)};
+      *(uint2*)(At + (row0 + step * i) * kTLd + 4 * lane + 256 * j) = uint2{f2bf_pair(o.x, o.y), f2bf_pair(o.z, o.w)};
+    }
+  if (xres && (lane >> 2) == (idx & 15)) {
+    float* xr = xres + row0 * 16 + 4 * (lane & 3);
+    if (idx < 16) {
+#pragma unroll
+      for (int i = 0; i < NR; ++i) *(float4*)(xr + step * i * 16) = xv[i][0];
+    } else {
+#pragma unroll
+      for (int i = 0; i < NR; ++i) *(float4*)(xr + step * i * 16) = xv[i][1];
+    }
+  }
+  if (y) {
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+      if (row0 + step * i <= last) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) gstore((float4*)(y + (size_t)g[i] * kTD + 4 * lane + 256 * j), xv[i][j]);
+      }
+  }
+}
+// all rows of the team: wave w takes rows w, w + 8, ..; the last round of eight is left out where none of its rows exists
+// (a row costs a wave 0.15 us of vector instructions, and every member normalises every row)
+template <int NR>
+__device__ __forceinline__ void stage_ln(const float* s, const int* grow, int n, const float4 (&gv)[2], const float4 (&bv)[2],
+                                         bf16_t* At, float* xres, int idx, int wave, int lane) {
+  if (n > kTW * (NR - 1)) stage_ln_rows<NR>(s, grow, wave, kTW, n - 1, gv, bv, At, xres, idx, nullptr, lane);
+  else stage_ln_rows<NR - 1>(s, grow, wave, kTW, n - 1, gv, bv, At, xres, idx, nullptr, lane);
+}
+// the up to 16 rows of a chunk
+__device__ __forceinline__ void stage_ln_chunk(const float* s, const int* grow, int n, const float4 (&gv)[2], const float4 (&bv)[2],
+                                               bf16_t* At, float* y, int wave, int lane) {
+  if (n > kTW) stage_ln_rows<2>(s, grow, wave, kTW, n - 1, gv, bv, At, nullptr, 0, y, lane);
+  else stage_ln_rows<1>(s, grow, wave, kTW, n - 1, gv, bv, At, nullptr, 0, y, lane);
+}
+// NR rows of bf16 rows src [*, 512] into At
+template <int NR>
+__device__ __forceinline__ void stage_rows(const bf16_t* src, const int* grow, int row0, int last, bf16_t* At, int lane) {
+  uint4 v[NR];
+#pragma unroll
+  for (int i = 0; i < NR; ++i)
+    v[i] = ld16_l2(src, (unsigned)__builtin_amdgcn_readfirstlane(grow[min(row0 + i, last)]) * (kTD * 2) + 16 * lane);
+#pragma unroll
+  for (int i = 0; i < NR; ++i) *(uint4*)(At + (row0 + i) * kTLd + 8 * lane) = v[i];
+}
+
+// the first layer's residual, this member's 16 columns of the embedded rows
+template <int ROWS>
+__device__ __forceinline__ void stage_first_residual(const float* x, const int* grow, int n, float* xres, int idx, int wave, int lane) {
+#pragma unroll
+  for (int p = 0; p < (ROWS + 31) / 32; ++p) {
+    const int row = 32 * p + wave * 4 + (lane >> 4);
+    if (row < n) xres[row * 16 + (lane & 15)] = gload(x + (size_t)grow[row] * kTD + idx * 16 + (lane & 15));
+  }
+}
+// FFN2's operand as [slice][row][528]: a wave takes the rows par, par + 2, .. of slice sl, eight in flight
+template <int ROWS>
+__device__ __forceinline__ void stage_ffn(const bf16_t* f, const int* grow, int n, bf16_t* At, int sl, int par, int lane) {
+#pragma unroll
+  for (int k0 = 0; k0 < ROWS / 2; k0 += 8) {
+    uint4 v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      v[k] = ld16_l2(f, (unsigned)__builtin_amdgcn_readfirstlane(grow[min(par + 2 * (k0 + k), n - 1)]) * (kTF * 2) + sl * 1024 + 16 * lane);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) *(uint4*)(At + (sl * ROWS + par + 2 * (k0 + k)) * kTLd + 8 * lane) = v[k];
+  }
+}
+__device__ __forceinline__ TeamChunk chunk_at(const TeamChunk* chunks, int c) {
+  TeamChunk t = chunks[c];
+  t.row = __builtin_amdgcn_readfirstlane(t.row); t.n = __builtin_amdgcn_readfirstlane(t.n);
+  t.off = __builtin_amdgcn_readfirstlane(t.off); t.causal = __builtin_amdgcn_readfirstlane(t.causal);
+  t.nk_base = __builtin_amdgcn_readfirstlane(t.nk_base); t.kv_self = __builtin_amdgcn_readfirstlane(t.kv_self);
+  t.kv_cross = __builtin_amdgcn_readfirstlane(t.kv_cross); t.nk_cross = __builtin_amdgcn_readfirstlane(t.nk_cross);
+  return t;
+}
+
+// One attention problem's chunk of up to 16 rows, head h, at most 16 NKT keys, by the four waves of a group: wave w holds
+// the score tiles of keys 16 w .. and 16 (w + 4) .., the waves' maxima and the unrounded exponentials go through LDS,
+// every wave sums the denominators in key order and computes 16 output columns.  Same order as attn_tiles_mfma: a score is
+// one chain over the head width, a lane's denominator adds its keys in ascending order, the output is one chain over the keys.
+struct AttnLds { bf16_t* Vt; bf16_t* Pt; f32x4* Pf; float* xmax; };
+template <int NKT> struct AttnDims { static constexpr int LDV = 16 * NKT + 16, VP = NKT * 16 * 8 / (64 * kGW), KT = NKT / kGW; };
+template <int NKT> struct AttnRegs { uint4 kf[AttnDims<NKT>::KT][2], vr[AttnDims<NKT>::VP]; };
+template <int NKT, bool L2>
+__device__ __forceinline__ void attn_request(const bf16_t* K, const bf16_t* V, int kv0, int nk_all, int h, int wave, int lane, AttnRegs<NKT>& g) {
+  const int r = lane & 15, kq = lane >> 4;
+#pragma unroll
+  for (int t = 0; t < AttnDims<NKT>::KT; ++t) {
+    const unsigned off = (unsigned)(kv0 + min(16 * (wave + kGW * t) + r, nk_all - 1)) * (kTD * 2) + (h * 64 + kq * 8) * 2;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) g.kf[t][s] = L2 ? ld16_l2(K, off + 64 * s) : ldg16((const char*)K + off + 64 * s);
+  }
+#pragma unroll
+  for (int it = 0; it < AttnDims<NKT>::VP; ++it) {
+    const int i = (wave * 64 + lane) + 64 * kGW * it, t = i % (16 * NKT), c = i / (16 * NKT);   // key t, channels 8 c ..
+    const unsigned off = (unsigned)(kv0 + min(t, nk_all - 1)) * (kTD * 2) + (h * 64 + c * 8) * 2;
+    g.vr[it] = L2 ? ld16_l2(V, off) : ldg16((const char*)V + off);
+  }
+}
+template <int NKT>
+__device__ __forceinline__ void attn_values(const AttnLds& L, const AttnRegs<NKT>& g, int nk_all, int wave, int lane) {
+  constexpr int LDV = AttnDims<NKT>::LDV;
+  const int nkp = (nk_all + 31) & ~31;
+#pragma unroll
+  for (int it = 0; it < AttnDims<NKT>::VP; ++it) {
+    const int i = (wave * 64 + lane) + 64 * kGW * it, t = i % (16 * NKT), c = i / (16 * NKT);
+    if (t < nkp) {
+      const uint4 v = t < nk_all ? g.vr[it] : uint4{0u, 0u, 0u, 0u};
+      bf16_t* dst = L.Vt + (c * 8) * LDV + t;
+      dst[0] = (bf16_t)(v.x & 0xffffu); dst[LDV] = (bf16_t)(v.x >> 16);
+      dst[2 * LDV] = (bf16_t)(v.y & 0xffffu); dst[3 * LDV] = (bf16_t)(v.y >> 16);
+      dst[4 * LDV] = (bf16_t)(v.z & 0xffffu); dst[5 * LDV] = (bf16_t)(v.z >> 16);
+      dst[6 * LDV] = (bf16_t)(v.w & 0xffffu); dst[7 * LDV] = (bf16_t)(v.w >> 16);
+    }
+  }
+}
+// (two workgroup barriers; the values are written ahead of the first)
+template <int NKT>
+__device__ __forceinline__ void attn_core(const AttnLds& L, const uint4 (&qf)[2], const AttnRegs<NKT>& g, int nk_all, int nk_base,
+                                          int off, int causal, float scale, bf16_t* att, const int* grow, int row, int n_rows,
+                                          int h, int wave, int lane) {
+  constexpr int LDV = AttnDims<NKT>::LDV, KT = AttnDims<NKT>::KT;
+  const int r = lane & 15, kq = lane >> 4;
+  const int nb = (nk_all + 31) >> 5, nt2 = 2 * nb;
+  f32x4 S[KT];
+#pragma unroll
+  for (int t = 0; t < KT; ++t) {
+    const int tile = wave + kGW * t;
+    S[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+      S[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, qf[s]), __builtin_bit_cast(bf16x8, g.kf[t][s]), S[t], 0, 0, 0);
+    const int key = 16 * tile + r;
+    float m[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int nkr = causal ? nk_base + off + 4 * kq + i + 1 : nk_base;
+      S[t][i] = key < nkr ? S[t][i] * scale : -INFINITY;
+      m[i] = row16_max(S[t][i]);
+    }
+    if (r == 0) *(float4*)(L.xmax + tile * 16 + 4 * kq) = float4{m[0], m[1], m[2], m[3]};
+  }
+  wg_bar();   // values and maxima
+  {
+    f32x4 mx = *(const f32x4*)(L.xmax + 4 * kq);
+#pragma unroll
+    for (int w = 1; w < NKT; ++w) {   // (tiles past the last key: -inf)
+      const f32x4 o = *(const f32x4*)(L.xmax + w * 16 + 4 * kq);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) mx[i] = fmaxf(mx[i], o[i]);
+    }
+#pragma unroll
+    for (int t = 0; t < KT; ++t) {
+      const int tile = wave + kGW * t;
+      if (tile < nt2) {
+        f32x4 p;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          p[i] = __builtin_amdgcn_exp2f((S[t][i] - mx[i]) * 1.44269504088896340736f);
+          L.Pt[(4 * kq + i) * LDV + r + 16 * tile] = f2bf(p[i]);
+        }
+        L.Pf[tile * 64 + lane] = p;
+      }
+    }
+  }
+  wg_bar();   // probabilities
+  f32x4 O = f32x4{0.f, 0.f, 0.f, 0.f}, ps = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int kb = 0; kb < NKT / 2; ++kb) {
+    if (kb < nb) {
+      const uint4 pa = *(const uint4*)(L.Pt + r * LDV + 32 * kb + 8 * kq);
+      const uint4 vb = *(const uint4*)(L.Vt + (16 * wave + r) * LDV + 32 * kb + 8 * kq);
+      const f32x4 p0 = L.Pf[(2 * kb) * 64 + lane], p1 = L.Pf[(2 * kb + 1) * 64 + lane];
+      O = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pa), __builtin_bit_cast(bf16x8, vb), O, 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { ps[i] += p0[i]; ps[i] += p1[i]; }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float l = row16_sum(ps[i]);
+    if (4 * kq + i < n_rows)
+      Store<bf16_t>::store(att + (size_t)grow[row + 4 * kq + i] * kTD + h * 64 + 16 * wave + r, O[i] / l);
+  }
+}
+
+template <int MT, int NKT, bool DEC>
+__global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
+  constexpr int ROWS = 16 * MT, RPW = ROWS / kTW;   // RPW: rows a wave stages
+  constexpr int LDV = AttnDims<NKT>::LDV;
+  extern __shared__ uint4 team_lds[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int team = (int)((xcc_id() - (unsigned)a.xcd0) & 7u);
+  if (team >= a.n_teams) return;
+  char* lds = (char*)team_lds;
+  bf16_t* At = (bf16_t*)lds;                                     // [ROWS][528], FFN2: [4 slices][ROWS][528]
+  float* xres = (float*)(lds + kSlices * ROWS * kTLd * 2);      // [ROWS][16]
+  f32x4* accx = (f32x4*)(xres + ROWS * 16);                      // [3 slices][MT][64]
+  TeamChunk* chunks = (TeamChunk*)(accx + 3 * MT * 64);          // [ROWS]
+  int* grow = (int*)(chunks + ROWS);                             // [ROWS] packed row of the team's row
+  int* rdst = grow + ROWS;                                       // [ROWS] its key / value row
+  int* misc = rdst + ROWS;                                       // member, chunks, chunks of segment 0; FFN2's slices done
+  unsigned* slices = (unsigned*)(misc + 4);
+  // attention: the row tile [16][528] and the queries [16][80] of the cross-attention first, then values and probabilities
+  bf16_t* Qt = At + 16 * kTLd;
+  AttnLds AL;
+  AL.Vt = Qt + 16 * kCrossqQld;
+  AL.Pt = AL.Vt + 64 * LDV;
+  AL.Pf = (f32x4*)(AL.Pt + 16 * LDV);
+  AL.xmax = (float*)(AL.Pf + NKT * 64);
+
+  unsigned* words = a.words + team * 64;
+  const int n0 = a.row_lo[0][team + 1] - a.row_lo[0][team], n1 = a.row_lo[1][team + 1] - a.row_lo[1][team];
+  // member number, row tables, attention chunks
+  if (threadIdx.x == 64 * kGW) misc[0] = (int)__hip_atomic_fetch_add(words, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (wave == 0) {
+    const int p0 = a.prob[team], np = a.prob[team + 1] - p0, np2 = a.prob2_off ? np : 0;
+    SeqDesc sd = {}, cd = {};
+    if (lane < np + np2) {
+      const int p = lane < np ? p0 + lane : a.prob2_off + p0 + lane - np;
+      sd = gload(a.self_desc + p);
+      if (DEC) cd = gload(a.cross_desc + p);
+    }
+    const int nc = (sd.nq + 15) >> 4;
+    int before = nc;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int up = __shfl_up(before, o);
+      if (lane >= o) before += up;
+    }
+    if (lane == 63) misc[1] = before;
+    if (lane == np - 1) misc[2] = before;
+    before -= nc;
+    const int row = lane < np ? sd.q_row0 - a.row_lo[0][team] : n0 + sd.q_row0 - a.row_lo[1][team];
+    for (int c = 0; c < nc; ++c)
+      if (before + c < ROWS) {
+        TeamChunk t;
+        t.row = row + 16 * c; t.n = min(16, sd.nq - 16 * c); t.off = 16 * c; t.causal = sd.causal; t.nk_base = sd.nk_base;
+        t.kv_self = sd.kv_row0; t.kv_cross = cd.kv_row0; t.nk_cross = cd.nk_base;
+        chunks[before + c] = t;
+      }
+  } else if (wave == 1) {
+    if (lane == 0) *slices = 0;
+    if (lane < ROWS) {
+      const int row = min(lane, n0 + n1 - 1), g = row < n0 ? a.row_lo[0][team] + row : a.row_lo[1][team] + row - n0;
+      grow[lane] = g;
+      rdst[lane] = gload(a.row_dst + g);
+    }
+  }
+  __syncthreads();
+  const int idx = __builtin_amdgcn_readfirstlane(misc[0]);
+  const int n_chunks_all = __builtin_amdgcn_readfirstlane(min(misc[1], ROWS)), n_chunks0 = __builtin_amdgcn_readfirstlane(min(misc[2], ROWS));
+  if (idx >= kTeamMembers) {   // more workgroups on the XCD than members: not how this grid is dealt out
+    if (threadIdx.x == 0) __hip_atomic_store(a.fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
+  constexpr int CPR = kTeamMembers / kTH;   // chunks a team works on at a time
+  const int c_first = idx >> 3;
+  typedef TeamOff<DEC> O;
+
+  TeamSync ts;
+  ts.count = words + 32; ts.fail = a.fail; ts.target = 0; ts.limit = a.form_ticks;
+  const int gw = wave & (kGW - 1), lane0 = lane, idx0 = idx;
+  float4 gv[2], bv[2];
+
+  // The two groups of waves take turns: one multiplies a stage's rows while the other requests the next stage's strips
+  // into its registers.  A CU's vector memory returns in order, so strips (from the last-level cache, 1 us) are requested
+  // when a stage's rows have arrived and return while the other group multiplies, stores and meets the team; and a wave that waits
+  // for its stores waits for every request before them, so the group that stores requests nothing.
+  // Group A: Q, K, V | self-attention | cross-attention | FFN1.  Group B: output projections | FFN2.
+  if (wave < kGW) {
+    // ------------------------------------------------------------------------------------------ group A
+    const bool watcher = gw == kGW - 1;
+    uint4 b[16];
+    float bias = 0.f;
+    {
+      const int lane = here(lane0), idx = here_s(idx0), r = lane & 15;
+      if (gw < 3) {
+        load_strip((const bf16_t*)(a.w + O::wqkv), (idx * 3 + gw) * 16, kTD, 0, lane, b);
+        bias = gload((const float*)(a.w + O::bqkv) + (idx * 3 + gw) * 16 + r);
+      }
+    }
+#pragma unroll 1
+    for (int l = 0; l < a.layers; ++l) {
+      int n = n0 + n1, n_chunks = n_chunks_all;
+      const char* wl = a.w + (size_t)l * O::kLayerBytes;       // the layer's matrices and vectors
+      // ---------------------------------------------------------------- Q, K, V
+      {
+        const int lane = here(lane0), idx = here_s(idx0), r = lane & 15, kq = lane >> 4;
+        if (l > 0) {
+          team_begin(ts, false, lane);
+          stage_ln<RPW>(a.s, grow, n, gv, bv, At, xres, idx, wave, lane);
+        } else {
+          stage_rows<RPW>(a.xa, grow, wave * RPW, n - 1, At, lane);
+          stage_first_residual<ROWS>(a.x, grow, n, xres, idx, wave, lane);
+        }
+        wg_bar();
+        if (gw < 3) {
+          const int strip = idx * 3 + gw, col = (strip * 16 + r) & (kTD - 1), part = strip >> 5;
+          bf16_t* out = (part == 0 ? a.q : (bf16_t*)((char*)(part == 1 ? a.K : a.V) + (size_t)l * a.kv_stride)) + col;
+          f32x4 acc[MT];
+          zero(acc);
+          mm16<MT>(At + r * kTLd + kq * 8, b, acc);
+#pragma unroll
+          for (int t = 0; t < MT; ++t) {
+            const int m = t * 16 + 4 * kq;
+            const int* dst = (part == 0 ? grow : rdst) + m;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (m + i < n) Store<bf16_t>::store(out + (size_t)dst[i] * kTD, acc[t][i] + bias);
+          }
+        }
+        team_end(ts, true, watcher, lane);
+      }
+      if (a.head_only && l + 1 == a.layers) { n = n0; n_chunks = n_chunks0; }   // only segment 0 goes on
+      // ---------------------------------------------------------------- self-attention
+      {
+        const int lane = here(lane0), idx = here_s(idx0), r = lane & 15, kq = lane >> 4, h = idx & (kTH - 1);
+        const bf16_t* Kl = (const bf16_t*)((const char*)a.K + (size_t)l * a.kv_stride);
+        const bf16_t* Vl = (const bf16_t*)((const char*)a.V + (size_t)l * a.kv_stride);
+        team_begin(ts, watcher, lane);
+#pragma unroll 1
+        for (int c = c_first; c < n_chunks; c += CPR) {
+          const TeamChunk ch = chunk_at(chunks, c);
+          const int nk_all = min(ch.causal ? ch.nk_base + ch.off + ch.n : ch.nk_base, 16 * NKT);
+          uint4 qf[2];
+          AttnRegs<NKT> g;
+          const unsigned qo = (unsigned)grow[ch.row + min(r, ch.n - 1)] * (kTD * 2) + (h * 64 + kq * 8) * 2;
+          attn_request<NKT, true>(Kl, Vl, ch.kv_self, nk_all, h, gw, lane, g);
+#pragma unroll
+          for (int s = 0; s < 2; ++s) qf[s] = ld16_l2(a.q, qo + 64 * s);
+          attn_values<NKT>(AL, g, nk_all, gw, lane);
+          attn_core<NKT>(AL, qf, g, nk_all, ch.nk_base, ch.off, ch.causal, a.scale, a.att, grow, ch.row, ch.n, h, gw, lane);
+          if (c + CPR < n_chunks) wg_bar();
+        }
+        team_end(ts, true, watcher, lane);
+      }
+      // ---------------------------------------------------------------- output projection (group B multiplies)
+      const int h = idx0 & (kTH - 1);
+      AttnRegs<NKT> cg;
+      {
+        const int lane = here(lane0), idx = here_s(idx0), r = lane & 15;
+        team_begin(ts, watcher, lane);
+        stage_rows<RPW>(a.att, grow, wave * RPW, n - 1, At, lane);
+        wg_bar();
+        if constexpr (DEC) {
+          if (c_first < n_chunks) {
+            load_ln((const float*)(wl + O::ln1g), (const float*)(wl + O::ln1b), lane, gv, bv);
+            const TeamChunk ch = chunk_at(chunks, c_first);
+            attn_request<NKT, false>((const bf16_t*)((const char*)a.Km + (size_t)l * a.m_stride), (const bf16_t*)((const char*)a.Vm + (size_t)l * a.m_stride),
+                                     ch.kv_cross, min(ch.nk_cross, 16 * NKT), h, gw, lane, cg);
+          }
+          bias = gload((const float*)(wl + O::b1) + (idx * 4 + gw) * 16 + r);
+          load_strip<0, 8>((const bf16_t*)(wl + O::w1), (idx * 4 + gw) * 16, kTD, 0, lane, b);
+        } else {
+          load_ln((const float*)(wl + O::ln_fg), (const float*)(wl + O::ln_fb), lane, gv, bv);
+          bias = gload((const float*)(wl + O::b1) + (idx * 4 + gw) * 16 + r);
+          load_strip((const bf16_t*)(wl + O::w1), (idx * 4 + gw) * 16, kTD, 0, lane, b);
+        }
+        team_end(ts, false, false, lane);
+      }
+      if constexpr (DEC) {
+        // -------------------------------------------------------------- cross-attention with its query projection
+        {
+          const int lane = here(lane0), r = lane & 15, kq = lane >> 4;
+          team_begin(ts, false, lane);
+#pragma unroll 1
+          for (int c = c_first; c < n_chunks; c += CPR) {
+            const TeamChunk ch = chunk_at(chunks, c);
+            const int nk_all = min(ch.nk_cross, 16 * NKT);
+            if (c != c_first)
+              attn_request<NKT, false>((const bf16_t*)((const char*)a.Km + (size_t)l * a.m_stride), (const bf16_t*)((const char*)a.Vm + (size_t)l * a.m_stride),
+                                       ch.kv_cross, nk_all, h, gw, lane, cg);
+            stage_ln_chunk(a.s, grow + ch.row, ch.n, gv, bv, At, h == 0 ? a.x : nullptr, wave, lane);
+            attn_values<NKT>(AL, cg, nk_all, gw, lane);
+            wg_bar();
+            wg_bar();   // group B has left the queries
+            uint4 qf[2];
+#pragma unroll
+            for (int s = 0; s < 2; ++s) qf[s] = *(const uint4*)(Qt + min(r, ch.n - 1) * kCrossqQld + kq * 8 + 32 * s);
+            attn_core<NKT>(AL, qf, cg, nk_all, nk_all, 0, 0, a.scale, a.att, grow, ch.row, ch.n, h, gw, lane);
+            if (c + CPR < n_chunks) wg_bar();
+          }
+          team_end(ts, true, watcher, lane);
+        }
+        // -------------------------------------------------------------- output projection (group B multiplies)
+        {
+          const int lane = here(lane0), idx = here_s(idx0), r = lane & 15;
+          team_begin(ts, watcher, lane);
+          stage_rows<RPW>(a.att, grow, wave * RPW, n - 1, At, lane);
+          wg_bar();
+          load_ln((const float*)(wl + O::ln_fg), (const float*)(wl + O::ln_fb), lane, gv, bv);
+          load_strip<8, 16>((const bf16_t*)(wl + O::w1), (idx * 4 + gw) * 16, kTD, 0, lane, b);
+          team_end(ts, false, false, lane);
+        }
+      }
+      // ---------------------------------------------------------------- FFN1
+      {
+        const int lane = here(lane0), idx = here_s(idx0), r = lane & 15, kq = lane >> 4;
+        team_begin(ts, false, lane);
+        stage_ln<RPW>(a.s, grow, n, gv, bv, At, xres, idx, wave, lane);
+        wg_bar();
+        bf16_t* out = a.f + (idx * 4 + gw) * 16 + r;
+        f32x4 acc[MT];
+        zero(acc);
+        mm16<MT>(At + r * kTLd + kq * 8, b, acc);
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+          const int m = t * 16 + 4 * kq;
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (m + i < n) Store<bf16_t>::store(out + (size_t)grow[m + i] * kTF, fmaxf(acc[t][i] + bias, 0.f));
+        }
+        team_end(ts, true, watcher, lane);
+      }
+      // ---------------------------------------------------------------- FFN2 (group B multiplies)
+      {
+        const int lane = here(lane0), idx = here_s(idx0), r = lane & 15;
+        team_begin(ts, watcher, lane);
+        stage_ffn<ROWS>(a.f, grow, n, At, gw, wave >> 2, lane);
+        wg_bar();
+        if (l + 1 < a.layers) {
+          load_ln((const float*)(wl + O::ln_lg), (const float*)(wl + O::ln_lb), lane, gv, bv);
+          if (gw < 3) {
+            bias = gload((const float*)(wl + O::kLayerBytes + O::bqkv) + (idx * 3 + gw) * 16 + r);
+            load_strip((const bf16_t*)(wl + O::kLayerBytes + O::wqkv), (idx * 3 + gw) * 16, kTD, 0, lane, b);
+          }
+        }
+        if (l + 1 < a.layers) team_end(ts, false, false, lane);
+      }
+    }
+    return;
+  }
+
+  // -------------------------------------------------------------------------------------------- group B
+  const bool watcher = gw == kGW - 1;
+  uint4 bo[16], bq[16];   // strips of the output projection, then FFN2 | of the query projection, then the second output projection
+  float bias_o = 0.f, bias_q = 0.f;
+  unsigned chain = 0;
+#pragma unroll 1
+  for (int l = 0; l < a.layers; ++l) {
+    int n = n0 + n1, n_chunks = n_chunks_all;
+    const char* wl = a.w + (size_t)l * O::kLayerBytes;
+    // ------------------------------------------------------------------ Q, K, V
+    {
+      const int lane = here(lane0), idx = here_s(idx0), r = lane & 15;
+      if (l > 0) {
+        team_begin(ts, watcher, lane);
+        stage_ln<RPW>(a.s, grow, n, gv, bv, At, xres, idx, wave, lane);
+      } else {
+        stage_rows<RPW>(a.xa, grow, wave * RPW, n - 1, At, lane);
+        stage_first_residual<ROWS>(a.x, grow, n, xres, idx, wave, lane);
+      }
+      wg_bar();
+      if (gw < MT) {
+        bias_o = gload((const float*)(wl + O::bo) + idx * 16 + r);
+        load_strip((const bf16_t*)(wl + O::wo), idx * 16, kTD, 0, lane, bo);
+      }
+      load_ln((const float*)(wl + (DEC ? O::ln1g : O::ln_fg)), (const float*)(wl + (DEC ? O::ln1b : O::ln_fb)), lane, gv, bv);
+      team_end(ts, false, false, lane);
+    }
+    if (a.head_only && l + 1 == a.layers) { n = n0; n_chunks = n_chunks0; }
+    // ------------------------------------------------------------------ self-attention
+    {
+      const int lane = here(lane0), r = lane & 15, h = here_s(idx0) & (kTH - 1);
+      team_begin(ts, false, lane);
+      for (int c = c_first; c < n_chunks; c += CPR) {
+        wg_bar();
+        if constexpr (DEC) {
+          if (c == c_first) {   // (behind the keys and values)
+            bias_q = gload((const float*)(wl + O::cbq) + h * 64 + gw * 16 + r);
+            load_strip((const bf16_t*)(wl + O::cwq), h * 64 + gw * 16, kTD, 0, lane, bq);
+          }
+        }
+        wg_bar();
+        if (c + CPR < n_chunks) wg_bar();
+      }
+      team_end(ts, false, false, lane);
+    }
+    // ------------------------------------------------------------------ output projection + residual
+    {
+      const int lane = here(lane0), idx = here_s(idx0), r = lane & 15, kq = lane >> 4;
+      team_begin(ts, false, lane);
+      stage_rows<RPW>(a.att, grow, wave * RPW, n - 1, At, lane);
+      wg_bar();
+      if (gw < MT && gw * 16 < n) {
+        f32x4 acc[1];
+        zero(acc);
+        mm16<1>(At + (gw * 16 + r) * kTLd + kq * 8, bo, acc);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int m = gw * 16 + 4 * kq + i;
+          if (m < n) gstore(a.s + (size_t)grow[m] * kTD + idx * 16 + r, acc[0][i] + bias_o + xres[m * 16 + r]);
+        }
+      }
+      team_end(ts, true, watcher, lane);
+    }
+    if constexpr (DEC) {
+      // ---------------------------------------------------------------- cross-attention: the queries
+      {
+        const int lane = here(lane0), idx = here_s(idx0), r = lane & 15, kq = lane >> 4, h = idx & (kTH - 1);
+        team_begin(ts, watcher, lane);
+        auto next_strips = [&]() {
+          if (gw < MT) {
+            bias_q = gload((const float*)(wl + O::cbo) + idx * 16 + r);
+            load_strip((const bf16_t*)(wl + O::cwo), idx * 16, kTD, 0, lane, bq);
+          }
+          load_ln((const float*)(wl + O::ln_fg), (const float*)(wl + O::ln_fb), lane, gv, bv);
+          bias_o = gload((const float*)(wl + O::b2) + idx * 16 + r);
+          load_strip<0, 8>((const bf16_t*)(wl + O::w2), idx * 16, kTF, 16 * gw, lane, bo);
+        };
+        if (c_first >= n_chunks) next_strips();
+#pragma unroll 1
+        for (int c = c_first; c < n_chunks; c += CPR) {
+          const int row = __builtin_amdgcn_readfirstlane(chunks[c].row), nr = __builtin_amdgcn_readfirstlane(chunks[c].n);
+          stage_ln_chunk(a.s, grow + row, nr, gv, bv, At, h == 0 ? a.x : nullptr, wave, lane);
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the rows kept for the residual are stored
+          wg_bar();
+          {
+            f32x4 acc[1];
+            zero(acc);
+            mm16<1>(At + r * kTLd + kq * 8, bq, acc);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) Qt[(4 * kq + i) * kCrossqQld + gw * 16 + r] = f2bf(acc[0][i] + bias_q);
+          }
+          wg_bar();
+          if (c + CPR >= n_chunks) next_strips();
+          wg_bar(); wg_bar();
+          if (c + CPR < n_chunks) wg_bar();
+        }
+        team_end(ts, false, false, lane);
+      }
+      // ---------------------------------------------------------------- output projection + residual
+      {
+        const int lane = here(lane0), idx = here_s(idx0), r = lane & 15, kq = lane >> 4;
+        team_begin(ts, false, lane);
+        float res[4] = {};
+        stage_rows<RPW>(a.att, grow, wave * RPW, n - 1, At, lane);
+        if (gw < MT && gw * 16 < n) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) res[i] = ld4_l2(a.x, (unsigned)grow[gw * 16 + 4 * kq + i] * (kTD * 4) + (idx * 16 + r) * 4);
+        }
+        wg_bar();
+        if (gw < MT && gw * 16 < n) {
+          f32x4 acc[1];
+          zero(acc);
+          mm16<1>(At + (gw * 16 + r) * kTLd + kq * 8, bq, acc);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int m = gw * 16 + 4 * kq + i;
+            if (m < n) gstore(a.s + (size_t)grow[m] * kTD + idx * 16 + r, acc[0][i] + bias_q + res[i]);
+          }
+        }
+        team_end(ts, true, watcher, lane);
+      }
+    }
+    // ------------------------------------------------------------------ FFN1
+    {
+      const int lane = here(lane0), idx = here_s(idx0), r = lane & 15;
+      team_begin(ts, watcher, lane);
+      stage_ln<RPW>(a.s, grow, n, gv, bv, At, xres, idx, wave, lane);
+      wg_bar();
+      if (!DEC) {
+        bias_o = gload((const float*)(wl + O::b2) + idx * 16 + r);
+        load_strip<0, 8>((const bf16_t*)(wl + O::w2), idx * 16, kTF, 16 * gw, lane, bo);
+      }
+      load_strip<8, 16>((const bf16_t*)(wl + O::w2), idx * 16, kTF, 16 * gw, lane, bo);
+      load_ln((const float*)(wl + O::ln_lg), (const float*)(wl + O::ln_lb), lane, gv, bv);
+      team_end(ts, false, false, lane);
+    }
+    // ------------------------------------------------------------------ FFN2 + residual: a wave per 512-k slice
+    {
+      const int lane = here(lane0), idx = here_s(idx0), r = lane & 15, kq = lane >> 4;
+      team_begin(ts, false, lane);
+      stage_ffn<ROWS>(a.f, grow, n, At, gw, wave >> 2, lane);
+      wg_bar();
+      // The sum of an element stays one chain: the accumulators go from wave to wave through LDS, a count says how many
+      // slices are in (a wave waits for the ones before it only, so the wait ends).
+      f32x4 acc[MT];
+      zero(acc);
+      mm16<MT>(At + (gw * ROWS + r) * kTLd + kq * 8, bo, acc, [&]() {
+        if (gw > 0) {
+          while (__hip_atomic_load(slices, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < chain + gw) {}
+          asm volatile("" ::: "memory");
+#pragma unroll
+          for (int t = 0; t < MT; ++t) acc[t] = accx[((gw - 1) * MT + t) * 64 + lane];
+        }
+      });
+      if (gw + 1 < kSlices) {
+#pragma unroll
+        for (int t = 0; t < MT; ++t) accx[(gw * MT + t) * 64 + lane] = acc[t];
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      } else {
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int m = t * 16 + 4 * kq + i;
+            if (m < n) gstore(a.s + (size_t)grow[m] * kTD + idx * 16 + r, acc[t][i] + bias_o + xres[m * 16 + r]);
+          }
+      }
+      if (lane == 0) __hip_atomic_store(slices, chain + gw + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      chain += kSlices;
+      if (l + 1 < a.layers) team_end(ts, true, watcher, lane);
+    }
+  }
+}
+
+// (more than half a CU's LDS: one member per CU)
+static size_t team_lds_bytes(int mt) {
+  const size_t rows = 16 * mt, b = (size_t)kSlices * rows * kTLd * 2 + rows * 16 * 4 + 3 * mt * 64 * 16 + rows * sizeof(TeamChunk) + 2 * rows * 4 + 64;
+  return b > 84 * 1024 ? b : 84 * 1024;
+}
+// MT by the rows of the largest team, NKT by the keys of the longest problem
+template <typename F>
+static void each_team_kernel(bool dec, const F& f) {
+#define AD_TEAM(MT, NKT)                                                                     \
+  if (dec) f(MT, NKT, &k_team<MT, NKT, true>); else f(MT, NKT, &k_team<MT, NKT, false>);
+  AD_TEAM(1, 4) AD_TEAM(1, 8) AD_TEAM(2, 4) AD_TEAM(2, 8)
+#undef AD_TEAM
+}
+bool prepare_team(bool decoder) {
+  bool ok = true;
+  each_team_kernel(decoder, [&](int mt, int, void (*k)(TeamArgs)) {
+    ok = ok && hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)team_lds_bytes(mt)) == hipSuccess;
+  });
+  if (!ok) (void)hipGetLastError();
+  return ok;
+}
+void launch_team(const TeamArgs& a, bool decoder, int max_rows, int max_keys, hipStream_t s) {
+  const int mt = max_rows <= 16 ? 1 : 2, nkt = max_keys <= 64 ? 4 : 8;
+  each_team_kernel(decoder, [&](int m, int nk, void (*k)(TeamArgs)) {
+    if (m == mt && nk == nkt) k<<<8 * kTeamMembers, kTeamThreads, team_lds_bytes(mt), s>>>(a);
+  });
+}
+
+}  // namespace ad

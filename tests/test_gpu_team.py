@@ -1,0 +1,180 @@
+"""Forwards whose layers run as one launch (a team of 32 workgroups on one XCD per group of sequences) against the same
+forwards launch by launch: logits, arg maxima, decode states and drafted tokens bit for bit, at the edges of the kernel's row
+tiles (16, 17, 32 rows a team), key ranges (64, 65, 128 keys), chunks (five chunks on a team that works on four at a time) and of its range
+(33 rows, 129 keys: the launches)."""
+import threading
+
+import numpy as np
+import pytest
+
+import paper_2205_10350_amd as ad
+from ad_inputs import SPECIAL, init_weights, model_dims
+
+pytestmark = pytest.mark.gpu
+
+DIMS = model_dims("base")
+W = {}
+
+
+def _context(drafter=False, batch=12, max_src=136, max_len=96, k_max=40):
+    for s in (7, 8):
+        if s not in W:
+            W[s] = init_weights(DIMS, s)
+    cfg = ad.make_config(DIMS, max_batch=batch, max_src=max_src, max_len=max_len, k_max=k_max, dtype="bf16", special=SPECIAL, debug_logits=True)
+    return ad.Context(cfg, W[7], W[8] if drafter else None)
+
+
+def _tokens(rng, n):
+    return rng.integers(5, DIMS["vocab"], size=n).astype(np.int32)
+
+
+@pytest.mark.parametrize("src,rows", [
+    ([25], [1]), ([7], [16]), ([1], [17]), ([64], [32]), ([65], [24]), ([128], [9]), ([129], [9]), ([30], [33]),
+    ([12, 33, 5], [16, 3, 32]), ([9] * 8, [1, 2, 4, 8, 9, 16, 24, 25]),
+    ([20, 3, 40, 8, 15, 16, 17, 33, 1, 64, 50, 2], [5, 1, 17, 1, 2, 16, 3, 7, 1, 1, 6, 4]),     # more sequences than teams
+    ([10] * 12, [1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1]),
+])
+def test_layers_as_one_launch_give_the_bits_of_the_launches(src, rows):
+    """Two calls a sequence (the second against a longer prefix, with one sequence sitting out), with every row of the first block
+    fed; the encoder runs as one launch where its rows allow."""
+    rng = np.random.default_rng(sum(src) + 131 * sum(rows))
+    srcs = [_tokens(rng, n) for n in src]
+    first = [list(_tokens(rng, n)) for n in rows]
+    ctx = _context()
+    try:
+        got = {}
+        for on in (0, 1):
+            ctx.set_option(ad.AD_OPT_TEAMS, on)
+            assert ctx.get_option(ad.AD_OPT_TEAMS) == on
+            ctx.encode(ad.AD_VERIFIER, srcs)
+            out = [ctx.verify(first, want_verified=True), ctx.debug_logits().view(np.uint32).copy()]
+            second = [[] if b == 1 else list(first[b][:1 + b % 3]) for b in range(len(src))]
+            out += [ctx.verify(second), ctx.debug_logits().view(np.uint32).copy(), ctx.output()]
+            got[on] = out
+        for x, y in zip(got[0], got[1]):
+            if isinstance(x, np.ndarray):
+                assert np.array_equal(x, y)
+            else:
+                for u, v in zip(x, y):
+                    assert np.array_equal(u, v)
+        assert ctx.get_option(ad.AD_OPT_TEAM_FAILURES) == 0
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("n", [64, 65, 128, 129])
+def test_team_forwards_against_long_prefixes(n):
+    """A block of 8 rows that ends at key n (own keys): the team kernels for 64 and 128 keys, and the launches beyond."""
+    rng = np.random.default_rng(n)
+    src = [_tokens(rng, 30)]
+    ctx = _context(batch=2, max_len=132, k_max=132)
+    try:
+        ctx.set_option(ad.AD_OPT_TEAMS, 0)
+        g = ctx.decode_greedy(src, max_out=[n - 8])[0][0]
+        if len(g) < n - 8:
+            pytest.skip("the greedy output ends earlier")
+        tail = list(_tokens(rng, 8))
+        got = []
+        for on in (0, 1):
+            ctx.set_option(ad.AD_OPT_TEAMS, on)
+            ctx.encode(ad.AD_VERIFIER, src)
+            assert ctx.verify([g])[0][0] == n - 8
+            got.append((ctx.verify([tail], want_verified=True)[2], ctx.debug_logits().view(np.uint32).copy()))
+        assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("lens,k", [([9], 4), ([9, 21, 2], 7), ([5] * 9, 3), ([40], 20)])
+def test_drafter_as_one_launch(lens, k):
+    """Mask rows and prefix rows of a sequence in one team, the last layer for the mask rows only; both encoders side by side."""
+    rng = np.random.default_rng(17 * len(lens) + k)
+    srcs = [_tokens(rng, n) for n in lens]
+    ctx = _context(drafter=True)
+    try:
+        got = {}
+        for on in (0, 1):
+            ctx.set_option(ad.AD_OPT_TEAMS, on)
+            out = []
+            for _ in range(2):
+                ctx.encode(ad.AD_VERIFIER, srcs)
+                ctx.encode(ad.AD_DRAFTER, srcs)
+                for step in range(3):
+                    d = ctx.draft_nat(k).copy()
+                    out.append(d)
+                    out.append(ctx.debug_logits().view(np.uint32).copy())
+                    out += list(ctx.verify([list(row[:k]) for row in d]))
+            got[on] = out
+        for x, y in zip(got[0], got[1]):
+            assert np.array_equal(x, y)
+        assert ctx.get_option(ad.AD_OPT_TEAM_FAILURES) == 0
+    finally:
+        ctx.close()
+
+
+def test_a_team_that_does_not_come_together_leaves_the_call_to_the_launches():
+    """The wait of the team's barrier set to nothing: every kernel gives up and exits, the calls are repeated launch by launch (the
+    encoders too) with the results they always have, and the launches keep the next calls."""
+    rng = np.random.default_rng(5)
+    srcs = [_tokens(rng, n) for n in (9, 30, 4)]
+    ctx = _context(drafter=True)
+    try:
+        ref, _ = ctx.decode_greedy(srcs, max_out=[20] * 3)
+        ctx.set_option(ad.AD_OPT_TEAMS, 0)
+        got = {}
+        for wait in (None, 0):
+            if wait is not None:
+                ctx.set_option(ad.AD_OPT_TEAMS, 1)
+                ctx.set_option(ad.AD_OPT_TEAM_WAIT, wait)
+            ctx.encode(ad.AD_VERIFIER, srcs)
+            ctx.encode(ad.AD_DRAFTER, srcs)
+            d = ctx.draft_nat(5).copy()
+            dl = ctx.debug_logits().view(np.uint32).copy()
+            if wait is not None:
+                assert ctx.get_option(ad.AD_OPT_TEAM_FAILURES) == 1
+                ctx.set_option(ad.AD_OPT_TEAM_WAIT, 0)      # (ends the launches' turn)
+            v = ctx.verify([g[:6] for g in ref], want_verified=True)
+            got[wait] = [d, dl, *v, ctx.debug_logits().view(np.uint32).copy()]
+            out = ctx.output()
+            if wait is not None:
+                assert ctx.get_option(ad.AD_OPT_TEAM_FAILURES) == 2
+                assert out == first
+            first = out
+        for x, y in zip(got[None], got[0]):
+            assert np.array_equal(x, y)
+        ctx.set_option(ad.AD_OPT_TEAM_WAIT, 0)              # the next decode's first call fails, the others are launches
+        assert ctx.decode_greedy(srcs, max_out=[20] * 3)[0] == ref
+        assert ctx.get_option(ad.AD_OPT_TEAM_FAILURES) == 3
+        ctx.set_option(ad.AD_OPT_TEAM_WAIT, 30000)
+        assert ctx.decode_greedy(srcs, max_out=[20] * 3)[0] == ref
+        assert ctx.get_option(ad.AD_OPT_TEAM_FAILURES) == 3
+    finally:
+        ctx.close()
+
+
+def test_two_contexts_in_two_threads():
+    """Teams of two contexts that want the same compute units at the same time: the same tokens."""
+    rng = np.random.default_rng(6)
+    srcs = [[_tokens(rng, n) for n in ns] for ns in ((9, 14), (12,))]
+    ctxs = [_context(batch=2), _context(batch=2)]
+    try:
+        ref = []
+        for c, s in zip(ctxs, srcs):
+            c.set_option(ad.AD_OPT_TEAMS, 0)
+            ref.append(c.decode_greedy(s, max_out=[24] * len(s))[0])
+            c.set_option(ad.AD_OPT_TEAMS, 1)
+        got = [[], []]
+
+        def run(i):
+            for _ in range(4):
+                got[i].append(ctxs[i].decode_greedy(srcs[i], max_out=[24] * len(srcs[i]))[0])
+        threads = [threading.Thread(target=run, args=(i,)) for i in range(2)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        for i in range(2):
+            assert got[i] == [ref[i]] * 4
+    finally:
+        for c in ctxs:
+            c.close()
