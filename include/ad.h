@@ -203,7 +203,8 @@ int ad_decode_gad(ad_ctx* ctx, const int32_t* src, const int32_t* src_len, int B
 /* ---- inspection ------------------------------------------------------------------------------ */
 
 /* Full logits [rows, vocab] (fp32, host) of the last ad_verify or ad_draft_nat, rows in
- * packed order (sequence by sequence).  Needs cfg.debug_logits; AD_ESTATE otherwise. */
+ * packed order (sequence by sequence).  Needs cfg.debug_logits; AD_ESTATE otherwise.  *rows is
+ * set to the rows there are also where rows_cap is too small for them (AD_EINVAL). */
 int ad_debug_logits(ad_ctx* ctx, float* logits, int rows_cap, int* rows);
 
 /* Re-launches the kernels of the last ad_verify forward on the context's stream without touching

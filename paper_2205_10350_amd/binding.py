@@ -401,11 +401,15 @@ class Context:
         return us.value
 
     def debug_logits(self):
-        cap = self.cfg.max_batch * self.cfg.k_max
-        buf = np.zeros((cap, self.cfg.vocab), dtype=np.float32)
-        rows = C.c_int(0)
-        _check(self.L.ad_debug_logits(self.h, buf.ctypes.data_as(C.POINTER(C.c_float)), cap, C.byref(rows)), self.h)
-        return buf[:rows.value].copy()
+        # asked for the rows first: an array of their exact size comes from memory the process already holds, one for the
+        # most rows a context can have is mapped, faulted in and unmapped on every call
+        one, rows = C.c_float(0), C.c_int(0)
+        rc = self.L.ad_debug_logits(self.h, C.byref(one), 0, C.byref(rows))
+        if rows.value < 1:
+            _check(rc, self.h)
+        buf = np.empty((rows.value, self.cfg.vocab), dtype=np.float32)
+        _check(self.L.ad_debug_logits(self.h, buf.ctypes.data_as(C.POINTER(C.c_float)), rows.value, C.byref(rows)), self.h)
+        return buf
 
     def time_verify_forward(self, reps=20, back_to_back=False):
         a, b, d = C.c_double(0), C.c_double(0), C.c_double(0)
