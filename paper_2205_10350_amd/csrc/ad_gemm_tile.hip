@@ -65,12 +65,92 @@ __device__ __forceinline__ void tile_apply(const Epi& e, const f32x4 (&acc)[MT],
     }
   }
 }
+// The same for a wave's SP strips together, by way of its own part of the LDS that held the rows: there a lane has 16 bytes of
+// one row, and a store covers 64 (bf16, SP = 2) to 256 (fp32, SP = 4) consecutive bytes of a row where tile_apply's covers 32 or
+// 64.  A tile's results leave all at once when its products are done, so these bytes are not hidden behind anything: of the
+// 36.8 us of 3249 rows x N 4096 x K 1024 (27 MB of results) 12 were theirs.  tile_apply / this, us: that product 36.5 / 31.5,
+// N 3072 32.6 / 28.9, N 12288 91.0 / 77.8, N 1024 with fp32 residuals 16.7 / 15.2 and K 4096 43.3 / 41.4; K = 512, 1120 rows, N
+// 1536 / 2048 / 6144 6.1 / 8.4 / 17.3 and 5.3 / 7.1 / 13.9, N 512 with residuals 4.3 and 4.4.  (Whole rows of the workgroup's
+// tile, 256 to 1024 bytes a row behind two barriers, measured the same as a wave's own part.)  The kernels of one strip a
+// wave, whose operands are requested before the products, stay with tile_apply: their results are few.
+// Everything a lane reads (bias, residual values, destination rows) is requested before the first result is put down.
+// (The SP strips lie inside one of the q / k / v ranges, or one layer's key or value range: those are multiples of 512 columns,
+// the width K, wide.)
+template <int MT, int SP, int EM, int BYTES>
+__device__ __forceinline__ void tile_finish(const Epi& e, const f32x4 (&acc)[SP][MT], char* tmp, int m0, int s0, int n_strips, int M,
+                                            int N, int lane) {
+  constexpr int EB = EM == EPI_RESID ? 4 : 2, LDB = SP * 16 * EB + 16;   // bytes of an element and of a row (16 apart: banks)
+  constexpr int PL = SP * EB, RW = 64 / PL;                              // 16-byte pieces of a row, rows a store covers
+  constexpr int CT = BYTES >= MT * 16 * LDB ? MT : BYTES >= MT * 8 * LDB ? MT / 2 : MT / 4;   // row tiles put down at once
+  static_assert(CT >= 1 && CT * 16 * LDB <= BYTES, "a chunk fits the wave's part");
+  constexpr int NI = CT * 16 / RW;
+  if (s0 >= n_strips) return;
+  const int r = lane & 15, c0 = 4 * (lane >> 4), d = e.d, n0 = s0 << 4;
+  const int row = lane / PL, piece = lane % PL, col = piece * (16 / EB);
+  const bool in_n = s0 + piece / EB < n_strips;
+  f32x4 bias[SP];
+#pragma unroll
+  for (int j = 0; j < SP; ++j) {
+    bias[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (e.bias) bias[j] = __builtin_bit_cast(f32x4, ldg16(e.bias + (min(s0 + j, n_strips - 1) << 4) + c0));
+  }
+  char* base = (char*)e.out0;
+  size_t ld = (size_t)N * EB;
+  bool by_dst = false;
+  if constexpr (EM == EPI_QKV) {
+    const int part = n0 / d;
+    ld = (size_t)d * 2; by_dst = part > 0;
+    base = (char*)(part == 0 ? e.out0 : part == 1 ? e.out1 : e.out2) + (n0 - part * d) * 2;
+  } else if constexpr (EM == EPI_KV) {
+    const int layer = n0 / (2 * d), c = n0 - layer * 2 * d;
+    ld = (size_t)d * 2; by_dst = true;
+    base = (char*)(c < d ? e.out1 : e.out2) + layer * e.layer_stride + (c < d ? c : c - d) * 2;
+  } else {
+    base += (size_t)n0 * EB;
+  }
+  base += piece * 16;
+#pragma unroll
+  for (int k0 = 0; k0 < MT; k0 += CT) {
+    const int mr = m0 + 16 * k0 + row;
+    uint4 res[NI];   // the residual values, or .x = the destination row
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int m = min(mr + i * RW, M - 1);
+      if constexpr (EM == EPI_RESID) res[i] = ldg16(e.resid + (size_t)m * N + min(n0 + col, N - 4));
+      else res[i].x = by_dst ? (unsigned)gload(e.row_dst + m) : (unsigned)m;
+    }
+#pragma unroll
+    for (int t = 0; t < CT; ++t)
+#pragma unroll
+      for (int j = 0; j < SP; ++j) {
+        f32x4 v = acc[j][k0 + t];
+        if (e.bias) v += bias[j];
+        if constexpr (EM == EPI_RELU) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) v[i] = fmaxf(v[i], 0.f);
+        }
+        char* at = tmp + (16 * t + r) * LDB + (16 * j + c0) * EB;
+        if constexpr (EM == EPI_RESID) *(uint4*)at = __builtin_bit_cast(uint4, v);
+        else *(uint2*)at = uint2{f2bf_pair(v[0], v[1]), f2bf_pair(v[2], v[3])};
+      }
+    // (a wave's LDS accesses take effect in order: only the compiler has to keep them so)
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      uint4 v = *(const uint4*)(tmp + (i * RW + row) * LDB + piece * 16);
+      if constexpr (EM == EPI_RESID) v = __builtin_bit_cast(uint4, __builtin_bit_cast(f32x4, v) + __builtin_bit_cast(f32x4, res[i]));
+      const int m = mr + i * RW;
+      if (in_n && m < M) gstore((uint4*)(base + (EM == EPI_RESID ? (size_t)m : (size_t)res[i].x) * ld), v);
+    }
+    asm volatile("" ::: "memory");
+  }
+}
 template <int MT, int SP, int D, int EM>
 __global__ __launch_bounds__(256) void k_gemm_bf16_tile(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M,
                                                         int N, int K, int m_tiles, int n_tiles, Epi e) {
   constexpr int BM = 16 * MT, NA = BM / 32, LD = 64 + 16;   // NA 16-byte pieces of a stage's rows per thread
   static_assert(D == 2 || D == 4 || D == 8, "D divides the stages of every K that is a multiple of 512");
-  __shared__ bf16_t At[2][BM * LD];
+  __shared__ __align__(16) bf16_t At[2][BM * LD];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r = lane & 15, kq = lane >> 4;
   // consecutive workgroups go to consecutive XCDs: XCD x works through the x-th eighth of the tiles, column tile by column
@@ -184,12 +264,14 @@ __global__ __launch_bounds__(256) void k_gemm_bf16_tile(const bf16_t* __restrict
   };
   for (int rd = 0; rd + 1 < rounds; ++rd) round(std::true_type{}, rd * D);
   round(std::false_type{}, (rounds - 1) * D);
+  if constexpr (PRE) {
 #pragma unroll
-  for (int j = 0; j < SP; ++j)
-    if (s0 + j < n_strips) {
-      if constexpr (!PRE) tile_request<MT, EM>(e, m0, (s0 + j) << 4, M, N, lane, g[j]);
-      tile_apply<MT, EM>(e, acc[j], g[j], m0, (s0 + j) << 4, M, N, lane);
-    }
+    for (int j = 0; j < SP; ++j)
+      if (s0 + j < n_strips) tile_apply<MT, EM>(e, acc[j], g[j], m0, (s0 + j) << 4, M, N, lane);
+  } else {   // (the last stage's fragments were read before its barrier: the rows' LDS is free)
+    constexpr int BYTES = 2 * BM * LD * 2 / 4;
+    tile_finish<MT, SP, EM, BYTES>(e, acc, (char*)At + wave * BYTES, m0, s0, n_strips, M, N, lane);
+  }
 }
 
 // The same product for many rows, where the matrix cores and not latencies are the bound: one register set per operand,
@@ -200,7 +282,7 @@ template <int MT, int SP, int EM>
 __global__ __launch_bounds__(256, 2) void k_gemm_bf16_roll(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M,
                                                            int N, int K, int m_tiles, int n_tiles, Epi e) {
   constexpr int BM = 16 * MT, NA = BM / 32, LD = 64 + 16, BUF = BM * LD;
-  __shared__ bf16_t At[3 * BUF];
+  __shared__ __align__(16) bf16_t At[3 * BUF];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r = lane & 15, kq = lane >> 4;
   const int per = (m_tiles * n_tiles + 7) >> 3, lin = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
@@ -280,13 +362,8 @@ __global__ __launch_bounds__(256, 2) void k_gemm_bf16_roll(const bf16_t* __restr
     const int x = cur;
     cur = nxt; nxt = wrt; wrt = x;
   }
-#pragma unroll
-  for (int j = 0; j < SP; ++j)
-    if (s0 + j < n_strips) {
-      TileRegs<MT> g;
-      tile_request<MT, EM>(e, m0, (s0 + j) << 4, M, N, lane, g);
-      tile_apply<MT, EM>(e, acc[j], g, m0, (s0 + j) << 4, M, N, lane);
-    }
+  constexpr int BYTES = 3 * BUF * 2 / 4;
+  tile_finish<MT, SP, EM, BYTES>(e, acc, (char*)At + wave * BYTES, m0, s0, n_strips, M, N, lane);
 }
 
 template <int MT, int SP, typename Go>
@@ -356,9 +433,10 @@ bool gemm_tile_takes(int M, int N, int K, bool has_ln, int mode) {
 // 128 x 128 rolling: two workgroups per CU; up to 640 of them a second round is nearly empty and the 64 x 128 rolling shape
 // wins: K = 512, N 3072 x 3000 rows (w(128, 128) 576) 28.5 / 26.2 us, K = 1536, N 6144 x 1300 (528) 54.0 / 44.0; but K = 2048,
 // N 2048 x 4096 (512) 45.1 / 49.7, K = 1024, N 3072 x 3531 (672) 40.8 / 43.1.
-// Measured at K = 1024 (64 x 128 / 64 x 128 rolling / 128 x 128 / 128 x 256): N 3072 x 626 rows (w 240) 8.3 / 9.0 / 12.0 / 18.4 us,
-// x 2000 (768) 23.1 / 21.3 / 23.0 / 26.7; N 4096 x 2000 (1024) 28.0 / 26.5 / 23.0 / 25.4, x 3252 (1632) 44 / 43 / 42 / 35.5 (770
-// TFLOP/s); N 12288 x 3252 120 / 122 / 108 / 94.6 (865 TFLOP/s).
+// (These figures, and those above gemm_tile_takes, are of all kernels with tile_apply's stores.)  With tile_finish at K = 1024 (64 x 128
+// two stages ahead / 64 x 128 rolling / 128 x 128 / 128 x 256): N 3072 x 626 rows (w 240) 7.3 / 8.4 / 10.9 / 15.9 us (four stages
+// 7.1), x 2000 (768) 18.6 / 19.0 / 19.7 / 21.0, x 3249 (1224) 29.1 / 29.4 / 30.4 / 29.6; N 4096 x 2000 (1024) 24.2 / 24.0 / 21.6 /
+// 23.2, x 3249 (1632) 39.1 / 39.3 / 38.1 / 32.1 (850 TFLOP/s); N 12288 x 3249 107 / 109 / 100 / 81 (1010 TFLOP/s).
 void launch_gemm_tile(const void* A_, const void* W_, int M, int N, int K, const Epi& e, hipStream_t s) {
   const bf16_t *A = (const bf16_t*)A_, *W = (const bf16_t*)W_;
   auto w = [&](int rows, int cols) { return ((M + rows - 1) / rows) * ((N + cols - 1) / cols); };
