@@ -27,6 +27,8 @@ namespace ad {
 constexpr int kRowsKeys = 512, kRowsKeysTail = 544;   // most keys without / with the fifth super-block
 constexpr int kRowsKld = 64 + 16;                     // row stride of the staged keys (32 bytes past a multiple of 64)
 constexpr int rows_key_tiles(int sb) { return sb < 4 ? 8 : 2; }   // 16-key tiles of super-block sb
+// (value_block; the up to four blocks past key 512 stay among themselves)
+__device__ __forceinline__ int rows_value_block(int b, int c, int r, bool whole) { return whole ? value_block(b, c, r) : b ^ ((2 * c + (r >> 3)) & 3); }
 template <int NSB, bool LONGK>
 __device__ __forceinline__ void attn_rows_tile(const uint4 (&qf)[2], bf16_t* __restrict__ out, const SeqDesc sd, int row0, int row_end,
                                                int h, int d, float scale, const bf16_t* Ks, const bf16_t* Vt, int ldv) {
@@ -103,7 +105,7 @@ __device__ __forceinline__ void attn_rows_tile(const uint4 (&qf)[2], bf16_t* __r
       }
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        const uint4 vf = *(const uint4*)(Vt + (16 * c + r) * ldv + 128 * sb + 32 * b + 8 * kq);
+        const uint4 vf = *(const uint4*)(Vt + (16 * c + r) * ldv + 8 * rows_value_block(16 * sb + 4 * b + kq, c, r, sb < 4));
         O[a][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf), __builtin_bit_cast(bf16x8, pf), O[a][c], 0, 0, 0);
       }
     }
@@ -120,13 +122,25 @@ __device__ __forceinline__ void attn_rows_tile(const uint4 (&qf)[2], bf16_t* __r
     p = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l), false, false);
     l = __uint_as_float(p[0]) + __uint_as_float(p[1]);
   }
-  if (row0 + r < row_end) {
-    bf16_t* op = out + (size_t)(sd.q_row0 + row0 + r) * d + h * DH + 4 * kq;
+  // channels 32 p + 8 kq .. + 7 of the lane's row from the four lanes that hold four of each 16: a store then covers 64
+  // consecutive bytes of a row (32 as they are)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const f32x4 o = O[0][c];
-      gstore((uint2*)(op + 16 * c), uint2{f2bf_pair(o[0] / l, o[1] / l), f2bf_pair(o[2] / l, o[3] / l)});
+  for (int p = 0; p < 2; ++p) {
+    unsigned x[2][2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const f32x4 o = O[0][2 * p + t];
+      x[t][0] = f2bf_pair(o[0] / l, o[1] / l);
+      x[t][1] = f2bf_pair(o[2] / l, o[3] / l);
     }
+    uint4 of;
+    auto u = __builtin_amdgcn_permlane32_swap(x[0][0], x[1][0], false, false);
+    auto w = __builtin_amdgcn_permlane16_swap(u[0], u[1], false, false);
+    of.x = w[0]; of.z = w[1];
+    u = __builtin_amdgcn_permlane32_swap(x[0][1], x[1][1], false, false);
+    w = __builtin_amdgcn_permlane16_swap(u[0], u[1], false, false);
+    of.y = w[0]; of.w = w[1];
+    if (row0 + r < row_end) gstore((uint4*)(out + (size_t)(sd.q_row0 + row0 + r) * d + h * DH + 32 * p + 8 * kq), of);
   }
 }
 __host__ __device__ inline int attn_rows_padded(int nk) { return nk <= kRowsKeys ? (nk + 127) / 128 * 128 : (nk + 31) / 32 * 32; }
@@ -189,7 +203,7 @@ __global__ __launch_bounds__(512) void k_attention_rows(const bf16_t* __restrict
         const unsigned lo = in[2 * pr][c >> 1], hi = in[2 * pr + 1][c >> 1];
         o[pr] = (c & 1) ? __builtin_amdgcn_perm(hi, lo, 0x07060302u) : __builtin_amdgcn_perm(hi, lo, 0x05040100u);
       }
-      *(uint4*)(Vt + (size_t)(g * 8 + c) * ldv + t0) = uint4{o[0], o[1], o[2], o[3]};
+      *(uint4*)(Vt + (size_t)(g * 8 + c) * ldv + (t0 ^ 8 * (t0 < kRowsKeys ? g : g & 3))) = uint4{o[0], o[1], o[2], o[3]};
     }
   };
   if (t0 < nkp) put_values(t0);
