@@ -24,9 +24,6 @@ struct TeamOff {
   static constexpr int ln_fg = DEC ? ln2g : ln1g, ln_fb = ln_fg + kVec;   // pending ahead of the FFN
   static constexpr int ln_lg = w1 + kFfn, ln_lb = ln_lg + kVec;           // the layer's last
   static constexpr int kLayerBytes = ln_lb + kVec;
-  // what the products read besides the matrices, as four runs of bytes (for the prefetch; the encoder has three)
-  static __device__ int vec(int i) { return i == 0 ? bqkv : i == 1 ? b1 : i == 2 ? b2 : cbq; }                          // b_qkv b_o ln1 | b1 | b2 ln_l | cross b ln2
-  static __device__ int vec_lines(int i) { return (i == 0 ? 6 * kVec : i == 1 ? kTeamF * 4 : i == 2 ? 3 * kVec : 6 * kVec) / 128; }
 };
 struct TeamArgs {
   int n_teams, xcd0, layers;          // teams on the XCDs xcd0, xcd0 + 1, ...

@@ -4,10 +4,17 @@
 // what they spend is the launch boundary (2.4 us), the trip of the rows from another XCD's writes and the fetch of
 // weights that could not be requested earlier.  Here the 32 compute units of an XCD form a team: one workgroup per CU,
 // resident for the whole stack, the stages separated by a barrier through that XCD's L2 (0.7 us; a stage's rows come
-// from the same L2, 0.3 us away), the next stage's weights requested before the barrier and brought into the L2 one to
-// two stages earlier by a wave that does nothing else.  Sequences never share a row of an attention or a LayerNorm, so
-// teams on different XCDs work on different sequences and never talk to each other; with one sequence seven XCDs idle,
-// which costs nothing: one XCD streams the base model's decoder layers (44 MB) from the last-level cache in 34 us.
+// from the same L2, 0.14 us away), the strips of the next stage requested while the present one's rows are multiplied by
+// other waves.  Sequences never share a row of an attention or a LayerNorm, so teams on different XCDs work on different
+// sequences and never talk to each other; with one sequence seven XCDs idle.
+//
+// What bounds it: one XCD streams the base model's decoder layers (44 MB) from the last-level cache in 34 us, of which about 30
+// stay exposed (a CU's vector memory returns in order: strips requested earlier are in the way of the rows); the trips of the
+// rows, 22-31 us; attention, 20-24; above 16 rows LayerNorm, which every member takes of every row.
+// Verify forward of the base model, us, this / a launch per stage: 1 sequence of 1, 4, 8, 16, 17, 25, 32 rows 148, 148, 151, 159, 176,
+// 184, 184 / 159, 171, 175, 179, 177, 181, 181 (the launches replayed as a graph; a call shape's first two appearances go out launch
+// by launch in 223, so that decodes with blocks of 25 rows gain 1-2 % all the same); 33 to 64 rows, four row tiles, 240 and more / 184-191: hence at most 32
+// rows; 8 sequences of 25 rows 200 / 224; 32 sequences of 1, 2, 4, 6, 8 rows 164, 166, 173, 190, 198 / 179, 185, 197, 223, 232.
 //
 // Stages of a layer: QKV | self-attention | output projection | cross-attention with its query projection | output
 // projection | FFN1 | FFN2 (the encoder without the middle two).  Members of a team split the columns of a product
@@ -430,10 +437,10 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
   float4 gv[2], bv[2];
 
   // The two groups of waves take turns: one multiplies a stage's rows while the other requests the next stage's strips
-  // into its registers.  A CU's vector memory returns in order, so strips (from the last-level cache, 1 us) are requested
-  // when a stage's rows have arrived and return while the other group multiplies, stores and meets the team; and a wave that waits
+  // into its registers.  A CU's vector memory returns in order, so strips (from the last-level cache: 64 KB a CU in 0.93 us, from
+  // the L2 in 0.56) are requested when a stage's rows have arrived and return while the other group multiplies, stores and meets the team; and a wave that waits
   // for its stores waits for every request before them, so the group that stores requests nothing.
-  // Group A: Q, K, V | self-attention | cross-attention | FFN1.  Group B: output projections | FFN2.
+  // Group A: Q, K, V | self-attention | cross-attention | FFN1.  Group B: output projections | cross queries | FFN2.
   if (wave < kGW) {
     // ------------------------------------------------------------------------------------------ group A
     const bool watcher = gw == kGW - 1;
@@ -551,7 +558,7 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
         }
         // -------------------------------------------------------------- output projection (group B multiplies)
         {
-          const int lane = here(lane0), idx = here_s(idx0), r = lane & 15;
+          const int lane = here(lane0), idx = here_s(idx0);
           team_begin(ts, watcher, lane);
           stage_rows<RPW>(a.att, grow, wave * RPW, n - 1, At, lane);
           wg_bar();
