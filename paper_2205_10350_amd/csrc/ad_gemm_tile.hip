@@ -8,8 +8,8 @@
 
 namespace ad {
 
-// C[M,N] = A[M,K] . W[N,K]^T, A row-major, W in operand tiles.  A workgroup of four waves owns BM = 16*MT rows x BN = 64*SP
-// columns: every wave all the rows, SP of the 16-column strips.  K is walked 64 at a time; a stage's rows go through registers
+// C[M,N] = A[M,K] . W[N,K]^T, A row-major, W in operand tiles.  A workgroup of NW waves owns BM = 16*MT rows x BN = 16*SP*NW
+// columns: every wave all the rows, SP of the 16-column strips.  K is walked 64 U at a time; a stage's rows go through registers
 // into LDS (two buffers), its weights straight into operand registers, D stages requested ahead.
 // The products are taken with the weights as the left operand, so that a lane holds four consecutive columns of one row:
 // acc[t][i] = row m0 + 16 t + lane % 16, column n0 + 4 (lane / 16) + i.  Same value per element as strip_epilogue.
@@ -145,11 +145,11 @@ __device__ __forceinline__ void tile_finish(const Epi& e, const f32x4 (&acc)[SP]
     asm volatile("" ::: "memory");
   }
 }
-template <int MT, int SP, int D, int EM>
-__global__ __launch_bounds__(256) void k_gemm_bf16_tile(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M,
+template <int MT, int SP, int D, int U, int NW, int EM>
+__global__ __launch_bounds__(64 * NW) void k_gemm_bf16_tile(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M,
                                                         int N, int K, int m_tiles, int n_tiles, Epi e) {
-  constexpr int BM = 16 * MT, NA = BM / 32, LD = 64 + 16;   // NA 16-byte pieces of a stage's rows per thread
-  static_assert(D == 2 || D == 4 || D == 8, "D divides the stages of every K that is a multiple of 512");
+  constexpr int BM = 16 * MT, BK = 64 * U, NA = BM * U / (8 * NW), LD = BK + 16;   // NA 16-byte pieces of a stage's rows per thread
+  static_assert(8 / U % D == 0, "D divides the stages of every K that is a multiple of 512");
   __shared__ __align__(16) bf16_t At[2][BM * LD];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r = lane & 15, kq = lane >> 4;
@@ -158,29 +158,29 @@ __global__ __launch_bounds__(256) void k_gemm_bf16_tile(const bf16_t* __restrict
   const int per = (m_tiles * n_tiles + 7) >> 3, lin = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
   if ((int)(blockIdx.x >> 3) >= per || lin >= m_tiles * n_tiles) return;
   const int tn = lin / m_tiles, tm = lin - tn * m_tiles;
-  const int m0 = tm * BM, n_strips = N >> 4, s0 = tn * 4 * SP + wave * SP;
+  const int m0 = tm * BM, n_strips = N >> 4, s0 = tn * NW * SP + wave * SP;
   const bf16_t* ap[NA];
   int a_lds[NA];
 #pragma unroll
   for (int i = 0; i < NA; ++i) {
-    const int row = (threadIdx.x >> 3) + 32 * i, c = threadIdx.x & 7;
+    const int row = threadIdx.x / (8 * U) + 8 * NW / U * i, c = threadIdx.x % (8 * U);
     ap[i] = A + (size_t)min(m0 + row, M - 1) * K + 8 * c;
     a_lds[i] = row * LD + 8 * c;
   }
   const bf16_t* wp[SP];
 #pragma unroll
   for (int j = 0; j < SP; ++j) wp[j] = W + (size_t)min(s0 + j, n_strips - 1) * 16 * K + lane * 8;
-  const int rounds = (K >> 6) / D;
-  uint4 ra[D][NA], rb[D][SP][2], af[2][2][MT];
+  const int n_st = K / BK, rounds = n_st / D;
+  uint4 ra[D][NA], rb[D][SP][2 * U], af[2][2 * U][MT];
   auto req_a = [&](int q, int st) {
 #pragma unroll
-    for (int i = 0; i < NA; ++i) ra[q][i] = ldg16(ap[i] + 64 * st);
+    for (int i = 0; i < NA; ++i) ra[q][i] = ldg16(ap[i] + BK * st);
   };
   auto req_b = [&](int q, int st) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int u = 0; u < 2 * U; ++u)
 #pragma unroll
-      for (int j = 0; j < SP; ++j) rb[q][j][u] = ldg16(wp[j] + (size_t)st * 1024 + u * 512);
+      for (int j = 0; j < SP; ++j) rb[q][j][u] = ldg16(wp[j] + (size_t)st * 1024 * U + u * 512);
   };
   auto put_a = [&](int q, int buf) {
 #pragma unroll
@@ -188,7 +188,7 @@ __global__ __launch_bounds__(256) void k_gemm_bf16_tile(const bf16_t* __restrict
   };
   auto get_a = [&](int buf) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int u = 0; u < 2 * U; ++u)
 #pragma unroll
       for (int t = 0; t < MT; ++t) af[buf][u][t] = *(const uint4*)(At[buf] + (16 * t + r) * LD + 32 * u + 8 * kq);
   };
@@ -198,10 +198,10 @@ __global__ __launch_bounds__(256) void k_gemm_bf16_tile(const bf16_t* __restrict
 #pragma unroll
   for (int q = 0; q < 2; ++q)
 #pragma unroll
-    for (int i = 0; i < NA; ++i) rp[q][i] = ldg16(ap[i] + 64 * q);
+    for (int i = 0; i < NA; ++i) rp[q][i] = ldg16(ap[i] + BK * q);
 #pragma unroll
   for (int q = 0; q < D; ++q) {
-    req_a((q + 2) % D, min(q + 2, (K >> 6) - 1));
+    req_a((q + 2) % D, min(q + 2, n_st - 1));
     req_b(q, q);
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -236,24 +236,24 @@ __global__ __launch_bounds__(256) void k_gemm_bf16_tile(const bf16_t* __restrict
       __builtin_amdgcn_sched_barrier(0);
       if (MORE || q + 2 < D) put_a((q + 2) % D, q & 1);
       if (MORE || q + 1 < D) get_a((q + 1) & 1);
-      if (MORE) req_a((q + 2) % D, q + 2 < D ? st + 2 + D : min(st + 2 + D, (K >> 6) - 1));
+      if (MORE) req_a((q + 2) % D, q + 2 < D ? st + 2 + D : min(st + 2 + D, n_st - 1));
 #pragma unroll
-      for (int u = 0; u < 2; ++u)
+      for (int u = 0; u < 2 * U; ++u)
 #pragma unroll
         for (int j = 0; j < SP; ++j) {
 #pragma unroll
           for (int t = 0; t < MT; ++t)
             acc[j][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, rb[q][j][u]), __builtin_bit_cast(bf16x8, af[q & 1][u][t]), acc[j][t], 0, 0, 0);
-          if (MORE) rb[q][j][u] = ldg16(wp[j] + (size_t)(st + D) * 1024 + u * 512);
+          if (MORE) rb[q][j][u] = ldg16(wp[j] + (size_t)(st + D) * 1024 * U + u * 512);
         }
       if (MORE || q + 2 < D) __builtin_amdgcn_sched_group_barrier(0x200, NA, 0);
 #pragma unroll
-      for (int g = 0; g < 2 * SP; ++g) {
+      for (int g = 0; g < 2 * U * SP; ++g) {
 #pragma unroll
         for (int i = 0; i < MT / 2; ++i) {
-          const int at = g * (MT / 2) + i;   // of SP * MT steps
+          const int at = g * (MT / 2) + i;   // of U * SP * MT steps
           __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-          if ((MORE || q + 1 < D) && 2 * at < 2 * MT) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+          if ((MORE || q + 1 < D) && at < U * MT) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
           if (MORE && at < NA) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
         }
         if (MORE) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
@@ -269,7 +269,7 @@ __global__ __launch_bounds__(256) void k_gemm_bf16_tile(const bf16_t* __restrict
     for (int j = 0; j < SP; ++j)
       if (s0 + j < n_strips) tile_apply<MT, EM>(e, acc[j], g[j], m0, (s0 + j) << 4, M, N, lane);
   } else {   // (the last stage's fragments were read before its barrier: the rows' LDS is free)
-    constexpr int BYTES = 2 * BM * LD * 2 / 4;
+    constexpr int BYTES = 2 * BM * LD * 2 / NW;
     tile_finish<MT, SP, EM, BYTES>(e, acc, (char*)At + wave * BYTES, m0, s0, n_strips, M, N, lane);
   }
 }
@@ -366,9 +366,9 @@ __global__ __launch_bounds__(256, 2) void k_gemm_bf16_roll(const bf16_t* __restr
   tile_finish<MT, SP, EM, BYTES>(e, acc, (char*)At + wave * BYTES, m0, s0, n_strips, M, N, lane);
 }
 
-template <int MT, int SP, typename Go>
+template <int MT, int SP, int NW = 4, typename Go>
 static void with_tile_shape(int M, int N, const Epi& e, const Go& go) {
-  const int m_tiles = (M + 16 * MT - 1) / (16 * MT), n_tiles = (N / 16 + 4 * SP - 1) / (4 * SP);
+  const int m_tiles = (M + 16 * MT - 1) / (16 * MT), n_tiles = (N / 16 + NW * SP - 1) / (NW * SP);
   const int grid = (m_tiles * n_tiles + 7) / 8 * 8;
   switch (e.mode) {
     case EPI_QKV: go(std::integral_constant<int, EPI_QKV>{}, grid, m_tiles, n_tiles); break;
@@ -378,10 +378,10 @@ static void with_tile_shape(int M, int N, const Epi& e, const Go& go) {
     default: go(std::integral_constant<int, EPI_RESID>{}, grid, m_tiles, n_tiles); break;
   }
 }
-template <int MT, int SP, int D>
+template <int MT, int SP, int D, int U = 1, int NW = 4>
 static void launch_tile(const bf16_t* A, const bf16_t* W, int M, int N, int K, const Epi& e, hipStream_t s) {
-  with_tile_shape<MT, SP>(M, N, e, [&](auto em_c, int grid, int m_tiles, int n_tiles) {
-    k_gemm_bf16_tile<MT, SP, D, decltype(em_c)::value><<<grid, 256, 0, s>>>(A, W, M, N, K, m_tiles, n_tiles, e);
+  with_tile_shape<MT, SP, NW>(M, N, e, [&](auto em_c, int grid, int m_tiles, int n_tiles) {
+    k_gemm_bf16_tile<MT, SP, D, U, NW, decltype(em_c)::value><<<grid, 64 * NW, 0, s>>>(A, W, M, N, K, m_tiles, n_tiles, e);
   });
 }
 template <int MT, int SP>
@@ -427,6 +427,11 @@ bool gemm_tile_takes(int M, int N, int K, bool has_ln, int mode) {
 }
 // Tile by the number of workgroups w(rows x columns of a tile): the smallest while they fit the CUs at once (a stage's latency is
 // the bound), larger ones as soon as there are enough of them (operand traffic from L2 and then the matrix cores are).
+// 32 x 32 (two waves) while those fit: the small tiles are bound by what a CU takes from L2 (32 x 64: 12 KB per 64 k in 82 ns, 95 % of
+// 64 bytes a clock), and 32 x 32 takes 8 KB on twice the CUs.  Both walk 128 k a stage, half the barriers.  32 x 64 with 64 k a
+// stage / with 128 / 32 x 32, us: N 1024 x 200 rows, K 1024 3.65 / 3.57 / 3.45, K 4096 8.04 / 7.63 / 7.23, K 1536 4.42 / 4.26 / 4.08; N 512 x
+// 400 rows, K 2048 5.14 / 4.94 / 4.69; past the line N 1024 x 400 rows, K 1024 3.84 / 3.76 / 4.45, K 4096 9.76 / 9.72 / 11.2.  Eight stages of
+// 64 k ahead 3.89 and 8.13 at 200 rows; the 64-row tiles gained nothing from longer stages.
 // 64 x 128: four stages ahead while there is one workgroup per CU, two (and two workgroups per CU) beyond: K = 1536, N 1536 x 700 /
 // 1024 / 1600 rows (w 132 / 192 / 300) 10.5 / 11.8 / 19.5 us with four, 12.6 / 13.8 / 18.0 with two; K = 512, N 3072 x 519 rows (216)
 // 8.9 / 9.4; K = 2048, N 1024 x 2049 rows (264) 21.9 / 19.3.
@@ -440,7 +445,8 @@ bool gemm_tile_takes(int M, int N, int K, bool has_ln, int mode) {
 void launch_gemm_tile(const void* A_, const void* W_, int M, int N, int K, const Epi& e, hipStream_t s) {
   const bf16_t *A = (const bf16_t*)A_, *W = (const bf16_t*)W_;
   auto w = [&](int rows, int cols) { return ((M + rows - 1) / rows) * ((N + cols - 1) / cols); };
-  if (w(32, 64) <= 256) launch_tile<2, 1, 4>(A, W, M, N, K, e, s);
+  if (w(32, 32) <= 256) launch_tile<2, 1, 2, 2, 2>(A, W, M, N, K, e, s);
+  else if (w(32, 64) <= 256) launch_tile<2, 1, 2, 2>(A, W, M, N, K, e, s);
   else if (w(64, 64) <= 256) launch_tile<4, 1, 4>(A, W, M, N, K, e, s);
   else if (w(64, 128) <= 256) launch_tile<4, 2, 4>(A, W, M, N, K, e, s);
   else if (w(64, 128) <= 450) launch_tile<4, 2, 2>(A, W, M, N, K, e, s);
