@@ -1100,7 +1100,7 @@ static int verify_call(ad_ctx* c, const int32_t* draft, const int32_t* k, int32_
   }
   TeamRun run;
   run.max_keys = std::max(self_keys, cross_keys);
-  bool team = mapped && !static_scratch && run.max_keys <= kTeamMaxKeys && team_deal(k, nullptr, B, &run) && team_usable(c, AD_VERIFIER, true);
+  bool team = mapped && !static_scratch && run.max_keys <= kTeamMaxKeys && c->can_team[AD_VERIFIER][1] && team_deal(k, nullptr, B, &run) && team_usable(c, AD_VERIFIER, true);
   if (team) {
     team_common(c, AD_VERIFIER, true, 2, &run);
     run.a.K = (bf16_storage*)(c->ws + p.cache_k); run.a.V = (bf16_storage*)(c->ws + p.cache_v); run.a.kv_stride = p.cache_layer_stride;
@@ -1232,7 +1232,7 @@ int ad_draft_nat(ad_ctx* c, int k, int32_t* draft_out) {
     if (!c->h_finished[b]) { seg[0].push_back(k); seg[1].push_back(c->h_len[b] + 1); }
   const TeamFail tf = team_fail_words(c, AD_DRAFTER);
   run.max_keys = std::max(self_keys, *std::max_element(c->h_src_len[AD_DRAFTER].begin(), c->h_src_len[AD_DRAFTER].begin() + B));
-  bool team = watch && run.max_keys <= kTeamMaxKeys && team_deal(seg[0].data(), seg[1].data(), live, &run) && team_usable(c, AD_DRAFTER, true);
+  bool team = watch && run.max_keys <= kTeamMaxKeys && c->can_team[AD_DRAFTER][1] && team_deal(seg[0].data(), seg[1].data(), live, &run) && team_usable(c, AD_DRAFTER, true);
   if (team) {
     team_common(c, AD_DRAFTER, true, 2, &run);
     run.a.head_only = 1; run.a.prob2_off = live;

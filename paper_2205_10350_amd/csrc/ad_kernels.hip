@@ -1291,17 +1291,11 @@ __global__ __launch_bounds__(1024) void k_argmax_accept(const int* __restrict__ 
   const int ticket = threadIdx.x == 0 && ticket_out ? *ticket_in : 0;
   const unsigned failed = (tf.a ? *tf.a : 0u) | (tf.b ? *tf.b : 0u);
   const int kb = gridDim.x == 1 ? M : k[b];   // a lone sequence owns all M rows
-  if (failed) {
-    if (threadIdx.x == 0) {
-      if (ticket_out) __hip_atomic_store(ticket_out + b, ((unsigned long long)ticket << 46) | ((unsigned long long)kTeamFailed << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-      else result[2 * b] = kTeamFailed;
-    }
-    return;
-  }
   if (kb == 0) {
     if (threadIdx.x == 0) {
-      if (ticket_out) __hip_atomic_store(ticket_out + b, (unsigned long long)ticket << 46, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-      else { result[2 * b] = 0; result[2 * b + 1] = 0; }
+      const unsigned n = failed ? kTeamFailed : 0u;
+      if (ticket_out) __hip_atomic_store(ticket_out + b, ((unsigned long long)ticket << 46) | ((unsigned long long)n << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      else { result[2 * b] = (int)n; result[2 * b + 1] = 0; }
     }
     return;
   }
@@ -1332,6 +1326,15 @@ __global__ __launch_bounds__(1024) void k_argmax_accept(const int* __restrict__ 
     }
   }
   __syncthreads();   // the sequence's arg maxima are in memory, visible to the whole workgroup
+  // (asked here and not at the start, where it would wait for every request above: 0.3 us a call; the arg maxima of a forward
+  // that failed are of stale rows and written over by the one that replaces it)
+  if (failed) {
+    if (threadIdx.x == 0) {
+      if (ticket_out) __hip_atomic_store(ticket_out + b, ((unsigned long long)ticket << 46) | ((unsigned long long)kTeamFailed << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      else result[2 * b] = kTeamFailed;
+    }
+    return;
+  }
   // first mismatch with the draft and first [EOS], every thread a row at a time
   for (int i = threadIdx.x; i < kb; i += blockDim.x) {
     const int t = o_hat[r0 + i];
