@@ -1281,7 +1281,7 @@ int ad_draft_nat(ad_ctx* c, int k, int32_t* draft_out) {
                           (unsigned long long*)(c->pin_dev + c->pl.d_slots), c->stream, tf);
     } else {
       vocab_finish(c, Mv, n_part);
-      launch_draft_scatter(c->at<int>(p.o_hat), c->at<int>(p.finished), B, k, km, c->at<int>(p.draft_out), c->stream);
+      launch_draft_scatter(c->at<int>(p.o_hat), c->at<int>(p.finished), B, k, km, c->at<int>(p.draft_out), c->stream, tf);
     }
   };
   for (;;) {
@@ -1309,29 +1309,27 @@ int ad_draft_nat(ad_ctx* c, int k, int32_t* draft_out) {
       }
       if (!seen) HIP_TRY(c, hipStreamSynchronize(c->stream));   // (the slots are written then too)
       for (int b = 0; b < B; ++b)
-        failed = failed || (!c->h_finished[b] && (int32_t)(unsigned)__atomic_load_n(slots + (size_t)b * km, __ATOMIC_ACQUIRE) == AD_NEVER - 1);
-      if (failed) {
-        const int rc = team_recover(c);
-        if (rc != AD_OK) return rc;
-        team = false;
-        continue;
-      }
-      if (seen) {
+        failed = failed || (!c->h_finished[b] && (int32_t)(unsigned)__atomic_load_n(slots + (size_t)b * km, __ATOMIC_ACQUIRE) == kTeamFailedToken);
+      if (!failed && seen) {
         for (int b = 0; b < B; ++b)
           for (int i = 0; i < km; ++i)
             draft_out[(size_t)b * km + i] = !c->h_finished[b] && i < k ? (int32_t)(unsigned)slots[(size_t)b * km + i] : AD_NEVER;
-      } else {
+      } else if (!failed) {
         // fall back to the stream: the tokens are in o_hat; scatter them as the other path does
         launch_draft_scatter(c->at<int>(p.o_hat), c->at<int>(p.finished), B, k, km, c->at<int>(p.draft_out), c->stream);
       }
     }
-    if (!seen) {
+    if (!seen && !failed) {
       HIP_TRY(c, hipMemcpyAsync(h, c->at<int>(p.draft_out), (size_t)B * km * 4, hipMemcpyDeviceToHost, c->stream));
       HIP_TRY(c, hipStreamSynchronize(c->stream));
       HIP_TRY(c, hipGetLastError());
-      memcpy(draft_out, h, (size_t)B * km * 4);
+      for (int b = 0; b < B; ++b) failed = failed || (!c->h_finished[b] && h[(size_t)b * km] == kTeamFailedToken);
+      if (!failed) memcpy(draft_out, h, (size_t)B * km * 4);
     }
-    break;
+    if (!failed) break;
+    const int rc = team_recover(c);
+    if (rc != AD_OK) return rc;
+    team = false;
   }
   c->last_logit_rows = Mv;
   c->last_M = 0;   // the row tables now describe the drafter's rows

@@ -135,9 +135,9 @@ void launch_argmax_finish(const float* part_val, const int* part_idx, int M, int
 void launch_draft_logit(int dtype, const void* A, const void* W, int M, int N, int K, const int* row_seq,
                         const int* row_start, const int* draft, int k_max, float* lp, int* col, hipStream_t s);
 // Fail words of the launch_team launches a result rests on (null: there was none).  One of them set: the rows are
-// not there; the result says so (accepted length kTeamFailed, drafted token AD_NEVER - 1) and the decode state stays as it was.
+// not there; the result says so (accepted length kTeamFailed, drafted tokens kTeamFailedToken) and the decode state stays as it was.
 struct TeamFail { const unsigned *a = nullptr, *b = nullptr; };
-constexpr int kTeamFailed = 0x3fff;
+constexpr int kTeamFailed = 0x3fff, kTeamFailedToken = AD_NEVER - 1;
 // second stage of the arg max over the drafter's M = live * k mask rows; token i of the l-th unfinished
 // sequence b goes to the 8-byte slot [b * k_max + i] of `slots` (host-visible) as (*ticket_in << 32 | token)
 void launch_argmax_draft(const float* part_val, const int* part_idx, int M, int stride, int n_part, int* o_hat,
@@ -193,7 +193,7 @@ void launch_assemble_embed_drafter(int dtype, const int* out, int max_len, const
                                    int M, const void* emb, const float* pe, int d, float sqrt_d, float* x, void* xa,
                                    hipStream_t s, unsigned* team_words = nullptr);
 void launch_draft_scatter(const int* o_hat, const int* finished, int B, int k, int k_max, int* draft_out,
-                          hipStream_t s);
+                          hipStream_t s, const TeamFail& tf = TeamFail{});
 
 // ---- host-only decode loops (ad_hostlogic.cpp) ------------------------------------------------------
 struct Backend {

@@ -941,7 +941,7 @@ __global__ __launch_bounds__(256) void k_argmax_draft(const float* __restrict__ 
   argmax_row(pv + (size_t)m * stride, pi + (size_t)m * stride, n_part, lane, v, idx);
   if (lane == 0) {
     o_hat[m] = idx;
-    __hip_atomic_store(slots + (size_t)b * k_max + i, ((unsigned long long)(unsigned)ticket << 32) | (unsigned)(failed ? AD_NEVER - 1 : idx),
+    __hip_atomic_store(slots + (size_t)b * k_max + i, ((unsigned long long)(unsigned)ticket << 32) | (unsigned)(failed ? kTeamFailedToken : idx),
                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
@@ -1252,19 +1252,20 @@ void launch_assemble_embed_drafter(int dtype, const int* out, int max_len, const
 
 // Drafted tokens of the unfinished sequences, back in [B, k_max] order (AD_NEVER elsewhere).
 __global__ void k_draft_scatter(const int* __restrict__ o_hat, const int* __restrict__ finished, int B, int k,
-                                int k_max, int* __restrict__ draft_out) {
+                                int k_max, int* __restrict__ draft_out, TeamFail tf) {
   if (threadIdx.x != 0) return;
+  const unsigned failed = (tf.a ? *tf.a : 0u) | (tf.b ? *tf.b : 0u);
   int live = 0;
   for (int b = 0; b < B; ++b) {
     for (int i = 0; i < k_max; ++i) draft_out[b * k_max + i] = AD_NEVER;
     if (finished[b]) continue;
-    for (int i = 0; i < k; ++i) draft_out[b * k_max + i] = o_hat[live * k + i];
+    for (int i = 0; i < k; ++i) draft_out[b * k_max + i] = failed ? kTeamFailedToken : o_hat[live * k + i];
     ++live;
   }
 }
 void launch_draft_scatter(const int* o_hat, const int* finished, int B, int k, int k_max, int* draft_out,
-                          hipStream_t s) {
-  k_draft_scatter<<<1, 64, 0, s>>>(o_hat, finished, B, k, k_max, draft_out);
+                          hipStream_t s, const TeamFail& tf) {
+  k_draft_scatter<<<1, 64, 0, s>>>(o_hat, finished, B, k, k_max, draft_out, tf);
 }
 
 // ------------------------------------------------------------------------------------- accept + rollback

@@ -152,6 +152,30 @@ def test_a_team_that_does_not_come_together_leaves_the_call_to_the_launches():
         ctx.close()
 
 
+@pytest.mark.parametrize("lens", [[9, 30, 4], [12]])
+def test_drafts_of_an_encoder_that_gave_up_without_the_watched_ticket(lens):
+    """AD_OPT_SPIN_WAIT 0: ad_draft_nat gets its tokens by a copy, and asks there too whether the drafter's encoder (and the
+    verifier's, whose memory the next ad_verify reads) came together."""
+    rng = np.random.default_rng(50 + len(lens))
+    srcs = [_tokens(rng, n) for n in lens]
+    ctx = _context(drafter=True)
+    try:
+        ctx.set_option(ad.AD_OPT_SPIN_WAIT, 0)
+        ctx.set_option(ad.AD_OPT_TEAM_WAIT, 0)
+        got = []
+        for teams in (1, 0):
+            ctx.set_option(ad.AD_OPT_TEAMS, teams)
+            ctx.encode(ad.AD_VERIFIER, srcs)
+            ctx.encode(ad.AD_DRAFTER, srcs)
+            d = ctx.draft_nat(5).copy()
+            got.append([d, ctx.debug_logits().view(np.uint32).copy(), *ctx.verify([list(row) for row in d]), ctx.debug_logits().view(np.uint32).copy()])
+            assert ctx.get_option(ad.AD_OPT_TEAM_FAILURES) == 1
+        for x, y in zip(*got):
+            assert np.array_equal(x, y)
+    finally:
+        ctx.close()
+
+
 def test_two_contexts_in_two_threads():
     """Teams of two contexts that want the same compute units at the same time: the same tokens."""
     rng = np.random.default_rng(6)
