@@ -76,7 +76,8 @@ struct Epi {
 };
 
 // ---- launchers (ad_kernels.hip).  dtype: AD_F32 / AD_BF16 selects storage + arithmetic ---------
-// (`team_words`, here and below: barrier state of a launch_team that follows, cleared by this launch; null: none)
+// (`team_words`, here and below: barrier state of a launch_team that follows, cleared by this launch; null: none.  launch_embed leaves
+// the fail word as it is: it begins the forwards that are timed one behind the other)
 void launch_embed(int dtype, const void* emb, const float* pe, const int* tok, const int* pos, int M,
                   int d, float sqrt_d, float* x, void* xa, hipStream_t s, unsigned* team_words = nullptr);
 constexpr int kTeamFail = 8 * 64, kTeamWords = kTeamFail + 64;   // per team a line for the member count and one for the arrivals; the fail word

@@ -17,9 +17,9 @@
 
 namespace ad {
 
-// barrier state of a launch_team that follows
-__device__ __forceinline__ void clear_team_words(unsigned* words) {
-  for (int i = threadIdx.x; i < kTeamWords; i += blockDim.x) words[i] = 0u;
+// barrier state of a launch_team that follows, its first n words
+__device__ __forceinline__ void clear_team_words(unsigned* words, int n = kTeamWords) {
+  for (int i = threadIdx.x; i < n; i += blockDim.x) words[i] = 0u;
 }
 // ------------------------------------------------------------------------------------- embed
 // x[m] = E[tok[m]] * sqrt(d) + PE[pos[m]]
@@ -28,7 +28,7 @@ __global__ void k_embed(const T* __restrict__ emb, const float* __restrict__ pe,
                         const int* __restrict__ pos, int d, float sqrt_d, float* __restrict__ x, T* __restrict__ xa,
                         unsigned* __restrict__ team_words) {
   const int m = blockIdx.x;
-  if (m == 0 && team_words) clear_team_words(team_words);
+  if (m == 0 && team_words) clear_team_words(team_words, kTeamFail);   // (the fail word gathers what all of several forwards say)
   const T* e = emb + (size_t)tok[m] * d;
   const float* p = pe + (size_t)pos[m] * d;
   for (int c = threadIdx.x; c < d; c += blockDim.x) {

@@ -176,6 +176,38 @@ def test_drafts_of_an_encoder_that_gave_up_without_the_watched_ticket(lens):
         ctx.close()
 
 
+def test_timed_forwards_that_give_up_leave_the_cache_as_it_was():
+    """ad_time_verify_forward repeats the last forward over accepted rows; where its teams give up, the keys and values it has
+    written are replaced, and the next block scores as it does without the timing."""
+    rng = np.random.default_rng(60)
+    srcs = [_tokens(rng, n) for n in (11, 30)]
+    more = [[int(t) for t in _tokens(rng, 6)] for _ in srcs]
+    ctx = _context(batch=2)
+    try:
+        ctx.set_option(ad.AD_OPT_TEAMS, 0)
+        ref, _ = ctx.decode_greedy(srcs, max_out=[20] * 2)
+        got = []
+        for teams, wait in ((0, None), (1, None), (1, 0)):
+            ctx.set_option(ad.AD_OPT_TEAMS, teams)
+            ctx.encode(ad.AD_VERIFIER, srcs)
+            n, _ = ctx.verify([g[:9] for g in ref])
+            assert list(n) == [9, 9]
+            if wait is not None:
+                ctx.set_option(ad.AD_OPT_TEAM_WAIT, wait)
+            if teams:
+                assert ctx.time_verify_forward(2)[0] > 0
+                assert ctx.get_option(ad.AD_OPT_TEAM_FAILURES) == (0 if wait is None else 1)
+                assert ctx.time_verify_forward(1, back_to_back=True)[0] > 0      # (the launches, from here on)
+                assert ctx.get_option(ad.AD_OPT_TEAM_FAILURES) == (0 if wait is None else 1)
+            got.append([*ctx.verify(more), ctx.debug_logits().view(np.uint32).copy()])
+        for g in got[1:]:
+            for x, y in zip(got[0], g):
+                assert np.array_equal(x, y)
+        assert ctx.get_option(ad.AD_OPT_TEAM_FAILURES) == 1
+    finally:
+        ctx.close()
+
+
 def test_two_contexts_in_two_threads():
     """Teams of two contexts that want the same compute units at the same time: the same tokens."""
     rng = np.random.default_rng(6)
