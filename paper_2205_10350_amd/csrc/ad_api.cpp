@@ -1482,10 +1482,14 @@ int ad_set_option(ad_ctx* c, int option, int value) {
   }
   if (option == AD_OPT_TEAM_WAIT) {
     if (value < 0 || value > 100000) return fail(c, AD_EINVAL, "AD_OPT_TEAM_WAIT must be 0 .. 100000 (10 ns steps)");
+    // The wait is an argument of captured launches: their graphs go.  One of them may still be running (ad_encode returns with its
+    // work queued, ad_verify and ad_draft_nat with the end of theirs).
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    if (c->stream2) HIP_TRY(c, hipStreamSynchronize(c->stream2));
+    for (auto& kv : c->graphs) (void)hipGraphExecDestroy(kv.second);
+    c->graphs.clear();
     c->team_ticks = value;
     c->team_rest = 0;
-    for (auto& kv : c->graphs) (void)hipGraphExecDestroy(kv.second);   // (the wait is an argument of captured launches)
-    c->graphs.clear();
     return AD_OK;
   }
   if (option == AD_OPT_OVERLAP_ENCODERS) {

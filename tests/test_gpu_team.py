@@ -208,6 +208,30 @@ def test_timed_forwards_that_give_up_leave_the_cache_as_it_was():
         ctx.close()
 
 
+def test_setting_the_wait_lets_replayed_graphs_finish():
+    """AD_OPT_TEAM_WAIT drops the graphs; ad_encode has returned with one of them queued, on either stream."""
+    rng = np.random.default_rng(70)
+    srcs = [_tokens(rng, 128) for _ in range(12)]
+    ctx = _context(drafter=True)
+    try:
+        got = []
+        for wait in (None, 20000, 30000):
+            for _ in range(4):
+                ctx.encode(ad.AD_VERIFIER, srcs)
+                ctx.encode(ad.AD_DRAFTER, srcs)
+            if wait is not None:
+                assert ctx.get_option(ad.AD_OPT_GRAPHS_CAPTURED) >= 2
+                ctx.set_option(ad.AD_OPT_TEAM_WAIT, wait)
+                assert ctx.stream.query() and ctx.get_option(ad.AD_OPT_GRAPHS_CAPTURED) == 0
+            d = ctx.draft_nat(4)
+            got.append([d.copy(), *ctx.verify([list(row) for row in d]), ctx.debug_logits().view(np.uint32).copy()])
+        for g in got[1:]:
+            for x, y in zip(got[0], g):
+                assert np.array_equal(x, y)
+    finally:
+        ctx.close()
+
+
 def test_two_contexts_in_two_threads():
     """Teams of two contexts that want the same compute units at the same time: the same tokens."""
     rng = np.random.default_rng(6)
