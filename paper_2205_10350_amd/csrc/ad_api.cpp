@@ -831,9 +831,8 @@ static int team_recover(ad_ctx* c) {
   if (c->stream2) HIP_TRY(c, hipStreamSynchronize(c->stream2));
   unsigned fail[3];
   for (int i = 0; i < 3; ++i) {
-    unsigned* w = (unsigned*)(c->ws + c->plan.team_words[i]) + kTeamFail;
-    HIP_TRY(c, hipMemcpy(&fail[i], w, 4, hipMemcpyDeviceToHost));
-    HIP_TRY(c, hipMemset(w, 0, 4));
+    const int rc = take_team_fail(c, i, &fail[i]);   // (on the stream the repeat runs on)
+    if (rc != AD_OK) return rc;
   }
   team_failed(c);
   for (int model = 0; model < 2; ++model) {

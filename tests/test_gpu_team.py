@@ -6,6 +6,7 @@ import threading
 
 import numpy as np
 import pytest
+import torch
 
 import paper_2205_10350_amd as ad
 from ad_inputs import SPECIAL, init_weights, model_dims
@@ -230,6 +231,41 @@ def test_setting_the_wait_lets_replayed_graphs_finish():
                 assert np.array_equal(x, y)
     finally:
         ctx.close()
+
+
+def test_a_repeat_does_not_wait_for_the_null_stream():
+    """What a call does after its teams gave up stays on the context's stream: work queued on the null stream goes on."""
+    rng = np.random.default_rng(80)
+    srcs = [_tokens(rng, 9)]
+    ctxs = []
+    try:
+        # (streams share hardware queues: a context whose stream runs beside the null stream is needed)
+        for _ in range(4):
+            ctxs.append(_context(batch=1))
+            ctx = ctxs[-1]
+            got = []
+            for teams in (0, 1):
+                ctx.set_option(ad.AD_OPT_TEAMS, teams)
+                ctx.set_option(ad.AD_OPT_TEAM_WAIT, 0)
+                torch.cuda.synchronize()
+                torch.cuda._sleep(200_000_000)
+                end = torch.cuda.Event()
+                end.record()
+                ctx.encode(ad.AD_VERIFIER, srcs)
+                got.append(ctx.verify([[7, 8, 9]]))
+                beside = not end.query()
+                if not beside:
+                    break
+            if teams:
+                break
+        else:
+            pytest.skip("no stream of four runs beside the null stream")
+        assert beside and ctx.get_option(ad.AD_OPT_TEAM_FAILURES) == 1
+        assert all(np.array_equal(x, y) for x, y in zip(*got))
+    finally:
+        torch.cuda.synchronize()
+        for ctx in ctxs:
+            ctx.close()
 
 
 def test_two_contexts_in_two_threads():
