@@ -791,10 +791,12 @@ static void encode_launches(ad_ctx* c, int model, const int* dev, int M, int B, 
   VerifyTables t = tables(c);
   const ModelW& w = c->w[model];
   const bool ver = model == AD_VERIFIER;
+  // (cleared without a team too: a fail word of the model's encoding before this one must not be taken for this one's)
+  unsigned* team_words = c->can_team[model][0] ? (unsigned*)(c->ws + p.team_words[model]) : nullptr;
   launch_assemble_embed_encoder(cf.dtype, dev + 2 * B, S, dev, dev + B, B, S, t, c->at<int>(p.src_len[model]),
                                 c->at<int>(p.max_out), ver ? c->at<int>(p.len) : nullptr, c->at<int>(p.pending),
                                 c->at<int>(p.finished), cf.bos, M, w.emb, c->at<float>(p.pe), d, sqrtf((float)d),
-                                c->at<float>(p.x), c->at<void>(p.xa), c->stream, team ? team->a.words : nullptr);
+                                c->at<float>(p.x), c->at<void>(p.xa), c->stream, team_words);
   c->ln_pending = nullptr;
   if (team) {
     launch_team(team->a, false, team->max_rows, team->max_keys, c->stream);

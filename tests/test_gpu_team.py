@@ -233,6 +233,32 @@ def test_setting_the_wait_lets_replayed_graphs_finish():
         ctx.close()
 
 
+def test_an_encoding_that_gave_up_is_forgotten_with_the_next():
+    """The sentences of an encoding whose teams gave up are replaced, by one that takes no team, before anything asks for them: the next
+    results are not taken for results of the old one."""
+    rng = np.random.default_rng(90)
+    old, new = [_tokens(rng, 9), _tokens(rng, 4)], [_tokens(rng, 12), _tokens(rng, 5)]
+    ctx = _context(drafter=True, batch=2)
+    try:
+        got = []
+        for first in (None, old):
+            if first is not None:
+                ctx.set_option(ad.AD_OPT_TEAMS, 1)
+                ctx.set_option(ad.AD_OPT_TEAM_WAIT, 0)
+                ctx.encode(ad.AD_VERIFIER, first)
+                ctx.encode(ad.AD_DRAFTER, first)
+            ctx.set_option(ad.AD_OPT_TEAMS, 0)
+            ctx.encode(ad.AD_VERIFIER, new)
+            ctx.encode(ad.AD_DRAFTER, new)
+            d = ctx.draft_nat(4)
+            got.append([d.copy(), *ctx.verify([list(row) for row in d]), ctx.debug_logits().view(np.uint32).copy()])
+            assert ctx.get_option(ad.AD_OPT_TEAM_FAILURES) == 0
+        for x, y in zip(*got):
+            assert np.array_equal(x, y)
+    finally:
+        ctx.close()
+
+
 def test_a_repeat_does_not_wait_for_the_null_stream():
     """What a call does after its teams gave up stays on the context's stream: work queued on the null stream goes on."""
     rng = np.random.default_rng(80)
