@@ -239,6 +239,7 @@ struct ad_ctx {
   bool team_on = true;
   int team_ticks = kTeamFormTicks;
   int team_rest = 0, team_failures = 0;
+  int team_backoff = 0, team_held = 0;   // the next rest is 32 << team_backoff; results in a row since it changed whose teams came together
   bool last_team = false;
   TeamRun last_run{};
 
@@ -393,8 +394,15 @@ static ad_ctx::TeamPart team_part(const TeamRun* t) {
 constexpr int kTeamGraphBatch = 4;
 // a team did not come together: the launches take over, for the next calls too (32, 64, .. 4096 of them)
 static void team_failed(ad_ctx* c) {
-  c->team_rest = 32 << std::min(c->team_failures, 7);
+  c->team_rest = 32 << c->team_backoff;
+  c->team_backoff = std::min(c->team_backoff + 1, 7);
+  c->team_held = 0;
   ++c->team_failures;
+}
+// The teams of a result came together: 64 such results in a row halve the next rest.  (A failure costs the 0.3 ms of the wait and the
+// repeat of 0.2 to 0.3 ms, a call with teams gains about 10 us over one without.)
+static void team_came_together(ad_ctx* c) {
+  if (c->team_backoff > 0 && ++c->team_held == 64) { --c->team_backoff; c->team_held = 0; }
 }
 
 // The fail word of the team launches over words `i`, read and cleared on the context's stream (waits for it; never captured).
@@ -1166,6 +1174,7 @@ static int verify_call(ad_ctx* c, const int32_t* draft, const int32_t* k, int32_
       for (int b = 0; b < B; ++b) ticket_out[b] = 0;
     team = false;
   }
+  if (team) team_came_together(c);
   int r0 = 0;
   for (int b = 0; b < B; ++b) {
     if (watch) {
@@ -1344,6 +1353,7 @@ int ad_draft_nat(ad_ctx* c, int k, int32_t* draft_out) {
     if (rc != AD_OK) return rc;
     team = false;
   }
+  if (team) team_came_together(c);
   c->last_logit_rows = Mv;
   c->last_M = 0;   // the row tables now describe the drafter's rows
   return AD_OK;

@@ -259,6 +259,34 @@ def test_an_encoding_that_gave_up_is_forgotten_with_the_next():
         ctx.close()
 
 
+def test_the_launches_turn_gets_shorter_again():
+    """Each failure doubles the calls that go without teams; 64 results in a row whose teams came together halve them again."""
+    srcs = [_tokens(np.random.default_rng(100), 9)]
+    ctx = _context(batch=1)
+
+    def calls():
+        ctx.encode(ad.AD_VERIFIER, srcs)
+        ctx.verify([[7]])
+        return ctx.get_option(ad.AD_OPT_TEAM_FAILURES)
+
+    def until_the_next_failure():
+        before = ctx.get_option(ad.AD_OPT_TEAM_FAILURES)
+        return next(i for i in range(1, 300) if calls() > before)
+    try:
+        ctx.set_option(ad.AD_OPT_TEAM_WAIT, 0)
+        assert calls() == 1                                # 32 calls (an encoding and a block each time) without teams, then 64
+        assert until_the_next_failure() == 16 + 1
+        assert until_the_next_failure() == 32 + 1
+        ctx.set_option(ad.AD_OPT_TEAM_WAIT, 30000)
+        for _ in range(3 * 64):
+            assert calls() == 3
+        ctx.set_option(ad.AD_OPT_TEAM_WAIT, 0)
+        assert calls() == 4
+        assert until_the_next_failure() == 16 + 1
+    finally:
+        ctx.close()
+
+
 def test_a_repeat_does_not_wait_for_the_null_stream():
     """What a call does after its teams gave up stays on the context's stream: work queued on the null stream goes on."""
     rng = np.random.default_rng(80)
