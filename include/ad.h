@@ -265,10 +265,11 @@ int ad_calibration_mfma(void* scratch_dev, size_t scratch_bytes, int32_t iters, 
  * width 512 (8 heads, FFN 2048) run all their layers in one launch, a team of 32 workgroups on one XCD per sequence or group of
  * sequences.  The workgroups of a team wait for each other; where other work keeps some of them from starting for 0.3 ms,
  * the call is repeated with a launch per stage, and so are the next calls for a while.  AD_OPT_TEAM_FAILURES (read only):
- * how often that happened.  AD_OPT_TEAM_WAIT (10 ns steps, 0 .. 100000, default 30000): that time; 0 gives every team up at
+ * how often that happened.  AD_OPT_TEAM_LAUNCHES (read only): the forwards of ad_encode, ad_verify and ad_draft_nat that went out so.  AD_OPT_TEAM_WAIT (10 ns steps, 0 .. 100000, default 30000): that time; 0 gives every team up at
  * once.  Setting it waits for the context's work and drops the graphs held.  Same results bit for bit. */
 enum { AD_OPT_GRAPHS = 3, AD_OPT_GRAPHS_CAPTURED = 4, AD_OPT_SPIN_WAIT = 5, AD_OPT_FUSE_CROSSQ = 6,
-       AD_OPT_OVERLAP_ENCODERS = 7, AD_OPT_TEAMS = 8, AD_OPT_TEAM_FAILURES = 9, AD_OPT_TEAM_WAIT = 10 };
+       AD_OPT_OVERLAP_ENCODERS = 7, AD_OPT_TEAMS = 8, AD_OPT_TEAM_FAILURES = 9, AD_OPT_TEAM_WAIT = 10,
+       AD_OPT_TEAM_LAUNCHES = 11 };
 int ad_set_option(ad_ctx* ctx, int option, int value);
 int ad_get_option(ad_ctx* ctx, int option, int* value);
 

@@ -37,6 +37,7 @@ AD_OPT_OVERLAP_ENCODERS = 7
 AD_OPT_TEAMS = 8
 AD_OPT_TEAM_FAILURES = 9
 AD_OPT_TEAM_WAIT = 10
+AD_OPT_TEAM_LAUNCHES = 11
 
 
 class AdConfig(C.Structure):

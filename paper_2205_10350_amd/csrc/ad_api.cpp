@@ -238,7 +238,7 @@ struct ad_ctx {
   bool can_team[2][2] = {{false, false}, {false, false}};   // [model][encoder, decoder]
   bool team_on = true;
   int team_ticks = kTeamFormTicks;
-  int team_rest = 0, team_failures = 0;
+  int team_rest = 0, team_failures = 0, team_launches = 0;
   int team_backoff = 0, team_held = 0;   // the next rest is 32 << team_backoff; results in a row since it changed whose teams came together
   bool last_team = false;
   TeamRun last_run{};
@@ -934,6 +934,7 @@ int ad_encode(ad_ctx* c, int model, const int32_t* src, const int32_t* src_len, 
     launched = run_as_graph(c, c->stream, key, launches, 0, team_part(&run));
   }
   if (!launched) launches();
+  if (team && (!launched || run.max_rows <= 16)) ++c->team_launches;
   if (side.on) {
     HIP_TRY(c, hipEventRecord(c->ev_enc2, c->stream));
     c->enc2_pending = true;
@@ -1136,7 +1137,7 @@ static int verify_call(ad_ctx* c, const int32_t* draft, const int32_t* k, int32_
   for (;;) {
     v.team = team ? &run : nullptr;
     c->last_team = team;
-    if (team) c->last_run = run;
+    if (team) { c->last_run = run; ++c->team_launches; }
     bool launched = false;
     if (mapped && !static_scratch && (!team || B <= kTeamGraphBatch)) {
       const unsigned long long key = shape_key(M, max_rows, B, (gadpp ? 1 : 0) | (watch ? 2 : 0) | (c->fuse_crossq ? 4 : 0) | (self_keys <= 64 ? 8 : 0) | (cross_keys <= 64 ? 16 : 0));
@@ -1315,6 +1316,7 @@ int ad_draft_nat(ad_ctx* c, int k, int32_t* draft_out) {
           for (int i = 0; i < k; ++i) slots[(size_t)b * km + i] = 0;
     }
     launches();
+    if (team) ++c->team_launches;
     bool seen = false, failed = false;
     if (watch) {
       // wait for the last slot of every live sequence first (it is written about when the others are),
@@ -1522,6 +1524,7 @@ int ad_get_option(ad_ctx* c, int option, int* value) {
   else if (option == AD_OPT_TEAMS) *value = c->team_on ? 1 : 0;
   else if (option == AD_OPT_TEAM_FAILURES) *value = c->team_failures;
   else if (option == AD_OPT_TEAM_WAIT) *value = c->team_ticks;
+  else if (option == AD_OPT_TEAM_LAUNCHES) *value = c->team_launches;
   else if (option == AD_OPT_OVERLAP_ENCODERS) *value = c->overlap_encoders ? 1 : 0;
   else return fail(c, AD_EINVAL, "unknown option");
   return AD_OK;

@@ -25,6 +25,13 @@ def _context(drafter=False, batch=12, max_src=136, max_len=96, k_max=40):
     return ad.Context(cfg, W[7], W[8] if drafter else None)
 
 
+def _launched(ctx, call):
+    """How many forwards of call() ran their layers as one launch."""
+    before = ctx.get_option(ad.AD_OPT_TEAM_LAUNCHES)
+    got = call()
+    return ctx.get_option(ad.AD_OPT_TEAM_LAUNCHES) - before, got
+
+
 def _tokens(rng, n):
     return rng.integers(5, DIMS["vocab"], size=n).astype(np.int32)
 
@@ -37,7 +44,7 @@ def _tokens(rng, n):
 ])
 def test_layers_as_one_launch_give_the_bits_of_the_launches(src, rows):
     """Two calls a sequence (the second against a longer prefix, with one sequence sitting out), with every row of the first block
-    fed; the encoder runs as one launch where its rows allow."""
+    fed; the encoder runs as one launch where its rows allow (at most 32 a sentence), the decoder at most 32 rows a team and 128 keys."""
     rng = np.random.default_rng(sum(src) + 131 * sum(rows))
     srcs = [_tokens(rng, n) for n in src]
     first = [list(_tokens(rng, n)) for n in rows]
@@ -47,10 +54,14 @@ def test_layers_as_one_launch_give_the_bits_of_the_launches(src, rows):
         for on in (0, 1):
             ctx.set_option(ad.AD_OPT_TEAMS, on)
             assert ctx.get_option(ad.AD_OPT_TEAMS) == on
-            ctx.encode(ad.AD_VERIFIER, srcs)
-            out = [ctx.verify(first, want_verified=True), ctx.debug_logits().view(np.uint32).copy()]
+            assert _launched(ctx, lambda: ctx.encode(ad.AD_VERIFIER, srcs))[0] == (on and max(src) <= 32)
+            n, v = _launched(ctx, lambda: ctx.verify(first, want_verified=True))
+            assert n == (on and max(src) <= 128 and max(rows) <= 32)
+            out = [v, ctx.debug_logits().view(np.uint32).copy()]
             second = [[] if b == 1 else list(first[b][:1 + b % 3]) for b in range(len(src))]
-            out += [ctx.verify(second), ctx.debug_logits().view(np.uint32).copy(), ctx.output()]
+            n, v = _launched(ctx, lambda: ctx.verify(second))
+            assert n == (on and max(src) <= 128)
+            out += [v, ctx.debug_logits().view(np.uint32).copy(), ctx.output()]
             got[on] = out
         for x, y in zip(got[0], got[1]):
             if isinstance(x, np.ndarray):
@@ -72,15 +83,16 @@ def test_team_forwards_against_long_prefixes(n):
     try:
         ctx.set_option(ad.AD_OPT_TEAMS, 0)
         g = ctx.decode_greedy(src, max_out=[n - 8])[0][0]
-        if len(g) < n - 8:
-            pytest.skip("the greedy output ends earlier")
+        assert len(g) == n - 8   # (another model or source if it ends earlier)
         tail = list(_tokens(rng, 8))
         got = []
         for on in (0, 1):
             ctx.set_option(ad.AD_OPT_TEAMS, on)
             ctx.encode(ad.AD_VERIFIER, src)
             assert ctx.verify([g])[0][0] == n - 8
-            got.append((ctx.verify([tail], want_verified=True)[2], ctx.debug_logits().view(np.uint32).copy()))
+            launched, v = _launched(ctx, lambda: ctx.verify([tail], want_verified=True))
+            assert launched == (on and n <= 128)
+            got.append((v[2], ctx.debug_logits().view(np.uint32).copy()))
         assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
     finally:
         ctx.close()
@@ -101,7 +113,8 @@ def test_drafter_as_one_launch(lens, k):
                 ctx.encode(ad.AD_VERIFIER, srcs)
                 ctx.encode(ad.AD_DRAFTER, srcs)
                 for step in range(3):
-                    d = ctx.draft_nat(k).copy()
+                    launched, d = _launched(ctx, lambda: ctx.draft_nat(k).copy())
+                    assert launched == on or step > 0
                     out.append(d)
                     out.append(ctx.debug_logits().view(np.uint32).copy())
                     out += list(ctx.verify([list(row[:k]) for row in d]))
@@ -345,6 +358,7 @@ def test_two_contexts_in_two_threads():
             t.join()
         for i in range(2):
             assert got[i] == [ref[i]] * 4
+            assert ctxs[i].get_option(ad.AD_OPT_TEAM_LAUNCHES) > 0
     finally:
         for c in ctxs:
             c.close()
