@@ -385,7 +385,7 @@ static ad_ctx::TeamPart team_part(const TeamRun* t) {
   ad_ctx::TeamPart k{};
   if (!t) return k;
   int i = 0;
-  k[i++] = t->a.n_teams; k[i++] = t->max_rows > 32 ? 4 : t->max_rows > 16 ? 2 : 1; k[i++] = t->max_keys > 64 ? 2 : 1;
+  k[i++] = t->a.n_teams; k[i++] = t->max_rows > 16 ? 2 : 1; k[i++] = t->max_keys > 64 ? 2 : 1;
   for (int j = 1; j <= 8; ++j) { k[i++] = j <= t->a.n_teams ? t->a.row_lo[0][j] : 0; k[i++] = j <= t->a.n_teams ? t->a.prob[j] : 0; k[i++] = j <= t->a.n_teams ? t->a.prob[j - 1] : 0; }
   return k;
 }

@@ -784,13 +784,15 @@ static size_t team_lds_bytes(int mt) {
   const size_t rows = 16 * mt, b = (size_t)kSlices * rows * kTLd * 2 + rows * 16 * 4 + 3 * mt * 64 * 16 + rows * sizeof(TeamChunk) + 2 * rows * 4 + 64;
   return b > 84 * 1024 ? b : 84 * 1024;
 }
-// MT by the rows of the largest team, NKT by the keys of the longest problem
+// MT by the rows of the largest team, NKT by the keys of the longest problem (an encoder's keys are its team's rows)
+static_assert(kTeamMaxRows <= 64, "four key tiles hold an encoder's keys");
 template <typename F>
 static void each_team_kernel(bool dec, const F& f) {
-#define AD_TEAM(MT, NKT)                                                                     \
-  if (dec) f(MT, NKT, &k_team<MT, NKT, true>); else f(MT, NKT, &k_team<MT, NKT, false>);
-  AD_TEAM(1, 4) AD_TEAM(1, 8) AD_TEAM(2, 4) AD_TEAM(2, 8)
-#undef AD_TEAM
+  if (dec) {
+    f(1, 4, &k_team<1, 4, true>); f(1, 8, &k_team<1, 8, true>); f(2, 4, &k_team<2, 4, true>); f(2, 8, &k_team<2, 8, true>);
+  } else {
+    f(1, 4, &k_team<1, 4, false>); f(2, 4, &k_team<2, 4, false>);
+  }
 }
 bool prepare_team(bool decoder) {
   bool ok = true;
