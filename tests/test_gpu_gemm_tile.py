@@ -44,9 +44,9 @@ def test_rows_do_not_depend_on_the_tile_shape(name):
             assert np.array_equal(ctx.debug_logits().view(np.uint32), alone), rows
 
 
-# FFN widths whose last column tile is ragged in every shape (24.5 and 32.5 tiles of 64 columns, 12.25 and 16.25 of 128), and inner
-# dimensions and widths that only the tiled kernels' general rules cover; the rows of the batch select each tile shape in
-# turn (32 x 64, 64 x 64, 64 x 128 four and two stages ahead, the three rolling ones)
+# FFN widths whose last column tile is ragged in every shape that can have one (24.5 and 32.5 tiles of 64 columns, 12.25 and 16.25 of
+# 128; widths are multiples of 32), and inner dimensions and widths that only the tiled kernels' general rules cover; the rows of
+# the batch select each tile shape in turn (32 x 32, 32 x 64, 64 x 64, 64 x 128 four and two stages ahead, the three rolling ones)
 EDGES = {
     "d1024, ffn 1568": (dict(enc_layers=1, dec_layers=1, d_model=1024, n_heads=16, d_ffn=1568, vocab=2000),
                         [97, 129, 321, 641, 1217, 2177, 4417, 6402]),
