@@ -767,7 +767,12 @@ static bool run_as_graph(ad_ctx* c, hipStream_t stream, unsigned long long shape
     c->graphs_on = false;
     return false;
   }
-  if (++c->graph_seen[key] < 3 || c->graphs.size() >= 512) return false;   // worth building once a shape keeps coming back
+  if (c->graphs.size() >= 512) return false;
+  // (how two to four sequences' rows are dealt out to teams is part of a shape: a million of them in a long run, so that the counts of
+  // those that have not come back are dropped now and then)
+  constexpr size_t kShapesCounted = 8192;
+  if (c->graph_seen.size() >= kShapesCounted && !c->graph_seen.count(key)) c->graph_seen.clear();
+  if (++c->graph_seen[key] < 3) return false;   // worth building once a shape keeps coming back
   if (hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal) != hipSuccess) {
     (void)hipGetLastError();
     c->graphs_on = false;
