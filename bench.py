@@ -35,7 +35,8 @@ MFMA_BF16_PEAK = 2.5e15  # FLOP/s dense bf16, MI355X published
 # profiles/bench_base_bs1_vocab_kernel_hbm_traffic.md): a figure of an earlier counter run, quoted
 # under `vocab_kernel.traffic_from_profile`, not a reading of this run
 VOCAB_KERNEL_TRAFFIC_BYTES = int(16336.9 * 1024 * (262144.0 / 131083.0) + 482.7 * 1024)
-# HBM bytes of one verify forward of the base model at batch 1, 25 rows: the sum over its 45 launches of
+# HBM bytes of one verify forward of the base model at batch 1, 25 rows, with a launch per stage (no counter run
+# exists of the one whose layers are one launch): the sum over its 45 launches of
 # FETCH_SIZE (48909.7 KiB x 2.000) and WRITE_SIZE (3566.1 KiB x 1.000) per dispatch, two rocprofv3 --pmc
 # runs of `bench.py --profile-forward 1 25 --calibration-copy`
 # (profiles/verify_forward_base_bs1_25rows_hbm_traffic.md).  A figure of that counter run, not a reading
@@ -164,7 +165,11 @@ def main():
     j = int(np.argsort([len(s) for s in srcs])[n_sent // 2])
     ctx.encode(ad.AD_VERIFIER, [srcs[j]], max_out=[max_out[j]])
     draft = (list(guides[j]) + [ad.AD_NEVER])[:int(max_out[j])]
-    ctx.verify([draft])
+    def as_teams(call):   # whether the verify call's layers went out as one launch, and with them those of the timed forwards
+        before = ctx.get_option(ad.AD_OPT_TEAM_LAUNCHES)
+        call()
+        return ctx.get_option(ad.AD_OPT_TEAM_LAUNCHES) > before
+    teams = as_teams(lambda: ctx.verify([draft]))
     M1 = len(draft)
     params = decoder_stream_params(dims)
     kv_bytes = dims["dec_layers"] * 2 * 2 * dims["d_model"] * (M1 + len(srcs[j]))
@@ -178,17 +183,20 @@ def main():
     # output projection + arg max: the [V, d] bf16 matrix once, the M x d bf16 rows once, the
     # per-row partial maxima written once
     voc_bytes = 2 * V * dims["d_model"] + 2 * M1 * dims["d_model"] + 8 * M1 * ((V // 16 + 7) // 8)
-    n_launches = 3 + dims["dec_layers"] * 7   # embedding, seven per decoder layer, output projection, arg-max finish
+    # embedding, seven per decoder layer at this row count (or one for all of them), output projection, arg-max finish
+    n_launches = 4 if teams else 3 + dims["dec_layers"] * 7
+    how = {True: "the layers as one launch", False: "a launch per stage"}
     # The path's roofline: one verify forward (embedding, six decoder layers, output projection with
     # the fused arg max and its finish) at the first-iteration shape of a typical sentence.
     # achieved = algorithmic bytes (every decoder weight the forward streams, once, plus the key /
     # value rows read) over the forward's duration: HIP events on the library's stream around 50
     # forwards launched back to back, / 50.
-    roofline = {"bound": "hbm", "kernel": f"verify forward, base model, batch 1 ({n_launches} launches per forward)",
+    roofline = {"bound": "hbm", "kernel": f"verify forward, base model, batch 1 ({how[teams]})",
                 "rows": M1, "us": fwd_us, "algorithmic_bytes": fwd_bytes,
                 "achieved": fwd_bytes / (fwd_us * 1e-6) / 1e9, "peak": HBM_PEAK / 1e9, "unit": "GB/s",
-                "frac": fwd_bytes / (fwd_us * 1e-6) / HBM_PEAK, "traffic": VERIFY_FORWARD_TRAFFIC_BYTES,
-                "traffic_source": "rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of `bench.py --profile-forward 1 25 "
+                "frac": fwd_bytes / (fwd_us * 1e-6) / HBM_PEAK, "traffic": None if teams else VERIFY_FORWARD_TRAFFIC_BYTES,
+                "traffic_source": "no counter run of the layers as one launch" if teams else
+                                  "rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of `bench.py --profile-forward 1 25 "
                                   "--calibration-copy`, summed over the forward's launches (profiles/)"}
     # the largest single kernel of that forward (42 % of its algorithmic bytes), context only.
     # `frac` = the matrix streamed from HBM on every launch; the figure with the matrix resident in
@@ -233,7 +241,7 @@ def main():
         ss, mo = batches[0]
         ctx.encode(ad.AD_VERIFIER, ss, max_out=mo)
         drafts = [(list(g) + [ad.AD_NEVER])[:int(m)] for g, m in zip(gd2[0], mo)]
-        ctx.verify(drafts)
+        teams32 = as_teams(lambda: ctx.verify(drafts))
         M32 = sum(len(d) for d in drafts)
         fwd32_us, voc32_us = ctx.time_verify_forward(20)
         flops = 2.0 * M32 * params
@@ -247,7 +255,7 @@ def main():
                 "decode_mfma_frac": 2.0 * rows2 * params / dt2 / MFMA_BF16_PEAK,
                 "vocab_kernel_us": voc32_us,
                 "vocab_kernel_mfma_frac": 2.0 * M32 * V * dims["d_model"] / (voc32_us * 1e-6) / MFMA_BF16_PEAK}
-        roofline_bs32 = {"bound": "mfma", "kernel": f"verify forward, base model, batch 32 ({n_launches} launches per forward)",
+        roofline_bs32 = {"bound": "mfma", "kernel": f"verify forward, base model, batch 32 ({how[teams32]})",
                          "rows": M32, "us": fwd32_us, "algorithmic_flops": flops,
                          "achieved": flops / (fwd32_us * 1e-6) / 1e12, "peak": MFMA_BF16_PEAK / 1e12, "unit": "TFLOP/s",
                          "frac": flops / (fwd32_us * 1e-6) / MFMA_BF16_PEAK, "traffic": None}

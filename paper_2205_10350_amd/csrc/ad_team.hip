@@ -1,20 +1,22 @@
 // A whole stack of layers in one launch: the rows of a few sequences stay on one XCD.
 //
-// A forward of a few rows as a launch per stage is a chain of 35-45 launches of 3-8 us whose products take 0.1 us each:
+// A forward of a few rows as a launch per stage is a chain of 32-45 launches of 3-8 us whose products take 0.1 us each:
 // what they spend is the launch boundary (2.4 us), the trip of the rows from another XCD's writes and the fetch of
 // weights that could not be requested earlier.  Here the 32 compute units of an XCD form a team: one workgroup per CU,
-// resident for the whole stack, the stages separated by a barrier through that XCD's L2 (0.7 us; a stage's rows come
-// from the same L2, 0.14 us away), the strips of the next stage requested while the present one's rows are multiplied by
+// resident for the whole stack, the stages separated by a barrier through that XCD's L2 (0.85 us with the stores it waits for; a stage's
+// rows come from the same L2, 0.5-0.7 us until they are in LDS), the strips of the next stage requested while the present one's rows are multiplied by
 // other waves.  Sequences never share a row of an attention or a LayerNorm, so teams on different XCDs work on different
 // sequences and never talk to each other; with one sequence seven XCDs idle.
 //
-// What bounds it: one XCD streams the base model's decoder layers (44 MB) from the last-level cache in 34 us, of which about 30
-// stay exposed (a CU's vector memory returns in order: strips requested earlier are in the way of the rows); the trips of the
-// rows, 22-31 us; attention, 20-24; above 16 rows LayerNorm, which every member takes of every row.
-// Verify forward of the base model, us, this / a launch per stage: 1 sequence of 1, 4, 8, 16, 17, 25, 32 rows 148, 148, 151, 159, 176,
-// 184, 184 / 159, 171, 175, 179, 177, 181, 181 (the launches replayed as a graph; a call shape's first two appearances go out launch
-// by launch in 223, so that decodes with blocks of 25 rows gain 1-2 % all the same); 33 to 64 rows, four row tiles, 240 and more / 184-191: hence at most 32
-// rows; 8 sequences of 25 rows 200 / 224; 32 sequences of 1, 2, 4, 6, 8 rows 164, 166, 173, 190, 198 / 179, 185, 197, 223, 232.
+// What bounds it (clock stamps at every stage, base model, a layer of 22 / 24 / 30 us at 1 / 16 / 25 rows): the meetings, 11.7 us a layer at one
+// row where seven barriers alone would take 5.9, the rest the other group's strips on their way, behind which stores and polls return
+// (35 us a forward; one XCD streams the layers' 44 MB from the last-level cache in 34 us); the rows' trips into LDS, 3.6 / 4.1 / 6.7 us
+// a layer, above 16 rows with the LayerNorm that every member takes of every row; the two attentions, 4.1 / 5.0 / 5.0.
+// Verify forward of the base model, us, this / a launch per stage, on two machines: 1 sequence of 1, 4, 8, 16, 17, 25, 32 rows 139, 143, 144, 150, 167,
+// 177, 177 / 159-172, 172, 175, 180, 178, 181, 183; on others 148-151 at one row and 184-192 at 25, where the launches stay at 181 (one XCD's pace
+// differs by machine, and this waits for it alone).  (The launches replayed as a graph; a call shape's first two appearances go out launch
+// by launch in 223.)  33 to 64 rows, four row tiles, 240 and more / 184-191: hence at most 32
+// rows; 8 sequences of 25 rows 207 / 222; 32 sequences of 1, 2, 4, 6, 8 rows 164, 166, 176, 196, 206 / 177, 182, 195, 221, 231.
 //
 // Stages of a layer: QKV | self-attention | output projection | cross-attention with its query projection | output
 // projection | FFN1 | FFN2 (the encoder without the middle two).  Members of a team split the columns of a product
