@@ -391,27 +391,36 @@ static void launch_roll(const bf16_t* A, const bf16_t* W, int M, int N, int K, c
   });
 }
 
-// Which layer GEMMs come here rather than to the kernels that keep all of K of their rows in LDS (measured, us there / here; a
-// pending LayerNorm, 2.5-3 us as a launch of its own, is inside both figures):
-//  K = 1024, LayerNorm pending: 64 / 80 / 130 / 250 / 626 rows x N 3072 6.1 / 6.4 / 8.5 / 11.5 / 15.9 there, 6.7 / 6.8 / 6.9 / 8.1 /
-//    10.8 here, x N 4096 6.2 / 8.1 / 10.6 / 11.5 / 20.5 there, 6.4 / 6.5 / 7.9 / 8.1 / 14.7 here; N 12288 (memory keys and values) 25
-//    rows 8.4 / 6.5, 626 rows 38.8 / 25, 3252 rows 221 / 100
-//  K = 1024, none: N 1024 80 / 130 / 626 / 3252 rows 3.4 / 4.7 / 6.4 / 26.1 there, 3.8 / 4.0 / 5.4 / 16.5 here; N 512 and 768
-//    130 / 160 / 161 rows 3.7 / 3.7 / 4.6 and 3.9 / 4.0 / 6.3 there, 4.0 / 4.1 / 4.1 and 4.2 / 4.2 / 4.1 here
-//  K = 4096: beyond the two rounds of one workgroup per CU that k_gemm_bf16_kchain makes (its comment); N 1024 130 / 626 / 3252 rows
-//    12.7 / 22.2 / 80 there, 8.2 / 14.6 / 43 here (matrix from the last-level cache; from memory 160 rows 15.3 / 13.6)
-//  K = 512, LayerNorm pending: below 1408 columns never (N 512 2048 rows 8.7 / 9.9, N 1024 1345 / 2048 / 4000 rows 8.7 / 9.4 / 15.7
-//    there, 10.5 / 12.0 / 17.9 here, N 1280 2048 / 3000 rows 12.0 / 17.3 there, 13.5 / 16.3 here); below 2048 from 1400 rows (N 1408
-//    1345 / 1400 rows 9.9 / 12.4 there, 10.7 / 10.8 here, N 1536 1345 / 1400 / 2048 rows 11.3 / 13.5 / 15.0 there, 11.9 / 12.0 / 14.1
-//    here); below 3072 from 600 rows where the 16-wave workgroups need a second round (N 2048 800 / 1120 rows 8.5 / 11.8 there and
-//    8.6 / 10.2 here, N 2080 567 / 620 / 900 rows 7.6 / 9.6 / 10.0 there, 8.6 / 8.7 / 9.5 here); below 4096 from 513 rows
-//    (N 3072 512 / 519 / 673 / 1024 rows 8.4 / 11.2 / 11.4 / 12.6 there, 8.8 / 8.9 / 10.4 / 12.0 here); N 4096 160 / 256 / 300 rows 6.1 /
-//    6.5 / 8.5 there with the ReLU, whose epilogue is a constant there, 6.7 / 7.0 / 8.5 here, 211 rows of keys and values 7.4 / 7.0; N 6144 128 / 160 / 200 / 1120 rows 7.0 / 7.7 / 10.2 / 30.3 there, 7.1 / 8.4 / 8.4 / 17.8 here
-//  K = 512, none: 400 / 576 / 1120 rows 2.8 / 3.9 / 4.2 there, 3.2 / 3.0 / 4.1 here
-//  K = 2048: N 512 400 / 576 / 1120 rows 5.6 / 8.1 / 8.7 there, 5.4 / 5.4 / 8.8 here, 1365 / 1800 / 2048 rows 9.8 / 11.0 / 12.3 there,
-//    10.2 / 11.8 / 12.9 here: beyond 1024 rows the eight-wave workgroups while they make one round; past it N 1024 1025 / 2048 rows
-//    20.1 / 20.8 there, 12.9 / 16.0 here, N 2048 1365 rows 29.9 / 21.8
-//  K = 1536: the same from 1600 rows, N 512 1300 / 1800 / 2048 / 2049 rows 9.3 / 9.6 / 10.0 / 13.9 there, 7.9 / 10.3 / 11.1 / 12.8 here
+// Which layer GEMMs come here rather than to the kernels that keep all of K of their rows in LDS.  Measured, us there / here, launches back
+// to back with their operands in the last-level cache; a pending LayerNorm, 2.5-3 us as a launch of its own, is inside both figures:
+//  K = 1024, LayerNorm pending: 64 / 80 / 96 / 97 / 130 / 250 / 626 rows x N 3072 4.9 / 5.1 / 6.9 / 6.8 / 7.1 / 9.7 / 21.2 there, 6.2 / 6.5 / 6.5 /
+//    6.6 / 6.7 / 8.3 / 10.5 here; 64 / 65 / 130 / 250 / 626 rows x N 4096 4.7 / 6.3 / 8.3 / 12.2 / 26.2 there, 5.7 / 6.1 / 7.5 / 7.8 / 13.3
+//    here; N 12288 (memory keys and values) 16 / 17 / 25 / 626 / 3249 rows 5.4 / 7.2 / 7.6 / 77 / 366 there, 6.0 / 6.0 / 6.1 / 23 / 84 here
+//  K = 1024, none: N 1024 80 / 128 / 129 / 626 / 3249 rows 3.0 / 3.1 / 4.2 / 7.6 / 25.9 there, 3.4 / 3.3 / 3.3 / 5.3 / 14.7 here; N 512 and 768
+//    128 / 160 / 161 rows 2.6 / 2.9 / 4.0 and 3.0 / 3.1 / 5.4 there, 3.3 / 3.3 / 3.3 and 3.4 / 3.4 / 3.4 here
+//  K = 4096: beyond the two rounds of one workgroup per CU that k_gemm_bf16_kchain makes (its comment); N 1024 64 / 65 / 80 / 128 / 129 / 626 /
+//    3249 rows 5.5 / 7.1 / 7.8 / 8.0 / 11.9 / 21.1 / 73.8 there, 7.1 / 7.2 / 7.2 / 7.1 / 7.2 / 13.4 / 39.9 here.  (So the second round no longer
+//    pays with the matrix in the last-level cache: 8-11 % from 80 to 128 rows; the line stands as measured in a forward, where the matrix
+//    comes from memory: 160 rows 15.3 / 13.6)
+//  K = 512, LayerNorm pending: below 1408 columns never (N 512 520 / 2048 / 4000 rows 5.2 / 8.1 / 10.3 there, 5.6 / 9.3 / 12.5 here, N 1024 520 /
+//    1345 / 2048 / 4000 rows 7.0 / 8.0 / 8.9 / 15.0 there, 6.4 / 8.8 / 10.5 / 16.1 here, N 1280 520 / 2048 / 3000 / 4000 rows 6.7 / 10.8 / 16.1 /
+//    17.9 there, 6.5 / 11.6 / 14.5 / 19.0 here); below 2048 from 1400 rows (N 1408 1120 / 1345 / 1400 rows 8.8 / 9.1 / 11.9 there, 8.4 /
+//    9.0 / 9.1 here, N 1536 1280 / 1345 / 1400 / 2048 rows 7.6 / 10.3 / 13.0 / 14.3 there, 8.9 / 9.9 / 10.1 / 11.8 here); below 3072 from 600
+//    rows where the 16-wave workgroups need a second round (N 2048 512 / 600 / 800 / 1024 / 1025 / 1120 rows 6.7 / 7.7 / 8.0 / 8.8 / 10.8 / 10.9
+//    there, 6.7 / 7.4 / 7.8 / 8.4 / 9.4 / 9.7 here, N 2080 567 / 599 / 620 / 900 rows 6.5 / 8.7 / 8.8 / 9.3 there, 7.4 / 7.5 / 7.5 / 8.1 here, N 2560
+//    400 / 600 / 800 / 801 rows 6.8 / 12.6 / 13.2 / 10.6 there, 7.1 / 7.7 / 9.1 / 9.0 here); below 4096 from 513 rows (N 3072 256 / 400 / 512 / 513 /
+//    1024 rows 5.8 / 7.4 / 7.8 / 10.1 / 12.4 there, 6.4 / 7.2 / 7.4 / 7.4 / 9.8 here); N 4096 160 / 256 / 257 / 300 rows 5.7 / 6.2 / 8.0 / 8.3 there
+//    with the ReLU, whose epilogue is a constant there, 6.2 / 6.4 / 7.1 / 7.2 here, 130 / 161 / 211 rows of keys and values 6.7 / 6.9 / 7.1 there,
+//    6.3 / 6.4 / 6.5 here; N 6144 96 / 128 / 160 / 161 / 1120 rows 6.7 / 6.9 / 7.0 / 9.6 / 28.0 there, 6.3 / 6.4 / 6.9 / 6.9 / 16.7 here
+//  K = 512, none: N 512 400 / 519 / 576 / 1120 rows 2.6 / 3.2 / 3.2 / 5.1 there, 2.8 / 2.9 / 2.9 / 4.0 here, N 1536 256 / 400 / 520 / 1120 rows 3.4 /
+//    4.7 / 6.1 / 8.3 there, 3.3 / 4.3 / 4.4 / 5.1 here
+//  K = 2048: N 512 192 / 400 / 519 / 576 / 1024 rows 5.2 / 5.3 / 6.9 / 7.8 / 8.0 there, 4.6 / 4.7 / 4.9 / 4.9 / 7.2 here, 1025 / 1365 / 2048 / 2049
+//    rows 8.0 / 8.7 / 11.4 / 17.2 there, 8.5 / 9.8 / 12.5 / 11.8 here: beyond 1024 rows the eight-wave workgroups while they make one round;
+//    past it N 1024 1025 / 2048 rows 19.4 / 19.4 there, 11.8 / 14.6 here, N 2048 1365 rows 28.3 / 19.7.  (Below 520 rows the line was drawn
+//    before the 32 x 32 tiles: N 1024 192 / 400 rows 5.3 / 7.1 there, 4.6 / 5.0 here, N 2048 192 / 400 rows 7.1 / 11.4 and 4.9 / 7.8)
+//  K = 1536: the same from 1600 rows, N 512 1300 / 1600 / 1800 / 2048 / 2049 rows 8.5 / 8.6 / 8.9 / 9.4 / 12.7 there, 7.4 / 9.2 / 9.8 / 10.7 / 9.6 here;
+//    N 512 / 1024 / 1536 128 rows 4.6 / 4.7 / 4.8 there, 3.9 / 4.0 / 4.1 here
+// Where "here" is ahead on the near side of a line, the line is as it was drawn with tile_apply's stores.
 bool gemm_tile_takes(int M, int N, int K, bool has_ln, int mode) {
   if (K % 512 || K < 512 || mode == EPI_ARGMAX || mode == EPI_COUNT) return false;
   if (K == 512 && has_ln) {
@@ -438,7 +447,7 @@ bool gemm_tile_takes(int M, int N, int K, bool has_ln, int mode) {
 // 128 x 128 rolling: two workgroups per CU; up to 640 of them a second round is nearly empty and the 64 x 128 rolling shape
 // wins: K = 512, N 3072 x 3000 rows (w(128, 128) 576) 28.5 / 26.2 us, K = 1536, N 6144 x 1300 (528) 54.0 / 44.0; but K = 2048,
 // N 2048 x 4096 (512) 45.1 / 49.7, K = 1024, N 3072 x 3531 (672) 40.8 / 43.1.
-// (These figures, and those above gemm_tile_takes, are of all kernels with tile_apply's stores.)  With tile_finish at K = 1024 (64 x 128
+// (These figures are of all kernels with tile_apply's stores.)  With tile_finish at K = 1024 (64 x 128
 // two stages ahead / 64 x 128 rolling / 128 x 128 / 128 x 256): N 3072 x 626 rows (w 240) 7.3 / 8.4 / 10.9 / 15.9 us (four stages
 // 7.1), x 2000 (768) 18.6 / 19.0 / 19.7 / 21.0, x 3249 (1224) 29.1 / 29.4 / 30.4 / 29.6; N 4096 x 2000 (1024) 24.2 / 24.0 / 21.6 /
 // 23.2, x 3249 (1632) 39.1 / 39.3 / 38.1 / 32.1 (850 TFLOP/s); N 12288 x 3249 107 / 109 / 100 / 81 (1010 TFLOP/s).
