@@ -238,7 +238,8 @@ struct ad_ctx {
   bool can_team[2][2] = {{false, false}, {false, false}};   // [model][encoder, decoder]
   bool team_on = true;
   int team_ticks = kTeamFormTicks;
-  int team_rest = 0, team_failures = 0, team_launches = 0;
+  int team_rest = 0, team_failures = 0;
+  unsigned team_launches = 0;
   int team_backoff = 0, team_held = 0;   // the next rest is 32 << team_backoff; results in a row since it changed whose teams came together
   bool last_team = false;
   TeamRun last_run{};
@@ -1529,7 +1530,7 @@ int ad_get_option(ad_ctx* c, int option, int* value) {
   else if (option == AD_OPT_TEAMS) *value = c->team_on ? 1 : 0;
   else if (option == AD_OPT_TEAM_FAILURES) *value = c->team_failures;
   else if (option == AD_OPT_TEAM_WAIT) *value = c->team_ticks;
-  else if (option == AD_OPT_TEAM_LAUNCHES) *value = c->team_launches;
+  else if (option == AD_OPT_TEAM_LAUNCHES) *value = (int)(c->team_launches & 0x7fffffffu);
   else if (option == AD_OPT_OVERLAP_ENCODERS) *value = c->overlap_encoders ? 1 : 0;
   else return fail(c, AD_EINVAL, "unknown option");
   return AD_OK;
