@@ -47,7 +47,7 @@ struct Plan {
   // drafter a second block of the same layout lies act2_shift bytes further on, for the drafter's
   // encoder running beside the verifier's on a stream of its own
   size_t act_begin = 0, act_end = 0, act2_shift = 0;
-  size_t pe, x, s, xa, q, att, tk, tv, f, part_val, part_idx, o_hat, o_val, logits, draft_lp, draft_col;
+  size_t pe, x, s, xa, q, att, tk, tv, f, team_s1, team_s2, team_xr, team_att2, part_val, part_idx, o_hat, o_val, logits, draft_lp, draft_col;
   size_t cache_k, cache_v, cache_layer_stride;          // [NL][B*l_cap, d]
   size_t mem_k[2], mem_v[2], mem_layer_stride;          // per model: [NL][B*max_src, d]
   size_t row_tok, row_pos, row_seq, row_dst, row_dst2, row_start, self_desc, cross_desc;
@@ -78,6 +78,12 @@ static Plan make_plan(const ad_config& c, bool with_drafter) {
   p.tk = take(m * d * p.esz);
   p.tv = take(m * d * p.esz);
   p.f = take(m * (size_t)c.d_ffn * p.esz);
+  // rows inside a layer of a team launch
+  const size_t tm = c.dtype == AD_BF16 && d == kTeamD ? std::min(m, (size_t)kTeamXRows) : 0;
+  p.team_s1 = take(tm * d * 4);
+  p.team_s2 = take(tm * d * 4);
+  p.team_xr = take(tm * d * 4);
+  p.team_att2 = take(tm * d * 2);
   p.row_tok = take(m * 4); p.row_pos = take(m * 4); p.row_seq = take(m * 4); p.row_dst = take(m * 4); p.row_dst2 = take(m * 4);
   p.row_start = take((B + 1) * 4);
   p.self_desc = take(2 * B * sizeof(SeqDesc));    // the drafter has two per sequence (mask rows, prefix rows)
@@ -373,6 +379,7 @@ static void team_common(const ad_ctx* c, int model, bool dec, int words, TeamRun
   a.form_ticks = (unsigned)c->team_ticks;
   a.w = (const char*)(dec ? c->w[model].dec[0].self.wqkv : c->w[model].enc[0].self.wqkv);
   a.x = c->at<float>(p.x); a.s = c->at<float>(p.s);
+  a.s1 = c->at<float>(p.team_s1); a.s2 = c->at<float>(p.team_s2); a.xr = c->at<float>(p.team_xr); a.att2 = c->at<bf16_storage>(p.team_att2);
   a.xa = c->at<bf16_storage>(p.xa); a.q = c->at<bf16_storage>(p.q); a.att = c->at<bf16_storage>(p.att); a.f = c->at<bf16_storage>(p.f);
   a.K = c->at<bf16_storage>(p.tk); a.V = c->at<bf16_storage>(p.tv); a.kv_stride = 0;
   a.Km = dec ? (const bf16_storage*)(c->ws + p.mem_k[model]) : nullptr;

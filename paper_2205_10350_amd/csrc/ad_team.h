@@ -10,6 +10,7 @@ typedef unsigned short bf16_storage;
 constexpr int kTeamMembers = 32;                 // workgroups of a team: the compute units of an XCD
 constexpr int kTeamD = 512, kTeamF = 2048;       // the model widths the kernel is built for (bf16, head width 64)
 constexpr int kTeamMaxRows = 32, kTeamMaxKeys = 128;
+constexpr int kTeamXRows = 8 * kTeamMaxRows;     // packed rows of a launch
 constexpr int kTeamFormTicks = 30000;            // 0.3 ms: an idle chip has a team together in a few us
 
 // Byte offsets of a layer's entries from its first byte (weight_layout; the launcher's caller checks them).
@@ -34,8 +35,12 @@ struct TeamArgs {
   unsigned form_ticks;                // how long the first barrier is waited for (10 ns each; 0: not at all)
   float scale;
   const char* w;                      // layer 0 (the others TeamOff::kLayerBytes apart)
-  float *x, *s;
-  bf16_storage *xa, *q, *att, *f;
+  const float* x;                     // the embedded rows, fp32 and bf16
+  const bf16_storage* xa;
+  float* s;                           // rows passed on inside a layer; in s the last layer's for the LayerNorm that follows
+  float *s1, *s2, *xr;                // (kTeamXRows packed rows)
+  bf16_storage* att2;
+  bf16_storage *q, *att, *f;
   bf16_storage *K, *V;                // keys / values of layer 0
   size_t kv_stride;                   // bytes to the next layer's
   const bf16_storage *Km, *Vm;        // memory keys / values

@@ -3,20 +3,21 @@
 // A forward of a few rows as a launch per stage is a chain of 32-45 launches of 3-8 us whose products take 0.1 us each:
 // what they spend is the launch boundary (2.4 us), the trip of the rows from another XCD's writes and the fetch of
 // weights that could not be requested earlier.  Here the 32 compute units of an XCD form a team: one workgroup per CU,
-// resident for the whole stack, the stages separated by a barrier through that XCD's L2 (0.85 us with the stores it waits for; a stage's
-// rows come from the same L2, 0.5-0.7 us until they are in LDS), the strips of the next stage requested while the present one's rows are multiplied by
-// other waves.  Sequences never share a row of an attention or a LayerNorm, so teams on different XCDs work on different
+// resident for the whole stack, the strips of the next stages requested while the present one's results are on their way.
+// Rows pass from stage to stage through the XCD's L2 without a barrier: whoever needs a row reads it until it is there (0.45 us from
+// a store to the row in the reader's LDS where nothing else is queued; a barrier over the team with the trip behind it took 1.4).
+// Sequences never share a row of an attention or a LayerNorm, so teams on different XCDs work on different
 // sequences and never talk to each other; with one sequence seven XCDs idle.
 //
-// What bounds it (clock stamps at every stage, base model, a layer of 22 / 24 / 30 us at 1 / 16 / 25 rows): the meetings, 11.7 us a layer at one
-// row where seven barriers alone would take 5.9, the rest the other group's strips on their way, behind which stores and polls return
-// (35 us a forward; one XCD streams the layers' 44 MB from the last-level cache in 34 us); the rows' trips into LDS, 3.6 / 4.1 / 6.7 us
-// a layer, above 16 rows with the LayerNorm that every member takes of every row; the two attentions, 4.1 / 5.0 / 5.0.
-// Verify forward of the base model, us, this / a launch per stage, on two machines: 1 sequence of 1, 4, 8, 16, 17, 25, 32 rows 139, 143, 144, 150, 167,
-// 177, 177 / 159-172, 172, 175, 180, 178, 181, 183; on others 148-151 at one row and 184-192 at 25, where the launches stay at 181 (one XCD's pace
-// differs by machine, and this waits for it alone).  (The launches replayed as a graph; a call shape's first two appearances go out launch
-// by launch in 223.)  33 to 64 rows, four row tiles, 240 and more / 184-191: hence at most 32
-// rows; 8 sequences of 25 rows 207 / 222; 32 sequences of 1, 2, 4, 6, 8 rows 164, 166, 176, 196, 206 / 177, 182, 195, 221, 231.
+// What bounds it (clock stamps at every workgroup barrier, base model, a layer of 14 / 17 / 26 us at 1 / 8 / 25 rows): products 2.9 us a layer
+// (FFN2's chain through four slices 1.2, the others 0.25-0.35 each), exchanges 0.45 us where no strips are queued and up to 1.5
+// behind them (one XCD streams a layer's 7.3 MB from the last-level cache in 5.7 us), the two attentions 2.9; above 16 rows the rows'
+// trips, 50 KB a member and stage, and the LayerNorm that every member takes of every row.
+// Verify forward of the base model, us, with barriers between the stages / this way, one machine: 1 sequence of 1, 4, 8, 16, 17, 25, 32 rows
+// 139, 143, 144, 150, 167, 178, 178 / 88, 101, 104, 116, 145, 156, 159; 8 sequences of 25 rows 207 / 171; 32 sequences of 1, 2, 4, 6, 8 rows
+// 164, 166, 176, 196, 206 / 117, 121, 136, 168, 180.  A launch per stage: 159-172, 172, 175, 180, 178, 181, 183; 222; 177, 182, 195, 221, 231
+// (the launches replayed as a graph; a call shape's first two appearances go out launch by launch in 223).  33 to 64 rows, four row
+// tiles, were 240 and more / 184-191 with barriers: hence at most 32 rows.
 //
 // Stages of a layer: QKV | self-attention | output projection | cross-attention with its query projection | output
 // projection | FFN1 | FFN2 (the encoder without the middle two).  Members of a team split the columns of a product
@@ -27,7 +28,7 @@
 // serves it.
 //
 // Exchanged rows are read with loads that miss the vector cache (sc1): a CU's L1 may hold the row of an earlier layer.
-// Waiting is bounded everywhere: a team that is not complete within form_ticks, or a barrier that takes kWaitTicks,
+// Waiting is bounded everywhere: a team that is not complete within form_ticks, or a row that takes kWaitTicks,
 // sets the fail word, the remaining waits return at once, and the caller runs the launches instead.
 #include <hip/hip_runtime.h>
 
@@ -66,32 +67,57 @@ __device__ __forceinline__ void wg_bar() {
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 }
-struct TeamSync {
-  unsigned* count;
-  unsigned* fail;
-  unsigned target;
-  unsigned long long limit;
+// A row goes from the CU that computes it to those that multiply it without a barrier: its place is set to all ones ahead of time,
+// nothing computed is stored as that, and whoever needs the row reads it until no piece of it is all ones.  (All ones is one of
+// the NaNs; a NaN with these bits is stored as its neighbour.)  Who sets a place back, and when: its writer, no later than the
+// store of an earlier exchange that every reader of the place has seen whole, and after an exchange that every reader of its former
+// content had to pass; the stores are answered for before the writer's next data leave (team_put_ready).
+__device__ __forceinline__ void unwrite16(void* base, unsigned off) { gstore((uint4*)((char*)base + off), uint4{~0u, ~0u, ~0u, ~0u}); }
+__device__ __forceinline__ unsigned written(float v) { return min(__float_as_uint(v), 0xfffffffeu); }
+__device__ __forceinline__ void put(float* p, float v) { gstore((unsigned*)p, written(v)); }
+__device__ __forceinline__ void put(bf16_t* p, float v) { gstore(p, (bf16_t)min((unsigned)f2bf(v), 0xfffeu)); }
+__device__ __forceinline__ void team_put_ready() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// has this wave seen a piece that is not written yet?  (fp32 words / bf16 halves)
+struct Seen32 {
+  unsigned m = 0;
+  __device__ __forceinline__ void add(const uint4& v) { m = max(max(m, v.x), max(max(v.y, v.z), v.w)); }
+  __device__ __forceinline__ bool all() const { return __builtin_amdgcn_ballot_w64(m == ~0u) == 0; }
 };
-// A stage ends: the group that computed waits for its stores (they are in the L2 then); every wave passes; one wave of
-// that group says so to the team and watches for the other members; every wave passes again.
-// (The watching wave must have no requests of its own in flight: they would return before its polls do.)
-__device__ __forceinline__ void team_end(TeamSync& ts, bool computed, bool watch, int lane) {
-  if (computed) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  wg_bar();
-  ts.target += kTeamMembers;
-  if (watch && lane == 0) (void)__hip_atomic_fetch_add(ts.count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void team_begin(TeamSync& ts, bool watch, int lane) {
-  if (watch) {
-    if (lane == 0) {
-      const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
-      for (unsigned spin = 0; ts.limit && __hip_atomic_load(ts.count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < ts.target; ++spin)
-        if ((spin & 15) == 15 && __builtin_amdgcn_s_memrealtime() - t0 >= ts.limit) ts.limit = 0;
-      if (ts.limit) ts.limit = kWaitTicks;
-      else __hip_atomic_store(ts.fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+struct Seen16 {
+  typedef unsigned short half2 __attribute__((ext_vector_type(2)));
+  half2 m = {0, 0};
+  __device__ __forceinline__ void add(const uint4& v, bool counts = true) {
+    half2 x = __builtin_elementwise_max(__builtin_elementwise_max(__builtin_bit_cast(half2, v.x), __builtin_bit_cast(half2, v.y)),
+                                        __builtin_elementwise_max(__builtin_bit_cast(half2, v.z), __builtin_bit_cast(half2, v.w)));
+    m = __builtin_elementwise_max(m, counts ? x : half2{0, 0});
+  }
+  __device__ __forceinline__ bool all() const { return __builtin_amdgcn_ballot_w64(m.x == 0xffff || m.y == 0xffff) == 0; }
+};
+struct TeamWait {
+  unsigned *fail, *gave_up;   // the launch's fail word; this workgroup's (LDS)
+  bool off;                   // wait no more
+};
+// attempt(): loads, and whether everything was there
+template <typename F>
+__device__ __forceinline__ void wait_for(TeamWait& tw, int lane, const F& attempt) {
+  unsigned long long t0 = 0;
+#pragma unroll 1
+  for (unsigned spin = 0;; ++spin) {
+    asm volatile("" ::: "memory");
+    if (attempt() || tw.off) return;
+    if ((spin & 15) == 0) {
+      const unsigned long long now = __builtin_amdgcn_s_memrealtime();
+      if (spin == 0) t0 = now;
+      else if (now - t0 >= kWaitTicks || __builtin_amdgcn_readfirstlane(__hip_atomic_load(tw.gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))) {
+        tw.off = true;
+        if (lane == 0) {
+          __hip_atomic_store(tw.gave_up, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          __hip_atomic_store(tw.fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        return;
+      }
     }
   }
-  wg_bar();
 }
 // a value the compiler cannot see through: what is computed from it is computed where it is used, not kept in registers
 // over the whole stack of layers
@@ -139,29 +165,43 @@ __device__ __forceinline__ void zero(f32x4 (&acc)[T]) {
 #pragma unroll
   for (int t = 0; t < T; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 }
-__device__ __forceinline__ void load_ln(const float* g, const float* b, int lane, float4 (&gv)[2], float4 (&bv)[2]) {
+// A LayerNorm's gains and biases go through LDS, [2][512]: a wave of group B brings a quarter (every wave bringing all of them for its
+// own rows was a quarter of all a CU requested)
+__device__ __forceinline__ uint4 load_ln(const float* g, const float* b, int gw, int lane) {
+  return ldg16((gw < 2 ? g : b) + 256 * (gw & 1) + 4 * lane);
+}
+__device__ __forceinline__ void keep_ln(float* lnv, const uint4& v, int gw, int lane) { *(uint4*)(lnv + 256 * gw + 4 * lane) = v; }
+// Rows row0, row0 + step, .. (NR of them; local indices, clamped to `last`) through LayerNorm into the same rows of At;
+// xres (nullable): the fp32 values of this member's 16 columns, the residual of its later strip; xr (nullable): those of head h's
+// 64 columns, for the others.
+template <int NR>
+__device__ __forceinline__ void stage_ln_rows(TeamWait& tw, const float* s, const int* grow, int row0, int step, int last, const float* lnv,
+                                              bf16_t* At, float* xres, int idx, float* xr, int h, int lane) {
+  if (row0 > last) return;
+  float4 xv[NR][2], gv[2], bv[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    gv[j] = gload((const float4*)(g + 4 * lane + 256 * j));
-    bv[j] = gload((const float4*)(b + 4 * lane + 256 * j));
+    gv[j] = *(const float4*)(lnv + 4 * lane + 256 * j);
+    bv[j] = *(const float4*)(lnv + kTD + 4 * lane + 256 * j);
   }
-}
-// Rows row0, row0 + step, .. (NR of them; local indices, clamped to `last`) through LayerNorm into the same rows of At;
-// xres (nullable): the fp32 values of this member's 16 columns, the residual of its later strip; y (nullable): the fp32 rows in memory.
-template <int NR>
-__device__ __forceinline__ void stage_ln_rows(const float* s, const int* grow, int row0, int step, int last, const float4 (&gv)[2],
-                                              const float4 (&bv)[2], bf16_t* At, float* xres, int idx, float* y, int lane) {
-  float4 xv[NR][2];
   int g[NR];
 #pragma unroll
   for (int i = 0; i < NR; ++i) g[i] = __builtin_amdgcn_readfirstlane(grow[min(row0 + step * i, last)]);
-#pragma unroll
-  for (int i = 0; i < NR; ++i)
+  auto load = [&](int i, Seen32& seen) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const uint4 u = ld16_l2(s, (unsigned)g[i] * (kTD * 4) + 16 * lane + 1024 * j);
       xv[i][j] = float4{__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w)};
+      seen.add(u);
     }
+  };
+  if (NR > 2) wait_for(tw, lane, [&]() { Seen32 seen; load(NR - 1, seen); return seen.all(); });   // (the others are there about then)
+  wait_for(tw, lane, [&]() {
+    Seen32 seen;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) load(i, seen);
+    return seen.all();
+  });
   float mean[NR], rstd[NR];
 #pragma unroll
   for (int i = 0; i < NR; ++i) ln_stats4<2>(xv[i], kTD, mean[i], rstd[i]);
@@ -175,49 +215,75 @@ __device__ __forceinline__ void stage_ln_rows(const float* s, const int* grow, i
       *(uint2*)(At + (row0 + step * i) * kTLd + 4 * lane + 256 * j) = uint2{f2bf_pair(o.x, o.y), f2bf_pair(o.z, o.w)};
     }
   if (xres && (lane >> 2) == (idx & 15)) {
-    float* xr = xres + row0 * 16 + 4 * (lane & 3);
+    float* xp = xres + row0 * 16 + 4 * (lane & 3);
     if (idx < 16) {
 #pragma unroll
-      for (int i = 0; i < NR; ++i) *(float4*)(xr + step * i * 16) = xv[i][0];
+      for (int i = 0; i < NR; ++i) *(float4*)(xp + step * i * 16) = xv[i][0];
     } else {
 #pragma unroll
-      for (int i = 0; i < NR; ++i) *(float4*)(xr + step * i * 16) = xv[i][1];
+      for (int i = 0; i < NR; ++i) *(float4*)(xp + step * i * 16) = xv[i][1];
     }
   }
-  if (y) {
+  if (xr && (lane >> 4) == (h & 3)) {
 #pragma unroll
     for (int i = 0; i < NR; ++i)
       if (row0 + step * i <= last) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j) gstore((float4*)(y + (size_t)g[i] * kTD + 4 * lane + 256 * j), xv[i][j]);
+        const float4 o = h < 4 ? xv[i][0] : xv[i][1];
+        gstore((uint4*)(xr + (size_t)g[i] * kTD + (h >> 2) * 256 + 4 * lane), uint4{written(o.x), written(o.y), written(o.z), written(o.w)});
       }
   }
 }
 // all rows of the team: wave w takes rows w, w + 8, ..; the last round of eight is left out where none of its rows exists
 // (a row costs a wave 0.15 us of vector instructions, and every member normalises every row)
 template <int NR>
-__device__ __forceinline__ void stage_ln(const float* s, const int* grow, int n, const float4 (&gv)[2], const float4 (&bv)[2],
+__device__ __forceinline__ void stage_ln(TeamWait& tw, const float* s, const int* grow, int n, const float* lnv,
                                          bf16_t* At, float* xres, int idx, int wave, int lane) {
-  if (n > kTW * (NR - 1)) stage_ln_rows<NR>(s, grow, wave, kTW, n - 1, gv, bv, At, xres, idx, nullptr, lane);
-  else stage_ln_rows<NR - 1>(s, grow, wave, kTW, n - 1, gv, bv, At, xres, idx, nullptr, lane);
+  if (n > kTW * (NR - 1)) stage_ln_rows<NR>(tw, s, grow, wave, kTW, n - 1, lnv, At, xres, idx, nullptr, 0, lane);
+  else stage_ln_rows<NR - 1>(tw, s, grow, wave, kTW, n - 1, lnv, At, xres, idx, nullptr, 0, lane);
 }
 // the up to 16 rows of a chunk
-__device__ __forceinline__ void stage_ln_chunk(const float* s, const int* grow, int n, const float4 (&gv)[2], const float4 (&bv)[2],
-                                               bf16_t* At, float* y, int wave, int lane) {
-  if (n > kTW) stage_ln_rows<2>(s, grow, wave, kTW, n - 1, gv, bv, At, nullptr, 0, y, lane);
-  else stage_ln_rows<1>(s, grow, wave, kTW, n - 1, gv, bv, At, nullptr, 0, y, lane);
+__device__ __forceinline__ void stage_ln_chunk(TeamWait& tw, const float* s, const int* grow, int n, const float* lnv,
+                                               bf16_t* At, float* xr, int h, int wave, int lane) {
+  if (n > kTW) stage_ln_rows<2>(tw, s, grow, wave, kTW, n - 1, lnv, At, nullptr, 0, xr, h, lane);
+  else stage_ln_rows<1>(tw, s, grow, wave, kTW, n - 1, lnv, At, nullptr, 0, xr, h, lane);
 }
-// NR rows of bf16 rows src [*, 512] into At
+// 1 KB pieces of NR bf16 rows, row0, row0 + step, .. of src (piece of row g at g * pitch + off), into rows of 528 at dst
 template <int NR>
-__device__ __forceinline__ void stage_rows(const bf16_t* src, const int* grow, int row0, int last, bf16_t* At, int lane) {
+__device__ __forceinline__ void stage_pieces(TeamWait& tw, const bf16_t* src, unsigned pitch, unsigned off, const int* grow, int row0, int step,
+                                             int last, bf16_t* dst, int lane) {
+  if (row0 > last) return;
   uint4 v[NR];
+  unsigned o[NR];
 #pragma unroll
-  for (int i = 0; i < NR; ++i)
-    v[i] = ld16_l2(src, (unsigned)__builtin_amdgcn_readfirstlane(grow[min(row0 + i, last)]) * (kTD * 2) + 16 * lane);
+  for (int i = 0; i < NR; ++i) o[i] = (unsigned)__builtin_amdgcn_readfirstlane(grow[min(row0 + step * i, last)]) * pitch + off;
+  if (NR > 2) wait_for(tw, lane, [&]() { Seen16 seen; seen.add(v[NR - 1] = ld16_l2(src, o[NR - 1] + 16 * lane)); return seen.all(); });
+  wait_for(tw, lane, [&]() {
+    Seen16 seen;
 #pragma unroll
-  for (int i = 0; i < NR; ++i) *(uint4*)(At + (row0 + i) * kTLd + 8 * lane) = v[i];
+    for (int i = 0; i < NR; ++i) v[i] = ld16_l2(src, o[i] + 16 * lane);
+#pragma unroll
+    for (int i = 0; i < NR; ++i) seen.add(v[i]);
+    return seen.all();
+  });
+#pragma unroll
+  for (int i = 0; i < NR; ++i) *(uint4*)(dst + (row0 + step * i) * kTLd + 8 * lane) = v[i];
+}
+// all rows [*, 512] of the team
+template <int NR>
+__device__ __forceinline__ void stage_rows(TeamWait& tw, const bf16_t* src, const int* grow, int n, bf16_t* At, int wave, int lane) {
+  if (n > kTW * (NR - 1)) stage_pieces<NR>(tw, src, kTD * 2, 0, grow, wave, kTW, n - 1, At, lane);
+  else stage_pieces<NR - 1>(tw, src, kTD * 2, 0, grow, wave, kTW, n - 1, At, lane);
 }
 
+// the embedded rows (written before this launch)
+template <int NR>
+__device__ __forceinline__ void stage_first(const bf16_t* src, const int* grow, int n, bf16_t* At, int wave, int lane) {
+  uint4 v[NR];
+#pragma unroll
+  for (int i = 0; i < NR; ++i) v[i] = ldg16(src + (size_t)__builtin_amdgcn_readfirstlane(grow[min(wave + kTW * i, n - 1)]) * kTD + 8 * lane);
+#pragma unroll
+  for (int i = 0; i < NR; ++i) *(uint4*)(At + (wave + kTW * i) * kTLd + 8 * lane) = v[i];
+}
 // the first layer's residual, this member's 16 columns of the embedded rows
 template <int ROWS>
 __device__ __forceinline__ void stage_first_residual(const float* x, const int* grow, int n, float* xres, int idx, int wave, int lane) {
@@ -227,18 +293,25 @@ __device__ __forceinline__ void stage_first_residual(const float* x, const int* 
     if (row < n) xres[row * 16 + (lane & 15)] = gload(x + (size_t)grow[row] * kTD + idx * 16 + (lane & 15));
   }
 }
-// FFN2's operand as [slice][row][528]: a wave takes the rows par, par + 2, .. of slice sl, eight in flight
+// FFN2's operand as [slice][row][528]: a wave takes the rows par, par + 2, .. of slice sl
 template <int ROWS>
-__device__ __forceinline__ void stage_ffn(const bf16_t* f, const int* grow, int n, bf16_t* At, int sl, int par, int lane) {
-#pragma unroll
-  for (int k0 = 0; k0 < ROWS / 2; k0 += 8) {
-    uint4 v[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k)
-      v[k] = ld16_l2(f, (unsigned)__builtin_amdgcn_readfirstlane(grow[min(par + 2 * (k0 + k), n - 1)]) * (kTF * 2) + sl * 1024 + 16 * lane);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) *(uint4*)(At + (sl * ROWS + par + 2 * (k0 + k)) * kTLd + 8 * lane) = v[k];
+__device__ __forceinline__ void stage_ffn(TeamWait& tw, const bf16_t* f, const int* grow, int n, bf16_t* At, int sl, int par, int lane) {
+  bf16_t* dst = At + sl * ROWS * kTLd;
+  if constexpr (ROWS == 16) {
+    if (n > 8) stage_pieces<8>(tw, f, kTF * 2, sl * 1024, grow, par, 2, n - 1, dst, lane);
+    else if (n > 2) stage_pieces<4>(tw, f, kTF * 2, sl * 1024, grow, par, 2, n - 1, dst, lane);
+    else stage_pieces<1>(tw, f, kTF * 2, sl * 1024, grow, par, 2, n - 1, dst, lane);
+  } else {
+    if (n > 24) stage_pieces<16>(tw, f, kTF * 2, sl * 1024, grow, par, 2, n - 1, dst, lane);
+    else stage_pieces<12>(tw, f, kTF * 2, sl * 1024, grow, par, 2, n - 1, dst, lane);
   }
+}
+// places of this member's next results, set back (a wave; offsets in bytes)
+// NP pieces of 16 bytes a row, rows [row0, row0 + count) of the table
+template <int NP>
+__device__ __forceinline__ void unwrite_rows(void* base, unsigned pitch, unsigned off, const int* rows, int count, int lane) {
+#pragma unroll 1
+  for (int m = lane / NP; m < count; m += 64 / NP) unwrite16(base, (unsigned)rows[m] * pitch + off + (lane % NP) * 16);
 }
 __device__ __forceinline__ TeamChunk chunk_at(const TeamChunk* chunks, int c) {
   TeamChunk t = chunks[c];
@@ -256,8 +329,9 @@ __device__ __forceinline__ TeamChunk chunk_at(const TeamChunk* chunks, int c) {
 struct AttnLds { bf16_t* Vt; bf16_t* Pt; f32x4* Pf; float* xmax; };
 template <int NKT> struct AttnDims { static constexpr int LDV = 16 * NKT + 16, VP = NKT * 16 * 8 / (64 * kGW), KT = NKT / kGW; };
 template <int NKT> struct AttnRegs { uint4 kf[AttnDims<NKT>::KT][2], vr[AttnDims<NKT>::VP]; };
+// (false: a key or value of the keys first_new.. is not written yet)
 template <int NKT, bool L2>
-__device__ __forceinline__ void attn_request(const bf16_t* K, const bf16_t* V, int kv0, int nk_all, int h, int wave, int lane, AttnRegs<NKT>& g) {
+__device__ __forceinline__ bool attn_request(const bf16_t* K, const bf16_t* V, int kv0, int nk_all, int h, int wave, int lane, AttnRegs<NKT>& g, int first_new = 0) {
   const int r = lane & 15, kq = lane >> 4;
 #pragma unroll
   for (int t = 0; t < AttnDims<NKT>::KT; ++t) {
@@ -271,6 +345,15 @@ __device__ __forceinline__ void attn_request(const bf16_t* K, const bf16_t* V, i
     const unsigned off = (unsigned)(kv0 + min(t, nk_all - 1)) * (kTD * 2) + (h * 64 + c * 8) * 2;
     g.vr[it] = L2 ? ld16_l2(V, off) : ldg16((const char*)V + off);
   }
+  if (!L2) return true;
+  Seen16 seen;
+#pragma unroll
+  for (int t = 0; t < AttnDims<NKT>::KT; ++t)
+#pragma unroll
+    for (int s = 0; s < 2; ++s) seen.add(g.kf[t][s], min(16 * (wave + kGW * t) + r, nk_all - 1) >= first_new);
+#pragma unroll
+  for (int it = 0; it < AttnDims<NKT>::VP; ++it) seen.add(g.vr[it], min(((wave * 64 + lane) + 64 * kGW * it) % (16 * NKT), nk_all - 1) >= first_new);
+  return seen.all();
 }
 template <int NKT>
 __device__ __forceinline__ void attn_values(const AttnLds& L, const AttnRegs<NKT>& g, int nk_all, int wave, int lane) {
@@ -355,7 +438,7 @@ __device__ __forceinline__ void attn_core(const AttnLds& L, const uint4 (&qf)[2]
   for (int i = 0; i < 4; ++i) {
     const float l = row16_sum(ps[i]);
     if (4 * kq + i < n_rows)
-      Store<bf16_t>::store(att + (size_t)grow[row + 4 * kq + i] * kTD + h * 64 + 16 * wave + r, O[i] / l);
+      put(att + (size_t)grow[row + 4 * kq + i] * kTD + h * 64 + 16 * wave + r, O[i] / l);
   }
 }
 
@@ -371,11 +454,13 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
   bf16_t* At = (bf16_t*)lds;                                     // [ROWS][528], FFN2: [4 slices][ROWS][528]
   float* xres = (float*)(lds + kSlices * ROWS * kTLd * 2);      // [ROWS][16]
   f32x4* accx = (f32x4*)(xres + ROWS * 16);                      // [3 slices][MT][64]
-  TeamChunk* chunks = (TeamChunk*)(accx + 3 * MT * 64);          // [ROWS]
+  float* lnv = (float*)(accx + 3 * MT * 64);                     // [2][512]
+  TeamChunk* chunks = (TeamChunk*)(lnv + 2 * kTD);               // [ROWS]
   int* grow = (int*)(chunks + ROWS);                             // [ROWS] packed row of the team's row
   int* rdst = grow + ROWS;                                       // [ROWS] its key / value row
   int* misc = rdst + ROWS;                                       // member, chunks, chunks of segment 0; FFN2's slices done
   unsigned* slices = (unsigned*)(misc + 4);
+  unsigned* gave_up = slices + 1;
   // attention: the row tile [16][528] and the queries [16][80] of the cross-attention first, then values and probabilities
   bf16_t* Qt = At + 16 * kTLd;
   AttnLds AL;
@@ -415,7 +500,7 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
         chunks[before + c] = t;
       }
   } else if (wave == 1) {
-    if (lane == 0) *slices = 0;
+    if (lane == 0) { *slices = 0; *gave_up = 0; }
     if (lane < ROWS) {
       const int row = min(lane, n0 + n1 - 1), g = row < n0 ? a.row_lo[0][team] + row : a.row_lo[1][team] + row - n0;
       grow[lane] = g;
@@ -433,23 +518,47 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
   const int c_first = idx >> 3;
   typedef TeamOff<DEC> O;
 
-  TeamSync ts;
-  ts.count = words + 32; ts.fail = a.fail; ts.target = 0; ts.limit = a.form_ticks;
+  TeamWait tw;
+  tw.fail = a.fail; tw.gave_up = gave_up; tw.off = false;
   const int gw = wave & (kGW - 1), lane0 = lane, idx0 = idx;
-  float4 gv[2], bv[2];
 
-  // The two groups of waves take turns: one multiplies a stage's rows while the other requests the next stage's strips
-  // into its registers.  A CU's vector memory returns in order, so strips (from the last-level cache: 64 KB a CU in 0.93 us, from
-  // the L2 in 0.56) are requested when a stage's rows have arrived and return while the other group multiplies, stores and meets the team; and a wave that waits
-  // for its stores waits for every request before them, so the group that stores requests nothing.
+  // The two groups of waves take turns: one multiplies a stage's rows and stores, then the other requests the next stages' strips
+  // into its registers.  A CU takes only so many requests at a time and answers them in order: stores behind 32 to 64 KB of strips
+  // (from the last-level cache 64 KB take 0.93 us) left 1.2 us after the product, so the strips go out behind the stores (a barrier
+  // says so, which also frees the rows' place in LDS) and return while the results of the others are on their way, or while attention computes.
   // Group A: Q, K, V | self-attention | cross-attention | FFN1.  Group B: output projections | cross queries | FFN2.
+  //
+  // Exchanges of a layer, who reads them, and where their places are set back (always at the beginning of a stage, ahead of the data
+  // its members store; a reader has seen those data whole, or data that took them, before it looks at the place; and whoever read the
+  // place's former content has stored data since which the writer has seen):
+  //   q, k, v    the members of a problem's chunk                        FFN2 of the layer before, or ahead of the team's barrier
+  //   att        all (those without a chunk have seen FFN2's rows only)  FFN2 of the layer before, or ahead of the team's barrier
+  //   s1         a chunk's members; the encoder: all                     Q, K, V
+  //   att2, xr   all (those without a chunk have seen att)               self-attention
+  //   s2         all (seen att2)                                         first output projection
+  //   f          all (seen s2; the encoder: s1)                          second output projection (the encoder: the only one)
+  //   s          all (seen f)                                            FFN1
+  auto unwrite_qkv = [&](int l, int n, int idx, int lane) {   // (a wave)
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      const int strip = idx * 3 + s, part = strip >> 5;
+      unwrite_rows<2>(part == 0 ? (void*)a.q : (char*)(part == 1 ? a.K : a.V) + (size_t)l * a.kv_stride, kTD * 2, ((strip * 16) & (kTD - 1)) * 2,
+                      part == 0 ? grow : rdst, n, lane);
+    }
+#pragma unroll 1
+    for (int c = c_first; c < n_chunks_all; c += CPR) {
+      const TeamChunk ch = chunk_at(chunks, c);
+      unwrite_rows<8>(a.att, kTD * 2, (idx & (kTH - 1)) * 128, grow + ch.row, ch.n, lane);
+    }
+  };
   if (wave < kGW) {
     // ------------------------------------------------------------------------------------------ group A
-    const bool watcher = gw == kGW - 1;
     uint4 b[16];
     float bias = 0.f;
     {
       const int lane = here(lane0), idx = here_s(idx0), r = lane & 15;
+      stage_first<RPW>(a.xa, grow, n0 + n1, At, wave, lane);
+      stage_first_residual<ROWS>(a.x, grow, n0 + n1, xres, idx, wave, lane);
       if (gw < 3) {
         load_strip((const bf16_t*)(a.w + O::wqkv), (idx * 3 + gw) * 16, kTD, 0, lane, b);
         bias = gload((const float*)(a.w + O::bqkv) + (idx * 3 + gw) * 16 + r);
@@ -462,14 +571,14 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
       // ---------------------------------------------------------------- Q, K, V
       {
         const int lane = here(lane0), idx = here_s(idx0), r = lane & 15, kq = lane >> 4;
-        if (l > 0) {
-          team_begin(ts, false, lane);
-          stage_ln<RPW>(a.s, grow, n, gv, bv, At, xres, idx, wave, lane);
-        } else {
-          stage_rows<RPW>(a.xa, grow, wave * RPW, n - 1, At, lane);
-          stage_first_residual<ROWS>(a.x, grow, n, xres, idx, wave, lane);
-        }
+        if (gw < MT) unwrite_rows<4>(a.s1, kTD * 4, idx * 64, grow + gw * 16, min(n - gw * 16, 16), lane);
+        if (l > 0) stage_ln<RPW>(tw, a.s, grow, n, lnv, At, xres, idx, wave, lane);
         wg_bar();
+        team_put_ready();
+        if (l == 0) {
+          wg_bar();   // the team is complete
+          tw.off = __builtin_amdgcn_readfirstlane(__hip_atomic_load(gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) != 0;
+        }
         if (gw < 3) {
           const int strip = idx * 3 + gw, col = (strip * 16 + r) & (kTD - 1), part = strip >> 5;
           bf16_t* out = (part == 0 ? a.q : (bf16_t*)((char*)(part == 1 ? a.K : a.V) + (size_t)l * a.kv_stride)) + col;
@@ -482,10 +591,10 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
             const int* dst = (part == 0 ? grow : rdst) + m;
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-              if (m + i < n) Store<bf16_t>::store(out + (size_t)dst[i] * kTD, acc[t][i] + bias);
+              if (m + i < n) put(out + (size_t)dst[i] * kTD, acc[t][i] + bias);
           }
         }
-        team_end(ts, true, watcher, lane);
+        wg_bar();
       }
       if (a.head_only && l + 1 == a.layers) { n = n0; n_chunks = n_chunks0; }   // only segment 0 goes on
       // ---------------------------------------------------------------- self-attention
@@ -493,7 +602,14 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
         const int lane = here(lane0), idx = here_s(idx0), r = lane & 15, kq = lane >> 4, h = idx & (kTH - 1);
         const bf16_t* Kl = (const bf16_t*)((const char*)a.K + (size_t)l * a.kv_stride);
         const bf16_t* Vl = (const bf16_t*)((const char*)a.V + (size_t)l * a.kv_stride);
-        team_begin(ts, watcher, lane);
+        if constexpr (DEC) {
+#pragma unroll 1
+          for (int c = c_first; c < n_chunks; c += CPR) {
+            const TeamChunk ch = chunk_at(chunks, c);
+            unwrite_rows<2>(a.att2, kTD * 2, h * 128 + gw * 32, grow + ch.row, ch.n, lane);
+            unwrite_rows<4>(a.xr, kTD * 4, h * 256 + gw * 64, grow + ch.row, ch.n, lane);
+          }
+        }
 #pragma unroll 1
         for (int c = c_first; c < n_chunks; c += CPR) {
           const TeamChunk ch = chunk_at(chunks, c);
@@ -501,26 +617,31 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
           uint4 qf[2];
           AttnRegs<NKT> g;
           const unsigned qo = (unsigned)grow[ch.row + min(r, ch.n - 1)] * (kTD * 2) + (h * 64 + kq * 8) * 2;
-          attn_request<NKT, true>(Kl, Vl, ch.kv_self, nk_all, h, gw, lane, g);
+          wait_for(tw, lane, [&]() {
+            Seen16 seen;
 #pragma unroll
-          for (int s = 0; s < 2; ++s) qf[s] = ld16_l2(a.q, qo + 64 * s);
+            for (int s = 0; s < 2; ++s) qf[s] = ld16_l2(a.q, qo + 64 * s);
+            const bool kv = attn_request<NKT, true>(Kl, Vl, ch.kv_self, nk_all, h, gw, lane, g, ch.causal ? ch.nk_base : 0);
+#pragma unroll
+            for (int s = 0; s < 2; ++s) seen.add(qf[s]);
+            return kv && seen.all();
+          });
+          team_put_ready();
           attn_values<NKT>(AL, g, nk_all, gw, lane);
           attn_core<NKT>(AL, qf, g, nk_all, ch.nk_base, ch.off, ch.causal, a.scale, a.att, grow, ch.row, ch.n, h, gw, lane);
-          if (c + CPR < n_chunks) wg_bar();
+          wg_bar();
         }
-        team_end(ts, true, watcher, lane);
       }
       // ---------------------------------------------------------------- output projection (group B multiplies)
       const int h = idx0 & (kTH - 1);
       AttnRegs<NKT> cg;
       {
         const int lane = here(lane0), idx = here_s(idx0), r = lane & 15;
-        team_begin(ts, watcher, lane);
-        stage_rows<RPW>(a.att, grow, wave * RPW, n - 1, At, lane);
+        stage_rows<RPW>(tw, a.att, grow, n, At, wave, lane);
+        wg_bar();
         wg_bar();
         if constexpr (DEC) {
           if (c_first < n_chunks) {
-            load_ln((const float*)(wl + O::ln1g), (const float*)(wl + O::ln1b), lane, gv, bv);
             const TeamChunk ch = chunk_at(chunks, c_first);
             attn_request<NKT, false>((const bf16_t*)((const char*)a.Km + (size_t)l * a.m_stride), (const bf16_t*)((const char*)a.Vm + (size_t)l * a.m_stride),
                                      ch.kv_cross, min(ch.nk_cross, 16 * NKT), h, gw, lane, cg);
@@ -528,17 +649,14 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
           bias = gload((const float*)(wl + O::b1) + (idx * 4 + gw) * 16 + r);
           load_strip<0, 8>((const bf16_t*)(wl + O::w1), (idx * 4 + gw) * 16, kTD, 0, lane, b);
         } else {
-          load_ln((const float*)(wl + O::ln_fg), (const float*)(wl + O::ln_fb), lane, gv, bv);
           bias = gload((const float*)(wl + O::b1) + (idx * 4 + gw) * 16 + r);
           load_strip((const bf16_t*)(wl + O::w1), (idx * 4 + gw) * 16, kTD, 0, lane, b);
         }
-        team_end(ts, false, false, lane);
       }
       if constexpr (DEC) {
         // -------------------------------------------------------------- cross-attention with its query projection
         {
           const int lane = here(lane0), r = lane & 15, kq = lane >> 4;
-          team_begin(ts, false, lane);
 #pragma unroll 1
           for (int c = c_first; c < n_chunks; c += CPR) {
             const TeamChunk ch = chunk_at(chunks, c);
@@ -546,35 +664,33 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
             if (c != c_first)
               attn_request<NKT, false>((const bf16_t*)((const char*)a.Km + (size_t)l * a.m_stride), (const bf16_t*)((const char*)a.Vm + (size_t)l * a.m_stride),
                                        ch.kv_cross, nk_all, h, gw, lane, cg);
-            stage_ln_chunk(a.s, grow + ch.row, ch.n, gv, bv, At, h == 0 ? a.x : nullptr, wave, lane);
+            stage_ln_chunk(tw, a.s1, grow + ch.row, ch.n, lnv, At, a.xr, h, wave, lane);
             attn_values<NKT>(AL, cg, nk_all, gw, lane);
             wg_bar();
             wg_bar();   // group B has left the queries
             uint4 qf[2];
 #pragma unroll
             for (int s = 0; s < 2; ++s) qf[s] = *(const uint4*)(Qt + min(r, ch.n - 1) * kCrossqQld + kq * 8 + 32 * s);
-            attn_core<NKT>(AL, qf, cg, nk_all, nk_all, 0, 0, a.scale, a.att, grow, ch.row, ch.n, h, gw, lane);
-            if (c + CPR < n_chunks) wg_bar();
+            attn_core<NKT>(AL, qf, cg, nk_all, nk_all, 0, 0, a.scale, a.att2, grow, ch.row, ch.n, h, gw, lane);
+            wg_bar();
           }
-          team_end(ts, true, watcher, lane);
         }
         // -------------------------------------------------------------- output projection (group B multiplies)
         {
           const int lane = here(lane0), idx = here_s(idx0);
-          team_begin(ts, watcher, lane);
-          stage_rows<RPW>(a.att, grow, wave * RPW, n - 1, At, lane);
+          stage_rows<RPW>(tw, a.att2, grow, n, At, wave, lane);
           wg_bar();
-          load_ln((const float*)(wl + O::ln_fg), (const float*)(wl + O::ln_fb), lane, gv, bv);
+          wg_bar();
           load_strip<8, 16>((const bf16_t*)(wl + O::w1), (idx * 4 + gw) * 16, kTD, 0, lane, b);
-          team_end(ts, false, false, lane);
         }
       }
       // ---------------------------------------------------------------- FFN1
       {
         const int lane = here(lane0), idx = here_s(idx0), r = lane & 15, kq = lane >> 4;
-        team_begin(ts, false, lane);
-        stage_ln<RPW>(a.s, grow, n, gv, bv, At, xres, idx, wave, lane);
+        if (gw < MT && l + 1 < a.layers) unwrite_rows<4>(a.s, kTD * 4, idx * 64, grow + gw * 16, min(n - gw * 16, 16), lane);
+        stage_ln<RPW>(tw, DEC ? a.s2 : a.s1, grow, n, lnv, At, xres, idx, wave, lane);
         wg_bar();
+        team_put_ready();
         bf16_t* out = a.f + (idx * 4 + gw) * 16 + r;
         f32x4 acc[MT];
         zero(acc);
@@ -584,34 +700,40 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
           const int m = t * 16 + 4 * kq;
 #pragma unroll
           for (int i = 0; i < 4; ++i)
-            if (m + i < n) Store<bf16_t>::store(out + (size_t)grow[m + i] * kTF, fmaxf(acc[t][i] + bias, 0.f));
+            if (m + i < n) put(out + (size_t)grow[m + i] * kTF, fmaxf(acc[t][i] + bias, 0.f));
         }
-        team_end(ts, true, watcher, lane);
+        wg_bar();
       }
       // ---------------------------------------------------------------- FFN2 (group B multiplies)
       {
         const int lane = here(lane0), idx = here_s(idx0), r = lane & 15;
-        team_begin(ts, watcher, lane);
-        stage_ffn<ROWS>(a.f, grow, n, At, gw, wave >> 2, lane);
+        stage_ffn<ROWS>(tw, a.f, grow, n, At, gw, wave >> 2, lane);
         wg_bar();
-        if (l + 1 < a.layers) {
-          load_ln((const float*)(wl + O::ln_lg), (const float*)(wl + O::ln_lb), lane, gv, bv);
-          if (gw < 3) {
-            bias = gload((const float*)(wl + O::kLayerBytes + O::bqkv) + (idx * 3 + gw) * 16 + r);
-            load_strip((const bf16_t*)(wl + O::kLayerBytes + O::wqkv), (idx * 3 + gw) * 16, kTD, 0, lane, b);
-          }
+        if (l + 1 < a.layers && gw < 3) {   // (FFN2's chain is long: these are there before it ends)
+          bias = gload((const float*)(wl + O::kLayerBytes + O::bqkv) + (idx * 3 + gw) * 16 + r);
+          load_strip((const bf16_t*)(wl + O::kLayerBytes + O::wqkv), (idx * 3 + gw) * 16, kTD, 0, lane, b);
         }
-        if (l + 1 < a.layers) team_end(ts, false, false, lane);
+        wg_bar();
       }
     }
     return;
   }
 
   // -------------------------------------------------------------------------------------------- group B
-  const bool watcher = gw == kGW - 1;
   uint4 bo[16], bq[16];   // strips of the output projection, then FFN2 | of the query projection, then the second output projection
+  uint4 ln = {};
   float bias_o = 0.f, bias_q = 0.f;
   unsigned chain = 0;
+  if (gw == kGW - 1) {   // this member is here, and its places can be read
+    unwrite_qkv(0, n0 + n1, idx, lane);
+    team_put_ready();
+    if (lane == 0) (void)__hip_atomic_fetch_add(words + 32, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  {
+    const int lane = here(lane0), idx = here_s(idx0);
+    stage_first<RPW>(a.xa, grow, n0 + n1, At, wave, lane);
+    stage_first_residual<ROWS>(a.x, grow, n0 + n1, xres, idx, wave, lane);
+  }
 #pragma unroll 1
   for (int l = 0; l < a.layers; ++l) {
     int n = n0 + n1, n_chunks = n_chunks_all;
@@ -619,26 +741,33 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
     // ------------------------------------------------------------------ Q, K, V
     {
       const int lane = here(lane0), idx = here_s(idx0), r = lane & 15;
-      if (l > 0) {
-        team_begin(ts, watcher, lane);
-        stage_ln<RPW>(a.s, grow, n, gv, bv, At, xres, idx, wave, lane);
-      } else {
-        stage_rows<RPW>(a.xa, grow, wave * RPW, n - 1, At, lane);
-        stage_first_residual<ROWS>(a.x, grow, n, xres, idx, wave, lane);
+      if (l > 0) stage_ln<RPW>(tw, a.s, grow, n, lnv, At, xres, idx, wave, lane);
+      wg_bar();
+      if (l == 0) {
+        if (gw == kGW - 1 && lane == 0) {
+          const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
+          bool late = a.form_ticks == 0;
+          for (unsigned spin = 0; !late && __hip_atomic_load(words + 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < kTeamMembers; ++spin)
+            late = (spin & 15) == 15 && __builtin_amdgcn_s_memrealtime() - t0 >= a.form_ticks;
+          if (late) {
+            __hip_atomic_store(a.fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(gave_up, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          }
+        }
+        wg_bar();
+        tw.off = __builtin_amdgcn_readfirstlane(__hip_atomic_load(gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) != 0;
       }
       wg_bar();
       if (gw < MT) {
         bias_o = gload((const float*)(wl + O::bo) + idx * 16 + r);
         load_strip((const bf16_t*)(wl + O::wo), idx * 16, kTD, 0, lane, bo);
       }
-      load_ln((const float*)(wl + (DEC ? O::ln1g : O::ln_fg)), (const float*)(wl + (DEC ? O::ln1b : O::ln_fb)), lane, gv, bv);
-      team_end(ts, false, false, lane);
+      ln = load_ln((const float*)(wl + (DEC ? O::ln1g : O::ln_fg)), (const float*)(wl + (DEC ? O::ln1b : O::ln_fb)), gw, lane);
     }
     if (a.head_only && l + 1 == a.layers) { n = n0; n_chunks = n_chunks0; }
     // ------------------------------------------------------------------ self-attention
     {
       const int lane = here(lane0), r = lane & 15, h = here_s(idx0) & (kTH - 1);
-      team_begin(ts, false, lane);
       for (int c = c_first; c < n_chunks; c += CPR) {
         wg_bar();
         if constexpr (DEC) {
@@ -648,39 +777,42 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
           }
         }
         wg_bar();
-        if (c + CPR < n_chunks) wg_bar();
+        wg_bar();
       }
-      team_end(ts, false, false, lane);
     }
     // ------------------------------------------------------------------ output projection + residual
     {
       const int lane = here(lane0), idx = here_s(idx0), r = lane & 15, kq = lane >> 4;
-      team_begin(ts, false, lane);
-      stage_rows<RPW>(a.att, grow, wave * RPW, n - 1, At, lane);
+      if (gw < MT) {
+        if constexpr (DEC) unwrite_rows<4>(a.s2, kTD * 4, idx * 64, grow + gw * 16, min(n - gw * 16, 16), lane);
+        else unwrite_rows<8>(a.f, kTF * 2, idx * 128, grow + gw * 16, min(n - gw * 16, 16), lane);
+      }
+      stage_rows<RPW>(tw, a.att, grow, n, At, wave, lane);
+      keep_ln(lnv, ln, gw, lane);
       wg_bar();
       if (gw < MT && gw * 16 < n) {
         f32x4 acc[1];
         zero(acc);
+        team_put_ready();
         mm16<1>(At + (gw * 16 + r) * kTLd + kq * 8, bo, acc);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int m = gw * 16 + 4 * kq + i;
-          if (m < n) gstore(a.s + (size_t)grow[m] * kTD + idx * 16 + r, acc[0][i] + bias_o + xres[m * 16 + r]);
+          if (m < n) put(a.s1 + (size_t)grow[m] * kTD + idx * 16 + r, acc[0][i] + bias_o + xres[m * 16 + r]);
         }
       }
-      team_end(ts, true, watcher, lane);
+      wg_bar();
     }
     if constexpr (DEC) {
       // ---------------------------------------------------------------- cross-attention: the queries
       {
         const int lane = here(lane0), idx = here_s(idx0), r = lane & 15, kq = lane >> 4, h = idx & (kTH - 1);
-        team_begin(ts, watcher, lane);
         auto next_strips = [&]() {
           if (gw < MT) {
             bias_q = gload((const float*)(wl + O::cbo) + idx * 16 + r);
             load_strip((const bf16_t*)(wl + O::cwo), idx * 16, kTD, 0, lane, bq);
           }
-          load_ln((const float*)(wl + O::ln_fg), (const float*)(wl + O::ln_fb), lane, gv, bv);
+          ln = load_ln((const float*)(wl + O::ln_fg), (const float*)(wl + O::ln_fb), gw, lane);
           bias_o = gload((const float*)(wl + O::b2) + idx * 16 + r);
           load_strip<0, 8>((const bf16_t*)(wl + O::w2), idx * 16, kTF, 16 * gw, lane, bo);
         };
@@ -688,8 +820,7 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
 #pragma unroll 1
         for (int c = c_first; c < n_chunks; c += CPR) {
           const int row = __builtin_amdgcn_readfirstlane(chunks[c].row), nr = __builtin_amdgcn_readfirstlane(chunks[c].n);
-          stage_ln_chunk(a.s, grow + row, nr, gv, bv, At, h == 0 ? a.x : nullptr, wave, lane);
-          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the rows kept for the residual are stored
+          stage_ln_chunk(tw, a.s1, grow + row, nr, lnv, At, a.xr, h, wave, lane);
           wg_bar();
           {
             f32x4 acc[1];
@@ -700,54 +831,61 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
           }
           wg_bar();
           if (c + CPR >= n_chunks) next_strips();
-          wg_bar(); wg_bar();
-          if (c + CPR < n_chunks) wg_bar();
+          wg_bar(); wg_bar(); wg_bar();
         }
-        team_end(ts, false, false, lane);
       }
       // ---------------------------------------------------------------- output projection + residual
       {
         const int lane = here(lane0), idx = here_s(idx0), r = lane & 15, kq = lane >> 4;
-        team_begin(ts, false, lane);
+        if (gw < MT) unwrite_rows<8>(a.f, kTF * 2, idx * 128, grow + gw * 16, min(n - gw * 16, 16), lane);
         float res[4] = {};
-        stage_rows<RPW>(a.att, grow, wave * RPW, n - 1, At, lane);
         if (gw < MT && gw * 16 < n) {
+          wait_for(tw, lane, [&]() {
+            bool there = true;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) res[i] = ld4_l2(a.x, (unsigned)grow[gw * 16 + 4 * kq + i] * (kTD * 4) + (idx * 16 + r) * 4);
+            for (int i = 0; i < 4; ++i) {
+              res[i] = ld4_l2(a.xr, (unsigned)grow[min(gw * 16 + 4 * kq + i, n - 1)] * (kTD * 4) + (idx * 16 + r) * 4);
+              there = there && __float_as_uint(res[i]) != ~0u;
+            }
+            return __builtin_amdgcn_ballot_w64(!there) == 0;
+          });
         }
+        stage_rows<RPW>(tw, a.att2, grow, n, At, wave, lane);
+        keep_ln(lnv, ln, gw, lane);
         wg_bar();
         if (gw < MT && gw * 16 < n) {
           f32x4 acc[1];
           zero(acc);
+          team_put_ready();
           mm16<1>(At + (gw * 16 + r) * kTLd + kq * 8, bq, acc);
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const int m = gw * 16 + 4 * kq + i;
-            if (m < n) gstore(a.s + (size_t)grow[m] * kTD + idx * 16 + r, acc[0][i] + bias_q + res[i]);
+            if (m < n) put(a.s2 + (size_t)grow[m] * kTD + idx * 16 + r, acc[0][i] + bias_q + res[i]);
           }
         }
-        team_end(ts, true, watcher, lane);
+        wg_bar();
       }
     }
     // ------------------------------------------------------------------ FFN1
     {
       const int lane = here(lane0), idx = here_s(idx0), r = lane & 15;
-      team_begin(ts, watcher, lane);
-      stage_ln<RPW>(a.s, grow, n, gv, bv, At, xres, idx, wave, lane);
+      stage_ln<RPW>(tw, DEC ? a.s2 : a.s1, grow, n, lnv, At, xres, idx, wave, lane);
+      wg_bar();
       wg_bar();
       if (!DEC) {
         bias_o = gload((const float*)(wl + O::b2) + idx * 16 + r);
         load_strip<0, 8>((const bf16_t*)(wl + O::w2), idx * 16, kTF, 16 * gw, lane, bo);
       }
       load_strip<8, 16>((const bf16_t*)(wl + O::w2), idx * 16, kTF, 16 * gw, lane, bo);
-      load_ln((const float*)(wl + O::ln_lg), (const float*)(wl + O::ln_lb), lane, gv, bv);
-      team_end(ts, false, false, lane);
+      ln = load_ln((const float*)(wl + O::ln_lg), (const float*)(wl + O::ln_lb), gw, lane);
     }
     // ------------------------------------------------------------------ FFN2 + residual: a wave per 512-k slice
     {
       const int lane = here(lane0), idx = here_s(idx0), r = lane & 15, kq = lane >> 4;
-      team_begin(ts, false, lane);
-      stage_ffn<ROWS>(a.f, grow, n, At, gw, wave >> 2, lane);
+      if (gw == kGW - 1 && l + 1 < a.layers) unwrite_qkv(l + 1, n0 + n1, idx, lane);
+      stage_ffn<ROWS>(tw, a.f, grow, n, At, gw, wave >> 2, lane);
+      keep_ln(lnv, ln, gw, lane);
       wg_bar();
       // The sum of an element stays one chain: the accumulators go from wave to wave through LDS, a count says how many
       // slices are in (a wave waits for the ones before it only, so the wait ends).
@@ -766,24 +904,25 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
         for (int t = 0; t < MT; ++t) accx[(gw * MT + t) * 64 + lane] = acc[t];
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       } else {
+        team_put_ready();
 #pragma unroll
         for (int t = 0; t < MT; ++t)
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const int m = t * 16 + 4 * kq + i;
-            if (m < n) gstore(a.s + (size_t)grow[m] * kTD + idx * 16 + r, acc[t][i] + bias_o + xres[m * 16 + r]);
+            if (m < n) put(a.s + (size_t)grow[m] * kTD + idx * 16 + r, acc[t][i] + bias_o + xres[m * 16 + r]);
           }
       }
       if (lane == 0) __hip_atomic_store(slices, chain + gw + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       chain += kSlices;
-      if (l + 1 < a.layers) team_end(ts, true, watcher, lane);
+      wg_bar();
     }
   }
 }
 
 // (more than half a CU's LDS: one member per CU)
 static size_t team_lds_bytes(int mt) {
-  const size_t rows = 16 * mt, b = (size_t)kSlices * rows * kTLd * 2 + rows * 16 * 4 + 3 * mt * 64 * 16 + rows * sizeof(TeamChunk) + 2 * rows * 4 + 64;
+  const size_t rows = 16 * mt, b = (size_t)kSlices * rows * kTLd * 2 + rows * 16 * 4 + 3 * mt * 64 * 16 + 2 * kTD * 4 + rows * sizeof(TeamChunk) + 2 * rows * 4 + 64;
   return b > 84 * 1024 ? b : 84 * 1024;
 }
 // MT by the rows of the largest team, NKT by the keys of the longest problem (an encoder's keys are its team's rows)

@@ -74,6 +74,36 @@ def test_layers_as_one_launch_give_the_bits_of_the_launches(src, rows):
         ctx.close()
 
 
+@pytest.mark.parametrize("name", ["dec.2.ln1.b", "dec.1.self.bk", "dec.4.self.bq", "dec.0.cross.bo", "dec.3.ffn.b1", "dec.3.ffn.b2", "enc.1.self.bv", "enc.2.ffn.b2"])
+def test_values_that_are_not_finite_pass_between_the_members(name):
+    """A place nobody has written yet is all ones, one of the NaNs: a value of these bits in a bias, as rows, keys, values or hidden units take
+    it up, comes through as a NaN (no team gives up), and what stays finite has the bits of the launches."""
+    if 7 not in W:
+        W[7] = init_weights(DIMS, 7)
+    w = dict(W[7])
+    w[name] = w[name].copy()
+    w[name].view(np.uint32)[77] = 0xffffffff
+    rng = np.random.default_rng(len(name))
+    srcs = [_tokens(rng, n) for n in (12, 30)]
+    blk = [[int(t) for t in _tokens(rng, n)] for n in (6, 20)]
+    ctx = ad.Context(ad.make_config(DIMS, max_batch=2, max_src=32, max_len=32, k_max=20, dtype="bf16", special=SPECIAL, debug_logits=True), w)
+    try:
+        got = {}
+        for on in (0, 1):
+            ctx.set_option(ad.AD_OPT_TEAMS, on)
+            ctx.encode(ad.AD_VERIFIER, srcs)
+            launched, _ = _launched(ctx, lambda: ctx.verify(blk, want_verified=True))
+            assert launched == on
+            got[on] = ctx.debug_logits().copy()
+        there = np.isfinite(got[0])
+        assert there.all() == (name == "dec.3.ffn.b1")   # (the ReLU takes a NaN for less than nothing)
+        assert np.array_equal(there, np.isfinite(got[1]))
+        assert np.array_equal(got[0][there].view(np.uint32), got[1][there].view(np.uint32))
+        assert ctx.get_option(ad.AD_OPT_TEAM_FAILURES) == 0
+    finally:
+        ctx.close()
+
+
 @pytest.mark.parametrize("n", [64, 65, 128, 129])
 def test_team_forwards_against_long_prefixes(n):
     """A block of 8 rows that ends at key n (own keys): the team kernels for 64 and 128 keys, and the launches beyond."""
