@@ -9,13 +9,13 @@
 // Sequences never share a row of an attention or a LayerNorm, so teams on different XCDs work on different
 // sequences and never talk to each other; with one sequence seven XCDs idle.
 //
-// What bounds it (clock stamps at every workgroup barrier, base model, a layer of 14 / 17 / 26 us at 1 / 8 / 25 rows): products 2.9 us a layer
-// (FFN2's chain through four slices 1.2, the others 0.25-0.35 each), exchanges 0.45 us where no strips are queued and up to 1.5
-// behind them (one XCD streams a layer's 7.3 MB from the last-level cache in 5.7 us), the two attentions 2.9; above 16 rows the rows'
+// What bounds it (clock stamps at every workgroup barrier, base model, a layer of 13 / 15 / 24 us at 1 / 8 / 25 rows): products 2.6 us a layer
+// (FFN2's chain through four slices 0.9, the others 0.25-0.35 each), exchanges 0.45 us where no strips are queued and up to 1.4
+// behind them (one XCD streams a layer's 7.3 MB from the last-level cache in 5.7 us), the two attentions 2.2; above 16 rows the rows'
 // trips, 50 KB a member and stage, and the LayerNorm that every member takes of every row.
 // Verify forward of the base model, us, with barriers between the stages / this way, one machine: 1 sequence of 1, 4, 8, 16, 17, 25, 32 rows
-// 139, 143, 144, 150, 167, 178, 178 / 88, 101, 104, 116, 145, 156, 159; 8 sequences of 25 rows 207 / 171; 32 sequences of 1, 2, 4, 6, 8 rows
-// 164, 166, 176, 196, 206 / 117, 121, 136, 168, 180.  A launch per stage: 159-172, 172, 175, 180, 178, 181, 183; 222; 177, 182, 195, 221, 231
+// 139, 143, 144, 150, 167, 178, 178 / 86, 95, 100, 114, 142, 151, 154; 8 sequences of 25 rows 207 / 168; 32 sequences of 1, 2, 4, 6, 8 rows
+// 164, 166, 176, 196, 206 / 112, 117, 133, 166, 179.  A launch per stage: 159-172, 172, 175, 180, 178, 181, 183; 222; 177, 182, 195, 221, 231
 // (the launches replayed as a graph; a call shape's first two appearances go out launch by launch in 223).  33 to 64 rows, four row
 // tiles, were 240 and more / 184-191 with barriers: hence at most 32 rows.
 //
@@ -67,12 +67,24 @@ __device__ __forceinline__ void wg_bar() {
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 }
+// barrier over the four waves of a group, through a count in LDS: the other group may be held up by its requests meanwhile
+__device__ __forceinline__ void group_wait(unsigned* count, unsigned target) {
+  while (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < target) {}
+  asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void group_bar(unsigned* count, unsigned& target, int lane) {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  target += kGW;
+  if (lane == 0) (void)__hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  group_wait(count, target);
+}
 // A row goes from the CU that computes it to those that multiply it without a barrier: its place is set to all ones ahead of time,
 // nothing computed is stored as that, and whoever needs the row reads it until no piece of it is all ones.  (All ones is one of
 // the NaNs; a NaN with these bits is stored as its neighbour.)  Who sets a place back, and when: its writer, no later than the
 // store of an earlier exchange that every reader of the place has seen whole, and after an exchange that every reader of its former
 // content had to pass; the stores are answered for before the writer's next data leave (team_put_ready).
 __device__ __forceinline__ void unwrite16(void* base, unsigned off) { gstore((uint4*)((char*)base + off), uint4{~0u, ~0u, ~0u, ~0u}); }
+__device__ __forceinline__ f32x4 unwritten4() { return __builtin_bit_cast(f32x4, uint4{~0u, ~0u, ~0u, ~0u}); }
 __device__ __forceinline__ unsigned written(float v) { return min(__float_as_uint(v), 0xfffffffeu); }
 __device__ __forceinline__ void put(float* p, float v) { gstore((unsigned*)p, written(v)); }
 __device__ __forceinline__ void put(bf16_t* p, float v) { gstore(p, (bf16_t)min((unsigned)f2bf(v), 0xfffeu)); }
@@ -130,12 +142,12 @@ __device__ __forceinline__ int here_s(int v) {
   return v;
 }
 
-// the 16 weight fragments (512 k) of the 16-column strip at column n0 of W [*, K], from step u0
+// the 16 weight fragments (512 k) of the 16-column strip at column n0 of W [*, K], from step u0 (one address register for all of them)
 template <int U0 = 0, int U1 = 16>
 __device__ __forceinline__ void load_strip(const bf16_t* W, int n0, int K, int u0, int lane, uint4 (&b)[16]) {
-  const bf16_t* wp = W + (size_t)n0 * K + u0 * 512 + lane * 8;
+  __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)(W + (size_t)n0 * K + u0 * 512), 0, 16384, 0x00027000);
 #pragma unroll
-  for (int u = U0; u < U1; ++u) b[u] = ldg16(wp + u * 512);
+  for (int u = U0; u < U1; ++u) b[u] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, 16 * lane, 1024 * u, 0));
 }
 // T tiles of 16 x 16 over 512 k, added to acc.  The operand reads are issued well before the products: left to itself the compiler
 // puts each read next to its use and the chain waits for LDS sixteen times (0.7 us instead of 0.3).
@@ -326,7 +338,7 @@ __device__ __forceinline__ TeamChunk chunk_at(const TeamChunk* chunks, int c) {
 // the score tiles of keys 16 w .. and 16 (w + 4) .., the waves' maxima and the unrounded exponentials go through LDS,
 // every wave sums the denominators in key order and computes 16 output columns.  Same order as attn_tiles_mfma: a score is
 // one chain over the head width, a lane's denominator adds its keys in ascending order, the output is one chain over the keys.
-struct AttnLds { bf16_t* Vt; bf16_t* Pt; f32x4* Pf; float* xmax; };
+struct AttnLds { bf16_t* Vt; bf16_t* Pt; f32x4* Pf; float* xmax; unsigned* count; };
 template <int NKT> struct AttnDims { static constexpr int LDV = 16 * NKT + 16, VP = NKT * 16 * 8 / (64 * kGW), KT = NKT / kGW; };
 template <int NKT> struct AttnRegs { uint4 kf[AttnDims<NKT>::KT][2], vr[AttnDims<NKT>::VP]; };
 // (false: a key or value of the keys first_new.. is not written yet)
@@ -372,9 +384,9 @@ __device__ __forceinline__ void attn_values(const AttnLds& L, const AttnRegs<NKT
     }
   }
 }
-// (two workgroup barriers; the values are written ahead of the first)
+// (two barriers of the group; the values are written ahead of the first)
 template <int NKT>
-__device__ __forceinline__ void attn_core(const AttnLds& L, const uint4 (&qf)[2], const AttnRegs<NKT>& g, int nk_all, int nk_base,
+__device__ __forceinline__ void attn_core(const AttnLds& L, unsigned& target, const uint4 (&qf)[2], const AttnRegs<NKT>& g, int nk_all, int nk_base,
                                           int off, int causal, float scale, bf16_t* att, const int* grow, int row, int n_rows,
                                           int h, int wave, int lane) {
   constexpr int LDV = AttnDims<NKT>::LDV, KT = AttnDims<NKT>::KT;
@@ -398,7 +410,7 @@ __device__ __forceinline__ void attn_core(const AttnLds& L, const uint4 (&qf)[2]
     }
     if (r == 0) *(float4*)(L.xmax + tile * 16 + 4 * kq) = float4{m[0], m[1], m[2], m[3]};
   }
-  wg_bar();   // values and maxima
+  group_bar(L.count, target, lane);   // values and maxima
   {
     f32x4 mx = *(const f32x4*)(L.xmax + 4 * kq);
 #pragma unroll
@@ -421,7 +433,7 @@ __device__ __forceinline__ void attn_core(const AttnLds& L, const uint4 (&qf)[2]
       }
     }
   }
-  wg_bar();   // probabilities
+  group_bar(L.count, target, lane);   // probabilities
   f32x4 O = f32x4{0.f, 0.f, 0.f, 0.f}, ps = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int kb = 0; kb < NKT / 2; ++kb) {
@@ -458,9 +470,9 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
   TeamChunk* chunks = (TeamChunk*)(lnv + 2 * kTD);               // [ROWS]
   int* grow = (int*)(chunks + ROWS);                             // [ROWS] packed row of the team's row
   int* rdst = grow + ROWS;                                       // [ROWS] its key / value row
-  int* misc = rdst + ROWS;                                       // member, chunks, chunks of segment 0; FFN2's slices done
-  unsigned* slices = (unsigned*)(misc + 4);
-  unsigned* gave_up = slices + 1;
+  int* misc = rdst + ROWS;                                       // member, chunks, chunks of segment 0
+  unsigned* gave_up = (unsigned*)(misc + 4);
+  unsigned* met_a = gave_up + 1;                                 // arrivals at group A's barriers
   // attention: the row tile [16][528] and the queries [16][80] of the cross-attention first, then values and probabilities
   bf16_t* Qt = At + 16 * kTLd;
   AttnLds AL;
@@ -468,11 +480,17 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
   AL.Pt = AL.Vt + 64 * LDV;
   AL.Pf = (f32x4*)(AL.Pt + 16 * LDV);
   AL.xmax = (float*)(AL.Pf + NKT * 64);
+  AL.count = met_a;
 
   unsigned* words = a.words + team * 64;
   const int n0 = a.row_lo[0][team + 1] - a.row_lo[0][team], n1 = a.row_lo[1][team + 1] - a.row_lo[1][team];
   // member number, row tables, attention chunks
   if (threadIdx.x == 64 * kGW) misc[0] = (int)__hip_atomic_fetch_add(words, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (wave >= kGW) {
+#pragma unroll
+    for (int i = 0; i < 3 * MT; i += kGW)
+      if (i + wave - kGW < 3 * MT) accx[(i + wave - kGW) * 64 + lane] = unwritten4();
+  }
   if (wave == 0) {
     const int p0 = a.prob[team], np = a.prob[team + 1] - p0, np2 = a.prob2_off ? np : 0;
     SeqDesc sd = {}, cd = {};
@@ -500,7 +518,7 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
         chunks[before + c] = t;
       }
   } else if (wave == 1) {
-    if (lane == 0) { *slices = 0; *gave_up = 0; }
+    if (lane == 0) { *gave_up = 0; *met_a = 0; }
     if (lane < ROWS) {
       const int row = min(lane, n0 + n1 - 1), g = row < n0 ? a.row_lo[0][team] + row : a.row_lo[1][team] + row - n0;
       grow[lane] = g;
@@ -555,6 +573,7 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
     // ------------------------------------------------------------------------------------------ group A
     uint4 b[16];
     float bias = 0.f;
+    unsigned met = 0;
     {
       const int lane = here(lane0), idx = here_s(idx0), r = lane & 15;
       stage_first<RPW>(a.xa, grow, n0 + n1, At, wave, lane);
@@ -568,6 +587,7 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
     for (int l = 0; l < a.layers; ++l) {
       int n = n0 + n1, n_chunks = n_chunks_all;
       const char* wl = a.w + (size_t)l * O::kLayerBytes;       // the layer's matrices and vectors
+      AttnRegs<NKT> cg;
       // ---------------------------------------------------------------- Q, K, V
       {
         const int lane = here(lane0), idx = here_s(idx0), r = lane & 15, kq = lane >> 4;
@@ -582,17 +602,19 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
         if (gw < 3) {
           const int strip = idx * 3 + gw, col = (strip * 16 + r) & (kTD - 1), part = strip >> 5;
           bf16_t* out = (part == 0 ? a.q : (bf16_t*)((char*)(part == 1 ? a.K : a.V) + (size_t)l * a.kv_stride)) + col;
+          int to[MT][4];
+#pragma unroll
+          for (int t = 0; t < MT; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) to[t][i] = (part == 0 ? grow : rdst)[t * 16 + 4 * kq + i];
           f32x4 acc[MT];
           zero(acc);
           mm16<MT>(At + r * kTLd + kq * 8, b, acc);
 #pragma unroll
-          for (int t = 0; t < MT; ++t) {
-            const int m = t * 16 + 4 * kq;
-            const int* dst = (part == 0 ? grow : rdst) + m;
+          for (int t = 0; t < MT; ++t)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-              if (m + i < n) put(out + (size_t)dst[i] * kTD, acc[t][i] + bias);
-          }
+              if (t * 16 + 4 * kq + i < n) put(out + (size_t)to[t][i] * kTD, acc[t][i] + bias);
         }
         wg_bar();
       }
@@ -627,25 +649,24 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
             return kv && seen.all();
           });
           team_put_ready();
+          if constexpr (DEC) {
+            if (c == c_first)
+              attn_request<NKT, false>((const bf16_t*)((const char*)a.Km + (size_t)l * a.m_stride), (const bf16_t*)((const char*)a.Vm + (size_t)l * a.m_stride),
+                                       ch.kv_cross, min(ch.nk_cross, 16 * NKT), h, gw, lane, cg);
+          }
           attn_values<NKT>(AL, g, nk_all, gw, lane);
-          attn_core<NKT>(AL, qf, g, nk_all, ch.nk_base, ch.off, ch.causal, a.scale, a.att, grow, ch.row, ch.n, h, gw, lane);
+          attn_core<NKT>(AL, met, qf, g, nk_all, ch.nk_base, ch.off, ch.causal, a.scale, a.att, grow, ch.row, ch.n, h, gw, lane);
           wg_bar();
         }
       }
       // ---------------------------------------------------------------- output projection (group B multiplies)
       const int h = idx0 & (kTH - 1);
-      AttnRegs<NKT> cg;
       {
         const int lane = here(lane0), idx = here_s(idx0), r = lane & 15;
         stage_rows<RPW>(tw, a.att, grow, n, At, wave, lane);
         wg_bar();
         wg_bar();
         if constexpr (DEC) {
-          if (c_first < n_chunks) {
-            const TeamChunk ch = chunk_at(chunks, c_first);
-            attn_request<NKT, false>((const bf16_t*)((const char*)a.Km + (size_t)l * a.m_stride), (const bf16_t*)((const char*)a.Vm + (size_t)l * a.m_stride),
-                                     ch.kv_cross, min(ch.nk_cross, 16 * NKT), h, gw, lane, cg);
-          }
           bias = gload((const float*)(wl + O::b1) + (idx * 4 + gw) * 16 + r);
           load_strip<0, 8>((const bf16_t*)(wl + O::w1), (idx * 4 + gw) * 16, kTD, 0, lane, b);
         } else {
@@ -664,14 +685,14 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
             if (c != c_first)
               attn_request<NKT, false>((const bf16_t*)((const char*)a.Km + (size_t)l * a.m_stride), (const bf16_t*)((const char*)a.Vm + (size_t)l * a.m_stride),
                                        ch.kv_cross, nk_all, h, gw, lane, cg);
-            stage_ln_chunk(tw, a.s1, grow + ch.row, ch.n, lnv, At, a.xr, h, wave, lane);
+            stage_ln_chunk(tw, a.s1, grow + ch.row, ch.n, lnv, At, a.xr, h, wave ^ kGW, lane);
             attn_values<NKT>(AL, cg, nk_all, gw, lane);
             wg_bar();
             wg_bar();   // group B has left the queries
             uint4 qf[2];
 #pragma unroll
             for (int s = 0; s < 2; ++s) qf[s] = *(const uint4*)(Qt + min(r, ch.n - 1) * kCrossqQld + kq * 8 + 32 * s);
-            attn_core<NKT>(AL, qf, cg, nk_all, nk_all, 0, 0, a.scale, a.att2, grow, ch.row, ch.n, h, gw, lane);
+            attn_core<NKT>(AL, met, qf, cg, nk_all, nk_all, 0, 0, a.scale, a.att2, grow, ch.row, ch.n, h, gw, lane);
             wg_bar();
           }
         }
@@ -688,7 +709,7 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
       {
         const int lane = here(lane0), idx = here_s(idx0), r = lane & 15, kq = lane >> 4;
         if (gw < MT && l + 1 < a.layers) unwrite_rows<4>(a.s, kTD * 4, idx * 64, grow + gw * 16, min(n - gw * 16, 16), lane);
-        stage_ln<RPW>(tw, DEC ? a.s2 : a.s1, grow, n, lnv, At, xres, idx, wave, lane);
+        stage_ln<RPW>(tw, DEC ? a.s2 : a.s1, grow, n, lnv, At, xres, idx, wave ^ kGW, lane);
         wg_bar();
         team_put_ready();
         bf16_t* out = a.f + (idx * 4 + gw) * 16 + r;
@@ -722,8 +743,8 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
   // -------------------------------------------------------------------------------------------- group B
   uint4 bo[16], bq[16];   // strips of the output projection, then FFN2 | of the query projection, then the second output projection
   uint4 ln = {};
+  unsigned met = 0;       // group A's barriers so far
   float bias_o = 0.f, bias_q = 0.f;
-  unsigned chain = 0;
   if (gw == kGW - 1) {   // this member is here, and its places can be read
     unwrite_qkv(0, n0 + n1, idx, lane);
     team_put_ready();
@@ -769,14 +790,14 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
     {
       const int lane = here(lane0), r = lane & 15, h = here_s(idx0) & (kTH - 1);
       for (int c = c_first; c < n_chunks; c += CPR) {
-        wg_bar();
         if constexpr (DEC) {
           if (c == c_first) {   // (behind the keys and values)
+            group_wait(met_a, met + kGW);
             bias_q = gload((const float*)(wl + O::cbq) + h * 64 + gw * 16 + r);
             load_strip((const bf16_t*)(wl + O::cwq), h * 64 + gw * 16, kTD, 0, lane, bq);
           }
         }
-        wg_bar();
+        met += 2 * kGW;
         wg_bar();
       }
     }
@@ -791,15 +812,18 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
       keep_ln(lnv, ln, gw, lane);
       wg_bar();
       if (gw < MT && gw * 16 < n) {
+        const int m0 = gw * 16 + 4 * kq;
+        int to[4];
+        float res[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { to[i] = grow[m0 + i]; res[i] = xres[(m0 + i) * 16 + r]; }
         f32x4 acc[1];
         zero(acc);
         team_put_ready();
         mm16<1>(At + (gw * 16 + r) * kTLd + kq * 8, bo, acc);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int m = gw * 16 + 4 * kq + i;
-          if (m < n) put(a.s1 + (size_t)grow[m] * kTD + idx * 16 + r, acc[0][i] + bias_o + xres[m * 16 + r]);
-        }
+        for (int i = 0; i < 4; ++i)
+          if (m0 + i < n) put(a.s1 + (size_t)to[i] * kTD + idx * 16 + r, acc[0][i] + bias_o + res[i]);
       }
       wg_bar();
     }
@@ -820,7 +844,7 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
 #pragma unroll 1
         for (int c = c_first; c < n_chunks; c += CPR) {
           const int row = __builtin_amdgcn_readfirstlane(chunks[c].row), nr = __builtin_amdgcn_readfirstlane(chunks[c].n);
-          stage_ln_chunk(tw, a.s1, grow + row, nr, lnv, At, a.xr, h, wave, lane);
+          stage_ln_chunk(tw, a.s1, grow + row, nr, lnv, At, a.xr, h, wave ^ kGW, lane);
           wg_bar();
           {
             f32x4 acc[1];
@@ -831,7 +855,8 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
           }
           wg_bar();
           if (c + CPR >= n_chunks) next_strips();
-          wg_bar(); wg_bar(); wg_bar();
+          met += 2 * kGW;
+          wg_bar();
         }
       }
       // ---------------------------------------------------------------- output projection + residual
@@ -854,15 +879,17 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
         keep_ln(lnv, ln, gw, lane);
         wg_bar();
         if (gw < MT && gw * 16 < n) {
+          const int m0 = gw * 16 + 4 * kq;
+          int to[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) to[i] = grow[m0 + i];
           f32x4 acc[1];
           zero(acc);
           team_put_ready();
           mm16<1>(At + (gw * 16 + r) * kTLd + kq * 8, bq, acc);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int m = gw * 16 + 4 * kq + i;
-            if (m < n) put(a.s2 + (size_t)grow[m] * kTD + idx * 16 + r, acc[0][i] + bias_q + res[i]);
-          }
+          for (int i = 0; i < 4; ++i)
+            if (m0 + i < n) put(a.s2 + (size_t)to[i] * kTD + idx * 16 + r, acc[0][i] + bias_q + res[i]);
         }
         wg_bar();
       }
@@ -870,7 +897,7 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
     // ------------------------------------------------------------------ FFN1
     {
       const int lane = here(lane0), idx = here_s(idx0), r = lane & 15;
-      stage_ln<RPW>(tw, DEC ? a.s2 : a.s1, grow, n, lnv, At, xres, idx, wave, lane);
+      stage_ln<RPW>(tw, DEC ? a.s2 : a.s1, grow, n, lnv, At, xres, idx, wave ^ kGW, lane);
       wg_bar();
       wg_bar();
       if (!DEC) {
@@ -887,34 +914,56 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
       stage_ffn<ROWS>(tw, a.f, grow, n, At, gw, wave >> 2, lane);
       keep_ln(lnv, ln, gw, lane);
       wg_bar();
-      // The sum of an element stays one chain: the accumulators go from wave to wave through LDS, a count says how many
-      // slices are in (a wave waits for the ones before it only, so the wait ends).
-      f32x4 acc[MT];
-      zero(acc);
-      mm16<MT>(At + (gw * ROWS + r) * kTLd + kq * 8, bo, acc, [&]() {
-        if (gw > 0) {
-          while (__hip_atomic_load(slices, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < chain + gw) {}
-          asm volatile("" ::: "memory");
-#pragma unroll
-          for (int t = 0; t < MT; ++t) acc[t] = accx[((gw - 1) * MT + t) * 64 + lane];
-        }
-      });
-      if (gw + 1 < kSlices) {
-#pragma unroll
-        for (int t = 0; t < MT; ++t) accx[(gw * MT + t) * 64 + lane] = acc[t];
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      } else {
-        team_put_ready();
+      // The sum of an element stays one chain: the accumulators go from wave to wave through LDS, a place that is all ones is not
+      // written yet (a wave waits for the one before it only, so the wait ends).
+      const bool last = gw + 1 == kSlices;
+      int to[MT][4];
+      float res[MT][4];
+      if (last) {
 #pragma unroll
         for (int t = 0; t < MT; ++t)
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const int m = t * 16 + 4 * kq + i;
-            if (m < n) put(a.s + (size_t)grow[m] * kTD + idx * 16 + r, acc[t][i] + bias_o + xres[m * 16 + r]);
+            to[t][i] = grow[t * 16 + 4 * kq + i];
+            res[t][i] = xres[(t * 16 + 4 * kq + i) * 16 + r];
           }
+        team_put_ready();
       }
-      if (lane == 0) __hip_atomic_store(slices, chain + gw + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      chain += kSlices;
+      f32x4 acc[MT];
+      zero(acc);
+      mm16<MT>(At + (gw * ROWS + r) * kTLd + kq * 8, bo, acc, [&]() {
+        if (gw > 0) {
+          f32x4* from = accx + (gw - 1) * MT * 64 + lane;
+          bool there;
+          do {
+            asm volatile("" ::: "memory");
+            unsigned m = 0;
+#pragma unroll
+            for (int t = 0; t < MT; ++t) {
+              acc[t] = from[t * 64];
+              const uint4 v = __builtin_bit_cast(uint4, acc[t]);
+              m = max(max(m, v.x), max(max(v.y, v.z), v.w));
+            }
+            there = __builtin_amdgcn_ballot_w64(m == ~0u) == 0;
+          } while (!there);
+        }
+      });
+      if (!last) {
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+          accx[(gw * MT + t) * 64 + lane] = f32x4{__uint_as_float(written(acc[t][0])), __uint_as_float(written(acc[t][1])),
+                                                  __uint_as_float(written(acc[t][2])), __uint_as_float(written(acc[t][3]))};
+      } else {
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (t * 16 + 4 * kq + i < n) put(a.s + (size_t)to[t][i] * kTD + idx * 16 + r, acc[t][i] + bias_o + res[t][i]);
+      }
+      if (gw > 0) {
+#pragma unroll
+        for (int t = 0; t < MT; ++t) accx[((gw - 1) * MT + t) * 64 + lane] = unwritten4();
+      }
       wg_bar();
     }
   }
