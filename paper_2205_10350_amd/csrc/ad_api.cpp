@@ -47,7 +47,7 @@ struct Plan {
   // drafter a second block of the same layout lies act2_shift bytes further on, for the drafter's
   // encoder running beside the verifier's on a stream of its own
   size_t act_begin = 0, act_end = 0, act2_shift = 0;
-  size_t pe, x, s, xa, q, att, tk, tv, f, team_s1, team_s2, team_xr, team_att2, part_val, part_idx, o_hat, o_val, logits, draft_lp, draft_col;
+  size_t pe, x, s, xa, q, att, tk, tv, f, team_slots, team_hop, team_k, team_v, part_val, part_idx, o_hat, o_val, logits, draft_lp, draft_col;
   size_t cache_k, cache_v, cache_layer_stride;          // [NL][B*l_cap, d]
   size_t mem_k[2], mem_v[2], mem_layer_stride;          // per model: [NL][B*max_src, d]
   size_t row_tok, row_pos, row_seq, row_dst, row_dst2, row_start, self_desc, cross_desc;
@@ -78,12 +78,12 @@ static Plan make_plan(const ad_config& c, bool with_drafter) {
   p.tk = take(m * d * p.esz);
   p.tv = take(m * d * p.esz);
   p.f = take(m * (size_t)c.d_ffn * p.esz);
-  // rows inside a layer of a team launch
-  const size_t tm = c.dtype == AD_BF16 && d == kTeamD ? std::min(m, (size_t)kTeamXRows) : 0;
-  p.team_s1 = take(tm * d * 4);
-  p.team_s2 = take(tm * d * 4);
-  p.team_xr = take(tm * d * 4);
-  p.team_att2 = take(tm * d * 2);
+  // what a team launch passes on: inside a layer, from layer to layer, keys and values that have no place in a cache
+  const size_t team_layers = c.dtype == AD_BF16 && d == kTeamD && c.d_ffn == kTeamF ? std::max(c.enc_layers, c.dec_layers) : 0;
+  p.team_slots = take(team_layers ? 8 * TeamSlot::kBytes : 0);
+  p.team_hop = take(team_layers * kTeamHopBytes);
+  p.team_k = take(team_layers * kTeamKvBytes);
+  p.team_v = take(team_layers * kTeamKvBytes);
   p.row_tok = take(m * 4); p.row_pos = take(m * 4); p.row_seq = take(m * 4); p.row_dst = take(m * 4); p.row_dst2 = take(m * 4);
   p.row_start = take((B + 1) * 4);
   p.self_desc = take(2 * B * sizeof(SeqDesc));    // the drafter has two per sequence (mask rows, prefix rows)
@@ -328,43 +328,64 @@ static bool team_layout_ok(const ad_config& c, const ModelW& w, bool dec) {
   }
   return true;
 }
-// Deals n problems of rows[i] (+ rows2[i]) packed rows out to teams, whole problems, in order; up to eight problems get a
-// team each, more are cut where the running row count passes an eighth of all.  false: a team would exceed the limits.
-static bool team_deal(const int* rows, const int* rows2, int n, TeamRun* t) {
-  int live = 0, M = 0;
+// Deals n problems of rows[i] (+ rows2[i]) packed rows out to teams on up to `xcds` XCDs.  Problems of more than 16 rows are cut into
+// pieces of at most 16 (a row tile) where there are XCDs for all of them, the teams of a problem then read each other's keys and
+// values; else whole problems, in order: up to eight problems get a team each, more are cut where the running row count passes an eighth of all.
+// XCDs left over take turns over the layers.  false: a team would exceed the limits.
+static bool team_deal(const int* rows, const int* rows2, int n, int xcds, int layers, TeamRun* t) {
+  int live = 0, M = 0, R0 = 0, pieces = 0;
   for (int i = 0; i < n; ++i) {
     const int w = rows[i] + (rows2 ? rows2[i] : 0);
-    M += w;
+    M += w; R0 += rows[i];
     live += w > 0;
+    pieces += (w + 15) / 16;
   }
   if (live < 1) return false;
   TeamArgs& a = t->a;
-  int team = -1, last_part = -1, at = 0, r0 = 0, r1 = 0, team_rows = 0, in_team = 0;
-  if (rows2)
-    for (int i = 0; i < n; ++i) r1 += rows[i];
   t->max_rows = 0;
-  for (int i = 0; i < n; ++i) {
-    const int w = rows[i] + (rows2 ? rows2[i] : 0);
-    if (w > 0) {
-      const int part = live <= 8 ? last_part + 1 : std::max(last_part, std::min(7, (int)((2LL * at + w) * 8 / (2LL * M))));
-      if (part != last_part) {
-        last_part = part;
+  a.shared = 0;
+  int team = -1, r0 = 0, r1 = R0;
+  if (pieces <= xcds) {
+    for (int i = 0; i < n; ++i) {
+      const int w = rows[i] + (rows2 ? rows2[i] : 0), p = (w + 15) / 16;
+      if (p > 1) a.shared = 1;
+      for (int j = 0; j < p; ++j) {
+        const int lo = w * j / p, hi = w * (j + 1) / p, lo0 = std::min(lo, rows[i]), hi0 = std::min(hi, rows[i]);
         ++team;
-        a.row_lo[0][team] = r0; a.row_lo[1][team] = r1; a.prob[team] = i;
-        team_rows = 0; in_team = 0;
+        a.row_lo[0][team] = r0 + lo0; a.row_n[0][team] = hi0 - lo0;
+        a.row_lo[1][team] = r1 + lo - lo0; a.row_n[1][team] = (hi - hi0) - (lo - lo0);
+        a.prob_lo[team] = i; a.prob_n[team] = 1;
+        t->max_rows = std::max(t->max_rows, hi - lo);
       }
+      r0 += rows[i]; r1 += rows2 ? rows2[i] : 0;
     }
-    if (team >= 0) {
-      ++in_team;
-      if (in_team * (rows2 ? 2 : 1) > 64) return false;   // a lane each when the team's chunks are listed
+  } else {
+    int last_part = -1, at = 0;
+    for (int i = 0; i < n; ++i) {
+      const int w = rows[i] + (rows2 ? rows2[i] : 0);
+      if (w > 0) {
+        const int part = live <= 8 ? last_part + 1 : std::max(last_part, std::min(7, (int)((2LL * at + w) * 8 / (2LL * M))));
+        if (part != last_part) {
+          last_part = part;
+          ++team;
+          a.row_lo[0][team] = r0; a.row_lo[1][team] = r1; a.row_n[0][team] = a.row_n[1][team] = 0;
+          a.prob_lo[team] = i; a.prob_n[team] = 0;
+        }
+      }
+      if (team >= 0) {
+        if (++a.prob_n[team] * (rows2 ? 2 : 1) > 64) return false;   // a lane each when the team's chunks are listed
+        a.row_n[0][team] += rows[i]; a.row_n[1][team] += rows2 ? rows2[i] : 0;
+        t->max_rows = std::max(t->max_rows, a.row_n[0][team] + a.row_n[1][team]);
+      }
+      at += w; r0 += rows[i]; r1 += rows2 ? rows2[i] : 0;
     }
-    team_rows += w; at += w; r0 += rows[i]; r1 += rows2 ? rows2[i] : 0;
-    t->max_rows = std::max(t->max_rows, team_rows);
   }
   a.n_teams = team + 1;
-  a.row_lo[0][team + 1] = r0; a.row_lo[1][team + 1] = r1; a.prob[team + 1] = n;
+  a.stations = std::max(1, std::min(std::min(xcds / a.n_teams, layers), kTeamStations));
   return t->max_rows <= kTeamMaxRows;
 }
+// (longer blocks and sources are the launches': their graphs are as fast)
+static bool team_rows_ok(const int* rows, int n) { return *std::max_element(rows, rows + n) <= kTeamMaxRows; }
 static bool team_usable(ad_ctx* c, int model, bool dec) {
   if (!c->team_on || !c->can_team[model][dec]) return false;
   if (c->team_rest > 0) { --c->team_rest; return false; }
@@ -378,10 +399,9 @@ static void team_common(const ad_ctx* c, int model, bool dec, int words, TeamRun
   a.scale = 1.0f / sqrtf(64.0f);
   a.form_ticks = (unsigned)c->team_ticks;
   a.w = (const char*)(dec ? c->w[model].dec[0].self.wqkv : c->w[model].enc[0].self.wqkv);
-  a.x = c->at<float>(p.x); a.s = c->at<float>(p.s);
-  a.s1 = c->at<float>(p.team_s1); a.s2 = c->at<float>(p.team_s2); a.xr = c->at<float>(p.team_xr); a.att2 = c->at<bf16_storage>(p.team_att2);
-  a.xa = c->at<bf16_storage>(p.xa); a.q = c->at<bf16_storage>(p.q); a.att = c->at<bf16_storage>(p.att); a.f = c->at<bf16_storage>(p.f);
-  a.K = c->at<bf16_storage>(p.tk); a.V = c->at<bf16_storage>(p.tv); a.kv_stride = 0;
+  a.x = c->at<float>(p.x); a.xa = c->at<bf16_storage>(p.xa); a.s = c->at<float>(p.s);
+  a.slots = c->at<char>(p.team_slots); a.hop = c->at<char>(p.team_hop);
+  a.K = c->at<bf16_storage>(p.team_k); a.V = c->at<bf16_storage>(p.team_v); a.kv_stride = kTeamKvBytes;
   a.Km = dec ? (const bf16_storage*)(c->ws + p.mem_k[model]) : nullptr;
   a.Vm = dec ? (const bf16_storage*)(c->ws + p.mem_v[model]) : nullptr;
   a.m_stride = p.mem_layer_stride;
@@ -392,9 +412,9 @@ static void team_common(const ad_ctx* c, int model, bool dec, int words, TeamRun
 static ad_ctx::TeamPart team_part(const TeamRun* t) {
   ad_ctx::TeamPart k{};
   if (!t) return k;
-  int i = 0;
-  k[i++] = t->a.n_teams; k[i++] = t->max_rows > 16 ? 2 : 1; k[i++] = t->max_keys > 64 ? 2 : 1;
-  for (int j = 1; j <= 8; ++j) { k[i++] = j <= t->a.n_teams ? t->a.row_lo[0][j] : 0; k[i++] = j <= t->a.n_teams ? t->a.prob[j] : 0; k[i++] = j <= t->a.n_teams ? t->a.prob[j - 1] : 0; }
+  const TeamArgs& a = t->a;
+  k[0] = a.n_teams | a.stations << 8 | (t->max_rows > 16 ? 1 << 16 : 0) | (t->max_keys > 64 ? 1 << 17 : 0) | a.shared << 18;
+  for (int j = 0; j < a.n_teams; ++j) { k[1 + 3 * j] = a.row_n[0][j]; k[2 + 3 * j] = a.prob_lo[j]; k[3 + 3 * j] = a.prob_n[j]; }
   return k;
 }
 // A team launch's arguments say how the rows are dealt out; with many sequences that hardly ever comes back, and four launches
@@ -930,11 +950,12 @@ int ad_encode(ad_ctx* c, int model, const int32_t* src, const int32_t* src_len, 
   // the layers as one launch where the teams can hold the rows; the two models' encoders side by side need XCDs of their own
   TeamRun run;
   run.max_keys = c->fw_max_rows;
-  bool team = mapped && run.max_keys <= kTeamMaxKeys && team_deal(src_len, nullptr, B, &run) && (!side.on || run.a.n_teams <= 4) &&
+  bool team = mapped && run.max_keys <= kTeamMaxKeys && team_rows_ok(src_len, B) &&
+              team_deal(src_len, nullptr, B, c->has_drafter && c->overlap_encoders ? 4 : 8, cf.enc_layers, &run) && (!side.on || run.a.n_teams <= 4) &&
               team_usable(c, model, false);
   if (team) {
     team_common(c, model, false, model, &run);
-    if (side.on) run.a.xcd0 = 8 - run.a.n_teams;
+    if (side.on) run.a.xcd0 = 8 - run.a.n_teams * run.a.stations;
   }
   auto launches = [&]() { encode_launches(c, model, dev, M, B, team ? &run : nullptr); };
   const unsigned long long key = (1ull << 63) | ((unsigned long long)model << 62) | shape_key(M, c->fw_max_rows, B, side.on ? 1 : 0);
@@ -1135,7 +1156,8 @@ static int verify_call(ad_ctx* c, const int32_t* draft, const int32_t* k, int32_
   }
   TeamRun run;
   run.max_keys = std::max(self_keys, cross_keys);
-  bool team = mapped && !static_scratch && run.max_keys <= kTeamMaxKeys && c->can_team[AD_VERIFIER][1] && team_deal(k, nullptr, B, &run) && team_usable(c, AD_VERIFIER, true);
+  bool team = mapped && !static_scratch && run.max_keys <= kTeamMaxKeys && c->can_team[AD_VERIFIER][1] && team_rows_ok(k, B) &&
+              team_deal(k, nullptr, B, 8, cf.dec_layers, &run) && team_usable(c, AD_VERIFIER, true);
   if (team) {
     team_common(c, AD_VERIFIER, true, 2, &run);
     run.a.K = (bf16_storage*)(c->ws + p.cache_k); run.a.V = (bf16_storage*)(c->ws + p.cache_v); run.a.kv_stride = p.cache_layer_stride;
@@ -1268,7 +1290,7 @@ int ad_draft_nat(ad_ctx* c, int k, int32_t* draft_out) {
     if (!c->h_finished[b]) { seg[0].push_back(k); seg[1].push_back(c->h_len[b] + 1); }
   const TeamFail tf = team_fail_words(c, AD_DRAFTER);
   run.max_keys = std::max(self_keys, *std::max_element(c->h_src_len[AD_DRAFTER].begin(), c->h_src_len[AD_DRAFTER].begin() + B));
-  bool team = watch && run.max_keys <= kTeamMaxKeys && c->can_team[AD_DRAFTER][1] && team_deal(seg[0].data(), seg[1].data(), live, &run) && team_usable(c, AD_DRAFTER, true);
+  bool team = watch && run.max_keys <= kTeamMaxKeys && c->can_team[AD_DRAFTER][1] && team_deal(seg[0].data(), seg[1].data(), live, 8, cf.dec_layers, &run) && team_usable(c, AD_DRAFTER, true);
   if (team) {
     team_common(c, AD_DRAFTER, true, 2, &run);
     run.a.head_only = 1; run.a.prob2_off = live;

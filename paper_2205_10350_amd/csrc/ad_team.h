@@ -10,6 +10,7 @@ typedef unsigned short bf16_storage;
 constexpr int kTeamMembers = 32;                 // workgroups of a team: the compute units of an XCD
 constexpr int kTeamD = 512, kTeamF = 2048;       // the model widths the kernel is built for (bf16, head width 64)
 constexpr int kTeamMaxRows = 32, kTeamMaxKeys = 128;
+constexpr int kTeamStations = 2;                 // XCDs that take turns over a team's layers: one requests strips while the other works
 constexpr int kTeamXRows = 8 * kTeamMaxRows;     // packed rows of a launch
 constexpr int kTeamFormTicks = 30000;            // 0.3 ms: an idle chip has a team together in a few us
 
@@ -26,21 +27,29 @@ struct TeamOff {
   static constexpr int ln_lg = w1 + kFfn, ln_lb = ln_lg + kVec;           // the layer's last
   static constexpr int kLayerBytes = ln_lb + kVec;
 };
+// A team's XCDs (stations) have buffers of their own for the rows on their way inside a layer: bytes from the first of them.
+struct TeamSlot {
+  static constexpr int kRow16 = kTeamMaxRows * kTeamD * 2, kRow32 = 2 * kRow16;
+  static constexpr int q = 0, att = kRow16, att2 = 2 * kRow16, s1 = 3 * kRow16, s2 = s1 + kRow32, s = s2 + kRow32, xr = s + kRow32, f = xr + kRow32;
+  static constexpr int kBytes = f + kTeamMaxRows * kTeamF * 2;
+};
+constexpr int kTeamHopBytes = 8 * kTeamMaxRows * kTeamD * 4;   // a layer's results on their way to the next XCD: [team][row][512] fp32
+constexpr int kTeamKvBytes = kTeamXRows * kTeamD * 2;          // a layer's keys (values) where they have no place in a cache: [packed row][512]
 struct TeamArgs {
-  int n_teams, xcd0, layers;          // teams on the XCDs xcd0, xcd0 + 1, ...
+  int n_teams, stations;              // team t's layers l, l + stations, .. run on XCD xcd0 + t + n_teams * (l % stations)
+  int xcd0, layers;
   int head_only;                      // in the last layer only segment 0's rows go on after the key / value projection
-  int row_lo[2][9];                   // packed rows of team t: segments [row_lo[s][t], row_lo[s][t + 1])
-  int prob[9];                        // its attention problems (descriptors)
+  int shared;                         // teams read each other's keys and values
+  int row_lo[2][8], row_n[2][8];      // packed rows of team t, two segments
+  int prob_lo[8], prob_n[8];          // its attention problems (descriptors); the rows of a problem that are another team's are left to that
   int prob2_off;                      // the descriptors of segment 1's problems lie this much further on (0: none)
   unsigned form_ticks;                // how long the first barrier is waited for (10 ns each; 0: not at all)
   float scale;
   const char* w;                      // layer 0 (the others TeamOff::kLayerBytes apart)
   const float* x;                     // the embedded rows, fp32 and bf16
   const bf16_storage* xa;
-  float* s;                           // rows passed on inside a layer; in s the last layer's for the LayerNorm that follows
-  float *s1, *s2, *xr;                // (kTeamXRows packed rows)
-  bf16_storage* att2;
-  bf16_storage *q, *att, *f;
+  float* s;                           // the last layer's rows, for the LayerNorm that follows
+  char *slots, *hop;                  // [8] TeamSlot, [layers] kTeamHopBytes
   bf16_storage *K, *V;                // keys / values of layer 0
   size_t kv_stride;                   // bytes to the next layer's
   const bf16_storage *Km, *Vm;        // memory keys / values

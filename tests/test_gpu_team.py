@@ -156,6 +156,67 @@ def test_drafter_as_one_launch(lens, k):
         ctx.close()
 
 
+@pytest.mark.parametrize("rows", [[17], [32], [20, 3], [17, 32, 18], [32, 17, 25, 20], [16, 17, 1, 1, 1, 1], [25, 25, 25, 25, 1]])
+def test_sequences_cut_into_pieces_on_several_xcds(rows):
+    """Two to eight teams, the pieces of a sequence reading each other's keys and values, one XCD a team and two that take turns (up to four teams);
+    against prefixes of 0 and 40 tokens (own keys in one and in two key ranges), eagerly and replayed; the last: more pieces than XCDs."""
+    rng = np.random.default_rng(sum(rows) + len(rows))
+    srcs = [_tokens(rng, 8 + 5 * i) for i in range(len(rows))]
+    blk = [list(_tokens(rng, r)) for r in rows]
+    ctx = _context()
+    try:
+        ctx.set_option(ad.AD_OPT_TEAMS, 0)
+        pre = ctx.decode_greedy(srcs, max_out=[30] * len(rows))[0]
+        got = {}
+        for on in (0, 1):
+            ctx.set_option(ad.AD_OPT_TEAMS, on)
+            out = []
+            for _ in range(4):      # (a graph from the third time where the shape has one)
+                ctx.encode(ad.AD_VERIFIER, srcs)
+                for step in range(2):
+                    launched, v = _launched(ctx, lambda: ctx.verify(blk, want_verified=True))
+                    assert launched == on
+                    out += [v[2], ctx.debug_logits().view(np.uint32).copy()]
+                    if step == 0:
+                        ctx.encode(ad.AD_VERIFIER, srcs)
+                        n, _ = ctx.verify([p[:30] for p in pre])
+                        assert list(n) == [30] * len(rows)
+            got[on] = out
+        for x, y in zip(got[0], got[1]):
+            assert np.array_equal(x, y)
+        assert ctx.get_option(ad.AD_OPT_TEAM_FAILURES) == 0
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("prefix,k", [(0, 17), (15, 1), (20, 30), (40, 40), (60, 40)])
+def test_drafts_of_more_rows_than_a_team_holds(prefix, k):
+    """Mask rows and prefix rows of one sequence over 2, 2, 4, 6 and 7 teams, every piece seeing all of them; teams without a mask row
+    end after the last layer's keys and values."""
+    rng = np.random.default_rng(prefix + k)
+    srcs = [_tokens(rng, 21)]
+    ctx = _context(drafter=True)
+    try:
+        ctx.set_option(ad.AD_OPT_TEAMS, 0)
+        g = ctx.decode_greedy(srcs, max_out=[96])[0][0]
+        assert len(g) == 96
+        got = []
+        for on in (0, 1):
+            ctx.set_option(ad.AD_OPT_TEAMS, on)
+            ctx.encode(ad.AD_VERIFIER, srcs)
+            ctx.encode(ad.AD_DRAFTER, srcs)
+            for lo in range(0, prefix, 30):
+                n, _ = ctx.verify([g[lo:min(lo + 30, prefix)]])
+                assert n[0] == min(30, prefix - lo)
+            launched, d = _launched(ctx, lambda: ctx.draft_nat(k).copy())
+            assert launched == on
+            got.append((d, ctx.debug_logits().view(np.uint32).copy()))
+        assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+        assert ctx.get_option(ad.AD_OPT_TEAM_FAILURES) == 0
+    finally:
+        ctx.close()
+
+
 def test_a_team_that_does_not_come_together_leaves_the_call_to_the_launches():
     """The wait of the team's barrier set to nothing: every kernel gives up and exits, the calls are repeated launch by launch (the
     encoders too) with the results they always have, and the launches keep the next calls."""
