@@ -17,7 +17,7 @@
 // products 2.6 us a layer (FFN2's chain through four slices 0.9, the others 0.25-0.35 each), seven exchanges of 0.4 to 1.2, the two
 // attentions 2.2, LayerNorms 0.9; with one XCD a team (32 sequences) strips on their way delay the exchanges by 2 to 3 us a layer.
 // Verify forward of the base model, us, with barriers between the stages on one XCD / this way, one machine: 1 sequence of 1, 4, 8, 16, 17,
-// 25, 32 rows 139, 143, 144, 150, 167, 178, 178 / 83, 92, 96, 108, 109, 111, 111; 8 sequences of 25 rows 207 / 164; 32 sequences of 1, 2, 4, 6, 8 rows
+// 25, 32 rows 139, 143, 144, 150, 167, 178, 178 / 80, 90, 94, 106, 108, 110, 110; 8 sequences of 25 rows 207 / 164; 32 sequences of 1, 2, 4, 6, 8 rows
 // 164, 166, 176, 196, 206 / 112, 116, 131, 157, 171.  A launch per stage: 159-172, 172, 175, 180, 178, 181, 183; 222; 177, 182, 195, 221, 231
 // (the launches replayed as a graph; a call shape's first two appearances go out launch by launch in 223).  33 to 64 rows on one XCD, four row
 // tiles, were 240 and more / 184-191 with barriers: hence at most 32 rows a team.
@@ -429,9 +429,9 @@ __device__ __forceinline__ void attn_values(const AttnLds& L, const AttnRegs<NKT
     }
   }
 }
-// (two barriers of the group; the values are written ahead of the first)
+// (two barriers, of the group by its count, of the workgroup without; the values are written ahead of the first)
 template <int NKT>
-__device__ __forceinline__ void attn_core(const AttnLds& L, unsigned& target, const uint4 (&qf)[2], const AttnRegs<NKT>& g, int nk_all, int nk_base,
+__device__ __forceinline__ void attn_core(const AttnLds& L, unsigned* target, const uint4 (&qf)[2], const AttnRegs<NKT>& g, int nk_all, int nk_base,
                                           int off, int causal, float scale, bf16_t* att, int row, int n_rows,
                                           int h, int wave, int lane) {
   constexpr int LDV = AttnDims<NKT>::LDV, KT = AttnDims<NKT>::KT;
@@ -455,7 +455,8 @@ __device__ __forceinline__ void attn_core(const AttnLds& L, unsigned& target, co
     }
     if (r == 0) *(float4*)(L.xmax + tile * 16 + 4 * kq) = float4{m[0], m[1], m[2], m[3]};
   }
-  group_bar(L.count, target, lane);   // values and maxima
+  if (target) group_bar(L.count, *target, lane);   // values and maxima
+  else wg_bar();
   {
     f32x4 mx = *(const f32x4*)(L.xmax + 4 * kq);
 #pragma unroll
@@ -478,7 +479,8 @@ __device__ __forceinline__ void attn_core(const AttnLds& L, unsigned& target, co
       }
     }
   }
-  group_bar(L.count, target, lane);   // probabilities
+  if (target) group_bar(L.count, *target, lane);   // probabilities
+  else wg_bar();
   f32x4 O = f32x4{0.f, 0.f, 0.f, 0.f}, ps = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int kb = 0; kb < NKT / 2; ++kb) {
@@ -676,13 +678,44 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
       const bool in_time = !AHEAD || l == 0;                   // this layer's strips are requested on the way
       const char* wl = a.w + (size_t)l * O::kLayerBytes;       // the layer's matrices and vectors
       AttnRegs<NKT> cg, eg;   // the memory's keys and values; the own ones that earlier forwards wrote (of the first chunk)
+      constexpr bool kEarly = AHEAD && DEC && NKT == 4;   // (where the registers hold them beside two sets of strips)
       bool early = false;
+      const int h = idx0 & (kTH - 1);
+      auto memory_keys = [&](const TeamChunk& ch, int lane) {
+        attn_request<NKT, false>((const bf16_t*)((const char*)a.Km + (size_t)l * a.m_stride), (const bf16_t*)((const char*)a.Vm + (size_t)l * a.m_stride),
+                                 ch.kv_cross, min(ch.nk_cross, 16 * NKT), h, gw, lane, cg);
+      };
       // ---------------------------------------------------------------- Q, K, V
       {
         const int lane = here(lane0), idx = here_s(idx0), r = lane & 15, kq = lane >> 4;
-        if constexpr (AHEAD && DEC && NKT == 4) {
+        if (AHEAD && l > 0) {
+          // The strips have gone through the L2 and taken the places of the rows to come with them: looked at once they are back
+          // (a first look past the L2 takes 0.8 to 1 us, and the row's arrival with it).
+          team_put_ready();
+          if (gw == kGW - 1) {
+            float seen = 0.f;
+            if (lane < n) seen = ld4_l2(xatt, lane * (kTD * 2) + (idx & (kTH - 1)) * 128);
+            if (c_first < n_chunks) {
+              const int first_new = ch0.causal ? ch0.nk_base : 0, nk_all = min(ch0.causal ? ch0.nk_base + ch0.off + ch0.n : ch0.nk_base, 16 * NKT);
+              const unsigned at = (idx & (kTH - 1)) * 128;
+              if (lane < ch0.n) seen += ld4_l2(xq, (unsigned)(ch0.row + lane) * (kTD * 2) + at);
+#pragma unroll
+              for (int t = 0; t < NKT / 4; ++t) {
+                const int key = first_new + 64 * t + lane;
+                const unsigned off = (unsigned)(ch0.kv_self + key) * (kTD * 2) + at;
+                if (key < nk_all) {
+                  seen += ld4_l2((const char*)a.K + (size_t)l * a.kv_stride, off);
+                  seen += ld4_l2((const char*)a.V + (size_t)l * a.kv_stride, off);
+                }
+              }
+            }
+            asm volatile("" :: "v"(seen));
+          }
+        }
+        if constexpr (kEarly) {
           if (c_first < n_chunks) {
             const TeamChunk& ch = ch0;
+            memory_keys(ch, lane);
             early = ch.causal && ch.nk_base > 0;
             if (early)
               attn_request<NKT, false>((const bf16_t*)((const char*)a.K + (size_t)l * a.kv_stride), (const bf16_t*)((const char*)a.V + (size_t)l * a.kv_stride),
@@ -727,11 +760,6 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
       }
       if (a.head_only && l + 1 == a.layers) { n = n0; n_chunks = n_chunks0; }   // only segment 0 goes on
       // ---------------------------------------------------------------- self-attention
-      const int h = idx0 & (kTH - 1);
-      auto memory_keys = [&](const TeamChunk& ch, int lane) {
-        attn_request<NKT, false>((const bf16_t*)((const char*)a.Km + (size_t)l * a.m_stride), (const bf16_t*)((const char*)a.Vm + (size_t)l * a.m_stride),
-                                 ch.kv_cross, min(ch.nk_cross, 16 * NKT), h, gw, lane, cg);
-      };
       {
         const int lane = here(lane0), r = lane & 15, kq = lane >> 4;
         const bf16_t* Kl = (const bf16_t*)((const char*)a.K + (size_t)l * a.kv_stride);
@@ -753,15 +781,14 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
             for (int s = 0; s < 2; ++s) seen.add(qf[s]);
             return kv && seen.all();
           });
-          if constexpr (AHEAD && DEC && NKT == 4) {
+          if constexpr (kEarly) {
             if (early && c == c_first) attn_older<NKT>(eg, ch.nk_base, gw, lane, g);
           }
-          team_put_ready();
-          if constexpr (DEC) {
+          if constexpr (DEC && !kEarly) {
             if (c == c_first) memory_keys(ch, lane);
           }
           attn_values<NKT>(AL, g, nk_all, gw, lane);
-          attn_core<NKT>(AL, met, qf, g, nk_all, ch.nk_base, ch.off, ch.causal, a.scale, xatt, ch.row, ch.n, h, gw, lane);
+          attn_core<NKT>(AL, in_time ? &met : nullptr, qf, g, nk_all, ch.nk_base, ch.off, ch.causal, a.scale, xatt, ch.row, ch.n, h, gw, lane);
           wg_bar();
         }
       }
@@ -796,7 +823,7 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
             uint4 qf[2];
 #pragma unroll
             for (int s = 0; s < 2; ++s) qf[s] = *(const uint4*)(Qt + min(r, ch.n - 1) * kCrossqQld + kq * 8 + 32 * s);
-            attn_core<NKT>(AL, met, qf, cg, nk_all, nk_all, 0, 0, a.scale, xatt2, ch.row, ch.n, h, gw, lane);
+            attn_core<NKT>(AL, &met, qf, cg, nk_all, nk_all, 0, 0, a.scale, xatt2, ch.row, ch.n, h, gw, lane);
             wg_bar();
           }
         }
@@ -935,6 +962,7 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
     // ------------------------------------------------------------------ Q, K, V
     {
       const int lane = here(lane0), idx = here_s(idx0);
+      if (AHEAD && l > 0) team_put_ready();   // (behind the strips: see group A)
       if (gw < MT) {
         unwrite_rows<4>(xs1, kTD * 4, idx * 64, gw * 16, min(n - gw * 16, 16), lane);
         if constexpr (DEC) unwrite_rows<4>(xs2, kTD * 4, idx * 64, gw * 16, min(n - gw * 16, 16), lane);
@@ -973,7 +1001,11 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
             request_queries(l, idx, lane);
           }
         }
-        met += 2 * kGW;
+        if (in_time) {
+          met += 2 * kGW;
+        } else {
+          wg_bar(); wg_bar();
+        }
         wg_bar();
       }
     }
