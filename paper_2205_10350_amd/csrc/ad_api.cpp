@@ -47,7 +47,7 @@ struct Plan {
   // drafter a second block of the same layout lies act2_shift bytes further on, for the drafter's
   // encoder running beside the verifier's on a stream of its own
   size_t act_begin = 0, act_end = 0, act2_shift = 0;
-  size_t pe, x, s, xa, q, att, tk, tv, f, team_slots, team_hop, team_k, team_v, part_val, part_idx, o_hat, o_val, logits, draft_lp, draft_col;
+  size_t pe, x, s, xa, q, att, tk, tv, f, team_slots, team_hop, team_k, team_v, team_kv_stride, part_val, part_idx, o_hat, o_val, logits, draft_lp, draft_col;
   size_t cache_k, cache_v, cache_layer_stride;          // [NL][B*l_cap, d]
   size_t mem_k[2], mem_v[2], mem_layer_stride;          // per model: [NL][B*max_src, d]
   size_t row_tok, row_pos, row_seq, row_dst, row_dst2, row_start, self_desc, cross_desc;
@@ -79,11 +79,13 @@ static Plan make_plan(const ad_config& c, bool with_drafter) {
   p.tv = take(m * d * p.esz);
   p.f = take(m * (size_t)c.d_ffn * p.esz);
   // what a team launch passes on: inside a layer, from layer to layer, keys and values that have no place in a cache
-  const size_t team_layers = c.dtype == AD_BF16 && d == kTeamD && c.d_ffn == kTeamF ? std::max(c.enc_layers, c.dec_layers) : 0;
-  p.team_slots = take(team_layers ? 8 * TeamSlot::kBytes : 0);
+  const bool team32 = c.dtype == AD_F32 && team_f32_widths((int)d, c.n_heads, c.d_ffn);
+  const size_t team_layers = team32 || (c.dtype == AD_BF16 && d == kTeamD && c.d_ffn == kTeamF) ? std::max(c.enc_layers, c.dec_layers) : 0;
+  p.team_slots = take(team32 ? team_layers * 8 * team_f32_slot_bytes((int)d) : team_layers ? 8 * TeamSlot::kBytes : 0);
   p.team_hop = take(team_layers * kTeamHopBytes);
-  p.team_k = take(team_layers * kTeamKvBytes);
-  p.team_v = take(team_layers * kTeamKvBytes);
+  p.team_kv_stride = team32 ? kTeamXRows * d * 4 : kTeamKvBytes;
+  p.team_k = take(team_layers * p.team_kv_stride);
+  p.team_v = take(team_layers * p.team_kv_stride);
   p.row_tok = take(m * 4); p.row_pos = take(m * 4); p.row_seq = take(m * 4); p.row_dst = take(m * 4); p.row_dst2 = take(m * 4);
   p.row_start = take((B + 1) * 4);
   p.self_desc = take(2 * B * sizeof(SeqDesc));    // the drafter has two per sequence (mask rows, prefix rows)
@@ -300,11 +302,11 @@ static VerifyTables tables(const ad_ctx* c) {
 }
 
 // ---- stacks of layers as one launch
-static bool team_layout_ok(const ad_config& c, const ModelW& w, bool dec) {
-  if (c.dtype != AD_BF16 || c.d_model != kTeamD || c.n_heads != kTeamD / 64 || c.d_ffn != kTeamF) return false;
+template <int D, int F, int ESZ>
+static bool team_offsets_ok(const ModelW& w, bool dec) {
   auto is = [](const void* p, const void* base, int off) { return (const char*)p == (const char*)base + off; };
   if (dec) {
-    typedef TeamOff<true> O;
+    typedef TeamOff<true, D, F, ESZ> O;
     const char* b = (const char*)w.dec[0].self.wqkv;
     for (const DecLayerW& L : w.dec) {
       if (!is(L.self.wqkv, b, O::wqkv) || !is(L.self.wo, b, O::wo) || !is(L.self.bqkv, b, O::bqkv) || !is(L.self.bo, b, O::bo) ||
@@ -317,7 +319,7 @@ static bool team_layout_ok(const ad_config& c, const ModelW& w, bool dec) {
     }
     return true;
   }
-  typedef TeamOff<false> O;
+  typedef TeamOff<false, D, F, ESZ> O;
   const char* b = (const char*)w.enc[0].self.wqkv;
   for (const EncLayerW& L : w.enc) {
     if (!is(L.self.wqkv, b, O::wqkv) || !is(L.self.wo, b, O::wo) || !is(L.self.bqkv, b, O::bqkv) || !is(L.self.bo, b, O::bo) ||
@@ -328,11 +330,18 @@ static bool team_layout_ok(const ad_config& c, const ModelW& w, bool dec) {
   }
   return true;
 }
+static bool team_layout_ok(const ad_config& c, const ModelW& w, bool dec) {
+  if (c.dtype == AD_F32) {
+    if (!team_f32_widths(c.d_model, c.n_heads, c.d_ffn)) return false;
+    return c.d_model == 128 ? team_offsets_ok<128, 512, 4>(w, dec) : team_offsets_ok<512, 2048, 4>(w, dec);
+  }
+  return c.dtype == AD_BF16 && c.d_model == kTeamD && c.n_heads == kTeamD / 64 && c.d_ffn == kTeamF && team_offsets_ok<kTeamD, kTeamF, 2>(w, dec);
+}
 // Deals n problems of rows[i] (+ rows2[i]) packed rows out to teams on up to `xcds` XCDs.  Problems of more than 16 rows are cut into
 // pieces of at most 16 (a row tile) where there are XCDs for all of them, the teams of a problem then read each other's keys and
 // values; else whole problems, in order: up to eight problems get a team each, more are cut where the running row count passes an eighth of all.
-// XCDs left over take turns over the layers.  false: a team would exceed the limits.
-static bool team_deal(const int* rows, const int* rows2, int n, int xcds, int layers, TeamRun* t) {
+// XCDs left over take turns over the layers.  false: a team would exceed its limits (max_rows).
+static bool team_deal(const int* rows, const int* rows2, int n, int xcds, int layers, int max_rows, TeamRun* t) {
   int live = 0, M = 0, R0 = 0, pieces = 0;
   for (int i = 0; i < n; ++i) {
     const int w = rows[i] + (rows2 ? rows2[i] : 0);
@@ -382,10 +391,19 @@ static bool team_deal(const int* rows, const int* rows2, int n, int xcds, int la
   }
   a.n_teams = team + 1;
   a.stations = std::max(1, std::min(std::min(xcds / a.n_teams, layers), kTeamStations));
-  return t->max_rows <= kTeamMaxRows;
+  return t->max_rows <= max_rows;
 }
 // (longer blocks and sources are the launches': their graphs are as fast)
+static int team_row_limit(const ad_ctx* c) { return c->cfg.dtype == AD_F32 ? kTeamF32Rows : kTeamMaxRows; }
 static bool team_rows_ok(const int* rows, int n) { return *std::max_element(rows, rows + n) <= kTeamMaxRows; }
+// Width 512 in fp32: an XCD takes 12 us for a layer's 16.8 MB and 7 for its products of 16 rows, so one or two full teams are no faster than the
+// launches over eight XCDs.  Verify forward, us, launches / teams: 1 sequence of 1, 8, 16, 25 rows 215, 252, 266, 272 / 209, 241, 270, 275; 4 of
+// 1, 4, 9, 16, 25 rows 239, 265, 299, 306, 356 / 214, 230, 278, 288, 360; 8 of 8 rows 305 / 308.  Encoder with its call: 1 of 8, 16 rows 192, 203 / 188,
+// 208; 4 of 8, 30 rows 207, 268 / 197, 258; 8 of 16 rows 270 / 243.  (Width 128: 60-74 / 39-49 and 69-78 / 55-61.)
+static bool team_pays(const ad_ctx* c, const TeamRun& t, bool dec) {
+  if (c->cfg.dtype != AD_F32 || c->cfg.d_model == 128) return true;
+  return (t.max_rows <= 8 || t.a.n_teams >= 4) && (!dec || t.a.stations > 1);
+}
 static bool team_usable(ad_ctx* c, int model, bool dec) {
   if (!c->team_on || !c->can_team[model][dec]) return false;
   if (c->team_rest > 0) { --c->team_rest; return false; }
@@ -396,18 +414,22 @@ static void team_common(const ad_ctx* c, int model, bool dec, int words, TeamRun
   TeamArgs& a = t->a;
   a.xcd0 = 0; a.head_only = 0; a.prob2_off = 0;
   a.layers = dec ? c->cfg.dec_layers : c->cfg.enc_layers;
-  a.scale = 1.0f / sqrtf(64.0f);
+  a.scale = 1.0f / sqrtf((float)(c->cfg.d_model / c->cfg.n_heads));
   a.form_ticks = (unsigned)c->team_ticks;
   a.w = (const char*)(dec ? c->w[model].dec[0].self.wqkv : c->w[model].enc[0].self.wqkv);
   a.x = c->at<float>(p.x); a.xa = c->at<bf16_storage>(p.xa); a.s = c->at<float>(p.s);
   a.slots = c->at<char>(p.team_slots); a.hop = c->at<char>(p.team_hop);
-  a.K = c->at<bf16_storage>(p.team_k); a.V = c->at<bf16_storage>(p.team_v); a.kv_stride = kTeamKvBytes;
+  a.K = c->at<bf16_storage>(p.team_k); a.V = c->at<bf16_storage>(p.team_v); a.kv_stride = p.team_kv_stride;
   a.Km = dec ? (const bf16_storage*)(c->ws + p.mem_k[model]) : nullptr;
   a.Vm = dec ? (const bf16_storage*)(c->ws + p.mem_v[model]) : nullptr;
   a.m_stride = p.mem_layer_stride;
   const VerifyTables vt = tables(c);
   a.self_desc = vt.self_desc; a.cross_desc = vt.cross_desc; a.row_dst = vt.row_dst;
   a.words = (unsigned*)(c->ws + p.team_words[words]); a.fail = a.words + kTeamFail;
+}
+static void run_team(const ad_ctx* c, const TeamRun& t, bool dec) {
+  if (c->cfg.dtype == AD_F32) launch_team_f32(t.a, c->cfg.d_model, dec, t.max_keys, c->stream);
+  else launch_team(t.a, dec, t.max_rows, t.max_keys, c->stream);
 }
 static ad_ctx::TeamPart team_part(const TeamRun* t) {
   ad_ctx::TeamPart k{};
@@ -570,7 +592,7 @@ static int verify_forward(ad_ctx* c, int M, hipEvent_t ev_a = nullptr, hipEvent_
   if (embedded) c->ln_pending = nullptr;
   else embed_rows(c, w, M);
   if (team) {
-    launch_team(team->a, true, team->max_rows, team->max_keys, c->stream);
+    run_team(c, *team, true);
     c->ln_pending = &w.dec.back().ln3;
   } else for (int l = 0; l < c->cfg.dec_layers; ++l) {
     const DecLayerW& L = w.dec[l];
@@ -736,7 +758,7 @@ int ad_create(const ad_config* cfg, const void* verifier_w, const void* drafter_
     if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus == 8 * kTeamMembers &&
         (size_t)plan.m_cap * kTeamF * 2 < (1u << 31) && plan.cache_layer_stride < (1u << 31)) {   // (32-bit offsets in the kernel)
       for (int i = 0; i < (c->has_drafter ? 2 : 1); ++i)
-        for (int dec = 0; dec < 2; ++dec) c->can_team[i][dec] = team_layout_ok(*cfg, c->w[i], dec != 0) && prepare_team(dec != 0);
+        for (int dec = 0; dec < 2; ++dec) c->can_team[i][dec] = team_layout_ok(*cfg, c->w[i], dec != 0) && (cfg->dtype == AD_F32 ? prepare_team_f32(cfg->d_model, dec != 0) : prepare_team(dec != 0));
     } else {
       (void)hipGetLastError();
     }
@@ -840,7 +862,7 @@ static void encode_launches(ad_ctx* c, int model, const int* dev, int M, int B, 
                                 c->at<float>(p.x), c->at<void>(p.xa), c->stream, team_words);
   c->ln_pending = nullptr;
   if (team) {
-    launch_team(team->a, false, team->max_rows, team->max_keys, c->stream);
+    run_team(c, *team, false);
     c->ln_pending = &w.enc.back().ln2;
   } else for (int l = 0; l < cf.enc_layers; ++l) {
     const EncLayerW& L = w.enc[l];
@@ -951,8 +973,8 @@ int ad_encode(ad_ctx* c, int model, const int32_t* src, const int32_t* src_len, 
   TeamRun run;
   run.max_keys = c->fw_max_rows;
   bool team = mapped && run.max_keys <= kTeamMaxKeys && team_rows_ok(src_len, B) &&
-              team_deal(src_len, nullptr, B, c->has_drafter && c->overlap_encoders ? 4 : 8, cf.enc_layers, &run) && (!side.on || run.a.n_teams <= 4) &&
-              team_usable(c, model, false);
+              team_deal(src_len, nullptr, B, c->has_drafter && c->overlap_encoders ? 4 : 8, cf.enc_layers, team_row_limit(c), &run) && (!side.on || run.a.n_teams <= 4) &&
+              team_pays(c, run, false) && team_usable(c, model, false);
   if (team) {
     team_common(c, model, false, model, &run);
     if (side.on) run.a.xcd0 = 8 - run.a.n_teams * run.a.stations;
@@ -1157,7 +1179,7 @@ static int verify_call(ad_ctx* c, const int32_t* draft, const int32_t* k, int32_
   TeamRun run;
   run.max_keys = std::max(self_keys, cross_keys);
   bool team = mapped && !static_scratch && run.max_keys <= kTeamMaxKeys && c->can_team[AD_VERIFIER][1] && team_rows_ok(k, B) &&
-              team_deal(k, nullptr, B, 8, cf.dec_layers, &run) && team_usable(c, AD_VERIFIER, true);
+              team_deal(k, nullptr, B, 8, cf.dec_layers, team_row_limit(c), &run) && team_pays(c, run, true) && team_usable(c, AD_VERIFIER, true);
   if (team) {
     team_common(c, AD_VERIFIER, true, 2, &run);
     run.a.K = (bf16_storage*)(c->ws + p.cache_k); run.a.V = (bf16_storage*)(c->ws + p.cache_v); run.a.kv_stride = p.cache_layer_stride;
@@ -1290,7 +1312,7 @@ int ad_draft_nat(ad_ctx* c, int k, int32_t* draft_out) {
     if (!c->h_finished[b]) { seg[0].push_back(k); seg[1].push_back(c->h_len[b] + 1); }
   const TeamFail tf = team_fail_words(c, AD_DRAFTER);
   run.max_keys = std::max(self_keys, *std::max_element(c->h_src_len[AD_DRAFTER].begin(), c->h_src_len[AD_DRAFTER].begin() + B));
-  bool team = watch && run.max_keys <= kTeamMaxKeys && c->can_team[AD_DRAFTER][1] && team_deal(seg[0].data(), seg[1].data(), live, 8, cf.dec_layers, &run) && team_usable(c, AD_DRAFTER, true);
+  bool team = watch && cf.dtype == AD_BF16 && run.max_keys <= kTeamMaxKeys && c->can_team[AD_DRAFTER][1] && team_deal(seg[0].data(), seg[1].data(), live, 8, cf.dec_layers, kTeamMaxRows, &run) && team_usable(c, AD_DRAFTER, true);
   if (team) {
     team_common(c, AD_DRAFTER, true, 2, &run);
     run.a.head_only = 1; run.a.prob2_off = live;
@@ -1309,7 +1331,7 @@ int ad_draft_nat(ad_ctx* c, int k, int32_t* draft_out) {
                                   c->at<void>(p.xa), c->stream, team ? run.a.words : nullptr);
     int rows = M;
     if (team) {
-      launch_team(run.a, true, run.max_rows, run.max_keys, c->stream);
+      run_team(c, run, true);
       c->ln_pending = &w.dec.back().ln3;
     }
     c->fw_nseq = 2 * live;

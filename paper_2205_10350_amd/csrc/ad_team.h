@@ -15,14 +15,14 @@ constexpr int kTeamXRows = 8 * kTeamMaxRows;     // packed rows of a launch
 constexpr int kTeamFormTicks = 30000;            // 0.3 ms: an idle chip has a team together in a few us
 
 // Byte offsets of a layer's entries from its first byte (weight_layout; the launcher's caller checks them).
-template <bool DEC>
+template <bool DEC, int D = kTeamD, int F = kTeamF, int ESZ = 2>
 struct TeamOff {
-  static constexpr int kMat = kTeamD * kTeamD * 2, kVec = kTeamD * 4, kAttn = 4 * kMat + 4 * kVec, kFfn = 2 * kTeamD * kTeamF * 2 + kTeamF * 4 + kVec;
+  static constexpr int kMat = D * D * ESZ, kVec = D * 4, kAttn = 4 * kMat + 4 * kVec, kFfn = 2 * D * F * ESZ + F * 4 + kVec;
   static constexpr int wqkv = 0, wo = 3 * kMat, bqkv = 4 * kMat, bo = bqkv + 3 * kVec;
   static constexpr int ln1g = kAttn, ln1b = ln1g + kVec;
   static constexpr int cwq = ln1b + kVec, cwo = cwq + 3 * kMat, cbq = cwq + 4 * kMat, cbo = cbq + 3 * kVec;   // decoder only
   static constexpr int ln2g = cwq + kAttn, ln2b = ln2g + kVec;                                              // decoder only
-  static constexpr int w1 = DEC ? ln2b + kVec : cwq, b1 = w1 + kTeamD * kTeamF * 2, w2 = b1 + kTeamF * 4, b2 = w2 + kTeamD * kTeamF * 2;
+  static constexpr int w1 = DEC ? ln2b + kVec : cwq, b1 = w1 + D * F * ESZ, w2 = b1 + F * 4, b2 = w2 + D * F * ESZ;
   static constexpr int ln_fg = DEC ? ln2g : ln1g, ln_fb = ln_fg + kVec;   // pending ahead of the FFN
   static constexpr int ln_lg = w1 + kFfn, ln_lb = ln_lg + kVec;           // the layer's last
   static constexpr int kLayerBytes = ln_lb + kVec;
@@ -58,6 +58,22 @@ struct TeamArgs {
   const int* row_dst;
   unsigned *words, *fail;             // both cleared before the launch
 };
+// ---- fp32 (ad_team_f32.hip): widths 128 (FFN 512, heads of 32) and 512 (2048, 64)
+constexpr int kTeamF32Rows = 16;                 // rows of a team
+template <int D, int F> struct TeamSlotF32 {     // a team's rows in one layer: [16] of these (bytes)
+  static constexpr int q = 0, att = D * 4, att2 = 2 * D * 4, s1 = 3 * D * 4, s2 = 4 * D * 4, xr = 5 * D * 4, f = 6 * D * 4, kRow = f + F * 4;
+  static constexpr int kBytes = kTeamF32Rows * kRow;
+};
+inline bool team_f32_widths(int d, int n_heads, int f) { return (d == 128 && n_heads == 4 && f == 512) || (d == 512 && n_heads == 8 && f == 2048); }
+inline size_t team_f32_slot_bytes(int d) { return d == 128 ? TeamSlotF32<128, 512>::kBytes : TeamSlotF32<512, 2048>::kBytes; }
+// LDS of the row tile: FFN2's operand, or the tile with the attention behind it
+__host__ __device__ constexpr size_t team_f32_rows_bytes(int d, int f, int dh) {
+  const size_t ffn = 16 * (size_t)(f + 4) * 4, att = (16 * (size_t)(d + 4) + 16 * 132 + 16 + 16 * (dh + 4)) * 4;
+  return ffn > att ? ffn : att;
+}
+bool prepare_team_f32(int d, bool decoder);
+void launch_team_f32(const TeamArgs& a, int d, bool decoder, int max_keys, hipStream_t s);
+
 // once per device before the first launch: what the kernels need of the runtime; false: they cannot run
 bool prepare_team(bool decoder);
 // at most kTeamMaxRows rows a team, kTeamMaxKeys keys a problem

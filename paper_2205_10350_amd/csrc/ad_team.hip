@@ -35,8 +35,7 @@
 // sets the fail word, the remaining waits return at once, and the caller runs the launches instead.
 #include <hip/hip_runtime.h>
 
-#include "ad_device.h"
-#include "ad_team.h"
+#include "ad_team_device.h"
 
 namespace ad {
 
@@ -45,31 +44,7 @@ constexpr int kTeamThreads = 64 * kTW;
 constexpr int kTD = kTeamD, kTF = kTeamF, kTH = kTD / 64;
 constexpr int kTLd = kTD + 16;                 // row stride in LDS (elements): 32 bytes past a multiple of 64
 constexpr int kSlices = kTF / kTD;             // 512-k slices of FFN2
-constexpr unsigned long long kWaitTicks = 200000;   // 100 MHz ticks: 2 ms
 
-struct TeamChunk { int row, n, off, causal, nk_base, kv_self, kv_cross, nk_cross; };   // up to 16 query rows of one attention problem
-
-__device__ __forceinline__ unsigned xcc_id() {
-  unsigned v;
-  asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(v));
-  return v & 15;
-}
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-// loads of rows another CU of the XCD wrote during this launch: past the vector cache, from the L2
-__device__ __forceinline__ uint4 ld16_l2(const void* base, unsigned off) {
-  __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0x7fffffff, 0x00027000);
-  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 16));
-}
-__device__ __forceinline__ float ld4_l2(const void* base, unsigned off) {
-  __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0x7fffffff, 0x00027000);
-  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, 0, 16));
-}
-// workgroup barrier that leaves memory requests in flight
-__device__ __forceinline__ void wg_bar() {
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
 // barrier over the four waves of a group, through a count in LDS: the other group may be held up by its requests meanwhile
 __device__ __forceinline__ void group_wait(unsigned* count, unsigned target) {
   while (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < target) {}
@@ -80,66 +55,6 @@ __device__ __forceinline__ void group_bar(unsigned* count, unsigned& target, int
   target += kGW;
   if (lane == 0) (void)__hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   group_wait(count, target);
-}
-// A row goes from the CU that computes it to those that multiply it without a barrier: its place is set to all ones ahead of time,
-// nothing computed is stored as that, and whoever needs the row reads it until no piece of it is all ones.  (All ones is one of
-// the NaNs; a NaN with these bits is stored as its neighbour.)  Who sets a place back, and when: its writer, no later than the
-// store of an earlier exchange that every reader of the place has seen whole, and after an exchange that every reader of its former
-// content had to pass; the stores are answered for before the writer's next data leave (team_put_ready).
-__device__ __forceinline__ void unwrite16(void* base, unsigned off) { gstore((uint4*)((char*)base + off), uint4{~0u, ~0u, ~0u, ~0u}); }
-__device__ __forceinline__ f32x4 unwritten4() { return __builtin_bit_cast(f32x4, uint4{~0u, ~0u, ~0u, ~0u}); }
-__device__ __forceinline__ unsigned written(float v) { return min(__float_as_uint(v), 0xfffffffeu); }
-__device__ __forceinline__ void put(float* p, float v) { gstore((unsigned*)p, written(v)); }
-// for readers on other XCDs: past this one's L2
-__device__ __forceinline__ void put_far(float* p, float v) { __hip_atomic_store((unsigned*)p, written(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ void put_far(bf16_t* p, float v) { __hip_atomic_store(p, (bf16_t)min((unsigned)f2bf(v), 0xfffeu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ void unwrite16_far(void* base, unsigned off) {
-  __hip_atomic_store((unsigned long long*)((char*)base + off), ~0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __hip_atomic_store((unsigned long long*)((char*)base + off + 8), ~0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void put(bf16_t* p, float v) { gstore(p, (bf16_t)min((unsigned)f2bf(v), 0xfffeu)); }
-__device__ __forceinline__ void team_put_ready() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-// has this wave seen a piece that is not written yet?  (fp32 words / bf16 halves)
-struct Seen32 {
-  unsigned m = 0;
-  __device__ __forceinline__ void add(const uint4& v) { m = max(max(m, v.x), max(max(v.y, v.z), v.w)); }
-  __device__ __forceinline__ bool all() const { return __builtin_amdgcn_ballot_w64(m == ~0u) == 0; }
-};
-struct Seen16 {
-  typedef unsigned short half2 __attribute__((ext_vector_type(2)));
-  half2 m = {0, 0};
-  __device__ __forceinline__ void add(const uint4& v, bool counts = true) {
-    half2 x = __builtin_elementwise_max(__builtin_elementwise_max(__builtin_bit_cast(half2, v.x), __builtin_bit_cast(half2, v.y)),
-                                        __builtin_elementwise_max(__builtin_bit_cast(half2, v.z), __builtin_bit_cast(half2, v.w)));
-    m = __builtin_elementwise_max(m, counts ? x : half2{0, 0});
-  }
-  __device__ __forceinline__ bool all() const { return __builtin_amdgcn_ballot_w64(m.x == 0xffff || m.y == 0xffff) == 0; }
-};
-struct TeamWait {
-  unsigned *fail, *gave_up;   // the launch's fail word; this workgroup's (LDS)
-  bool off;                   // wait no more
-};
-// attempt(): loads, and whether everything was there
-template <typename F>
-__device__ __forceinline__ void wait_for(TeamWait& tw, int lane, const F& attempt) {
-  unsigned long long t0 = 0;
-#pragma unroll 1
-  for (unsigned spin = 0;; ++spin) {
-    asm volatile("" ::: "memory");
-    if (attempt() || tw.off) return;
-    if ((spin & 15) == 0) {
-      const unsigned long long now = __builtin_amdgcn_s_memrealtime();
-      if (spin == 0) t0 = now;
-      else if (now - t0 >= kWaitTicks || __builtin_amdgcn_readfirstlane(__hip_atomic_load(tw.gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))) {
-        tw.off = true;
-        if (lane == 0) {
-          __hip_atomic_store(tw.gave_up, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          __hip_atomic_store(tw.fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        return;
-      }
-    }
-  }
 }
 // a value the compiler cannot see through: what is computed from it is computed where it is used, not kept in registers
 // over the whole stack of layers
@@ -358,14 +273,6 @@ __device__ __forceinline__ void unwrite_rows(void* base, unsigned pitch, unsigne
 #pragma unroll 1
   for (int m = lane / NP; m < count; m += 64 / NP) unwrite16(base, (unsigned)(row0 + m) * pitch + off + (lane % NP) * 16);
 }
-__device__ __forceinline__ TeamChunk chunk_at(const TeamChunk* chunks, int c) {
-  TeamChunk t = chunks[c];
-  t.row = __builtin_amdgcn_readfirstlane(t.row); t.n = __builtin_amdgcn_readfirstlane(t.n);
-  t.off = __builtin_amdgcn_readfirstlane(t.off); t.causal = __builtin_amdgcn_readfirstlane(t.causal);
-  t.nk_base = __builtin_amdgcn_readfirstlane(t.nk_base); t.kv_self = __builtin_amdgcn_readfirstlane(t.kv_self);
-  t.kv_cross = __builtin_amdgcn_readfirstlane(t.kv_cross); t.nk_cross = __builtin_amdgcn_readfirstlane(t.nk_cross);
-  return t;
-}
 
 // One attention problem's chunk of up to 16 rows, head h, at most 16 NKT keys, by the four waves of a group: wave w holds
 // the score tiles of keys 16 w .. and 16 (w + 4) .., the waves' maxima and the unrounded exponentials go through LDS,
@@ -539,43 +446,8 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
     for (int i = 0; i < 3 * MT; i += kGW)
       if (i + wave - kGW < 3 * MT) accx[(i + wave - kGW) * 64 + lane] = unwritten4();
   }
-  if (wave == 0) {
-    const int p0 = a.prob_lo[team], np = a.prob_n[team], np2 = a.prob2_off ? np : 0;
-    SeqDesc sd = {}, cd = {};
-    if (lane < np + np2) {
-      const int p = lane < np ? p0 + lane : a.prob2_off + p0 + lane - np;
-      sd = gload(a.self_desc + p);
-      if (DEC) cd = gload(a.cross_desc + p);
-    }
-    // the problem's rows that are this team's
-    const int lo = a.row_lo[lane < np ? 0 : 1][team], first = max(sd.q_row0, lo);
-    const int off = first - sd.q_row0, nq = max(0, min(sd.q_row0 + sd.nq, lo + (lane < np ? n0 : n1)) - first);
-    const int nc = (nq + 15) >> 4;
-    int before = nc;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int up = __shfl_up(before, o);
-      if (lane >= o) before += up;
-    }
-    if (lane == 63) misc[1] = before;
-    if (lane == np - 1) misc[2] = before;
-    before -= nc;
-    const int row = (lane < np ? 0 : n0) + first - lo;
-    for (int c = 0; c < nc; ++c)
-      if (before + c < ROWS) {
-        TeamChunk t;
-        t.row = row + 16 * c; t.n = min(16, nq - 16 * c); t.off = off + 16 * c; t.causal = sd.causal; t.nk_base = sd.nk_base;
-        t.kv_self = sd.kv_row0; t.kv_cross = cd.kv_row0; t.nk_cross = cd.nk_base;
-        chunks[before + c] = t;
-      }
-  } else if (wave == 1) {
-    if (lane == 0) { *gave_up = 0; *met_a = 0; }
-    if (lane < ROWS) {
-      const int row = min(lane, n0 + n1 - 1), g = row < n0 ? a.row_lo[0][team] + row : a.row_lo[1][team] + row - n0;
-      grow[lane] = g;
-      rdst[lane] = gload(a.row_dst + g);
-    }
-  }
+  team_lists<ROWS, DEC>(a, team, n0, n1, chunks, grow, rdst, misc + 1, wave, lane);
+  if (threadIdx.x == 64) { *gave_up = 0; *met_a = 0; }
   __syncthreads();
   const int idx = __builtin_amdgcn_readfirstlane(misc[0]);
   const int n_chunks_all = __builtin_amdgcn_readfirstlane(min(misc[1], ROWS)), n_chunks0 = __builtin_amdgcn_readfirstlane(min(misc[2], ROWS));
@@ -907,20 +779,8 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
       request_ffn2(l, idx, lane);
     }
   };
-  auto wait_count = [&](unsigned* count, unsigned target) {
-    if (lane0 == 0) {
-      const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
-      bool late = a.form_ticks == 0;
-      for (unsigned spin = 0; !late && __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target; ++spin)
-        late = (spin & 15) == 15 && __builtin_amdgcn_s_memrealtime() - t0 >= a.form_ticks;
-      if (late) {
-        __hip_atomic_store(a.fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(gave_up, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      }
-    }
-  };
   // before the first look at a place that another XCD writes: all XCDs' members are there, their places set back
-  auto wait_all = [&]() { wait_count(a.words + 48, a.n_teams * stations); };
+  auto wait_all = [&]() { team_wait_count(a, a.words + 48, a.n_teams * stations, gave_up, lane0); };
   {
     const int lane = here(lane0), idx = here_s(idx0);
     if (gw == kGW - 1) {   // this member is here, and its places can be read
@@ -938,16 +798,14 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
           }
         }
       }
-      team_put_ready();
-      if (lane == 0 && __hip_atomic_fetch_add(words + 32, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kTeamMembers - 1)
-        (void)__hip_atomic_fetch_add(a.words + 48, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      team_arrive(a, words, lane);
     }
     if (station == 0) {
       stage_first<RPW>(a.xa, grow, n0 + n1, At, wave, lane);
       stage_first_residual<ROWS>(a.x, grow, n0 + n1, xres, idx, wave, lane);
     }
     if (gw == kGW - 1) {
-      wait_count(words + 32, kTeamMembers);
+      team_wait_count(a, words + 32, kTeamMembers, gave_up, lane0);
       if (AHEAD && station > 0) wait_all();
     }
     wg_bar();
