@@ -981,16 +981,16 @@ int ad_encode(ad_ctx* c, int model, const int32_t* src, const int32_t* src_len, 
   }
   auto launches = [&]() { encode_launches(c, model, dev, M, B, team ? &run : nullptr); };
   const unsigned long long key = (1ull << 63) | ((unsigned long long)model << 62) | shape_key(M, c->fw_max_rows, B, side.on ? 1 : 0);
-  // Beyond 16 rows a team the launches, replayed as a graph, are as fast or faster (one sequence of 27 tokens, encode to first
-  // result: 286 against 308 us; launched one by one 340): the team serves the shapes that have no graph yet.
+  // Teams of more than 16 rows serve every call (one model, encode to the first token of 8 sequences of 17, 25, 32 tokens, 16 of 12, 16 and
+  // 32 of 8: 251, 261, 263, 258, 268, 282 us, the launches as a graph 281, 300, 306, 301, 308, 324), but on more than four XCDs they would
+  // leave the other model's encoder no place beside them: the graph goes before them there, once there is one (both encoders, a draft
+  // and a token, 4 sequences of 32 tokens 430 us with teams and 475 without, 5 of 25, 30 and 6 of 22 565, 575, 567 and 494, 505, 502).
+  const bool crowded = team && run.max_rows > 16 && run.a.n_teams > 4 && c->has_drafter && c->overlap_encoders;
   bool launched = false;
-  if (!team || run.max_rows > 16) {
-    launched = run_as_graph(c, c->stream, key, [&]() { encode_launches(c, model, dev, M, B, nullptr); });
-  } else if (B <= kTeamGraphBatch) {
-    launched = run_as_graph(c, c->stream, key, launches, 0, team_part(&run));
-  }
+  if (!team || crowded) launched = run_as_graph(c, c->stream, key, [&]() { encode_launches(c, model, dev, M, B, nullptr); });
+  else if (B <= kTeamGraphBatch) launched = run_as_graph(c, c->stream, key, launches, 0, team_part(&run));
   if (!launched) launches();
-  if (team && (!launched || run.max_rows <= 16)) ++c->team_launches;
+  if (team && !(crowded && launched)) ++c->team_launches;
   if (side.on) {
     HIP_TRY(c, hipEventRecord(c->ev_enc2, c->stream));
     c->enc2_pending = true;

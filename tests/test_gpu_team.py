@@ -189,6 +189,33 @@ def test_sequences_cut_into_pieces_on_several_xcds(rows):
         ctx.close()
 
 
+@pytest.mark.parametrize("drafter,lens,teams", [
+    (False, [25] * 8, 4), (False, [32] * 8, 4), (False, [7] * 12 + [32, 1], 4),   # 17 to 32 rows a team on eight XCDs
+    (True, [32] * 4, 4), (True, [20, 31, 29], 4),                                 # on four, beside the other model's
+    (True, [30] * 5, 2)])                                                         # on five: until the shape has its graph
+def test_encoders_with_more_than_16_rows_a_team(drafter, lens, teams):
+    """Four encodings of one shape, other tokens each, the graph of the launches there from the third on: how many go out as teams,
+    and the scores of the launches every time."""
+    rng = np.random.default_rng(sum(lens))
+    ctx = _context(drafter, batch=14, max_src=40, max_len=16, k_max=4)
+    try:
+        calls = [[_tokens(rng, n) for n in lens] for _ in range(4)]
+        got = {}
+        for on in (1, 0):
+            ctx.set_option(ad.AD_OPT_TEAMS, on)
+            n, got[on] = 0, []
+            for srcs in calls:
+                n += _launched(ctx, lambda: ctx.encode(ad.AD_VERIFIER, srcs))[0]
+                ctx.verify([[int(s[0])] for s in srcs])
+                got[on].append(ctx.debug_logits().view(np.uint32).copy())
+            assert n == (teams if on else 0)
+        for x, y in zip(got[1], got[0]):
+            assert np.array_equal(x, y)
+        assert ctx.get_option(ad.AD_OPT_TEAM_FAILURES) == 0
+    finally:
+        ctx.close()
+
+
 @pytest.mark.parametrize("prefix,k", [(0, 17), (15, 1), (20, 30), (40, 40), (60, 40)])
 def test_drafts_of_more_rows_than_a_team_holds(prefix, k):
     """Mask rows and prefix rows of one sequence over 2, 2, 4, 6 and 7 teams, every piece seeing all of them; teams without a mask row
