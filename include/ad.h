@@ -261,9 +261,11 @@ int ad_calibration_mfma(void* scratch_dev, size_t scratch_bytes, int32_t iters, 
  * ad_encode(AD_VERIFIER) runs on a second stream of the library's own (default priority), in a
  * second block of activation buffers, beside the verifier's encoder instead of behind it; the
  * first ad_draft_nat makes the context's stream wait for it.  Same results bit for bit.
- * AD_OPT_TEAMS (0/1, default 1): forwards of at most 32 rows a team and 128 keys of a bf16 model of
- * width 512 (8 heads, FFN 2048) run all their layers in one launch, a team of 32 workgroups on one XCD per sequence or group of
- * sequences.  The workgroups of a team wait for each other; where other work keeps some of them from starting for 0.3 ms,
+ * AD_OPT_TEAMS (0/1, default 1): forwards of sequences of at most 32 rows and 128 keys (drafts: as
+ * many rows as eight XCDs hold) run all their layers in one
+ * launch: a bf16 model of width 512 (8 heads, FFN 2048), or an fp32 model of width 128 (4 heads, FFN 512) or, where it pays,
+ * 512 (8 heads, FFN 2048).  A team of 32 workgroups on one XCD (or two by turns) holds a group of sequences, or 16 rows of a
+ * longer one; at most 32 rows (fp32: 16).  The workgroups of a team wait for each other; where other work keeps some of them from starting for 0.3 ms,
  * the call is repeated with a launch per stage, and so are the next calls for a while.  AD_OPT_TEAM_FAILURES (read only):
  * how often that happened.  AD_OPT_TEAM_LAUNCHES (read only): the forwards of ad_encode, ad_verify and ad_draft_nat that went out so.  AD_OPT_TEAM_WAIT (10 ns steps, 0 .. 100000, default 30000): that time; 0 gives every team up at
  * once.  Setting it waits for the context's work and drops the graphs held.  Same results bit for bit. */

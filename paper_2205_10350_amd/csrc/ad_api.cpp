@@ -393,8 +393,8 @@ static bool team_deal(const int* rows, const int* rows2, int n, int xcds, int la
   a.stations = std::max(1, std::min(std::min(xcds / a.n_teams, layers), kTeamStations));
   return t->max_rows <= max_rows;
 }
-// (longer blocks and sources are the launches': their graphs are as fast)
 static int team_row_limit(const ad_ctx* c) { return c->cfg.dtype == AD_F32 ? kTeamF32Rows : kTeamMaxRows; }
+// (blocks and sources beyond AD_OPT_TEAMS' 32 rows a sequence are the launches')
 static bool team_rows_ok(const int* rows, int n) { return *std::max_element(rows, rows + n) <= kTeamMaxRows; }
 // Width 512 in fp32: an XCD takes 12 us for a layer's 16.8 MB and 7 for its products of 16 rows, so one or two full teams are no faster than the
 // launches over eight XCDs.  Verify forward, us, launches / teams: 1 sequence of 1, 8, 16, 25 rows 215, 252, 266, 272 / 209, 241, 270, 275; 4 of
@@ -450,7 +450,7 @@ static void team_failed(ad_ctx* c) {
   ++c->team_failures;
 }
 // The teams of a result came together: 64 such results in a row halve the next rest.  (A failure costs the 0.3 ms of the wait and the
-// repeat of 0.2 to 0.3 ms, a call with teams gains about 10 us over one without.)
+// repeat of 0.2 to 0.3 ms, a call with teams gains 20 to 80 us over one without.)
 static void team_came_together(ad_ctx* c) {
   if (c->team_backoff > 0 && ++c->team_held == 64) { --c->team_backoff; c->team_held = 0; }
 }
