@@ -185,9 +185,6 @@ static void* static_scratch_for_current_device() {
 
 using namespace ad;
 
-// One team launch: its arguments, the most rows of a team and the most keys of a problem (they select the kernel).
-struct TeamRun { TeamArgs a; int max_rows, max_keys; };
-
 struct ad_ctx {
   ad_config cfg;
   Plan plan;
@@ -340,8 +337,9 @@ static bool team_layout_ok(const ad_config& c, const ModelW& w, bool dec) {
 // Deals n problems of rows[i] (+ rows2[i]) packed rows out to teams on up to `xcds` XCDs.  Problems of more than 16 rows are cut into
 // pieces of at most 16 (a row tile) where there are XCDs for all of them, the teams of a problem then read each other's keys and
 // values; else whole problems, in order: up to eight problems get a team each, more are cut where the running row count passes an eighth of all.
-// XCDs left over take turns over the layers.  false: a team would exceed its limits (max_rows).
-static bool team_deal(const int* rows, const int* rows2, int n, int xcds, int layers, int max_rows, TeamRun* t) {
+// XCDs left over take turns over the layers, of teams of one row tile (the others have no kernel for that: a cut by running counts can leave
+// four teams or fewer beside a long sequence).  false: a team would exceed its limits (max_rows).
+bool ad::team_deal(const int* rows, const int* rows2, int n, int xcds, int layers, int max_rows, TeamRun* t) {
   int live = 0, M = 0, R0 = 0, pieces = 0;
   for (int i = 0; i < n; ++i) {
     const int w = rows[i] + (rows2 ? rows2[i] : 0);
@@ -390,7 +388,7 @@ static bool team_deal(const int* rows, const int* rows2, int n, int xcds, int la
     }
   }
   a.n_teams = team + 1;
-  a.stations = std::max(1, std::min(std::min(xcds / a.n_teams, layers), kTeamStations));
+  a.stations = t->max_rows > 16 ? 1 : std::max(1, std::min(std::min(xcds / a.n_teams, layers), kTeamStations));
   return t->max_rows <= max_rows;
 }
 static int team_row_limit(const ad_ctx* c) { return c->cfg.dtype == AD_F32 ? kTeamF32Rows : kTeamMaxRows; }
@@ -404,8 +402,9 @@ static bool team_pays(const ad_ctx* c, const TeamRun& t, bool dec) {
   if (c->cfg.dtype != AD_F32 || c->cfg.d_model == 128) return true;
   return (t.max_rows <= 8 || t.a.n_teams >= 4) && (!dec || t.a.stations > 1);
 }
-static bool team_usable(ad_ctx* c, int model, bool dec) {
+static bool team_usable(ad_ctx* c, int model, bool dec, const TeamRun& t) {
   if (!c->team_on || !c->can_team[model][dec]) return false;
+  if (c->cfg.dtype == AD_BF16 && !team_has_kernel(dec, t.max_rows, t.max_keys, t.a.stations)) return false;
   if (c->team_rest > 0) { --c->team_rest; return false; }
   return true;
 }
@@ -974,7 +973,7 @@ int ad_encode(ad_ctx* c, int model, const int32_t* src, const int32_t* src_len, 
   run.max_keys = c->fw_max_rows;
   bool team = mapped && run.max_keys <= kTeamMaxKeys && team_rows_ok(src_len, B) &&
               team_deal(src_len, nullptr, B, c->has_drafter && c->overlap_encoders ? 4 : 8, cf.enc_layers, team_row_limit(c), &run) && (!side.on || run.a.n_teams <= 4) &&
-              team_pays(c, run, false) && team_usable(c, model, false);
+              team_pays(c, run, false) && team_usable(c, model, false, run);
   if (team) {
     team_common(c, model, false, model, &run);
     if (side.on) run.a.xcd0 = 8 - run.a.n_teams * run.a.stations;
@@ -1179,7 +1178,7 @@ static int verify_call(ad_ctx* c, const int32_t* draft, const int32_t* k, int32_
   TeamRun run;
   run.max_keys = std::max(self_keys, cross_keys);
   bool team = mapped && !static_scratch && run.max_keys <= kTeamMaxKeys && c->can_team[AD_VERIFIER][1] && team_rows_ok(k, B) &&
-              team_deal(k, nullptr, B, 8, cf.dec_layers, team_row_limit(c), &run) && team_pays(c, run, true) && team_usable(c, AD_VERIFIER, true);
+              team_deal(k, nullptr, B, 8, cf.dec_layers, team_row_limit(c), &run) && team_pays(c, run, true) && team_usable(c, AD_VERIFIER, true, run);
   if (team) {
     team_common(c, AD_VERIFIER, true, 2, &run);
     run.a.K = (bf16_storage*)(c->ws + p.cache_k); run.a.V = (bf16_storage*)(c->ws + p.cache_v); run.a.kv_stride = p.cache_layer_stride;
@@ -1312,7 +1311,7 @@ int ad_draft_nat(ad_ctx* c, int k, int32_t* draft_out) {
     if (!c->h_finished[b]) { seg[0].push_back(k); seg[1].push_back(c->h_len[b] + 1); }
   const TeamFail tf = team_fail_words(c, AD_DRAFTER);
   run.max_keys = std::max(self_keys, *std::max_element(c->h_src_len[AD_DRAFTER].begin(), c->h_src_len[AD_DRAFTER].begin() + B));
-  bool team = watch && cf.dtype == AD_BF16 && run.max_keys <= kTeamMaxKeys && c->can_team[AD_DRAFTER][1] && team_deal(seg[0].data(), seg[1].data(), live, 8, cf.dec_layers, kTeamMaxRows, &run) && team_usable(c, AD_DRAFTER, true);
+  bool team = watch && cf.dtype == AD_BF16 && run.max_keys <= kTeamMaxKeys && c->can_team[AD_DRAFTER][1] && team_deal(seg[0].data(), seg[1].data(), live, 8, cf.dec_layers, kTeamMaxRows, &run) && team_usable(c, AD_DRAFTER, true, run);
   if (team) {
     team_common(c, AD_DRAFTER, true, 2, &run);
     run.a.head_only = 1; run.a.prob2_off = live;

@@ -58,6 +58,11 @@ struct TeamArgs {
   const int* row_dst;
   unsigned *words, *fail;             // both cleared before the launch
 };
+// One team launch: its arguments, the most rows of a team and the most keys of a problem (they select the kernel).
+struct TeamRun { TeamArgs a; int max_rows, max_keys; };
+// the deal of n problems' rows to teams (ad_api.cpp; max_keys is the caller's)
+bool team_deal(const int* rows, const int* rows2, int n, int xcds, int layers, int max_rows, TeamRun* t);
+
 // ---- fp32 (ad_team_f32.hip): widths 128 (FFN 512, heads of 32) and 512 (2048, 64)
 constexpr int kTeamF32Rows = 16;                 // rows of a team
 template <int D, int F> struct TeamSlotF32 {     // a team's rows in one layer: [16] of these (bytes)
@@ -76,6 +81,8 @@ void launch_team_f32(const TeamArgs& a, int d, bool decoder, int max_keys, hipSt
 
 // once per device before the first launch: what the kernels need of the runtime; false: they cannot run
 bool prepare_team(bool decoder);
+// whether there is a kernel for teams of max_rows rows, problems of max_keys keys and so many XCDs a team: launch_team's condition
+bool team_has_kernel(bool decoder, int max_rows, int max_keys, int stations);
 // at most kTeamMaxRows rows a team, kTeamMaxKeys keys a problem
 void launch_team(const TeamArgs& a, bool decoder, int max_rows, int max_keys, hipStream_t s);
 

@@ -1054,7 +1054,7 @@ static size_t team_lds_bytes(int mt) {
   return b > 84 * 1024 ? b : 84 * 1024;
 }
 // MT by the rows of the largest team, NKT by the keys of the longest problem, AHEAD where every team has several XCDs
-// (teams of more than 16 rows are dealt out only where there are no XCDs left over)
+// (dealt to teams of one row tile only)
 template <typename F>
 static void each_team_kernel(bool dec, const F& f) {
   if (dec) {
@@ -1065,19 +1065,28 @@ static void each_team_kernel(bool dec, const F& f) {
     f(1, 4, true, &k_team<1, 4, false, true>); f(1, 8, true, &k_team<1, 8, false, true>);
   }
 }
+typedef void (*TeamKernel)(TeamArgs);
+static TeamKernel team_kernel(bool dec, int max_rows, int max_keys, int stations) {
+  TeamKernel found = nullptr;
+  if (max_rows < 1 || max_rows > kTeamMaxRows || max_keys < 1 || max_keys > kTeamMaxKeys) return found;
+  const int mt = max_rows <= 16 ? 1 : 2, nkt = max_keys <= 64 ? 4 : 8;
+  each_team_kernel(dec, [&](int m, int nk, bool ahead, TeamKernel k) {
+    if (m == mt && nk == nkt && ahead == (stations > 1)) found = k;
+  });
+  return found;
+}
+bool team_has_kernel(bool decoder, int max_rows, int max_keys, int stations) { return team_kernel(decoder, max_rows, max_keys, stations) != nullptr; }
 bool prepare_team(bool decoder) {
   bool ok = true;
-  each_team_kernel(decoder, [&](int mt, int, bool, void (*k)(TeamArgs)) {
+  each_team_kernel(decoder, [&](int mt, int, bool, TeamKernel k) {
     ok = ok && hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)team_lds_bytes(mt)) == hipSuccess;
   });
   if (!ok) (void)hipGetLastError();
   return ok;
 }
 void launch_team(const TeamArgs& a, bool decoder, int max_rows, int max_keys, hipStream_t s) {
-  const int mt = max_rows <= 16 ? 1 : 2, nkt = max_keys <= 64 ? 4 : 8;
-  each_team_kernel(decoder, [&](int m, int nk, bool ahead, void (*k)(TeamArgs)) {
-    if (m == mt && nk == nkt && ahead == (a.stations > 1)) k<<<8 * kTeamMembers, kTeamThreads, team_lds_bytes(mt), s>>>(a);
-  });
+  const TeamKernel k = team_kernel(decoder, max_rows, max_keys, a.stations);
+  k<<<8 * kTeamMembers, kTeamThreads, team_lds_bytes(max_rows <= 16 ? 1 : 2), s>>>(a);
 }
 
 }  // namespace ad

@@ -244,6 +244,34 @@ def test_drafts_of_more_rows_than_a_team_holds(prefix, k):
         ctx.close()
 
 
+@pytest.mark.parametrize("rows", [[1] * 8 + [17], [17] + [1] * 8, [1] * 4 + [32] + [1] * 4, [1] * 12 + [32], [1] * 31 + [25], [25] + [1] * 31, [1] * 8 + [16, 16]])
+def test_one_long_sequence_among_many_short_ones(rows):
+    """More than eight sequences cut into few teams, one of them above a row tile (two to four teams, which would leave XCDs over): the encoder over
+    sources of these lengths, then the blocks."""
+    rng = np.random.default_rng(sum(rows) + 7 * rows[0])
+    srcs = [_tokens(rng, n) for n in rows]
+    blk = [list(_tokens(rng, n)) for n in rows]
+    other = [_tokens(rng, n) for n in rows]
+    ctx = _context(batch=32, max_src=40, max_len=40, k_max=32)
+    try:
+        got = {}
+        for on in (0, 1):
+            ctx.set_option(ad.AD_OPT_TEAMS, on)
+            ctx.encode(ad.AD_VERIFIER, other)       # (what a forward that does not run would leave behind)
+            ctx.verify([b[::-1] for b in blk])
+            assert _launched(ctx, lambda: ctx.encode(ad.AD_VERIFIER, srcs))[0] == on
+            launched, v = _launched(ctx, lambda: ctx.verify(blk, want_verified=True))
+            assert launched == on
+            got[on] = [v[2], ctx.debug_logits().view(np.uint32).copy()]
+            ctx.verify([b[:1] for b in blk])        # over the keys the block left
+            got[on].append(ctx.debug_logits().view(np.uint32).copy())
+        for x, y in zip(got[0], got[1]):
+            assert np.array_equal(x, y)
+        assert ctx.get_option(ad.AD_OPT_TEAM_FAILURES) == 0
+    finally:
+        ctx.close()
+
+
 def test_a_team_that_does_not_come_together_leaves_the_call_to_the_launches():
     """The wait of the team's barrier set to nothing: every kernel gives up and exits, the calls are repeated launch by launch (the
     encoders too) with the results they always have, and the launches keep the next calls."""
