@@ -488,7 +488,8 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
   //   s2         all (seen att2)                                         before Q, K, V
   //   f          all (seen s2; the encoder: s1)                          during self-attention
   //   s          all (seen f)                                            before FFN1 (group A)
-  // What other XCDs read (hop; keys and values that teams share) has a place for every layer, set back ahead of the first barrier.
+  // What other XCDs read (hop; keys and values that teams share) has a place for every layer, set back ahead of the writer's first barrier;
+  // its readers have seen the arrival of all XCDs before their first look (wait_all).
   auto unwrite_attn = [&](int n, int idx, int lane) {   // q, att (a wave)
 #pragma unroll
     for (int s = 0; s < 3; ++s)
@@ -779,7 +780,10 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
       request_ffn2(l, idx, lane);
     }
   };
-  // before the first look at a place that another XCD writes: all XCDs' members are there, their places set back
+  // Before the first look at a place that another XCD writes: all XCDs' members are there, their places set back.  The second XCD of a team
+  // looks at the first one's rows at once, the first at the second one's ahead of its second layer (by then the count is complete on an
+  // idle chip; without this wait a second XCD that starts late has the rows of an earlier forward taken for its own), all at shared
+  // keys and values ahead of the first attention.
   auto wait_all = [&]() { team_wait_count(a, a.words + 48, a.n_teams * stations, gave_up, lane0); };
   {
     const int lane = here(lane0), idx = here_s(idx0);
@@ -834,6 +838,7 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
       }
       if constexpr (AHEAD) {
         if (l > 0) keep_ln(lnv, ln, gw, lane);
+        if (l == stations && !far_kv && gw == kGW - 1 && !tw.off) wait_all();   // (station 0)
         wg_bar();
         if (l >= 2 && stations > 2 && wave < n)
           wait_for(tw, lane, [&]() { __builtin_amdgcn_s_sleep(4); return __float_as_uint(ld4_l2(hop(l - 2), wave * (kTD * 4))) != ~0u; });

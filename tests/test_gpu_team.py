@@ -481,6 +481,76 @@ def test_a_repeat_does_not_wait_for_the_null_stream():
             ctx.close()
 
 
+def _verify_beside_the_drafters_encoder(ctx, rng, rows, vocab, draft_src=32, passes=6):
+    """Blocks verified while the drafter's encoder, on the library's second stream, holds XCDs 4 to 7: the second XCDs of the teams start late.
+    -> logits of all blocks, forwards with teams"""
+    got, n = [], 0
+    for _ in range(passes):
+        ctx.encode(ad.AD_VERIFIER, [rng.integers(5, vocab, size=2).astype(np.int32) for _ in rows])
+        for beside in (False, True, False):
+            blk = [list(rng.integers(5, vocab, size=k).astype(np.int32)) for k in rows]
+            if beside:
+                ctx.encode(ad.AD_DRAFTER, [rng.integers(5, vocab, size=draft_src).astype(np.int32) for _ in rows])
+            launched, _ = _launched(ctx, lambda: ctx.verify(blk))
+            n += launched
+            got.append(ctx.debug_logits().view(np.uint32).copy())
+    return got, n
+
+
+@pytest.mark.parametrize("rows", [[9, 16, 12, 13], [1, 1, 1, 1], [16, 1, 5], [25, 9], [25, 25]])
+def test_the_second_xcd_of_a_team_may_start_late(rows):
+    """The first XCD has done its layer long before the second is there, and the places of the second's rows hold those of an earlier forward
+    until then: nothing of them is taken (every pass has other tokens), and no team gives up within the wait of 1 ms."""
+    ctx = _context(drafter=True, batch=4, max_src=40, max_len=96, k_max=32)
+    try:
+        ctx.set_option(ad.AD_OPT_TEAM_WAIT, 100000)
+        assert ctx.get_option(ad.AD_OPT_OVERLAP_ENCODERS) == 1
+        got = {}
+        for on in (0, 1):
+            ctx.set_option(ad.AD_OPT_TEAMS, on)
+            got[on], n = _verify_beside_the_drafters_encoder(ctx, np.random.default_rng(len(rows) + sum(rows)), rows, DIMS["vocab"])
+            assert n == 18 * on
+        for x, y in zip(got[0], got[1]):
+            assert np.array_equal(x, y)
+        assert ctx.get_option(ad.AD_OPT_TEAM_FAILURES) == 0
+    finally:
+        ctx.close()
+
+
+def test_teams_of_two_contexts_beside_each_other():
+    """Forwards of 1 row and of 25 rows from two threads, a stream each, over the same XCDs: the launches' bits whoever comes first."""
+    rows = ([1], [25])
+    calls = [[list(_tokens(np.random.default_rng(100 * i + j), r[0])) for j in range(24)] for i, r in enumerate(rows)]
+    src = [_tokens(np.random.default_rng(9), 8)]
+    ctxs = [_context(batch=1, max_src=16, max_len=64, k_max=32) for _ in rows]
+    try:
+        got = [{}, {}]
+
+        def run(i, on):
+            out = []
+            for blk in calls[i]:
+                ctxs[i].encode(ad.AD_VERIFIER, src)
+                ctxs[i].verify([blk])
+                out.append(ctxs[i].debug_logits().view(np.uint32).copy())
+            got[i][on] = out
+        for on in (0, 1):
+            for c in ctxs:
+                c.set_option(ad.AD_OPT_TEAMS, on)
+            threads = [threading.Thread(target=run, args=(i, on)) for i in range(2)]
+            for t in threads:
+                t.start()
+            for t in threads:
+                t.join()
+        for i in range(2):
+            assert len(got[i][1]) == 24
+            for x, y in zip(got[i][0], got[i][1]):
+                assert np.array_equal(x, y)
+            assert ctxs[i].get_option(ad.AD_OPT_TEAM_LAUNCHES) > 0
+    finally:
+        for c in ctxs:
+            c.close()
+
+
 def test_two_contexts_in_two_threads():
     """Teams of two contexts that want the same compute units at the same time: the same tokens."""
     rng = np.random.default_rng(6)
