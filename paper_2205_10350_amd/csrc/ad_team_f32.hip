@@ -14,7 +14,8 @@
 // (a branch around loads has them copied, hence waited for, where it ends: 208 -> 310 us at width 512).
 //
 // Every exchanged row has a place of its own for every layer, all ones until it is written (ad_team_device.h), set back before the team's
-// first barrier: at 16 rows of width 512 and six layers 2 MB a team, 0.4 us.
+// first barrier: at 16 rows of width 512 and six layers 2 MB a team, 0.4 us.  Whoever reads what another XCD writes has seen the arrival of
+// all XCDs before: the second XCD of a team, and all where teams share keys, at that barrier, the first XCD after its first layer.
 #include <hip/hip_runtime.h>
 
 #include "ad_team_device.h"
@@ -598,6 +599,9 @@ __global__ __launch_bounds__(kFThreads) void k_team_f32(TeamArgs a) {
         }
       }
     }
+    // The next rows come from the second XCD: it has set their places back.  (Verify forward of width 512, us, without a wait / here / at the
+    // first barrier: 1 row 209.0 / 210.1 / 210.4, 4 sequences of 8 rows 250.0 / 251.7 / 254.2, of 16 rows 288.2 / 290.0 / 290.7.)
+    if (wave == 7 && l == 0 && far_hop) team_wait_count(a, a.words + 48, a.n_teams * a.stations, gave_up, lane);
     wg_bar();
   }
 }

@@ -124,6 +124,44 @@ def test_values_that_are_not_finite_pass_between_the_members(model, name):
         ctx.close()
 
 
+# (an encoder long enough to be in the way)
+LATE = {"d128": dict(model_dims("tiny"), enc_layers=6, dec_layers=5), "d512": dict(enc_layers=4, dec_layers=5, d_model=512, n_heads=8, d_ffn=2048, vocab=2000)}
+
+
+@pytest.mark.parametrize("model", LATE)
+@pytest.mark.parametrize("rows", [[9, 16, 12, 13], [1, 1, 1, 1], [8, 1, 5], [25, 9]])
+def test_the_second_xcd_of_a_team_may_start_late(model, rows):
+    """Blocks verified while the drafter's encoder, on the library's second stream, holds XCDs 4 to 7: the places of the second XCD's rows
+    hold those of an earlier forward until it is there, and nothing of them is taken (every pass has other tokens)."""
+    dims, key = LATE[model], "late " + model
+    if key not in W:
+        W[key] = init_weights(dims, 22), init_weights(dims, 23)
+    cfg = ad.make_config(dims, max_batch=4, max_src=16, max_len=96, k_max=32, dtype="fp32", special=SPECIAL, debug_logits=True)
+    ctx = ad.Context(cfg, *W[key])
+    try:
+        ctx.set_option(ad.AD_OPT_TEAM_WAIT, 100000)
+        assert ctx.get_option(ad.AD_OPT_OVERLAP_ENCODERS) == 1
+        got = {}
+        for on in (0, 1):
+            ctx.set_option(ad.AD_OPT_TEAMS, on)
+            rng = np.random.default_rng(len(rows) + sum(rows))
+            got[on], n = [], 0
+            for _ in range(6):
+                ctx.encode(ad.AD_VERIFIER, [rng.integers(5, dims["vocab"], size=2).astype(np.int32) for _ in rows])
+                for beside in (False, True, False):
+                    blk = [list(rng.integers(5, dims["vocab"], size=k).astype(np.int32)) for k in rows]
+                    if beside:
+                        assert _launched(ctx, lambda: ctx.encode(ad.AD_DRAFTER, [rng.integers(5, dims["vocab"], size=16 if len(rows) == 4 else 8).astype(np.int32) for _ in rows]))[0] == on
+                    n += _launched(ctx, lambda: ctx.verify(blk))[0]
+                    got[on].append(ctx.debug_logits().view(np.uint32).copy())
+            assert n == on * (18 if model == "d128" or max(rows) <= 16 else 0)   # (width 512: four teams, or teams of at most eight rows)
+        for x, y in zip(got[0], got[1]):
+            assert np.array_equal(x, y)
+        assert ctx.get_option(ad.AD_OPT_TEAM_FAILURES) == 0
+    finally:
+        ctx.close()
+
+
 @pytest.mark.parametrize("model", MODELS)
 def test_a_team_that_does_not_come_together_leaves_the_call_to_the_launches(model):
     rng = np.random.default_rng(5)
