@@ -74,10 +74,8 @@ __device__ __forceinline__ void load_strip(const bf16_t* W, int n0, int K, int u
 #pragma unroll
   for (int u = U0; u < U1; ++u) b[u] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, 16 * lane, 1024 * u, 0));
 }
-// T tiles of 16 x 16 over 512 k, added to acc.  The operand reads are issued well before the products: left to itself the compiler
-// puts each read next to its use and the chain waits for LDS sixteen times (0.7 us instead of 0.3).
-// ready(): called with the first reads on their way.
-// The same with a quarter of the operands in registers at a time and the next quarter on its way (where two sets of strips fill them).
+// T tiles of 16 x 16 over 512 k, added to acc, a quarter of the operands in registers at a time and the next quarter on its way (where two
+// sets of strips fill them)
 template <int T>
 __device__ __forceinline__ void mm16_lean(const bf16_t* a_lane, const uint4 (&b)[16], f32x4 (&acc)[T]) {
   constexpr int U = 4 / T;
@@ -102,6 +100,8 @@ __device__ __forceinline__ void mm16_lean(const bf16_t* a_lane, const uint4 (&b)
   }
   __builtin_amdgcn_sched_barrier(0);
 }
+// The same with the operands of 16 / T steps in registers, read well before the products: left to itself the compiler puts each read next to
+// its use and the chain waits for LDS sixteen times (0.7 us instead of 0.3).  ready(): called with the first reads on their way.
 template <int T, typename F = NoOp>
 __device__ __forceinline__ void mm16(const bf16_t* a_lane, const uint4 (&b)[16], f32x4 (&acc)[T], const F& ready = F{}) {
   constexpr int U = 16 / T;
@@ -595,11 +595,7 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
                                        ch.kv_self, min(ch.nk_base, 16 * NKT), idx & (kTH - 1), gw, lane, eg);
           }
         }
-        if constexpr (AHEAD) {
-          wg_bar();   // the LayerNorm's vectors
-          if (l >= 2 && stations > 2 && wave < n)   // look seldom until the layer before this one's predecessor is done
-            wait_for(tw, lane, [&]() { __builtin_amdgcn_s_sleep(4); return __float_as_uint(ld4_l2(hop(l - 2), wave * (kTD * 4))) != ~0u; });
-        }
+        if constexpr (AHEAD) wg_bar();   // the LayerNorm's vectors
         if (l > 0) stage_ln<RPW>(tw, AHEAD ? hop(l - 1) : xs, n, lnv, At, xres, idx, wave, lane);
         wg_bar();
         team_put_ready();
@@ -840,8 +836,6 @@ __global__ __launch_bounds__(kTeamThreads) void k_team(TeamArgs a) {
         if (l > 0) keep_ln(lnv, ln, gw, lane);
         if (l == stations && !far_kv && gw == kGW - 1 && !tw.off) wait_all();   // (station 0)
         wg_bar();
-        if (l >= 2 && stations > 2 && wave < n)
-          wait_for(tw, lane, [&]() { __builtin_amdgcn_s_sleep(4); return __float_as_uint(ld4_l2(hop(l - 2), wave * (kTD * 4))) != ~0u; });
       }
       if (l > 0) stage_ln<RPW>(tw, AHEAD ? hop(l - 1) : xs, n, lnv, At, xres, idx, wave, lane);
       team_put_ready();

@@ -431,8 +431,6 @@ __global__ __launch_bounds__(kFThreads) void k_team_f32(TeamArgs a) {
       if (DEC) request_out2();
       request_ffn1(); request_ffn2();
     };
-    if (l >= 2 && a.stations > 2 && wave < n)   // look seldom until the layer before this one's predecessor is done
-      wait_for(tw, lane, [&]() { __builtin_amdgcn_s_sleep(4); return __float_as_uint(ld4_l2(hop(l - 2), wave * (D * 4))) != ~0u; });
     if (l > 0) stage_ln<D>(tw, hop(l - 1), D * 4, n, ln, At, wave, lane);
     wg_bar();
 #pragma unroll
