@@ -265,8 +265,10 @@ int ad_calibration_mfma(void* scratch_dev, size_t scratch_bytes, int32_t iters, 
  * many rows as eight XCDs hold) run all their layers in one
  * launch: a bf16 model of width 512 (8 heads, FFN 2048), or an fp32 model of width 128 (4 heads, FFN 512) or, where it pays,
  * 512 (8 heads, FFN 2048).  A team of 32 workgroups on one XCD (or two by turns) holds a group of sequences, or 16 rows of a
- * longer one; at most 32 rows (fp32: 16).  The workgroups of a team wait for each other; where other work keeps some of them from starting for 0.3 ms,
- * the call is repeated with a launch per stage, and so are the next calls for a while.  AD_OPT_TEAM_FAILURES (read only):
+ * longer one; at most 32 rows (fp32: 16).  What that occupies: two XCDs for one sequence of up to 16 rows, four for one of 17 to 32, all
+ * eight from four sequences on, each compute unit of them whole while the layers run (bf16, width 512: 70 to 170 us).
+ * The workgroups of a team wait for each other; where other work (another context or stream) keeps some of them from starting for
+ * 0.3 ms (the first XCD of a team waits that long for its members and once more for the second XCD), the call is repeated with a launch per stage, and so are the next calls for a while.  AD_OPT_TEAM_FAILURES (read only):
  * how often that happened.  AD_OPT_TEAM_LAUNCHES (read only): the forwards of ad_encode, ad_verify and ad_draft_nat that went out so.  AD_OPT_TEAM_WAIT (10 ns steps, 0 .. 100000, default 30000): that time; 0 gives every team up at
  * once.  Setting it waits for the context's work and drops the graphs held.  Same results bit for bit. */
 enum { AD_OPT_GRAPHS = 3, AD_OPT_GRAPHS_CAPTURED = 4, AD_OPT_SPIN_WAIT = 5, AD_OPT_FUSE_CROSSQ = 6,

@@ -395,8 +395,8 @@ static int team_row_limit(const ad_ctx* c) { return c->cfg.dtype == AD_F32 ? kTe
 // (blocks and sources beyond AD_OPT_TEAMS' 32 rows a sequence are the launches')
 static bool team_rows_ok(const int* rows, int n) { return *std::max_element(rows, rows + n) <= kTeamMaxRows; }
 // Width 512 in fp32: an XCD takes 12 us for a layer's 16.8 MB and 7 for its products of 16 rows, so one or two full teams are no faster than the
-// launches over eight XCDs.  Verify forward, us, launches / teams: 1 sequence of 1, 8, 16, 25 rows 215, 252, 266, 272 / 209, 241, 270, 275; 4 of
-// 1, 4, 9, 16, 25 rows 239, 265, 299, 306, 356 / 214, 230, 278, 288, 360; 8 of 8 rows 305 / 308.  Encoder with its call: 1 of 8, 16 rows 192, 203 / 188,
+// launches over eight XCDs.  Verify forward, us, launches / teams: 1 sequence of 1, 8, 16, 25 rows 215, 250, 266, 272 / 209, 241, 270, 275; 4 of
+// 1, 4, 9, 16, 25 rows 238, 264, 298, 306, 357 / 215, 231, 279, 289, 360; 2 of 1, 8 rows 222, 264 / 212, 245, 3 of them 230, 269 / 212, 249; 8 of 8 rows 305 / 308.  Encoder with its call: 1 of 8, 16 rows 192, 203 / 188,
 // 208; 4 of 8, 30 rows 207, 268 / 197, 258; 8 of 16 rows 270 / 243.  (Width 128: 60-74 / 39-49 and 69-78 / 55-61.)
 static bool team_pays(const ad_ctx* c, const TeamRun& t, bool dec) {
   if (c->cfg.dtype != AD_F32 || c->cfg.d_model == 128) return true;

@@ -11,14 +11,19 @@
 // XCDs for all: pieces read each other's keys and values (agent-scope stores past the writer's L2, 0.5-0.6 us one way), all else of a row is its own.
 // Where XCDs are left over a team has two and they take turns over the layers: one requests a layer's strips (an XCD streams a
 // layer's 7.3 MB from the last-level cache in 5.7 us) while the other works on the layer before, and the rows go across as keys do.  (Three or
-// more: no faster, 81 us of layers at 1 row with two or three, 83 with six: all members of all XCDs have to be there first.)
+// more: no faster, 81 us of layers at 1 row with two or three, 83 with six: all members of all XCDs have to be there first.)  Verify forward, us,
+// one XCD a team / two, teams of 1, 8, 16 rows: one team 85, 99, 111 / 80, 94, 105; two 86, 99, 112 / 82, 97, 109; three 89, 104, 116 / 83, 98, 109; four
+// 97, 110, 121 / 88, 103, 114.
+//
+// Registers (512 threads, 256 a lane at most): 229 to 256.  Only k_team<1, 8, true, true> (two XCDs, 65 to 128 keys) spills vector registers, 16 of
+// them (40 bytes of scratch a lane), once a layer; it has no place for the older keys requested ahead either (kEarly).
 //
 // What bounds it (clock stamps at every workgroup barrier, base model, a layer of 11.5 / 14 / 16 us at 1 / 8 / 25 rows on two XCDs a team):
 // products 2.6 us a layer (FFN2's chain through four slices 0.9, the others 0.25-0.35 each), seven exchanges of 0.4 to 1.2, the two
 // attentions 2.2, LayerNorms 0.9; with one XCD a team (32 sequences) strips on their way delay the exchanges by 2 to 3 us a layer.
-// Verify forward of the base model, us, with barriers between the stages on one XCD / this way, one machine: 1 sequence of 1, 4, 8, 16, 17,
-// 25, 32 rows 139, 143, 144, 150, 167, 178, 178 / 80, 90, 94, 106, 108, 110, 110; 8 sequences of 25 rows 207 / 164; 32 sequences of 1, 2, 4, 6, 8 rows
-// 164, 166, 176, 196, 206 / 112, 116, 131, 157, 171.  A launch per stage: 159-172, 172, 175, 180, 178, 181, 183; 222; 177, 182, 195, 221, 231
+// Verify forward of the base model, us, with barriers between the stages on one XCD / this way: 1 sequence of 1, 4, 8, 16, 17,
+// 25, 32 rows 139, 143, 144, 150, 167, 177, 177 / 80, 89, 94, 105, 106, 110, 109; 8 sequences of 25 rows 207 / 165; 32 sequences of 1, 2, 4, 6, 8 rows
+// 164, 166, 176, 196, 206 / 111, 117, 131, 157, 170.  A launch per stage: 159-172, 172, 175, 180, 178, 181, 183; 222; 177, 182, 195, 221, 231
 // (the launches replayed as a graph; a call shape's first two appearances go out launch by launch in 223).  33 to 64 rows on one XCD, four row
 // tiles, were 240 and more / 184-191 with barriers: hence at most 32 rows a team.
 //

@@ -9,7 +9,9 @@
 //
 // What bounds it (clock stamps at every workgroup barrier): at width 128 the seven exchanges of a layer, 0.7 to 1.2 us each with what is summed
 // in between, 13 us a layer; at width 512 what an XCD takes from the last-level cache, 16.8 MB a layer in 12 us, and the products of
-// its 32 units, 7 us for 16 rows, of 25 us a layer.  Both sides' figures stand at team_pays in ad_api.cpp.  Not kept: the keys that earlier
+// its 32 units, 7 us for 16 rows, of 25 us a layer.  The decoder at width 512 asks for more registers than there are: 47 spilled (176 bytes of scratch a
+// lane) with up to 64 keys, 153 (440) with up to 128, 5 (24) in the encoder with up to 128; at width 128 only the decoder with up to 128 keys, 8 (36).
+// Both sides' figures, with the spills in, stand at team_pays in ad_api.cpp.  Not kept: the keys that earlier
 // forwards wrote requested ahead (39.0 -> 39.9 us at width 128), FFN1's strips requested in two places, in and beside the attention
 // (a branch around loads has them copied, hence waited for, where it ends: 208 -> 310 us at width 512).
 //
